@@ -506,37 +506,112 @@ __global__ void force_commit_kernel(const int32_t* forced, int32_t* grid, int32_
 // ---------------------------------------------------------------------------- register-resident rows
 //
 // Fast variants for rows of at most 1024 * E entries: a thread keeps its E scaled logits in
-// registers for the whole kernel (one coalesced read of the row), the radix select counts
-// digits in per-wave LDS histograms (all logits of a row share their high bits, so a single
-// shared histogram serialises on two or three counters), the digit scan runs on one wave, and
-// the fp64 weights exp(z - zmax) are computed once and reused by the sum and by the
-// inverse-CDF scan.  Same decisions, to the bit, as the generic functions above.
+// registers for the whole kernel (one coalesced read of the row).  Same decisions, to the bit, as
+// the generic functions above.
+//
+// What bounds them is neither memory nor arithmetic but the chain of phases of one workgroup: each
+// phase is a few hundred cycles of work and ends in a barrier of 16 waves.  So:
+//   - entry e of thread t is index (e / 4) * 4096 + 4 t + e % 4 (E / 4 chunks of 16 KB): a wave's
+//     request is one contiguous kilobyte.  A thread that owned 16 consecutive entries touched 64
+//     cache lines per request, 1.7 us of address processing for a 64 KB row;
+//   - every block-wide exchange has LDS words of its own, so it costs one barrier (behind the
+//     writes) instead of two, and every wave folds the 16 per-wave values by itself with DPP moves;
+//   - one histogram of 1024 bins for the block: LDS atomics of different waves never meet in one
+//     instruction, so per-wave copies only add a merge; every wave scans the bins by itself.
+// A slot of Slots may be written again once every thread has passed a barrier after reading it.
 
-constexpr int kCand = 256;   // entries of the threshold's first-digit bin that are ranked directly
+constexpr int kBins = NT;    // bins of the first, linear cut of the value range
+constexpr int kCand = 256;   // entries of the threshold's bin that are ranked directly
+constexpr int kCap = 2048;   // longest list of kept entries
+static_assert(NW == 16, "per-wave values are folded by one row of 16 lanes");
+
+struct alignas(16) Slots {
+    float2 mm[NW];           // minimum / maximum of a wave
+    unsigned long long key[NW];
+    double sum[NW];
+    double scan[4][NW];
+    int cnt[2][NW];
+    int pick;
+};
 struct FastShared {
-    unsigned hist[NW][256];
-    unsigned tot[256];
-    alignas(16) unsigned cand_rel[kCand];
+    unsigned hist[kBins];
+    float cand_z[kCand];
     int cand_idx[kCand];
     unsigned cand_rank[kCand];   // candidates that come before each one (see rank_candidates)
-    unsigned cand_n;
+    unsigned cand_n, found_bin;
+    float tau_z;
+    int tie_cut;
+    Slots s;
     Shared sh;
 };
 
+template <int E> __device__ __forceinline__ int entry(int e) { return (e >> 2) * (4 * NT) + (int)threadIdx.x * 4 + (e & 3); }
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+// Sum over the block of one double per thread.  One barrier.
+__device__ __forceinline__ double sum1(double v, double (&slot)[NW]) {
+    v = wave_sum_d(v);
+    if ((threadIdx.x & 63) == 0) slot[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = slot[threadIdx.x & 15];
+    ROW_ALLREDUCE(t, addd, dpp_d)
+    return t;
+}
+__device__ __forceinline__ unsigned long long maxu64(unsigned long long a, unsigned long long b) { return a > b ? a : b; }
+template <int CTRL> __device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
+    return ((unsigned long long)(unsigned)dpp_i<CTRL>((int)(v >> 32)) << 32) | (unsigned)dpp_i<CTRL>((int)(unsigned)v);
+}
+// Largest of one 64-bit key per thread.  One barrier.
+__device__ __forceinline__ unsigned long long max1(unsigned long long v, unsigned long long (&slot)[NW]) {
+    ROW_ALLREDUCE(v, maxu64, dpp_u64)
+    const unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
+    unsigned long long m = 0ull;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        m = maxu64(m, ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)hi, 16 * r) << 32) |
+                          (unsigned)__builtin_amdgcn_readlane((int)lo, 16 * r));
+    if ((threadIdx.x & 63) == 0) slot[threadIdx.x >> 6] = m;
+    __syncthreads();
+    unsigned long long t = slot[threadIdx.x & 15];
+    ROW_ALLREDUCE(t, maxu64, dpp_u64)
+    return t;
+}
+// Folds the per-wave totals in `slot`: `base` = sum of the waves before this one, returns the block's total.
+__device__ __forceinline__ double wave_base_d(const double* slot, int wave, double& base) {
+    double v = slot[threadIdx.x & 15];
+    v += dpp_d<0x111>(v);
+    v += dpp_d<0x112>(v);
+    v += dpp_d<0x114>(v);
+    v += dpp_d<0x118>(v);
+    const double b = lane_d(v, wave > 0 ? wave - 1 : 0);
+    base = wave > 0 ? b : 0.0;
+    return lane_d(v, 15);
+}
+__device__ __forceinline__ int wave_base_i(const int* slot, int wave, int& base) {
+    int v = slot[threadIdx.x & 15];
+    v += dpp_i<0x111>(v);
+    v += dpp_i<0x112>(v);
+    v += dpp_i<0x114>(v);
+    v += dpp_i<0x118>(v);
+    const int b = __builtin_amdgcn_readlane(v, wave > 0 ? wave - 1 : 0);
+    base = wave > 0 ? b : 0;
+    return __builtin_amdgcn_readlane(v, 15);
+}
+
 // Ranks of all gathered candidates at once (fs.cand_rank[i] = candidates that come before candidate
-// i - larger key first, lower index first among equal keys -, zeroed by the caller): the cnt x cnt comparisons are spread over the block - NT / cnt threads share a
-// candidate, each compares it with a slice of the list and adds its count with one LDS atomic -
-// instead of one wave walking the whole list per 64 candidates.  All threads call; ends with a barrier.
+// i - larger value first, lower index first among equals -, zeroed by the caller): the cnt x cnt
+// comparisons are spread over the block - NT / cnt threads share a candidate, each compares it with a
+// slice of the list and adds its count with one LDS atomic.  All threads call; ends with a barrier.
 __device__ __forceinline__ void rank_candidates(FastShared& fs, unsigned cnt) {
     const unsigned per = max(1u, (unsigned)NT / cnt), len = (cnt + per - 1u) / per;
     const unsigned i = threadIdx.x % cnt, c = threadIdx.x / cnt;
     if (c < per) {
-        const unsigned mine = fs.cand_rel[i];
+        const float mine = fs.cand_z[i];
         const int mi = fs.cand_idx[i];
         const unsigned j1 = min(cnt, (c + 1u) * len);
         unsigned part = 0u;
         for (unsigned j = c * len; j < j1; ++j) {
-            const unsigned r = fs.cand_rel[j];
+            const float r = fs.cand_z[j];
             part += (r > mine || (r == mine && fs.cand_idx[j] < mi)) ? 1u : 0u;
         }
         if (part) atomicAdd(&fs.cand_rank[i], part);
@@ -544,40 +619,107 @@ __device__ __forceinline__ void rank_candidates(FastShared& fs, unsigned cnt) {
     __syncthreads();
 }
 
-// Inverse of fkey (the key of -0 maps back to +0).
-__device__ __forceinline__ float key_to_float(unsigned k) {
-    return __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
-}
-
 template <int E>
 __device__ __forceinline__ void load_row(const float* lc, const float* lu, float scale, float inv_t, float* out, int n,
                                          float (&z)[E]) {
-    const int base = threadIdx.x * E;
-    if ((n & 3) == 0 && (E & 3) == 0 && base + E <= n) {
+    if ((n & 3) == 0 && ((reinterpret_cast<uintptr_t>(lc) | reinterpret_cast<uintptr_t>(lu) | reinterpret_cast<uintptr_t>(out)) & 15) == 0) {
+        float4 a[E / 4], u[E / 4];
 #pragma unroll
         for (int q = 0; q < E / 4; ++q) {
-            float4 a = *reinterpret_cast<const float4*>(lc + base + 4 * q);
+            const int j = entry<E>(4 * q);
+            a[q] = j < n ? *reinterpret_cast<const float4*>(lc + j) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            if (lu) u[q] = j < n ? *reinterpret_cast<const float4*>(lu + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int q = 0; q < E / 4; ++q) {
+            const int j = entry<E>(4 * q);
             if (lu) {
-                const float4 u = *reinterpret_cast<const float4*>(lu + base + 4 * q);
-                a.x = fmaf(scale, a.x - u.x, u.x); a.y = fmaf(scale, a.y - u.y, u.y);
-                a.z = fmaf(scale, a.z - u.z, u.z); a.w = fmaf(scale, a.w - u.w, u.w);
+                a[q].x = fmaf(scale, a[q].x - u[q].x, u[q].x); a[q].y = fmaf(scale, a[q].y - u[q].y, u[q].y);
+                a[q].z = fmaf(scale, a[q].z - u[q].z, u[q].z); a[q].w = fmaf(scale, a[q].w - u[q].w, u[q].w);
             }
-            if (out) *reinterpret_cast<float4*>(out + base + 4 * q) = a;
-            z[4 * q] = a.x * inv_t; z[4 * q + 1] = a.y * inv_t; z[4 * q + 2] = a.z * inv_t; z[4 * q + 3] = a.w * inv_t;
+            if (out && j < n) *reinterpret_cast<float4*>(out + j) = a[q];
+            // entries past the end: their key lies below that of every finite value
+            z[4 * q] = j < n ? a[q].x * inv_t : -INFINITY; z[4 * q + 1] = j < n ? a[q].y * inv_t : -INFINITY;
+            z[4 * q + 2] = j < n ? a[q].z * inv_t : -INFINITY; z[4 * q + 3] = j < n ? a[q].w * inv_t : -INFINITY;
         }
     } else {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int j = base + e;
+            const int j = entry<E>(e);
             if (j < n) {
                 const float l = lu ? fmaf(scale, lc[j] - lu[j], lu[j]) : lc[j];
                 if (out) out[j] = l;
                 z[e] = l * inv_t;
             } else {
-                z[e] = -INFINITY;  // its key lies below that of every finite value
+                z[e] = -INFINITY;
             }
         }
     }
+}
+
+// Exact radix select on the order-preserving keys, for rows the linear cut does not thin out (ties,
+// odd distributions, infinite logits): the value of the K-th largest entry and up to which index entries
+// equal to it are kept (fs.tau_z, fs.tie_cut; ends with a barrier).
+template <int E>
+__device__ __forceinline__ void radix_select(const float (&z)[E], int n, int K, FastShared& fs) {
+    Shared& sh = fs.sh;
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    unsigned prefix = 0u, mask = 0u, remaining = (unsigned)K, count_eq = 0u;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        __syncthreads();
+        if (threadIdx.x < 256) fs.hist[threadIdx.x] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const unsigned k = fkey(z[e]);
+            if (entry<E>(e) < n && (k & mask) == prefix) atomicAdd(&fs.hist[(k >> shift) & 255u], 1u);
+        }
+        __syncthreads();
+        if (wave == 0) {  // lane owns bins 4*lane .. 4*lane+3; suffix sums from the top bin down
+            const unsigned cs[4] = {fs.hist[lane * 4], fs.hist[lane * 4 + 1], fs.hist[lane * 4 + 2], fs.hist[lane * 4 + 3]};
+            const unsigned own = cs[0] + cs[1] + cs[2] + cs[3];
+            const unsigned inc = (unsigned)wave_incl_scan_i((int)own);
+            unsigned cum = (unsigned)__builtin_amdgcn_readlane((int)inc, 63) - inc;   // entries in higher lanes' bins
+#pragma unroll
+            for (int q = 3; q >= 0; --q) {
+                if (cum < remaining && cum + cs[q] >= remaining) {   // exactly one lane and bin
+                    sh.b_prefix = prefix | ((unsigned)(lane * 4 + q) << shift);
+                    sh.b_remaining = remaining - cum;
+                    sh.b_count_eq = cs[q];
+                }
+                cum += cs[q];
+            }
+        }
+        __syncthreads();
+        prefix = sh.b_prefix;
+        remaining = sh.b_remaining;
+        count_eq = sh.b_count_eq;
+        mask |= 255u << shift;
+    }
+    if (threadIdx.x == 0) {
+        fs.tau_z = __uint_as_float((prefix & 0x80000000u) ? (prefix ^ 0x80000000u) : ~prefix);
+        fs.tie_cut = 0x7FFFFFFF;
+    }
+    __syncthreads();
+    if (remaining < count_eq) {   // keep only the first `remaining` entries equal to the threshold, in index order
+        int before = 0;           // equal entries of the chunks already passed
+#pragma unroll
+        for (int q = 0; q < E / 4; ++q) {
+            int c = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c += (entry<E>(4 * q + e) < n && fkey(z[4 * q + e]) == prefix) ? 1 : 0;
+            const int at = before + block_excl_scan_i(c, sh);
+            int seen = at;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (entry<E>(4 * q + e) < n && fkey(z[4 * q + e]) == prefix && ++seen == (int)remaining) fs.tie_cut = entry<E>(4 * q + e);
+            __syncthreads();
+            if (threadIdx.x == NT - 1) sh.b_int = at + c;
+            __syncthreads();
+            before = sh.b_int;
+        }
+    }
+    __syncthreads();
 }
 
 // Which entries of the row held in z the warp keeps (see warp_stats): arg-max, top-k threshold
@@ -585,315 +727,321 @@ __device__ __forceinline__ void load_row(const float* lc, const float* lu, float
 // *kmask: bit e set iff the thread's entry e is kept (not set in the greedy case).
 template <int E>
 __device__ __forceinline__ WarpStat warp_select(const float (&z)[E], int n, int top_k, int greedy, FastShared& fs, unsigned* kmask) {
-    Shared& sh = fs.sh;
-    const int base = threadIdx.x * E, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
     WarpStat st;
     st.total = 1.0; st.zmax = 0.f; st.tau = 0x007FFFFFu; st.tie_cut = -1; st.onehot = -1;  // keeps every finite entry
     *kmask = 0u;
-    if (greedy) {
-        float best = -INFINITY;
-#pragma unroll
-        for (int e = 0; e < E; ++e) best = fmaxf(best, z[e]);
-        const float gmax = block_max_f(best, sh);
-        int idx = 0x7FFFFFFF;
-#pragma unroll
-        for (int e = E - 1; e >= 0; --e)
-            if (base + e < n && z[e] == gmax) idx = base + e;
-        st.onehot = block_min_i(idx, sh);
-        return st;
-    }
-    const int K = min(top_k, n);
-    if (K < n) {
-        // The keys of a row share their high bits (sign, most of the exponent): radix digits are
-        // taken from (key - smallest key) shifted up to the top bit, so that the first digit
-        // already spreads the row over the 256 bins (few LDS atomics collide, fewer passes).
-        float gmin = INFINITY, gmax = -INFINITY;
+    if (greedy) {   // arg-max, lowest index first: the largest (key, ~index)
+        unsigned long long best = 0ull;
 #pragma unroll
         for (int e = 0; e < E; ++e)
-            if (base + e < n) { gmin = fminf(gmin, z[e]); gmax = fmaxf(gmax, z[e]); }
-        block_minmax_f(gmin, gmax, sh);
-        const unsigned kmin = fkey(gmin), kmax = fkey(gmax);  // the key order is the value order
-        const int sh0 = kmax > kmin ? __clz((int)(kmax - kmin)) : 31;
-        // First the row is cut into 256 bins that are linear in the value (the float keys are
-        // logarithmic: two or three of their first digits would hold nearly everything); the
-        // threshold's bin then holds a few dozen entries, which are ranked directly.  If it holds
-        // too many (ties, odd distributions), the exact radix select on the keys takes over.
-        bool lin = gmax > gmin && gmin > -INFINITY && gmax < INFINITY;
-        const float scale = lin ? 255.99f / (gmax - gmin) : 0.f;
-        unsigned rel[E];
+            if (entry<E>(e) < n)
+                best = maxu64(best, ((unsigned long long)fkey(z[e]) << 32) | (0xFFFFFFFFu - (unsigned)entry<E>(e)));
+        best = max1(best, fs.s.key);
+        st.onehot = (int)(0xFFFFFFFFu - (unsigned)best);
+        return st;
+    }
+    float gmin = INFINITY, gmax = -INFINITY;
 #pragma unroll
-        for (int e = 0; e < E; ++e) rel[e] = (fkey(z[e]) - kmin) << sh0;
-        unsigned prefix = 0u, mask = 0u, remaining = (unsigned)K, count_eq = 0u;
-        int ranked_cut = -1;
-        for (int shift = 24; shift >= 0 && shift + 8 > sh0;) {  // digits below bit sh0 are all zero
+    for (int e = 0; e < E; ++e)
+        if (entry<E>(e) < n) { gmin = fminf(gmin, z[e]); gmax = fmaxf(gmax, z[e]); }
+    gmin = wave_min_f(gmin);
+    gmax = wave_max_f(gmax);
+    if (lane == 0) fs.s.mm[threadIdx.x >> 6] = make_float2(gmin, gmax);
+    fs.hist[threadIdx.x] = 0u;
+    if (threadIdx.x < (unsigned)kCand) fs.cand_rank[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) { fs.cand_n = 0u; fs.s.pick = 0x7FFFFFFF; }
+    __syncthreads();
+    {
+        const float2 m = fs.s.mm[threadIdx.x & 15];
+        gmin = m.x; gmax = m.y;
+        ROW_ALLREDUCE(gmin, fminf, dpp_f)
+        ROW_ALLREDUCE(gmax, fmaxf, dpp_f)
+        gmin = lane_f(gmin, 0);
+        gmax = lane_f(gmax, 0);
+    }
+    st.zmax = gmax;   // the largest entry is always kept
+    const int K = min(top_k, n);
+    if (K < n) {
+        // The row is cut into bins that are linear in the value; the threshold's bin then holds a few
+        // dozen entries (about 16 of a 16384-entry row at top-k 1000), which are ranked directly.
+        bool done = false;
+        float tz = 0.f;
+        int cut = 0x7FFFFFFF;
+        if (gmax > gmin && gmin > -INFINITY && gmax < INFINITY) {
+            const float scale = ((float)kBins - 0.01f) / (gmax - gmin);
+            auto bin_of = [&](int e) { return min((unsigned)kBins - 1u, (unsigned)((z[e] - gmin) * scale)); };
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (entry<E>(e) < n) atomicAdd(&fs.hist[bin_of(e)], 1u);
             __syncthreads();
+            // every wave: the highest bin b with (entries in bins >= b) >= K.  Lane l holds bins
+            // 256 j + 4 l .. + 3 of the four quarters j; from the top quarter down.
+            int4 c[4];
+            int tot[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) fs.hist[wave][lane * 4 + q] = 0u;
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const unsigned digit = lin ? min(255u, (unsigned)((z[e] - gmin) * scale)) : ((rel[e] >> shift) & 255u);
-                if (base + e < n && (lin || (rel[e] & mask) == prefix)) atomicAdd(&fs.hist[wave][digit], 1u);
+            for (int j = 0; j < 4; ++j) {
+                c[j] = *reinterpret_cast<const int4*>(&fs.hist[j * 256 + lane * 4]);
+                int t = (c[j].x + c[j].y) + (c[j].z + c[j].w);
+                t += dpp_i<0xB1>(t); t += dpp_i<0x4E>(t); t += dpp_i<0x141>(t); t += dpp_i<0x140>(t);
+                tot[j] = (__builtin_amdgcn_readlane(t, 0) + __builtin_amdgcn_readlane(t, 16)) +
+                         (__builtin_amdgcn_readlane(t, 32) + __builtin_amdgcn_readlane(t, 48));
             }
-            __syncthreads();
-            if (threadIdx.x < 256) {
-                unsigned t = 0u;
+            int above = 0, qsel = 0;
+            int4 cc = c[0];
+            bool hit = false;
 #pragma unroll
-                for (int q = 0; q < NW; ++q) t += fs.hist[q][threadIdx.x];
-                fs.tot[threadIdx.x] = t;
+            for (int j = 3; j >= 0; --j)
+                if (!hit) {
+                    if (above + tot[j] >= K) { hit = true; qsel = j; cc = c[j]; }
+                    else above += tot[j];
+                }
+            const int own = (cc.x + cc.y) + (cc.z + cc.w);
+            const int inc = wave_incl_scan_i(own);
+            int cum = above + __builtin_amdgcn_readlane(inc, 63) - inc;   // entries in bins above this lane's
+            int fb = -1, want = 0, cnt = 0;
+            const int cs[4] = {cc.x, cc.y, cc.z, cc.w};
+#pragma unroll
+            for (int q = 3; q >= 0; --q) {
+                if (cum < K && cum + cs[q] >= K) { fb = qsel * 256 + lane * 4 + q; want = K - cum; cnt = cs[q]; }
+                cum += cs[q];
             }
-            __syncthreads();
-            if (wave == 0) {  // lane owns bins 4*lane .. 4*lane+3; suffix sums from the top bin down
-                const unsigned c0 = fs.tot[lane * 4], c1 = fs.tot[lane * 4 + 1], c2 = fs.tot[lane * 4 + 2], c3 = fs.tot[lane * 4 + 3];
-                unsigned suf = c0 + c1 + c2 + c3;  // inclusive suffix over lanes >= this one
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const unsigned t = __shfl_down(suf, o, 64);
-                    if (lane + o < 64) suf += t;
-                }
-                const unsigned above = suf - (c0 + c1 + c2 + c3);  // entries in higher lanes' bins
-                // highest bin b with (entries in bins >= b) >= remaining
-                int found = -1;
-                unsigned rem_out = 0u, cnt_out = 0u;
-                unsigned cum = above;
-                const unsigned cs[4] = {c0, c1, c2, c3};
-#pragma unroll
-                for (int q = 3; q >= 0; --q) {
-                    if (found < 0 && cum < remaining && cum + cs[q] >= remaining) {
-                        found = lane * 4 + q; rem_out = remaining - cum; cnt_out = cs[q];
-                    }
-                    cum += cs[q];
-                }
-                if (found >= 0) {  // exactly one lane finds it
-                    sh.b_prefix = lin ? (unsigned)found : (prefix | ((unsigned)found << shift));
-                    sh.b_remaining = rem_out;
-                    sh.b_count_eq = cnt_out;
-                }
-            }
-            __syncthreads();
-            if (lin) {
-                const unsigned bin = sh.b_prefix, want = sh.b_remaining, cnt = sh.b_count_eq;
-                if (cnt > (unsigned)kCand) { lin = false; continue; }  // same digit again, on the keys
-                if (threadIdx.x == 0) fs.cand_n = 0u;
-                if (threadIdx.x < (unsigned)kCand) fs.cand_rank[threadIdx.x] = 0u;
-                __syncthreads();
+            const int src = (int)__ffsll((unsigned long long)__ballot(fb >= 0)) - 1;   // exactly one lane finds it
+            fb = __builtin_amdgcn_readlane(fb, src);
+            want = __builtin_amdgcn_readlane(want, src);
+            cnt = __builtin_amdgcn_readlane(cnt, src);
+            if (cnt <= kCand) {
 #pragma unroll
                 for (int e = 0; e < E; ++e)
-                    if (base + e < n && min(255u, (unsigned)((z[e] - gmin) * scale)) == bin) {
+                    if (entry<E>(e) < n && bin_of(e) == (unsigned)fb) {
                         const unsigned at = atomicAdd(&fs.cand_n, 1u);
-                        if (at < (unsigned)kCand) { fs.cand_rel[at] = rel[e]; fs.cand_idx[at] = base + e; }
+                        if (at < (unsigned)kCand) { fs.cand_z[at] = z[e]; fs.cand_idx[at] = entry<E>(e); }
                     }
                 __syncthreads();
-                rank_candidates(fs, cnt);
-                if (threadIdx.x < cnt && fs.cand_rank[threadIdx.x] + 1u == want) { sh.b_prefix = fs.cand_rel[threadIdx.x]; sh.b_int = fs.cand_idx[threadIdx.x]; }
-                __syncthreads();
-                prefix = sh.b_prefix;
-                ranked_cut = sh.b_int;
-                break;
-            }
-            prefix = sh.b_prefix;
-            remaining = sh.b_remaining;
-            count_eq = sh.b_count_eq;
-            mask |= 255u << shift;
-            if (shift == 24 && count_eq <= (unsigned)kCand) {
-                // Few entries share the threshold's first digit: gather them and rank each one
-                // directly (larger value first, lower index first among equals); the entry of
-                // rank `remaining` is the threshold and the tie cut in one.
-                if (threadIdx.x == 0) fs.cand_n = 0u;
-                if (threadIdx.x < (unsigned)kCand) fs.cand_rank[threadIdx.x] = 0u;
-                __syncthreads();
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (base + e < n && (rel[e] & mask) == prefix) {
-                        const unsigned at = atomicAdd(&fs.cand_n, 1u);
-                        if (at < (unsigned)kCand) { fs.cand_rel[at] = rel[e]; fs.cand_idx[at] = base + e; }
+                if (cnt <= 64) {   // every wave ranks them by itself: one candidate per lane
+                    const float mz = lane < cnt ? fs.cand_z[lane] : 0.f;
+                    const int mi = lane < cnt ? fs.cand_idx[lane] : 0;
+                    int rank = 0;
+                    for (int j = 0; j < cnt; ++j) {
+                        const float oz = lane_f(mz, j);
+                        const int oi = __builtin_amdgcn_readlane(mi, j);
+                        rank += (oz > mz || (oz == mz && oi < mi)) ? 1 : 0;
                     }
-                __syncthreads();
-                rank_candidates(fs, count_eq);
-                if (threadIdx.x < count_eq && fs.cand_rank[threadIdx.x] + 1u == remaining) { sh.b_prefix = fs.cand_rel[threadIdx.x]; sh.b_int = fs.cand_idx[threadIdx.x]; }
-                __syncthreads();
-                prefix = sh.b_prefix;
-                ranked_cut = sh.b_int;
-                break;
+                    const int w = (int)__ffsll((unsigned long long)__ballot(lane < cnt && rank + 1 == want)) - 1;
+                    tz = lane_f(mz, w);
+                    cut = __builtin_amdgcn_readlane(mi, w);
+                } else {
+                    rank_candidates(fs, (unsigned)cnt);
+                    if (threadIdx.x < (unsigned)cnt && fs.cand_rank[threadIdx.x] + 1u == (unsigned)want) {
+                        fs.tau_z = fs.cand_z[threadIdx.x];
+                        fs.tie_cut = fs.cand_idx[threadIdx.x];
+                    }
+                    __syncthreads();
+                    tz = fs.tau_z;
+                    cut = fs.tie_cut;
+                }
+                done = true;
             }
-            if (count_eq == 1u && shift > 0) {  // a single entry is left under the prefix: it is the K-th
-                __syncthreads();
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (base + e < n && (rel[e] & mask) == prefix) sh.b_prefix = rel[e];
-                __syncthreads();
-                prefix = sh.b_prefix;
-                break;
-            }
-            shift -= 8;
         }
-        st.tau = (prefix >> sh0) + kmin;
-        st.tie_cut = 0x7FFFFFFF;
-        if (ranked_cut >= 0) {
-            st.tie_cut = ranked_cut;
-        } else if (remaining < count_eq) {  // keep only the first `remaining` entries equal to tau
-            int c = 0;
-#pragma unroll
-            for (int e = 0; e < E; ++e) c += (base + e < n && rel[e] == prefix) ? 1 : 0;
-            const int before = block_excl_scan_i(c, sh);
-            __syncthreads();
-            if (before < (int)remaining && before + c >= (int)remaining) {
-                int seen = before;
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (base + e < n && rel[e] == prefix && ++seen == (int)remaining) sh.b_int = base + e;
-            }
-            __syncthreads();
-            st.tie_cut = sh.b_int;
+        if (!done) {
+            radix_select<E>(z, n, K, fs);
+            tz = fs.tau_z;
+            cut = fs.tie_cut;
         }
+        st.tau = fkey(tz);
+        st.tie_cut = cut;
         unsigned km = 0u;
 #pragma unroll
         for (int e = 0; e < E; ++e)
-            km |= (base + e < n && (rel[e] > prefix || (rel[e] == prefix && base + e <= st.tie_cut))) ? (1u << e) : 0u;
+            km |= (entry<E>(e) < n && (z[e] > tz || (z[e] == tz && entry<E>(e) <= cut))) ? (1u << e) : 0u;
         *kmask = km;
-        st.zmax = gmax;  // the largest entry is always kept
         return st;
     }
-    float zm = -INFINITY;
 #pragma unroll
-    for (int e = 0; e < E; ++e) zm = fmaxf(zm, z[e]);
-    st.zmax = block_max_f(zm, sh);
-#pragma unroll
-    for (int e = 0; e < E; ++e) *kmask |= (base + e < n && kept(st, z[e], base + e)) ? (1u << e) : 0u;
+    for (int e = 0; e < E; ++e) *kmask |= (entry<E>(e) < n && kept(st, z[e], entry<E>(e))) ? (1u << e) : 0u;
     return st;
 }
 
 template <int E>
 __device__ __forceinline__ unsigned kept_mask(const WarpStat& st, const float (&z)[E], int n) {
-    const int base = threadIdx.x * E;
     unsigned km = 0u;
 #pragma unroll
-    for (int e = 0; e < E; ++e) km |= (base + e < n && kept(st, z[e], base + e)) ? (1u << e) : 0u;
+    for (int e = 0; e < E; ++e) km |= (entry<E>(e) < n && kept(st, z[e], entry<E>(e))) ? (1u << e) : 0u;
     return km;
 }
 
 // Weight of every entry of the row in registers; sets st.total.
 template <int E>
-__device__ void dense_weights(WarpStat& st, const float (&z)[E], double (&w)[E], Shared& sh) {
-    const int base = threadIdx.x * E;
+__device__ void dense_weights(WarpStat& st, const float (&z)[E], double (&w)[E], Slots& sl) {
     if (st.onehot >= 0) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) w[e] = (base + e == st.onehot) ? 1.0 : 0.0;
+        for (int e = 0; e < E; ++e) w[e] = (entry<E>(e) == st.onehot) ? 1.0 : 0.0;
         st.total = 1.0;
         return;
     }
     double s = 0.0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        w[e] = kept(st, z[e], base + e) ? exp((double)z[e] - (double)st.zmax) : 0.0;
+        w[e] = kept(st, z[e], entry<E>(e)) ? exp((double)z[e] - (double)st.zmax) : 0.0;
         s += w[e];
     }
-    st.total = block_sum_d(s, sh);
+    st.total = sum1(s, sl.sum);
 }
 
 // When top-k keeps at most kCap entries, they are gathered - in index order - into a list in
 // LDS and the fp64 exponentials are evaluated for those only (the other 15 of 16 entries of a
-// 16384-entry row would cost a software exp each for a weight of zero).
-constexpr int kCap = 2048;
+// 16384-entry row would cost a software exp each for a weight of zero).  Thread t owns the list's
+// entries t and NT + t.
 struct CompactList {
     int idx[kCap];
     float z[kCap];
-    double w[kCap];
 };
 
 __host__ __device__ __forceinline__ bool use_list(int top_k, int n, int greedy) { return !greedy && top_k < n && top_k <= kCap; }
 
+// Gathers the kept entries (at most kCap) and returns their number; ends with a barrier.  The counts of
+// two chunks share a word (at most kCap in all).
 template <int E>
-__device__ int compact_row(unsigned kmask, const float (&z)[E], CompactList& L, Shared& sh) {
-    const int base = threadIdx.x * E;
-    const int c = __popc(kmask);
-    int at = block_excl_scan_i(c, sh);
-    if (threadIdx.x == NT - 1) sh.b_int = at + c;
+__device__ __forceinline__ int compact_row(unsigned kmask, const float (&z)[E], CompactList& L, Slots& sl) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    int c[(E + 7) / 8], inc[(E + 7) / 8], base[(E + 7) / 8], tot[(E + 7) / 8];
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-        if ((kmask >> e) & 1u) {
-            if (at < kCap) { L.idx[at] = base + e; L.z[at] = z[e]; }
-            ++at;
-        }
+    for (int h = 0; h < (E + 7) / 8; ++h) {
+        c[h] = __popc((kmask >> (8 * h)) & 0xFu) | (__popc((kmask >> (8 * h + 4)) & 0xFu) << 16);
+        inc[h] = wave_incl_scan_i(c[h]);
+        if (lane == 63) sl.cnt[h][threadIdx.x >> 6] = inc[h];
+    }
     __syncthreads();
-    return min(sh.b_int, kCap);
-}
-
-// w[i] = exp(z[i] - zmax) over the list (thread t owns entries 2t, 2t+1); returns the sum.
-__device__ double list_weights(CompactList& L, int Kc, float zmax, Shared& sh) {
-    const int i0 = threadIdx.x * 2;
-    double s = 0.0;
+    int before = 0;
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-        if (i0 + q < Kc) {
-            const double w = exp((double)L.z[i0 + q] - (double)zmax);
-            L.w[i0 + q] = w;
-            s += w;
-        }
-    return block_sum_d(s, sh);
+    for (int h = 0; h < (E + 7) / 8; ++h) tot[h] = wave_base_i(sl.cnt[h], wave, base[h]);
+#pragma unroll
+    for (int q = 0; q < E / 4; ++q) {
+        const int h = q >> 1, sft = (q & 1) * 16;
+        int at = before + (((base[h] + inc[h] - c[h]) >> sft) & 0xFFFF);
+        before += (tot[h] >> sft) & 0xFFFF;
+#pragma unroll
+        for (int e = 4 * q; e < 4 * q + 4; ++e)
+            if ((kmask >> e) & 1u) {
+                if (at < kCap) { L.idx[at] = entry<E>(e); L.z[at] = z[e]; }
+                ++at;
+            }
+    }
+    __syncthreads();
+    return min(before, kCap);
 }
 
-// Inverse-CDF draw over list weights w (ascending index order); returns the token index.
-__device__ int list_inv_cdf(const double* w, const int* idx, int Kc, double total, float u, Shared& sh) {
-    const int i0 = threadIdx.x * 2;
-    __syncthreads();  // the weights were written by other threads
-    const double w0 = i0 < Kc ? w[i0] : 0.0, w1 = i0 + 1 < Kc ? w[i0 + 1] : 0.0;
-    double c = block_excl_scan_d(w0 + w1, sh);
+// Weights exp(z - zmax) of the thread's two list entries (0 past the end).
+__device__ __forceinline__ void list_weights(const CompactList& L, int Kc, float zmax, double (&w)[2]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int i = (int)threadIdx.x + h * NT;
+        w[h] = i < Kc ? exp((double)L.z[i] - (double)zmax) : 0.0;
+    }
+}
+
+// Running sums of the list weights w (entries t and NT + t of thread t): c[h] = sum of all entries up to
+// and including the thread's own; returns the total.  One barrier.
+__device__ __forceinline__ double list_scan(const double (&w)[2], int Kc, double (&c)[2], double (&s0)[NW], double (&s1)[NW]) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const bool two = Kc > NT;
+    const double i0 = wave_incl_scan_d(w[0]), i1 = two ? wave_incl_scan_d(w[1]) : 0.0;
+    if (lane == 63) {
+        s0[threadIdx.x >> 6] = i0;
+        if (two) s1[threadIdx.x >> 6] = i1;
+    }
+    __syncthreads();
+    double b0, b1 = 0.0, t1 = 0.0;
+    const double t0 = wave_base_d(s0, wave, b0);
+    if (two) t1 = wave_base_d(s1, wave, b1);
+    c[0] = b0 + i0;
+    c[1] = t0 + b1 + i1;
+    return t0 + t1;
+}
+
+// Inverse-CDF draw from running sums c of list weights w: the first entry whose running sum exceeds
+// target, else the last one with weight.  sl.pick holds 0x7FFFFFFF on entry (set before the last
+// barrier).  Returns the position in the list; all threads call.
+__device__ __forceinline__ int list_pick(const double (&w)[2], const double (&c)[2], double target, Slots& sl, Shared& sh) {
+    int cand = 0x7FFFFFFF, last = -1;
+#pragma unroll
+    for (int h = 1; h >= 0; --h)
+        if (w[h] > 0.0) {
+            last = max(last, (int)threadIdx.x + h * NT);
+            if (c[h] > target) cand = (int)threadIdx.x + h * NT;
+        }
+    cand = wave_min_i(cand);
+    if ((threadIdx.x & 63) == 0 && cand != 0x7FFFFFFF) atomicMin(&sl.pick, cand);
+    __syncthreads();
+    cand = sl.pick;
+    if (cand != 0x7FFFFFFF) return cand;
+    return max(0, block_max_i(last, sh));
+}
+
+// Inverse-CDF draw from the dense per-thread weights w (ascending index order).
+template <int E>
+__device__ int inv_cdf_row(const double (&w)[E], double total, float u, Slots& sl, Shared& sh) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    double s[E / 4], inc[E / 4];
+    __syncthreads();   // the slots may still be read by an earlier exchange
+    if (threadIdx.x == 0) sl.pick = 0x7FFFFFFF;
+#pragma unroll
+    for (int q = 0; q < E / 4; ++q) {
+        s[q] = (w[4 * q] + w[4 * q + 1]) + (w[4 * q + 2] + w[4 * q + 3]);
+        inc[q] = wave_incl_scan_d(s[q]);
+        if (lane == 63) sl.scan[q][threadIdx.x >> 6] = inc[q];
+    }
+    __syncthreads();
     const double target = (double)u * total;
     int cand = 0x7FFFFFFF, last = -1;
-    if (w0 > 0.0) { c += w0; last = i0; if (c > target) cand = i0; }
-    if (w1 > 0.0) { c += w1; last = i0 + 1; if (c > target && cand == 0x7FFFFFFF) cand = i0 + 1; }
-    cand = block_min_i(cand, sh);
-    if (cand != 0x7FFFFFFF) return idx[cand];
-    last = block_max_i(last, sh);
-    return idx[max(last, 0)];
+    double before = 0.0;
+#pragma unroll
+    for (int q = 0; q < E / 4; ++q) {
+        double base;
+        const double t = wave_base_d(sl.scan[q], wave, base);
+        double c = before + base + (inc[q] - s[q]);
+        before += t;
+#pragma unroll
+        for (int e = 4 * q; e < 4 * q + 4; ++e)
+            if (w[e] > 0.0) {
+                c += w[e];
+                last = entry<E>(e);
+                if (c > target && cand == 0x7FFFFFFF) cand = entry<E>(e);
+            }
+    }
+    cand = wave_min_i(cand);
+    if (lane == 0 && cand != 0x7FFFFFFF) atomicMin(&sl.pick, cand);
+    __syncthreads();
+    cand = sl.pick;
+    if (cand != 0x7FFFFFFF) return cand;
+    return block_max_i(last, sh);
 }
-
-template <int E>
-__device__ int inv_cdf_row(const double (&w)[E], double total, float u, Shared& sh);
 
 // One row, start to finish: the warp's statistics (with total) and, if u != null, a draw.
 template <int E>
-__device__ WarpStat warp_and_draw(const float (&z)[E], int n, int top_k, int greedy, FastShared& fs, CompactList& L,
-                                  const float* u, int* drawn) {
+__device__ __forceinline__ WarpStat warp_and_draw(const float (&z)[E], int n, int top_k, int greedy, FastShared& fs, CompactList& L,
+                                                  const float* u, int* drawn) {
     unsigned kmask = 0u;
     WarpStat st = warp_select<E>(z, n, top_k, greedy, fs, &kmask);
     if (st.onehot >= 0) {
         st.total = 1.0;
         if (u) *drawn = st.onehot;
     } else if (use_list(top_k, n, greedy)) {
-        const int Kc = compact_row<E>(kmask, z, L, fs.sh);
-        st.total = list_weights(L, Kc, st.zmax, fs.sh);
-        if (u) *drawn = list_inv_cdf(L.w, L.idx, Kc, st.total, *u, fs.sh);
+        const int Kc = compact_row<E>(kmask, z, L, fs.s);
+        double w[2], c[2];
+        list_weights(L, Kc, st.zmax, w);
+        if (u) {
+            st.total = list_scan(w, Kc, c, fs.s.scan[0], fs.s.scan[1]);
+            *drawn = L.idx[list_pick(w, c, (double)*u * st.total, fs.s, fs.sh)];
+        } else {
+            st.total = sum1(w[0] + w[1], fs.s.sum);
+        }
     } else {
         double w[E];
-        dense_weights<E>(st, z, w, fs.sh);
-        if (u) *drawn = inv_cdf_row<E>(w, st.total, *u, fs.sh);
+        dense_weights<E>(st, z, w, fs.s);
+        if (u) *drawn = inv_cdf_row<E>(w, st.total, *u, fs.s, fs.sh);
     }
     return st;
-}
-
-// Inverse-CDF draw from the per-thread weights w (ascending index order).
-template <int E>
-__device__ int inv_cdf_row(const double (&w)[E], double total, float u, Shared& sh) {
-    const int base = threadIdx.x * E;
-    double s = 0.0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) s += w[e];
-    double c = block_excl_scan_d(s, sh);
-    const double target = (double)u * total;
-    int cand = 0x7FFFFFFF, last = -1;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        if (w[e] > 0.0) {
-            c += w[e];
-            last = base + e;
-            if (c > target && cand == 0x7FFFFFFF) cand = base + e;
-        }
-    }
-    cand = block_min_i(cand, sh);
-    if (cand != 0x7FFFFFFF) return cand;
-    return block_max_i(last, sh);
 }
 
 template <int E>
@@ -962,74 +1110,87 @@ __global__ __launch_bounds__(NT) void accept_commit_fast(
     const int32_t* draft, int32_t* grid, int32_t* n, const uint32_t* hid, uint32_t* hprev, int hid_words,
     int32_t* out_na, int32_t* out_tok, unsigned long long* counters, int k, int n_seq_streams, SampParams P,
     UniformSrc us) {
+    __shared__ Slots sl;
     __shared__ Shared sh;
     __shared__ CompactList L;
-    __shared__ double res_list[kCap];
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, lane = threadIdx.x & 63;
     const int ke = k_eff[b];
     if (threadIdx.x <= k) out_tok[b * (k + 1) + threadIdx.x] = -1;
     if (ke < 0) {
         if (threadIdx.x == 0) out_na[b] = -1;
         return;
     }
-    int a = 0;
-    for (; a < ke; ++a) {
-        const int dj = draft[b * P.kstride + a] - P.samp_lo;
-        const WarpStat ps = pstat[b * P.kstride + a], qs = qstat[b * P.kstride + a];
-        const double pd = weight_of(ps, logit_b + ((size_t)b * P.kstride + a) * P.Vs, P.inv_t, dj) / ps.total;
-        const double qd = weight_of(qs, dlogit_b + ((size_t)b * P.kstride + a) * P.Vs, P.inv_t, dj) / qs.total;
-        const float u = pick_uniform(us, us.acc, b * k + a, b, kSlotAcc + a);
-        if (!((double)u * qd < pd)) break;
+    if (threadIdx.x == 0) sl.pick = 0x7FFFFFFF;
+    // Accept scan: the tests do not depend on each other, so lane i of every wave makes test i and the
+    // first rejection is where the scan stops (k <= 63).
+    bool rejected = false;
+    if (lane < ke) {
+        const int dj = draft[b * P.kstride + lane] - P.samp_lo;
+        const WarpStat ps = pstat[b * P.kstride + lane], qs = qstat[b * P.kstride + lane];
+        const double pd = weight_of(ps, logit_b + ((size_t)b * P.kstride + lane) * P.Vs, P.inv_t, dj) / ps.total;
+        const double qd = weight_of(qs, dlogit_b + ((size_t)b * P.kstride + lane) * P.Vs, P.inv_t, dj) / qs.total;
+        const float u = pick_uniform(us, us.acc, b * k + lane, b, kSlotAcc + lane);
+        rejected = !((double)u * qd < pd);
     }
+    const unsigned long long rej = __ballot(rejected);
+    const int a = rej ? (int)__ffsll(rej) - 1 : ke;
     const float uf = pick_uniform(us, us.fin, b, b, kSlotFinal);
     const float* prow = logit_b + ((size_t)b * P.kstride + a) * P.Vs;
     const WarpStat ps = pstat[b * P.kstride + a];
-    const int base = threadIdx.x * E;
     int y;
     if (ps.onehot < 0 && use_list(P.top_k, P.Vs, P.greedy)) {
         // the kept entries of p (a superset of the residual's support) as a list; q only where p > 0
         float z[E];
         load_row<E>(prow, nullptr, 0.f, P.inv_t, nullptr, P.Vs, z);
-        const int Kc = compact_row<E>(kept_mask<E>(ps, z, P.Vs), z, L, sh);
-        (void)list_weights(L, Kc, ps.zmax, sh);
+        const int Kc = compact_row<E>(kept_mask<E>(ps, z, P.Vs), z, L, sl);
+        double w[2], c[2];
+        list_weights(L, Kc, ps.zmax, w);
+        bool resid = false;
         if (a < ke) {
             const float* qrow = dlogit_b + ((size_t)b * P.kstride + a) * P.Vs;
             const WarpStat qs = qstat[b * P.kstride + a];
-            const int i0 = threadIdx.x * 2;
-            double s = 0.0;
+            double r[2] = {0.0, 0.0};
 #pragma unroll
-            for (int q2 = 0; q2 < 2; ++q2)
-                if (i0 + q2 < Kc) {
-                    const double q = weight_of(qs, qrow, P.inv_t, L.idx[i0 + q2]) / qs.total;
-                    const double r = L.w[i0 + q2] / ps.total - q;
-                    res_list[i0 + q2] = r > 0.0 ? r : 0.0;
-                    s += res_list[i0 + q2];
+            for (int h = 0; h < 2; ++h) {
+                const int i = (int)threadIdx.x + h * NT;
+                if (i < Kc) {
+                    const double v = w[h] / ps.total - weight_of(qs, qrow, P.inv_t, L.idx[i]) / qs.total;
+                    r[h] = v > 0.0 ? v : 0.0;
                 }
-            const double R = block_sum_d(s, sh);
-            y = (R > 0.0) ? list_inv_cdf(res_list, L.idx, Kc, R, uf, sh) : list_inv_cdf(L.w, L.idx, Kc, ps.total, uf, sh);
-        } else {
-            y = list_inv_cdf(L.w, L.idx, Kc, ps.total, uf, sh);
+            }
+            const double R = list_scan(r, Kc, c, sl.scan[0], sl.scan[1]);
+            if (R > 0.0) {
+                resid = true;
+                y = L.idx[list_pick(r, c, (double)uf * R, sl, sh)];
+            }
+        }
+        if (!resid) {
+            (void)list_scan(w, Kc, c, sl.scan[2], sl.scan[3]);
+            y = L.idx[list_pick(w, c, (double)uf * ps.total, sl, sh)];
         }
     } else {
-    double w[E];
+        double w[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) w[e] = base + e < P.Vs ? weight_of(ps, prow, P.inv_t, base + e) : 0.0;
-    if (a < ke) {
-        const float* qrow = dlogit_b + ((size_t)b * P.kstride + a) * P.Vs;
-        const WarpStat qs = qstat[b * P.kstride + a];
-        double res[E], s = 0.0;
+        for (int e = 0; e < E; ++e) w[e] = entry<E>(e) < P.Vs ? weight_of(ps, prow, P.inv_t, entry<E>(e)) : 0.0;
+        bool resid = false;
+        if (a < ke) {
+            const float* qrow = dlogit_b + ((size_t)b * P.kstride + a) * P.Vs;
+            const WarpStat qs = qstat[b * P.kstride + a];
+            double res[E], s = 0.0;
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const double q = base + e < P.Vs ? weight_of(qs, qrow, P.inv_t, base + e) / qs.total : 0.0;
-            const double r = w[e] / ps.total - q;
-            res[e] = r > 0.0 ? r : 0.0;
-            s += res[e];
+            for (int e = 0; e < E; ++e) {
+                const double q = entry<E>(e) < P.Vs ? weight_of(qs, qrow, P.inv_t, entry<E>(e)) / qs.total : 0.0;
+                const double r = w[e] / ps.total - q;
+                res[e] = r > 0.0 ? r : 0.0;
+                s += res[e];
+            }
+            const double R = sum1(s, sl.sum);
+            if (R > 0.0) {
+                resid = true;
+                y = inv_cdf_row<E>(res, R, uf, sl, sh);
+            }
         }
-        const double R = block_sum_d(s, sh);
-        y = (R > 0.0) ? inv_cdf_row<E>(res, R, uf, sh) : inv_cdf_row<E>(w, ps.total, uf, sh);
-    } else {
-        y = inv_cdf_row<E>(w, ps.total, uf, sh);
-    }
+        if (!resid) y = inv_cdf_row<E>(w, ps.total, uf, sl, sh);
     }
     const int nb = n[b];
     for (int s2 = b; s2 < n_seq_streams; s2 += P.B) {
@@ -1037,13 +1198,13 @@ __global__ __launch_bounds__(NT) void accept_commit_fast(
         uint32_t* dst = hprev + (size_t)s2 * hid_words;
         for (int i = threadIdx.x; i < hid_words; i += NT) dst[i] = src[i];
     }
-    __syncthreads();
+    for (int i = threadIdx.x; i < a; i += NT) {
+        const int t = draft[b * P.kstride + i];
+        grid[(size_t)b * P.N + nb + i] = t;
+        out_tok[b * (k + 1) + i] = t;
+    }
+    __syncthreads();   // every thread has read n[b] before it changes
     if (threadIdx.x == 0) {
-        for (int i = 0; i < a; ++i) {
-            const int t = draft[b * P.kstride + i];
-            grid[(size_t)b * P.N + nb + i] = t;
-            out_tok[b * (k + 1) + i] = t;
-        }
         grid[(size_t)b * P.N + nb + a] = P.samp_lo + y;
         out_tok[b * (k + 1) + a] = P.samp_lo + y;
         out_na[b] = a;
@@ -1065,25 +1226,74 @@ __device__ __forceinline__ int row_candidates(const int32_t* m_rows, int row, in
     return m_rows ? max(0, min(m, m_rows[row])) : m;
 }
 
-// Kept entries of a row gathered as scaled logits only (no indices): for the sum of their weights.
-template <int E>
-__device__ int compact_z(unsigned kmask, const float (&z)[E], float (&qz)[kCap], Shared& sh) {
-    const int c = __popc(kmask);
-    int at = block_excl_scan_i(c, sh);
-    if (threadIdx.x == NT - 1) sh.b_int = at + c;
+// The same recursion with the running target held as a list (index in LDS, the thread's two values in
+// registers): top-k leaves at most kCap entries of p with mass, max(0, p - q) lives on those, and fp64
+// exponentials are evaluated for kept entries only.
+struct WalkShared {
+    double pick;
+    double R[2][NW];   // residual sums, alternating between candidates
+};
+
+// Candidate i of a position against the running target (list entries w of this thread, list of length Kp):
+// accepts, or moves on to the residual.  qs, qrow: the proposal's statistics and logits.  True: accepted.
+__device__ __forceinline__ bool walk_step(const CompactList& L, int Kp, double (&w)[2], const WarpStat& qs, const float* qrow,
+                                          float inv_t, int s_in, int n, float u, int parity, WalkShared& ws, double* resid_out) {
+    const bool s_ok = (unsigned)s_in < (unsigned)n;   // a token outside the slice is rejected, never read
+    const int s = s_ok ? s_in : 0;
+    const float ls = qrow[s];                         // same address for every lane
+    double res[2] = {0.0, 0.0};
+    float lq[2];
+    int idx[2];
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-        if ((kmask >> e) & 1u) {
-            if (at < kCap) qz[at] = z[e];
-            ++at;
+    for (int h = 0; h < 2; ++h) {
+        const int i = (int)threadIdx.x + h * NT;
+        idx[h] = i < Kp ? L.idx[i] : -1;
+        lq[h] = i < Kp ? qrow[idx[h]] : 0.f;
+    }
+    auto weight = [&](float l, int j) {
+        if (qs.onehot >= 0) return j == qs.onehot ? 1.0 : 0.0;
+        const float z = l * inv_t;
+        return kept(qs, z, j) ? exp((double)z - (double)qs.zmax) : 0.0;
+    };
+    const double qd = s_ok ? weight(ls, s) / qs.total : 1.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        if (idx[h] >= 0) {
+            if (idx[h] == s) ws.pick = w[h];
+            const double r = w[h] - weight(lq[h], idx[h]) / qs.total;
+            res[h] = r > 0.0 ? r : 0.0;
         }
+    const double R = sum1(res[0] + res[1], ws.R[parity]);   // its barrier also publishes pick
+    const double pd = s_ok ? ws.pick : 0.0;
+    if (resid_out && threadIdx.x == 0) *resid_out = R;
+    if ((double)u * qd < pd) return true;
+    if (R > 0.0) {
+        w[0] = res[0] / R;
+        w[1] = res[1] / R;
+    }
+    __syncthreads();   // every thread has read pick
+    if (threadIdx.x == 0) ws.pick = 0.0;   // p^(i)(s) if s has no mass left
     __syncthreads();
-    return min(sh.b_int, kCap);
+    return false;
 }
 
-// The same recursion with the running target held as a list in LDS: top-k leaves at most kCap
-// entries of p with mass, max(0, p - q) lives on those, and fp64 exponentials are evaluated for
-// kept entries only, two per thread (the dense form spends one per vocabulary entry).
+// The end of a walk: the token of the accepted candidate, or a draw from the running target.
+__device__ __forceinline__ void walk_finish(const CompactList& L, int Kp, const double (&w)[2], int acc, int mr, int tok, float u,
+                                            int row, int m, Slots& sl, Shared& sh, int32_t* out_index, int32_t* out_token,
+                                            double* out_resid) {
+    if (acc == mr) {
+        double c[2];
+        const double total = list_scan(w, Kp, c, sl.scan[0], sl.scan[1]);
+        tok = L.idx[list_pick(w, c, (double)u * total, sl, sh)];
+    }
+    if (threadIdx.x == 0) {
+        out_index[row] = acc;
+        out_token[row] = tok;
+        if (out_resid)
+            for (int i = (acc == mr ? mr : acc + 1); i < m; ++i) out_resid[(size_t)row * m + i] = -1.0;   // steps not evaluated
+    }
+}
+
 template <int E>
 __global__ __launch_bounds__(NT) void multi_verify_list_kernel(const float* p_logits, const float* q_logits,
                                                                const int32_t* cand, const float* u_acc,
@@ -1091,12 +1301,13 @@ __global__ __launch_bounds__(NT) void multi_verify_list_kernel(const float* p_lo
                                                                int n, float inv_t, int top_k, int32_t* out_index,
                                                                int32_t* out_token, double* out_resid) {
     __shared__ FastShared fs;
-    __shared__ CompactList L;       // entries of p with mass: index, scaled logit, current p^(i)
-    __shared__ float qz[kCap];      // kept scaled logits of the proposal at hand
-    __shared__ double pick;
-    const int row = blockIdx.x, i0 = threadIdx.x * 2;
+    __shared__ CompactList L, Q;    // kept entries of the target, of the proposal at hand
+    __shared__ WalkShared ws;
+    const int row = blockIdx.x;
     const int mr = row_candidates(m_rows, row, m);
     int Kp = 0, acc = mr, tok = -1;
+    double w[2] = {0.0, 0.0};
+    if (threadIdx.x == 0) ws.pick = 0.0;
     // One loop over the target row (i = -1) and the proposal rows, so that the top-k selection has
     // a single call site and is inlined with its LDS operands (a second copy would be called
     // through generic pointers).
@@ -1106,65 +1317,26 @@ __global__ __launch_bounds__(NT) void multi_verify_list_kernel(const float* p_lo
         unsigned km = 0u;
         load_row<E>(qrow, nullptr, 0.f, inv_t, nullptr, n, z);
         WarpStat qs = warp_select<E>(z, n, top_k, 0, fs, &km);
+        CompactList& G = i < 0 ? L : Q;
+        const int Kq = compact_row<E>(km, z, G, fs.s);
+        double wq[2];
+        list_weights(G, Kq, qs.zmax, wq);
+        qs.total = sum1(wq[0] + wq[1], fs.s.sum);
         if (i < 0) {   // p^(1): the kept entries of the target, normalised
-            Kp = compact_row<E>(km, z, L, fs.sh);
-            const double Zp = list_weights(L, Kp, qs.zmax, fs.sh);
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-                if (i0 + e < Kp) L.w[i0 + e] /= Zp;   // the thread's own entries
+            Kp = Kq;
+            w[0] = wq[0] / qs.total;
+            w[1] = wq[1] / qs.total;
             continue;
         }
-        const int Kq = compact_z<E>(km, z, qz, fs.sh);
-        double sq = 0.0;
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-            if (i0 + e < Kq) sq += exp((double)qz[i0 + e] - (double)qs.zmax);
-        if (threadIdx.x == 0) pick = 0.0;   // p^(i)(s) if s has no mass left
-        qs.total = block_sum_d(sq, fs.sh);
-        const int s_in = cand[(size_t)row * m + i];
-        const bool s_ok = (unsigned)s_in < (unsigned)n;   // a token outside the slice is rejected, never read
-        const int s = s_ok ? s_in : 0;
-        double res[2], rs = 0.0;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            res[e] = 0.0;
-            if (i0 + e < Kp) {
-                const int j = L.idx[i0 + e];
-                const double pv = L.w[i0 + e];
-                if (j == s) pick = pv;
-                const double r = pv - weight_of(qs, qrow, inv_t, j) / qs.total;
-                res[e] = r > 0.0 ? r : 0.0;
-                rs += res[e];
-            }
-        }
-        const double R = block_sum_d(rs, fs.sh);   // its barriers also publish pick
-        const double pd = s_ok ? pick : 0.0, qd = s_ok ? weight_of(qs, qrow, inv_t, s) / qs.total : 1.0;
-        if (out_resid && threadIdx.x == 0) out_resid[(size_t)row * m + i] = R;
-        if ((double)u_acc[(size_t)row * m + i] * qd < pd) {
+        const int s = cand[(size_t)row * m + i];
+        if (walk_step(L, Kp, w, qs, qrow, inv_t, s, n, u_acc[(size_t)row * m + i], i & 1, ws,
+                      out_resid ? &out_resid[(size_t)row * m + i] : nullptr)) {
             acc = i;
             tok = s;
             break;
         }
-        if (R > 0.0) {
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-                if (i0 + e < Kp) L.w[i0 + e] = res[e] / R;
-        }
     }
-    if (acc == mr) {
-        double sp = 0.0;
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-            if (i0 + e < Kp) sp += L.w[i0 + e];
-        const double total = block_sum_d(sp, fs.sh);
-        tok = list_inv_cdf(L.w, L.idx, Kp, total, u_final[row], fs.sh);
-    }
-    if (threadIdx.x == 0) {
-        out_index[row] = acc;
-        out_token[row] = tok;
-        if (out_resid)
-            for (int i = (acc == mr ? mr : acc + 1); i < m; ++i) out_resid[(size_t)row * m + i] = -1.0;   // steps not evaluated
-    }
+    walk_finish(L, Kp, w, acc, mr, tok, u_final[row], row, m, fs.s, fs.sh, out_index, out_token, out_resid);
 }
 
 // The same in two launches when the caller lends room for the rows' statistics: the top-k
@@ -1192,70 +1364,33 @@ __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_lo
                                                                int n, float inv_t, const WarpStat* stats,
                                                                int32_t* out_index, int32_t* out_token,
                                                                double* out_resid) {
+    __shared__ Slots sl;
     __shared__ Shared sh;
-    __shared__ CompactList L;       // entries of p with mass: index, scaled logit, current p^(i)
-    __shared__ double pick;
-    const int row = blockIdx.x, i0 = threadIdx.x * 2;
+    __shared__ CompactList L;
+    __shared__ WalkShared ws;
+    const int row = blockIdx.x;
     const int mr = row_candidates(m_rows, row, m);
     const WarpStat ps = stats[(size_t)row * (m + 1)];
+    if (threadIdx.x == 0) { ws.pick = 0.0; sl.pick = 0x7FFFFFFF; }
     float z[E];
     load_row<E>(p_logits + (size_t)row * n, nullptr, 0.f, inv_t, nullptr, n, z);
-    const int Kp = compact_row<E>(kept_mask<E>(ps, z, n), z, L, sh);
-    const double Zp = list_weights(L, Kp, ps.zmax, sh);
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-        if (i0 + e < Kp) L.w[i0 + e] /= Zp;   // the thread's own entries
+    const int Kp = compact_row<E>(kept_mask<E>(ps, z, n), z, L, sl);
+    double w[2];
+    list_weights(L, Kp, ps.zmax, w);
+    w[0] /= ps.total;
+    w[1] /= ps.total;
     int acc = mr, tok = -1;
     for (int i = 0; i < mr; ++i) {
-        const float* qrow = q_logits + ((size_t)row * m + i) * n;
         const WarpStat qs = stats[(size_t)row * (m + 1) + 1 + i];
-        const int s_in = cand[(size_t)row * m + i];
-        const bool s_ok = (unsigned)s_in < (unsigned)n;   // a token outside the slice is rejected, never read
-        const int s = s_ok ? s_in : 0;
-        if (threadIdx.x == 0) pick = 0.0;   // p^(i)(s) if s has no mass left
-        __syncthreads();
-        double res[2], rs = 0.0;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            res[e] = 0.0;
-            if (i0 + e < Kp) {
-                const int j = L.idx[i0 + e];
-                const double pv = L.w[i0 + e];
-                if (j == s) pick = pv;
-                const double r = pv - weight_of(qs, qrow, inv_t, j) / qs.total;
-                res[e] = r > 0.0 ? r : 0.0;
-                rs += res[e];
-            }
-        }
-        const double R = block_sum_d(rs, sh);   // its barriers also publish pick
-        const double pd = s_ok ? pick : 0.0, qd = s_ok ? weight_of(qs, qrow, inv_t, s) / qs.total : 1.0;
-        __syncthreads();   // pick is rewritten at the top of the next round
-        if (out_resid && threadIdx.x == 0) out_resid[(size_t)row * m + i] = R;
-        if ((double)u_acc[(size_t)row * m + i] * qd < pd) {
+        const int s = cand[(size_t)row * m + i];
+        if (walk_step(L, Kp, w, qs, q_logits + ((size_t)row * m + i) * n, inv_t, s, n, u_acc[(size_t)row * m + i], i & 1, ws,
+                      out_resid ? &out_resid[(size_t)row * m + i] : nullptr)) {
             acc = i;
             tok = s;
             break;
         }
-        if (R > 0.0) {
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-                if (i0 + e < Kp) L.w[i0 + e] = res[e] / R;
-        }
     }
-    if (acc == mr) {
-        double sp = 0.0;
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-            if (i0 + e < Kp) sp += L.w[i0 + e];
-        const double total = block_sum_d(sp, sh);
-        tok = list_inv_cdf(L.w, L.idx, Kp, total, u_final[row], sh);
-    }
-    if (threadIdx.x == 0) {
-        out_index[row] = acc;
-        out_token[row] = tok;
-        if (out_resid)
-            for (int i = (acc == mr ? mr : acc + 1); i < m; ++i) out_resid[(size_t)row * m + i] = -1.0;   // steps not evaluated
-    }
+    walk_finish(L, Kp, w, acc, mr, tok, u_final[row], row, m, sl, sh, out_index, out_token, out_resid);
 }
 
 template <int E>
@@ -1266,32 +1401,35 @@ __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits,
                                                           int32_t* out_token, double* out_resid) {
     __shared__ FastShared fs;
     __shared__ double pick[2];
-    const int row = blockIdx.x, base = threadIdx.x * E;
+    const int row = blockIdx.x;
     const int mr = row_candidates(m_rows, row, m);
-    float z[E];
-    unsigned km;
-    load_row<E>(p_logits + (size_t)row * n, nullptr, 0.f, inv_t, nullptr, n, z);
-    WarpStat ps = warp_select<E>(z, n, top_k, greedy, fs, &km);
-    double p[E];
-    dense_weights<E>(ps, z, p, fs.sh);
-#pragma unroll
-    for (int e = 0; e < E; ++e) p[e] /= ps.total;
     int acc = mr, tok = -1;
-    for (int i = 0; i < mr; ++i) {
+    double p[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) p[e] = 0.0;
+    for (int i = -1; i < mr; ++i) {   // i = -1: the target row (one call site of the selection, see multi_verify_list_kernel)
         if (threadIdx.x == 0) {   // a candidate outside the slice has no owner: p = 0, q = 1 rejects it
             pick[0] = 0.0;
             pick[1] = 1.0;
         }
-        load_row<E>(q_logits + ((size_t)row * m + i) * n, nullptr, 0.f, inv_t, nullptr, n, z);
+        float z[E];
+        unsigned km;
+        load_row<E>(i < 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + i) * n, nullptr, 0.f, inv_t, nullptr, n, z);
         WarpStat qs = warp_select<E>(z, n, top_k, greedy, fs, &km);
         double q[E];
-        dense_weights<E>(qs, z, q, fs.sh);
+        dense_weights<E>(qs, z, q, fs.s);
+        __syncthreads();   // the sum's words are used again below; pick[] is initialised
+        if (i < 0) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) p[e] = q[e] / qs.total;
+            continue;
+        }
         const int s = cand[(size_t)row * m + i];
         double rs = 0.0;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             q[e] /= qs.total;
-            if (base + e == s) {   // the owner of the candidate's entry publishes p^(i)(s), q_i(s)
+            if (entry<E>(e) == s) {   // the owner of the candidate's entry publishes p^(i)(s), q_i(s)
                 pick[0] = p[e];
                 pick[1] = q[e];
             }
@@ -1299,7 +1437,7 @@ __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits,
             q[e] = r > 0.0 ? r : 0.0;   // q now holds max(0, p^(i) - q_i)
             rs += q[e];
         }
-        const double R = block_sum_d(rs, fs.sh);   // its barriers also publish pick[]
+        const double R = sum1(rs, fs.s.scan[0]);   // its barrier also publishes pick[]
         const double pd = pick[0], qd = pick[1];
         if (out_resid && threadIdx.x == 0) out_resid[(size_t)row * m + i] = R;
         const bool accept = (double)u_acc[(size_t)row * m + i] * qd < pd;
@@ -1318,8 +1456,9 @@ __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits,
         double sp = 0.0;
 #pragma unroll
         for (int e = 0; e < E; ++e) sp += p[e];
-        const double total = block_sum_d(sp, fs.sh);
-        tok = inv_cdf_row<E>(p, total, u_final[row], fs.sh);
+        __syncthreads();
+        const double total = sum1(sp, fs.s.sum);
+        tok = inv_cdf_row<E>(p, total, u_final[row], fs.s, fs.sh);
     }
     if (threadIdx.x == 0) {
         out_index[row] = acc;
@@ -1368,11 +1507,12 @@ void launch_plan(hawk_ctx* c, int k) {
 }
 
 // Entries per thread of the register-resident kernels for this vocabulary slice (0: too large).
-static int fast_e(const hawk_ctx* c) { return c->Vs <= 4 * NT ? 4 : (c->Vs <= 16 * NT ? 16 : 0); }
+static int entries_per_thread(int n) { return n <= 4 * NT ? 4 : (n <= 8 * NT ? 8 : (n <= 16 * NT ? 16 : 0)); }
+static int fast_e(const hawk_ctx* c) { return entries_per_thread(c->Vs); }
 
 void launch_first_token(hawk_ctx* c, const UniformSrc& us) {
     if (fast_e(c)) {
-        auto kern = fast_e(c) == 4 ? first_token_fast<4> : first_token_fast<16>;
+        auto kern = fast_e(c) == 4 ? first_token_fast<4> : (fast_e(c) == 8 ? first_token_fast<8> : first_token_fast<16>);
         kern<<<c->B, NT, 0, c->stream>>>(wsp<float>(c, c->off.logit_s), wsp<float>(c, c->off.logit_b),
                                          wsp<int32_t>(c, c->off.grid), wsp<int32_t>(c, c->off.n), samp_params(c), us);
         return;
@@ -1388,7 +1528,7 @@ void launch_draft_sample(hawk_ctx* c, int i, int k, const UniformSrc& us, const 
     if (dm.kind == 1) { fs.table = wsp<int32_t>(c, c->off.forced); fs.stride = k; }
     if (dm.kind == 2) { fs.table = wsp<int32_t>(c, c->off.replay); fs.stride = c->N; fs.relative = 1; }
     if (fast_e(c)) {
-        auto kern = fast_e(c) == 4 ? draft_sample_fast<4> : draft_sample_fast<16>;
+        auto kern = fast_e(c) == 4 ? draft_sample_fast<4> : (fast_e(c) == 8 ? draft_sample_fast<8> : draft_sample_fast<16>);
         kern<<<c->B, NT, 0, c->stream>>>(wsp<float>(c, c->off.dlogit_s), wsp<float>(c, c->off.dlogit_b),
                                          wsp<int32_t>(c, c->off.n), wsp<int32_t>(c, c->off.k_eff),
                                          wsp<int32_t>(c, c->off.draft), wsp<WarpStat>(c, c->off.qstat), i, k,
@@ -1403,7 +1543,7 @@ void launch_draft_sample(hawk_ctx* c, int i, int k, const UniformSrc& us, const 
 
 void launch_verify_stats(hawk_ctx* c, int k) {
     if (fast_e(c)) {
-        auto kern = fast_e(c) == 4 ? verify_stats_fast<4> : verify_stats_fast<16>;
+        auto kern = fast_e(c) == 4 ? verify_stats_fast<4> : (fast_e(c) == 8 ? verify_stats_fast<8> : verify_stats_fast<16>);
         kern<<<dim3(k + 1, c->B), NT, 0, c->stream>>>(wsp<float>(c, c->off.logit_s), wsp<float>(c, c->off.logit_b),
                                                       wsp<int32_t>(c, c->off.k_eff), wsp<WarpStat>(c, c->off.pstat), k,
                                                       samp_params(c));
@@ -1416,7 +1556,7 @@ void launch_verify_stats(hawk_ctx* c, int k) {
 
 void launch_accept_commit(hawk_ctx* c, int k, const UniformSrc& us) {
     if (fast_e(c)) {
-        auto kern = fast_e(c) == 4 ? accept_commit_fast<4> : accept_commit_fast<16>;
+        auto kern = fast_e(c) == 4 ? accept_commit_fast<4> : (fast_e(c) == 8 ? accept_commit_fast<8> : accept_commit_fast<16>);
         kern<<<c->B, NT, 0, c->stream>>>(
             wsp<float>(c, c->off.logit_b), wsp<float>(c, c->off.dlogit_b), wsp<WarpStat>(c, c->off.pstat),
             wsp<WarpStat>(c, c->off.qstat), wsp<int32_t>(c, c->off.k_eff), wsp<int32_t>(c, c->off.draft),
@@ -1448,12 +1588,12 @@ void launch_force_commit(hawk_ctx* c, int cnt) {
 
 int launch_sample_rows(const float* logits, const int32_t* skip, const float* u, int rows, int n, float temperature,
                        int top_k, int32_t* out_token, hipStream_t stream) {
-    const int E = n <= 4 * NT ? 4 : (n <= 16 * NT ? 16 : 0);
+    const int E = entries_per_thread(n);
     if (!E) return HAWK_EINVAL;
     const int greedy = (temperature == 0.0f || top_k == 1) ? 1 : 0;
     const float inv_t = greedy ? 1.0f : 1.0f / temperature;
     const int tk = top_k < n ? top_k : n;
-    auto kern = E == 4 ? sample_rows_kernel<4> : sample_rows_kernel<16>;
+    auto kern = E == 4 ? sample_rows_kernel<4> : (E == 8 ? sample_rows_kernel<8> : sample_rows_kernel<16>);
     kern<<<rows, NT, 0, stream>>>(logits, skip, u, n, inv_t, tk, greedy, out_token);
     return hipGetLastError() == hipSuccess ? HAWK_OK : HAWK_EDEVICE;
 }
@@ -1464,24 +1604,24 @@ int launch_multi_verify(const float* p_logits, const float* q_logits, const int3
                         const float* u_final, const int32_t* m_rows, int rows, int m, int n, float temperature, int top_k,
                         int32_t* out_index, int32_t* out_token, double* out_resid, void* workspace,
                         size_t workspace_bytes, hipStream_t stream) {
-    const int E = n <= 4 * NT ? 4 : (n <= 16 * NT ? 16 : 0);
+    const int E = entries_per_thread(n);
     if (!E) return HAWK_EINVAL;
     const int greedy = (temperature == 0.0f || top_k == 1) ? 1 : 0;
     const float inv_t = greedy ? 1.0f : 1.0f / temperature;
     const int tk = top_k < n ? top_k : n;
     if (use_list(tk, n, greedy) && workspace && workspace_bytes >= multi_verify_workspace_bytes(rows, m)) {
         WarpStat* stats = static_cast<WarpStat*>(workspace);
-        auto k1 = E == 4 ? multi_row_stats_kernel<4> : multi_row_stats_kernel<16>;
-        auto k2 = E == 4 ? multi_verify_walk_kernel<4> : multi_verify_walk_kernel<16>;
+        auto k1 = E == 4 ? multi_row_stats_kernel<4> : (E == 8 ? multi_row_stats_kernel<8> : multi_row_stats_kernel<16>);
+        auto k2 = E == 4 ? multi_verify_walk_kernel<4> : (E == 8 ? multi_verify_walk_kernel<8> : multi_verify_walk_kernel<16>);
         k1<<<dim3(m + 1, rows), NT, 0, stream>>>(p_logits, q_logits, m_rows, m, n, inv_t, tk, stats);
         k2<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, stats, out_index, out_token,
                                     out_resid);
     } else if (use_list(tk, n, greedy)) {
-        auto kern = E == 4 ? multi_verify_list_kernel<4> : multi_verify_list_kernel<16>;
+        auto kern = E == 4 ? multi_verify_list_kernel<4> : (E == 8 ? multi_verify_list_kernel<8> : multi_verify_list_kernel<16>);
         kern<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, tk, out_index, out_token,
                                       out_resid);
     } else {
-        auto kern = E == 4 ? multi_verify_kernel<4> : multi_verify_kernel<16>;
+        auto kern = E == 4 ? multi_verify_kernel<4> : (E == 8 ? multi_verify_kernel<8> : multi_verify_kernel<16>);
         kern<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, tk, greedy, out_index,
                                       out_token, out_resid);
     }
