@@ -155,6 +155,7 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     o.out_na = take(B * 4); o.out_tok = take(B * ks * 4); o.inv_freq = take((size_t)(hd / 2) * 8);
     o.replay = take(B * c->Nmax * 4); o.cond = take(S * (size_t)g->max_cond * d * 4);
     o.tree = take(TreeArea(B).bytes);
+    o.llen = take(list_len_bytes(B * ks)); o.lidx = take(list_idx_bytes(B * ks)); o.lw = take(list_w_bytes(B * ks));
     const size_t widest = 3 * d > m ? 3 * d : m;
     c->split_bytes = g->dtype == HAWK_BF16 ? M * widest * 4 : 0;
     o.split = c->split_bytes ? take(c->split_bytes) : 0;

@@ -20,7 +20,7 @@ struct WarpStat {
     float zmax;         // largest scaled logit
     uint32_t tau;       // order-preserving key of the smallest kept scaled logit
     int32_t tie_cut;    // entries equal to tau are kept up to and including this index
-    int32_t onehot;     // >= 0: the row is the point mass on this index (greedy / replay)
+    int32_t onehot;     // >= 0: the row is the point mass on this index (greedy / replay); negative: it is not
 };
 
 // Where the uniforms of a step come from: host-supplied tables already copied to the
@@ -62,6 +62,7 @@ struct Offsets {  // byte offsets into the workspace
     size_t tree;    // candidate tree of a tree pass: int32 depth[64], then uint64 ancestors[64], then walk state
     size_t split;   // bf16 hi / lo planes of a GEMM input (batched shapes; 0: not present)
     size_t split2;  // second pair of planes: written by a GEMM's own epilogue while it reads the first
+    size_t llen, lidx, lw;   // lists of the kept entries of the last verify pass's rows (sampling.hip: ListStore), [B][k_max + 1]
     size_t gpack;   // tile-major copy of the GEMM weights for the MFMA GEMM / GEMV kernels (0: not present)
     size_t total;
 };
@@ -215,6 +216,9 @@ int launch_multi_verify(const float* p_logits, const float* q_logits, const int3
                         int32_t* out_index, int32_t* out_token, double* out_resid, void* workspace,
                         size_t workspace_bytes, hipStream_t stream);
 size_t multi_verify_workspace_bytes(int rows, int m);
+size_t list_len_bytes(size_t rows);   // workspace of the rows' lists: lengths, indices, weights
+size_t list_idx_bytes(size_t rows);
+size_t list_w_bytes(size_t rows);
 int launch_multi_verify_static(const float* p_logits, const float* q_logits, const int32_t* cand, const float* u_acc,
                                const float* u_final, const int32_t* m_rows, int rows, int m, int n, float temperature,
                                int top_k, int32_t* out_index, int32_t* out_token, double* out_resid, hipStream_t stream);

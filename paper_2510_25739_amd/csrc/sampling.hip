@@ -509,28 +509,35 @@ __global__ void force_commit_kernel(const int32_t* forced, int32_t* grid, int32_
 // registers for the whole kernel (one coalesced read of the row).  Same decisions, to the bit, as
 // the generic functions above.
 //
-// What bounds them is neither memory nor arithmetic but the chain of phases of one workgroup: each
-// phase is a few hundred cycles of work and ends in a barrier of 16 waves.  So:
+// What bounds them is the instruction issue of one compute unit: a wave's vector instruction takes
+// four cycles and a SIMD has four of the block's sixteen waves, so one instruction per entry of a
+// 16384-entry row is 256 cycles (0.1 us), and work that every wave repeats costs four times as much as
+// work of one wave.  So:
 //   - entry e of thread t is index (e / 4) * 4096 + 4 t + e % 4 (E / 4 chunks of 16 KB): a wave's
-//     request is one contiguous kilobyte.  A thread that owned 16 consecutive entries touched 64
-//     cache lines per request, 1.7 us of address processing for a 64 KB row;
-//   - every block-wide exchange has LDS words of its own, so it costs one barrier (behind the
-//     writes) instead of two, and every wave folds the 16 per-wave values by itself with DPP moves;
-//   - one histogram of 1024 bins for the block: LDS atomics of different waves never meet in one
-//     instruction, so per-wave copies only add a merge; every wave scans the bins by itself.
-// A slot of Slots may be written again once every thread has passed a barrier after reading it.
+//     request is one contiguous kilobyte;
+//   - places past the end of the row hold NaN, which no comparison keeps: no bounds checks per entry;
+//   - an entry's bin of the first, linear cut of the value range is computed once and kept; the entries
+//     at or above the threshold's bin go to a list in LDS with one comparison each, their places counted
+//     from lane masks; which of the few entries of the threshold's bin itself survive is settled meanwhile,
+//     and those that do not get weight zero;
+//   - every block-wide exchange has LDS words of its own and costs one barrier (behind the writes).
+// Draw from a 16384-entry row at top-k 1000: 20 us with bounds checks, per-thread segments and
+// per-wave histograms, 14 us with coalesced rows and single barriers.
+// A word of Slots may be written again once every thread has passed a barrier after reading it.
 
 constexpr int kBins = NT;    // bins of the first, linear cut of the value range
 constexpr int kCand = 256;   // entries of the threshold's bin that are ranked directly
-constexpr int kCap = 2048;   // longest list of kept entries
+constexpr int kTopCap = 2048;               // largest top-k that takes the list form
+constexpr int kCap = kTopCap + kCand;       // entries of a list: the kept ones and the rest of the threshold's bin
+constexpr int kLH = (kCap + NT - 1) / NT;   // list entries per thread: t, NT + t, 2 NT + t
 static_assert(NW == 16, "per-wave values are folded by one row of 16 lanes");
 
 struct alignas(16) Slots {
     float2 mm[NW];           // minimum / maximum of a wave
     unsigned long long key[NW];
     double sum[NW];
-    double scan[4][NW];
-    int cnt[2][NW];
+    double scan[2][4][NW];
+    int cnt[4 * NW];         // [chunk][wave]
     int pick;
 };
 struct FastShared {
@@ -538,12 +545,17 @@ struct FastShared {
     float cand_z[kCand];
     int cand_idx[kCand];
     unsigned cand_rank[kCand];   // candidates that come before each one (see rank_candidates)
-    unsigned cand_n, found_bin;
+    unsigned cand_n;
+    int bin, want, count;        // the threshold's bin, how many of its entries are kept, how many it has
     float tau_z;
     int tie_cut;
     Slots s;
     Shared sh;
 };
+// The entries a top-k row keeps: z > tz, or z == tz up to index cut.
+struct Threshold { float tz; int cut; };
+__device__ __forceinline__ bool keeps(const Threshold& t, float z, int j) { return z > t.tz || (z == t.tz && j <= t.cut); }
+__device__ __forceinline__ float key_to_float(unsigned k) { return __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k); }
 
 template <int E> __device__ __forceinline__ int entry(int e) { return (e >> 2) * (4 * NT) + (int)threadIdx.x * 4 + (e & 3); }
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
@@ -619,39 +631,39 @@ __device__ __forceinline__ void rank_candidates(FastShared& fs, unsigned cnt) {
     __syncthreads();
 }
 
+// The row's guided, scaled logits into registers (and the guided row to `out`); NaN past the end.
 template <int E>
 __device__ __forceinline__ void load_row(const float* lc, const float* lu, float scale, float inv_t, float* out, int n,
                                          float (&z)[E]) {
+    const float nan = __uint_as_float(0x7FC00000u);
     if ((n & 3) == 0 && ((reinterpret_cast<uintptr_t>(lc) | reinterpret_cast<uintptr_t>(lu) | reinterpret_cast<uintptr_t>(out)) & 15) == 0) {
         float4 a[E / 4], u[E / 4];
 #pragma unroll
         for (int q = 0; q < E / 4; ++q) {
             const int j = entry<E>(4 * q);
-            a[q] = j < n ? *reinterpret_cast<const float4*>(lc + j) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            if (lu) u[q] = j < n ? *reinterpret_cast<const float4*>(lu + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+            a[q] = make_float4(nan, nan, nan, nan);
+            if (j < n) a[q] = *reinterpret_cast<const float4*>(lc + j);
+            if (lu && j < n) u[q] = *reinterpret_cast<const float4*>(lu + j);
         }
 #pragma unroll
         for (int q = 0; q < E / 4; ++q) {
             const int j = entry<E>(4 * q);
-            if (lu) {
+            if (lu && j < n) {
                 a[q].x = fmaf(scale, a[q].x - u[q].x, u[q].x); a[q].y = fmaf(scale, a[q].y - u[q].y, u[q].y);
                 a[q].z = fmaf(scale, a[q].z - u[q].z, u[q].z); a[q].w = fmaf(scale, a[q].w - u[q].w, u[q].w);
             }
             if (out && j < n) *reinterpret_cast<float4*>(out + j) = a[q];
-            // entries past the end: their key lies below that of every finite value
-            z[4 * q] = j < n ? a[q].x * inv_t : -INFINITY; z[4 * q + 1] = j < n ? a[q].y * inv_t : -INFINITY;
-            z[4 * q + 2] = j < n ? a[q].z * inv_t : -INFINITY; z[4 * q + 3] = j < n ? a[q].w * inv_t : -INFINITY;
+            z[4 * q] = a[q].x * inv_t; z[4 * q + 1] = a[q].y * inv_t; z[4 * q + 2] = a[q].z * inv_t; z[4 * q + 3] = a[q].w * inv_t;
         }
     } else {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int j = entry<E>(e);
+            z[e] = nan;
             if (j < n) {
                 const float l = lu ? fmaf(scale, lc[j] - lu[j], lu[j]) : lc[j];
                 if (out) out[j] = l;
                 z[e] = l * inv_t;
-            } else {
-                z[e] = -INFINITY;
             }
         }
     }
@@ -722,250 +734,285 @@ __device__ __forceinline__ void radix_select(const float (&z)[E], int n, int K, 
     __syncthreads();
 }
 
-// Which entries of the row held in z the warp keeps (see warp_stats): arg-max, top-k threshold
-// and tie cut, maximum.  The weights themselves come from dense_weights or from a CompactList.
-// *kmask: bit e set iff the thread's entry e is kept (not set in the greedy case).
+// Arg-max of the row, lowest index first: the largest (key, ~index).  One barrier.
 template <int E>
-__device__ __forceinline__ WarpStat warp_select(const float (&z)[E], int n, int top_k, int greedy, FastShared& fs, unsigned* kmask) {
-    const int lane = threadIdx.x & 63;
-    WarpStat st;
-    st.total = 1.0; st.zmax = 0.f; st.tau = 0x007FFFFFu; st.tie_cut = -1; st.onehot = -1;  // keeps every finite entry
-    *kmask = 0u;
-    if (greedy) {   // arg-max, lowest index first: the largest (key, ~index)
-        unsigned long long best = 0ull;
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            if (entry<E>(e) < n)
-                best = maxu64(best, ((unsigned long long)fkey(z[e]) << 32) | (0xFFFFFFFFu - (unsigned)entry<E>(e)));
-        best = max1(best, fs.s.key);
-        st.onehot = (int)(0xFFFFFFFFu - (unsigned)best);
-        return st;
-    }
-    float gmin = INFINITY, gmax = -INFINITY;
+__device__ __forceinline__ int arg_max(const float (&z)[E], int n, Slots& sl) {
+    unsigned long long best = 0ull;
 #pragma unroll
     for (int e = 0; e < E; ++e)
-        if (entry<E>(e) < n) { gmin = fminf(gmin, z[e]); gmax = fmaxf(gmax, z[e]); }
+        if (entry<E>(e) < n) best = maxu64(best, ((unsigned long long)fkey(z[e]) << 32) | (0xFFFFFFFFu - (unsigned)entry<E>(e)));
+    best = max1(best, sl.key);
+    return (int)(0xFFFFFFFFu - (unsigned)best);
+}
+
+// Clears the words a selection counts in, then the smallest and largest entry of the row.  One barrier.
+template <int E>
+__device__ __forceinline__ void row_minmax(const float (&z)[E], float& gmin, float& gmax, FastShared& fs) {
+    gmin = INFINITY;
+    gmax = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < E; ++e) { gmin = fminf(gmin, z[e]); gmax = fmaxf(gmax, z[e]); }
     gmin = wave_min_f(gmin);
     gmax = wave_max_f(gmax);
-    if (lane == 0) fs.s.mm[threadIdx.x >> 6] = make_float2(gmin, gmax);
+    if ((threadIdx.x & 63) == 0) fs.s.mm[threadIdx.x >> 6] = make_float2(gmin, gmax);
     fs.hist[threadIdx.x] = 0u;
     if (threadIdx.x < (unsigned)kCand) fs.cand_rank[threadIdx.x] = 0u;
     if (threadIdx.x == 0) { fs.cand_n = 0u; fs.s.pick = 0x7FFFFFFF; }
     __syncthreads();
-    {
-        const float2 m = fs.s.mm[threadIdx.x & 15];
-        gmin = m.x; gmax = m.y;
-        ROW_ALLREDUCE(gmin, fminf, dpp_f)
-        ROW_ALLREDUCE(gmax, fmaxf, dpp_f)
-        gmin = lane_f(gmin, 0);
-        gmax = lane_f(gmax, 0);
-    }
-    st.zmax = gmax;   // the largest entry is always kept
-    const int K = min(top_k, n);
-    if (K < n) {
-        // The row is cut into bins that are linear in the value; the threshold's bin then holds a few
-        // dozen entries (about 16 of a 16384-entry row at top-k 1000), which are ranked directly.
-        bool done = false;
-        float tz = 0.f;
-        int cut = 0x7FFFFFFF;
-        if (gmax > gmin && gmin > -INFINITY && gmax < INFINITY) {
-            const float scale = ((float)kBins - 0.01f) / (gmax - gmin);
-            auto bin_of = [&](int e) { return min((unsigned)kBins - 1u, (unsigned)((z[e] - gmin) * scale)); };
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                if (entry<E>(e) < n) atomicAdd(&fs.hist[bin_of(e)], 1u);
-            __syncthreads();
-            // every wave: the highest bin b with (entries in bins >= b) >= K.  Lane l holds bins
-            // 256 j + 4 l .. + 3 of the four quarters j; from the top quarter down.
-            int4 c[4];
-            int tot[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                c[j] = *reinterpret_cast<const int4*>(&fs.hist[j * 256 + lane * 4]);
-                int t = (c[j].x + c[j].y) + (c[j].z + c[j].w);
-                t += dpp_i<0xB1>(t); t += dpp_i<0x4E>(t); t += dpp_i<0x141>(t); t += dpp_i<0x140>(t);
-                tot[j] = (__builtin_amdgcn_readlane(t, 0) + __builtin_amdgcn_readlane(t, 16)) +
-                         (__builtin_amdgcn_readlane(t, 32) + __builtin_amdgcn_readlane(t, 48));
-            }
-            int above = 0, qsel = 0;
-            int4 cc = c[0];
-            bool hit = false;
-#pragma unroll
-            for (int j = 3; j >= 0; --j)
-                if (!hit) {
-                    if (above + tot[j] >= K) { hit = true; qsel = j; cc = c[j]; }
-                    else above += tot[j];
-                }
-            const int own = (cc.x + cc.y) + (cc.z + cc.w);
-            const int inc = wave_incl_scan_i(own);
-            int cum = above + __builtin_amdgcn_readlane(inc, 63) - inc;   // entries in bins above this lane's
-            int fb = -1, want = 0, cnt = 0;
-            const int cs[4] = {cc.x, cc.y, cc.z, cc.w};
-#pragma unroll
-            for (int q = 3; q >= 0; --q) {
-                if (cum < K && cum + cs[q] >= K) { fb = qsel * 256 + lane * 4 + q; want = K - cum; cnt = cs[q]; }
-                cum += cs[q];
-            }
-            const int src = (int)__ffsll((unsigned long long)__ballot(fb >= 0)) - 1;   // exactly one lane finds it
-            fb = __builtin_amdgcn_readlane(fb, src);
-            want = __builtin_amdgcn_readlane(want, src);
-            cnt = __builtin_amdgcn_readlane(cnt, src);
-            if (cnt <= kCand) {
-#pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (entry<E>(e) < n && bin_of(e) == (unsigned)fb) {
-                        const unsigned at = atomicAdd(&fs.cand_n, 1u);
-                        if (at < (unsigned)kCand) { fs.cand_z[at] = z[e]; fs.cand_idx[at] = entry<E>(e); }
-                    }
-                __syncthreads();
-                if (cnt <= 64) {   // every wave ranks them by itself: one candidate per lane
-                    const float mz = lane < cnt ? fs.cand_z[lane] : 0.f;
-                    const int mi = lane < cnt ? fs.cand_idx[lane] : 0;
-                    int rank = 0;
-                    for (int j = 0; j < cnt; ++j) {
-                        const float oz = lane_f(mz, j);
-                        const int oi = __builtin_amdgcn_readlane(mi, j);
-                        rank += (oz > mz || (oz == mz && oi < mi)) ? 1 : 0;
-                    }
-                    const int w = (int)__ffsll((unsigned long long)__ballot(lane < cnt && rank + 1 == want)) - 1;
-                    tz = lane_f(mz, w);
-                    cut = __builtin_amdgcn_readlane(mi, w);
-                } else {
-                    rank_candidates(fs, (unsigned)cnt);
-                    if (threadIdx.x < (unsigned)cnt && fs.cand_rank[threadIdx.x] + 1u == (unsigned)want) {
-                        fs.tau_z = fs.cand_z[threadIdx.x];
-                        fs.tie_cut = fs.cand_idx[threadIdx.x];
-                    }
-                    __syncthreads();
-                    tz = fs.tau_z;
-                    cut = fs.tie_cut;
-                }
-                done = true;
-            }
-        }
-        if (!done) {
-            radix_select<E>(z, n, K, fs);
-            tz = fs.tau_z;
-            cut = fs.tie_cut;
-        }
-        st.tau = fkey(tz);
-        st.tie_cut = cut;
-        unsigned km = 0u;
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            km |= (entry<E>(e) < n && (z[e] > tz || (z[e] == tz && entry<E>(e) <= cut))) ? (1u << e) : 0u;
-        *kmask = km;
-        return st;
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) *kmask |= (entry<E>(e) < n && kept(st, z[e], entry<E>(e))) ? (1u << e) : 0u;
-    return st;
+    const float2 m = fs.s.mm[threadIdx.x & 15];
+    gmin = m.x; gmax = m.y;
+    ROW_ALLREDUCE(gmin, fminf, dpp_f)
+    ROW_ALLREDUCE(gmax, fmaxf, dpp_f)
+    gmin = lane_f(gmin, 0);
+    gmax = lane_f(gmax, 0);
 }
 
-template <int E>
-__device__ __forceinline__ unsigned kept_mask(const WarpStat& st, const float (&z)[E], int n) {
-    unsigned km = 0u;
+// One wave: the highest bin b of fs.hist with (entries in bins >= b) >= K (fs.bin), how many of its
+// entries are among the K largest (fs.want) and how many it has (fs.count; `pads` places past the end of the
+// row were counted in bin 0).  Lane l holds bins 256 j + 4 l .. + 3 of the four quarters j.
+__device__ __forceinline__ void find_bin(FastShared& fs, int K, int pads) {
+    const int lane = threadIdx.x & 63;
+    int4 c[4];
+    int tot[4];
 #pragma unroll
-    for (int e = 0; e < E; ++e) km |= (entry<E>(e) < n && kept(st, z[e], entry<E>(e))) ? (1u << e) : 0u;
-    return km;
+    for (int j = 0; j < 4; ++j) {
+        c[j] = *reinterpret_cast<const int4*>(&fs.hist[j * 256 + lane * 4]);
+        int t = (c[j].x + c[j].y) + (c[j].z + c[j].w);
+        t += dpp_i<0xB1>(t); t += dpp_i<0x4E>(t); t += dpp_i<0x141>(t); t += dpp_i<0x140>(t);
+        tot[j] = (__builtin_amdgcn_readlane(t, 0) + __builtin_amdgcn_readlane(t, 16)) +
+                 (__builtin_amdgcn_readlane(t, 32) + __builtin_amdgcn_readlane(t, 48));
+    }
+    int above = 0, qsel = 0;
+    int4 cc = c[0];
+    bool hit = false;
+#pragma unroll
+    for (int j = 3; j >= 1; --j)
+        if (!hit) {
+            if (above + tot[j] >= K) { hit = true; qsel = j; cc = c[j]; }
+            else above += tot[j];
+        }
+    const int inc = wave_incl_scan_i((cc.x + cc.y) + (cc.z + cc.w));
+    int cum = above + __builtin_amdgcn_readlane(inc, 63) - inc;   // entries in bins above this lane's
+    const int cs[4] = {cc.x, cc.y, cc.z, cc.w};
+#pragma unroll
+    for (int q = 3; q >= 0; --q) {
+        if (cum < K && cum + cs[q] >= K) {   // exactly one lane and bin
+            const int b = qsel * 256 + lane * 4 + q;
+            fs.bin = b;
+            fs.want = K - cum;
+            fs.count = cs[q] - (b == 0 ? pads : 0);
+        }
+        cum += cs[q];
+    }
 }
 
-// Weight of every entry of the row in registers; sets st.total.
-template <int E>
-__device__ void dense_weights(WarpStat& st, const float (&z)[E], double (&w)[E], Slots& sl) {
-    if (st.onehot >= 0) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) w[e] = (entry<E>(e) == st.onehot) ? 1.0 : 0.0;
-        st.total = 1.0;
-        return;
+// At most 64 candidates, one per lane: wave w compares them with candidates w, w + 16, .. and adds up how many
+// of those come before each one (larger value first, lower index first among equals); behind the next
+// barrier the one that `want - 1` others precede is the threshold (ranked_threshold).
+__device__ __forceinline__ void rank_by_waves(FastShared& fs, int cnt) {
+    const int lane = threadIdx.x & 63;
+    const float mz = lane < cnt ? fs.cand_z[lane] : 0.f;
+    const int mi = lane < cnt ? fs.cand_idx[lane] : 0;
+    unsigned part = 0u;
+    for (int j = wave_id(); j < cnt; j += NW) {
+        const float oz = fs.cand_z[j];
+        const int oi = fs.cand_idx[j];
+        part += (oz > mz || (oz == mz && oi < mi)) ? 1u : 0u;
     }
-    double s = 0.0;
+    if (lane < cnt && part) atomicAdd(&fs.cand_rank[lane], part);
+}
+__device__ __forceinline__ Threshold ranked_threshold(const FastShared& fs, bool pending) {
+    Threshold t = {fs.tau_z, fs.tie_cut};
+    if (pending) {
+        const int lane = threadIdx.x & 63;
+        const unsigned long long hit = __ballot(lane < fs.count && fs.cand_rank[lane] + 1u == (unsigned)fs.want);
+        const int l = (int)__ffsll(hit) - 1;   // exactly one lane
+        t.tz = lane_f(fs.cand_z[lane], l);
+        t.cut = __builtin_amdgcn_readlane(fs.cand_idx[lane], l);
+    }
+    return t;
+}
+
+// Bins of the row's entries, linear between its smallest and largest one (places past the end: bin 0).
+template <int E>
+__device__ __forceinline__ void linear_bins(const float (&z)[E], float gmin, float gmax, unsigned (&bin)[E]) {
+    const float scale = ((float)kBins - 0.01f) / (gmax - gmin);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        w[e] = kept(st, z[e], entry<E>(e)) ? exp((double)z[e] - (double)st.zmax) : 0.0;
-        s += w[e];
+        const float f = (z[e] - gmin) * scale;
+        asm("v_cvt_u32_f32 %0, %1" : "=v"(bin[e]) : "v"(f));   // NaN converts to 0
     }
-    st.total = sum1(s, sl.sum);
 }
 
-// When top-k keeps at most kCap entries, they are gathered - in index order - into a list in
-// LDS and the fp64 exponentials are evaluated for those only (the other 15 of 16 entries of a
-// 16384-entry row would cost a software exp each for a weight of zero).  Thread t owns the list's
-// entries t and NT + t.
+// The cut of a row at its K-th largest entry (K < n).  On return hi[e] is larger than `lim` or equal to it
+// for every kept entry e and for the entries that share the threshold's bin; the exact threshold is in
+// fs.tau_z / fs.tie_cut, or, if `pending`, still to be found by rank_by_waves (behind a barrier) and
+// ranked_threshold (behind another).  tag: -2 - (the threshold's bin), -1 if hi holds the exact
+// decision (WarpStat::onehot of such a row: any negative value means no point mass, and the tag lets another
+// kernel gather the same list).
+template <int E>
+__device__ __forceinline__ void cut_row(const float (&z)[E], int n, int K, FastShared& fs, float& gmax, unsigned (&hi)[E],
+                                        unsigned& lim, bool& pending, int& tag) {
+    float gmin;
+    row_minmax<E>(z, gmin, gmax, fs);
+    pending = false;
+    tag = -1;
+    if (gmax > gmin && gmin > -INFINITY && gmax < INFINITY) {
+        linear_bins<E>(z, gmin, gmax, hi);
+#pragma unroll
+        for (int e = 0; e < E; ++e) atomicAdd(&fs.hist[hi[e]], 1u);
+        __syncthreads();
+        if (threadIdx.x < 64) find_bin(fs, K, E * NT - n);
+        __syncthreads();
+        lim = (unsigned)__builtin_amdgcn_readfirstlane(fs.bin);
+        const int cnt = __builtin_amdgcn_readfirstlane(fs.count);
+        if (cnt <= kCand) {
+            tag = -2 - (int)lim;
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (hi[e] == lim && entry<E>(e) < n) {
+                    const unsigned at = atomicAdd(&fs.cand_n, 1u);
+                    fs.cand_z[at] = z[e];
+                    fs.cand_idx[at] = entry<E>(e);
+                }
+            if (cnt <= 64) {
+                pending = true;
+                return;
+            }
+            const unsigned want = (unsigned)fs.want;
+            __syncthreads();
+            rank_candidates(fs, (unsigned)cnt);
+            if (threadIdx.x < (unsigned)cnt && fs.cand_rank[threadIdx.x] + 1u == want) {
+                fs.tau_z = fs.cand_z[threadIdx.x];
+                fs.tie_cut = fs.cand_idx[threadIdx.x];
+            }
+            __syncthreads();
+            return;
+        }
+    }
+    radix_select<E>(z, n, K, fs);
+    const Threshold t = {fs.tau_z, fs.tie_cut};
+    lim = 1u;
+#pragma unroll
+    for (int e = 0; e < E; ++e) hi[e] = keeps(t, z[e], entry<E>(e)) ? 1u : 0u;
+}
+
+// When top-k keeps at most kTopCap entries, they are gathered - in index order - into a list in LDS
+// and the fp64 exponentials are evaluated for those only (the other 15 of 16 entries of a 16384-entry
+// row would cost a software exp each for a weight of zero).  Thread t owns entries t, NT + t, 2 NT + t.
 struct CompactList {
-    int idx[kCap];
-    float z[kCap];
+    int2 e[kCap];   // index, scaled logit (bits)
 };
 
-__host__ __device__ __forceinline__ bool use_list(int top_k, int n, int greedy) { return !greedy && top_k < n && top_k <= kCap; }
+__host__ __device__ __forceinline__ bool use_list(int top_k, int n, int greedy) { return !greedy && top_k < n && top_k <= kTopCap; }
 
-// Gathers the kept entries (at most kCap) and returns their number; ends with a barrier.  The counts of
-// two chunks share a word (at most kCap in all).
+// Per-wave counts of the entries with hi[e] >= lim, for place_entries behind the next barrier.
 template <int E>
-__device__ __forceinline__ int compact_row(unsigned kmask, const float (&z)[E], CompactList& L, Slots& sl) {
-    const int lane = threadIdx.x & 63, wave = wave_id();
-    int c[(E + 7) / 8], inc[(E + 7) / 8], base[(E + 7) / 8], tot[(E + 7) / 8];
-#pragma unroll
-    for (int h = 0; h < (E + 7) / 8; ++h) {
-        c[h] = __popc((kmask >> (8 * h)) & 0xFu) | (__popc((kmask >> (8 * h + 4)) & 0xFu) << 16);
-        inc[h] = wave_incl_scan_i(c[h]);
-        if (lane == 63) sl.cnt[h][threadIdx.x >> 6] = inc[h];
-    }
-    __syncthreads();
-    int before = 0;
-#pragma unroll
-    for (int h = 0; h < (E + 7) / 8; ++h) tot[h] = wave_base_i(sl.cnt[h], wave, base[h]);
+__device__ __forceinline__ void count_entries(const unsigned (&hi)[E], unsigned lim, Slots& sl) {
 #pragma unroll
     for (int q = 0; q < E / 4; ++q) {
-        const int h = q >> 1, sft = (q & 1) * 16;
-        int at = before + (((base[h] + inc[h] - c[h]) >> sft) & 0xFFFF);
-        before += (tot[h] >> sft) & 0xFFFF;
+        int c = 0;
+#pragma unroll
+        for (int e = 4 * q; e < 4 * q + 4; ++e) c += __popcll(__ballot(hi[e] >= lim));
+        if ((threadIdx.x & 63) == 0) sl.cnt[q * NW + (threadIdx.x >> 6)] = c;
+    }
+}
+// Writes those entries into the list in index order; returns their number.
+template <int E>
+__device__ __forceinline__ int place_entries(const unsigned (&hi)[E], unsigned lim, const float (&z)[E], CompactList& L, const Slots& sl) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int v = lane < 4 * E ? sl.cnt[lane] : 0;   // chunk-major, wave-minor: the order of the indices
+    const int inc = wave_incl_scan_i(v);
+#pragma unroll
+    for (int q = 0; q < E / 4; ++q) {
+        int at = __builtin_amdgcn_readlane(inc - v, q * NW + wave);
+#pragma unroll
+        for (int e = 4 * q; e < 4 * q + 4; ++e) {   // entries of the lanes before this one
+            const unsigned long long m = __ballot(hi[e] >= lim);
+            at = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)at));
+        }
 #pragma unroll
         for (int e = 4 * q; e < 4 * q + 4; ++e)
-            if ((kmask >> e) & 1u) {
-                if (at < kCap) { L.idx[at] = entry<E>(e); L.z[at] = z[e]; }
+            if (hi[e] >= lim) {
+                if (at < kCap) L.e[at] = make_int2(entry<E>(e), __float_as_int(z[e]));
                 ++at;
             }
     }
-    __syncthreads();
-    return min(before, kCap);
+    return min(__builtin_amdgcn_readlane(inc, 4 * E - 1), kCap);
 }
 
-// Weights exp(z - zmax) of the thread's two list entries (0 past the end).
-__device__ __forceinline__ void list_weights(const CompactList& L, int Kc, float zmax, double (&w)[2]) {
+// The list of a top-k row: its length, its largest entry and the exact threshold.
+template <int E>
+__device__ __forceinline__ int select_list(const float (&z)[E], int n, int K, FastShared& fs, CompactList& L, Threshold& t, WarpStat& st) {
+    unsigned hi[E], lim;
+    bool pending;
+    cut_row<E>(z, n, K, fs, st.zmax, hi, lim, pending, st.onehot);
+    count_entries<E>(hi, lim, fs.s);
+    __syncthreads();
+    if (pending) rank_by_waves(fs, fs.count);
+    const int Kc = place_entries<E>(hi, lim, z, L, fs.s);
+    __syncthreads();
+    t = ranked_threshold(fs, pending);
+    st.tau = fkey(t.tz);
+    st.tie_cut = t.cut;
+    return Kc;
+}
+
+// Weights exp(z - zmax) of the thread's list entries (0 past the end and for entries that are not kept).
+__device__ __forceinline__ void list_weights(const CompactList& L, int Kc, float zmax, const Threshold& t, int (&idx)[kLH], double (&w)[kLH]) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < kLH; ++h) {
         const int i = (int)threadIdx.x + h * NT;
-        w[h] = i < Kc ? exp((double)L.z[i] - (double)zmax) : 0.0;
+        w[h] = 0.0;
+        idx[h] = -1;
+        if (i < Kc) {
+            const int2 v = L.e[i];
+            idx[h] = v.x;
+            const float z = __int_as_float(v.y);
+            if (keeps(t, z, v.x)) w[h] = exp((double)z - (double)zmax);
+        }
     }
 }
+__device__ __forceinline__ double sum3(const double (&w)[kLH]) {
+    double s = w[0];
+#pragma unroll
+    for (int h = 1; h < kLH; ++h) s += w[h];
+    return s;
+}
 
-// Running sums of the list weights w (entries t and NT + t of thread t): c[h] = sum of all entries up to
-// and including the thread's own; returns the total.  One barrier.
-__device__ __forceinline__ double list_scan(const double (&w)[2], int Kc, double (&c)[2], double (&s0)[NW], double (&s1)[NW]) {
+// Running sums of the list weights w: c[h] = sum of all entries up to and including the thread's own
+// entry h; returns the total.  One barrier.
+__device__ __forceinline__ double list_scan(const double (&w)[kLH], int Kc, double (&c)[kLH], double (&s)[4][NW]) {
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const bool two = Kc > NT;
-    const double i0 = wave_incl_scan_d(w[0]), i1 = two ? wave_incl_scan_d(w[1]) : 0.0;
-    if (lane == 63) {
-        s0[threadIdx.x >> 6] = i0;
-        if (two) s1[threadIdx.x >> 6] = i1;
-    }
+    double inc[kLH];
+#pragma unroll
+    for (int h = 0; h < kLH; ++h)
+        if (h * NT < Kc) {
+            inc[h] = wave_incl_scan_d(w[h]);
+            if (lane == 63) s[h][threadIdx.x >> 6] = inc[h];
+        }
     __syncthreads();
-    double b0, b1 = 0.0, t1 = 0.0;
-    const double t0 = wave_base_d(s0, wave, b0);
-    if (two) t1 = wave_base_d(s1, wave, b1);
-    c[0] = b0 + i0;
-    c[1] = t0 + b1 + i1;
-    return t0 + t1;
+    double before = 0.0;
+#pragma unroll
+    for (int h = 0; h < kLH; ++h) {
+        c[h] = 0.0;
+        if (h * NT < Kc) {
+            double base;
+            const double t = wave_base_d(s[h], wave, base);
+            c[h] = before + base + inc[h];
+            before += t;
+        }
+    }
+    return before;
 }
 
 // Inverse-CDF draw from running sums c of list weights w: the first entry whose running sum exceeds
 // target, else the last one with weight.  sl.pick holds 0x7FFFFFFF on entry (set before the last
 // barrier).  Returns the position in the list; all threads call.
-__device__ __forceinline__ int list_pick(const double (&w)[2], const double (&c)[2], double target, Slots& sl, Shared& sh) {
+__device__ __forceinline__ int list_pick(const double (&w)[kLH], const double (&c)[kLH], double target, Slots& sl, Shared& sh) {
     int cand = 0x7FFFFFFF, last = -1;
 #pragma unroll
-    for (int h = 1; h >= 0; --h)
+    for (int h = kLH - 1; h >= 0; --h)
         if (w[h] > 0.0) {
             last = max(last, (int)threadIdx.x + h * NT);
             if (c[h] > target) cand = (int)threadIdx.x + h * NT;
@@ -980,7 +1027,7 @@ __device__ __forceinline__ int list_pick(const double (&w)[2], const double (&c)
 
 // Inverse-CDF draw from the dense per-thread weights w (ascending index order).
 template <int E>
-__device__ int inv_cdf_row(const double (&w)[E], double total, float u, Slots& sl, Shared& sh) {
+__device__ __forceinline__ int inv_cdf_row(const double (&w)[E], double total, float u, Slots& sl, Shared& sh) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     double s[E / 4], inc[E / 4];
     __syncthreads();   // the slots may still be read by an earlier exchange
@@ -989,7 +1036,7 @@ __device__ int inv_cdf_row(const double (&w)[E], double total, float u, Slots& s
     for (int q = 0; q < E / 4; ++q) {
         s[q] = (w[4 * q] + w[4 * q + 1]) + (w[4 * q + 2] + w[4 * q + 3]);
         inc[q] = wave_incl_scan_d(s[q]);
-        if (lane == 63) sl.scan[q][threadIdx.x >> 6] = inc[q];
+        if (lane == 63) sl.scan[0][q][threadIdx.x >> 6] = inc[q];
     }
     __syncthreads();
     const double target = (double)u * total;
@@ -998,7 +1045,7 @@ __device__ int inv_cdf_row(const double (&w)[E], double total, float u, Slots& s
 #pragma unroll
     for (int q = 0; q < E / 4; ++q) {
         double base;
-        const double t = wave_base_d(sl.scan[q], wave, base);
+        const double t = wave_base_d(sl.scan[0][q], wave, base);
         double c = before + base + (inc[q] - s[q]);
         before += t;
 #pragma unroll
@@ -1017,30 +1064,81 @@ __device__ int inv_cdf_row(const double (&w)[E], double total, float u, Slots& s
     return block_max_i(last, sh);
 }
 
-// One row, start to finish: the warp's statistics (with total) and, if u != null, a draw.
+// The statistics (with total) of a row that does not take the list form - greedy, every entry kept, or more
+// than kTopCap kept - and the weight of every entry of the thread.
+template <int E>
+__device__ __forceinline__ WarpStat dense_row(const float (&z)[E], int n, int top_k, int greedy, FastShared& fs, double (&w)[E]) {
+    WarpStat st;
+    st.total = 1.0; st.zmax = 0.f; st.tau = 0x007FFFFFu; st.tie_cut = -1; st.onehot = -1;  // keeps every finite entry
+    if (greedy) {
+        st.onehot = arg_max<E>(z, n, fs.s);
+#pragma unroll
+        for (int e = 0; e < E; ++e) w[e] = (entry<E>(e) == st.onehot) ? 1.0 : 0.0;
+        return st;
+    }
+    Threshold t = {-INFINITY, -1};
+    if (top_k < n) {
+        unsigned hi[E], lim;
+        bool pending;
+        int tag;
+        cut_row<E>(z, n, top_k, fs, st.zmax, hi, lim, pending, tag);
+        __syncthreads();
+        if (pending) rank_by_waves(fs, fs.count);
+        __syncthreads();
+        t = ranked_threshold(fs, pending);
+        st.tau = fkey(t.tz);
+        st.tie_cut = t.cut;
+    } else {
+        float gmin;
+        row_minmax<E>(z, gmin, st.zmax, fs);
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        w[e] = keeps(t, z[e], entry<E>(e)) ? exp((double)z[e] - (double)st.zmax) : 0.0;
+        s += w[e];
+        __builtin_amdgcn_sched_barrier(0);   // one exponential at a time: interleaved ones spill
+    }
+    st.total = sum1(s, fs.s.sum);
+    return st;
+}
+
+// Where a row's list goes for the kernel that needs it next: its length, then per entry the index and the weight
+// (kCap entries each).
+struct ListStore { int32_t* len; int32_t* idx; double* w; };
+
+// One row, start to finish: the warp's statistics (with total) and, if u != null, a draw; its list, if it has
+// one, also goes to `store` when that is given.
 template <int E>
 __device__ __forceinline__ WarpStat warp_and_draw(const float (&z)[E], int n, int top_k, int greedy, FastShared& fs, CompactList& L,
-                                                  const float* u, int* drawn) {
-    unsigned kmask = 0u;
-    WarpStat st = warp_select<E>(z, n, top_k, greedy, fs, &kmask);
-    if (st.onehot >= 0) {
-        st.total = 1.0;
-        if (u) *drawn = st.onehot;
-    } else if (use_list(top_k, n, greedy)) {
-        const int Kc = compact_row<E>(kmask, z, L, fs.s);
-        double w[2], c[2];
-        list_weights(L, Kc, st.zmax, w);
-        if (u) {
-            st.total = list_scan(w, Kc, c, fs.s.scan[0], fs.s.scan[1]);
-            *drawn = L.idx[list_pick(w, c, (double)*u * st.total, fs.s, fs.sh)];
-        } else {
-            st.total = sum1(w[0] + w[1], fs.s.sum);
+                                                  const float* u, int* drawn, const ListStore store = {nullptr, nullptr, nullptr}) {
+    WarpStat st;
+    if (use_list(top_k, n, greedy)) {
+        Threshold t;
+        const int Kc = select_list<E>(z, n, top_k, fs, L, t, st);
+        int idx[kLH];
+        double w[kLH], c[kLH];
+        list_weights(L, Kc, st.zmax, t, idx, w);
+        if (store.len) {
+            if (threadIdx.x == 0) *store.len = Kc;
+#pragma unroll
+            for (int h = 0; h < kLH; ++h)
+                if (idx[h] >= 0) {
+                    store.idx[threadIdx.x + h * NT] = idx[h];
+                    store.w[threadIdx.x + h * NT] = w[h];
+                }
         }
-    } else {
-        double w[E];
-        dense_weights<E>(st, z, w, fs.s);
-        if (u) *drawn = inv_cdf_row<E>(w, st.total, *u, fs.s, fs.sh);
+        if (u) {
+            st.total = list_scan(w, Kc, c, fs.s.scan[0]);
+            *drawn = L.e[list_pick(w, c, (double)*u * st.total, fs.s, fs.sh)].x;
+        } else {
+            st.total = sum1(sum3(w), fs.s.sum);
+        }
+        return st;
     }
+    double w[E];
+    st = dense_row<E>(z, n, top_k, greedy, fs, w);
+    if (u) *drawn = st.onehot >= 0 ? st.onehot : inv_cdf_row<E>(w, st.total, *u, fs.s, fs.sh);
     return st;
 }
 
@@ -1089,9 +1187,16 @@ __global__ __launch_bounds__(NT) void draft_sample_fast(const float* dlogit_s, f
     }
 }
 
+__device__ __forceinline__ ListStore list_at(int32_t* len, int32_t* idx, double* w, size_t row) {
+    ListStore l;
+    l.len = len + row; l.idx = idx + row * kCap; l.w = w + row * kCap;
+    return l;
+}
+
 template <int E>
 __global__ __launch_bounds__(NT) void verify_stats_fast(const float* logit_s, float* logit_b, const int32_t* k_eff,
-                                                        WarpStat* pstat, int k, SampParams P) {
+                                                        WarpStat* pstat, int32_t* llen, int32_t* lidx, double* lw, int k,
+                                                        SampParams P) {
     __shared__ FastShared fs;
     __shared__ CompactList L;
     const int r = blockIdx.x, b = blockIdx.y;
@@ -1100,19 +1205,19 @@ __global__ __launch_bounds__(NT) void verify_stats_fast(const float* logit_s, fl
     load_row<E>(logit_s + ((size_t)b * (k + 1) + r) * P.Vs,
                 P.use_cfg ? logit_s + ((size_t)(P.B + b) * (k + 1) + r) * P.Vs : nullptr, P.cfg_scale, P.inv_t,
                 logit_b + ((size_t)b * P.kstride + r) * P.Vs, P.Vs, z);
-    const WarpStat st = warp_and_draw<E>(z, P.Vs, P.top_k, P.greedy, fs, L, nullptr, nullptr);
+    const ListStore store = list_at(llen, lidx, lw, (size_t)b * P.kstride + r);
+    const WarpStat st = warp_and_draw<E>(z, P.Vs, P.top_k, P.greedy, fs, L, nullptr, nullptr, store);
     if (threadIdx.x == 0) pstat[b * P.kstride + r] = st;
 }
 
 template <int E>
 __global__ __launch_bounds__(NT) void accept_commit_fast(
-    const float* logit_b, const float* dlogit_b, const WarpStat* pstat, const WarpStat* qstat, const int32_t* k_eff,
-    const int32_t* draft, int32_t* grid, int32_t* n, const uint32_t* hid, uint32_t* hprev, int hid_words,
-    int32_t* out_na, int32_t* out_tok, unsigned long long* counters, int k, int n_seq_streams, SampParams P,
+    const float* logit_b, const float* dlogit_b, const WarpStat* pstat, const WarpStat* qstat, int32_t* llen, int32_t* lidx,
+    double* lw, const int32_t* k_eff, const int32_t* draft, int32_t* grid, int32_t* n, const uint32_t* hid, uint32_t* hprev,
+    int hid_words, int32_t* out_na, int32_t* out_tok, unsigned long long* counters, int k, int n_seq_streams, SampParams P,
     UniformSrc us) {
     __shared__ Slots sl;
     __shared__ Shared sh;
-    __shared__ CompactList L;
     const int b = blockIdx.x, lane = threadIdx.x & 63;
     const int ke = k_eff[b];
     if (threadIdx.x <= k) out_tok[b * (k + 1) + threadIdx.x] = -1;
@@ -1138,41 +1243,49 @@ __global__ __launch_bounds__(NT) void accept_commit_fast(
     const float* prow = logit_b + ((size_t)b * P.kstride + a) * P.Vs;
     const WarpStat ps = pstat[b * P.kstride + a];
     int y;
-    if (ps.onehot < 0 && use_list(P.top_k, P.Vs, P.greedy)) {
-        // the kept entries of p (a superset of the residual's support) as a list; q only where p > 0
-        float z[E];
-        load_row<E>(prow, nullptr, 0.f, P.inv_t, nullptr, P.Vs, z);
-        const int Kc = compact_row<E>(kept_mask<E>(ps, z, P.Vs), z, L, sl);
-        double w[2], c[2];
-        list_weights(L, Kc, ps.zmax, w);
-        bool resid = false;
+    bool resid = false;
+    if (use_list(P.top_k, P.Vs, P.greedy)) {
+        // the kept entries of p (a superset of the residual's support) as the list verify_stats_fast left; q only where p > 0
+        const ListStore src = list_at(llen, lidx, lw, (size_t)b * P.kstride + a);
+        const int Kc = *src.len;
+        int idx[kLH];
+        double w[kLH], c[kLH];
+#pragma unroll
+        for (int h = 0; h < kLH; ++h) {
+            const int i = (int)threadIdx.x + h * NT;
+            idx[h] = -1;
+            w[h] = 0.0;
+            if (i < Kc) { idx[h] = src.idx[i]; w[h] = src.w[i]; }
+        }
+        int at = 0;
+        __syncthreads();   // sl.pick is set
         if (a < ke) {
             const float* qrow = dlogit_b + ((size_t)b * P.kstride + a) * P.Vs;
             const WarpStat qs = qstat[b * P.kstride + a];
-            double r[2] = {0.0, 0.0};
+            double r[kLH];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int i = (int)threadIdx.x + h * NT;
-                if (i < Kc) {
-                    const double v = w[h] / ps.total - weight_of(qs, qrow, P.inv_t, L.idx[i]) / qs.total;
+            for (int h = 0; h < kLH; ++h) {
+                r[h] = 0.0;
+                if (idx[h] >= 0) {
+                    const double v = w[h] / ps.total - weight_of(qs, qrow, P.inv_t, idx[h]) / qs.total;
                     r[h] = v > 0.0 ? v : 0.0;
                 }
             }
-            const double R = list_scan(r, Kc, c, sl.scan[0], sl.scan[1]);
+            const double R = list_scan(r, Kc, c, sl.scan[0]);
             if (R > 0.0) {
                 resid = true;
-                y = L.idx[list_pick(r, c, (double)uf * R, sl, sh)];
+                at = list_pick(r, c, (double)uf * R, sl, sh);
             }
         }
         if (!resid) {
-            (void)list_scan(w, Kc, c, sl.scan[2], sl.scan[3]);
-            y = L.idx[list_pick(w, c, (double)uf * ps.total, sl, sh)];
+            (void)list_scan(w, Kc, c, sl.scan[1]);
+            at = list_pick(w, c, (double)uf * ps.total, sl, sh);
         }
+        y = src.idx[at];
     } else {
         double w[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) w[e] = entry<E>(e) < P.Vs ? weight_of(ps, prow, P.inv_t, entry<E>(e)) : 0.0;
-        bool resid = false;
         if (a < ke) {
             const float* qrow = dlogit_b + ((size_t)b * P.kstride + a) * P.Vs;
             const WarpStat qs = qstat[b * P.kstride + a];
@@ -1226,30 +1339,25 @@ __device__ __forceinline__ int row_candidates(const int32_t* m_rows, int row, in
     return m_rows ? max(0, min(m, m_rows[row])) : m;
 }
 
-// The same recursion with the running target held as a list (index in LDS, the thread's two values in
-// registers): top-k leaves at most kCap entries of p with mass, max(0, p - q) lives on those, and fp64
-// exponentials are evaluated for kept entries only.
+// The same recursion with the running target held as a list (the thread's entries in registers): top-k
+// leaves at most kTopCap entries of p with mass, max(0, p - q) lives on those, and fp64 exponentials are
+// evaluated for list entries only.
 struct WalkShared {
     double pick;
     double R[2][NW];   // residual sums, alternating between candidates
 };
 
-// Candidate i of a position against the running target (list entries w of this thread, list of length Kp):
+// Candidate i of a position against the running target (list entries idx, w of this thread):
 // accepts, or moves on to the residual.  qs, qrow: the proposal's statistics and logits.  True: accepted.
-__device__ __forceinline__ bool walk_step(const CompactList& L, int Kp, double (&w)[2], const WarpStat& qs, const float* qrow,
-                                          float inv_t, int s_in, int n, float u, int parity, WalkShared& ws, double* resid_out) {
+__device__ __forceinline__ bool walk_step(const int (&idx)[kLH], double (&w)[kLH], const WarpStat& qs, const float* qrow, float inv_t,
+                                          int s_in, int n, float u, int parity, WalkShared& ws, double* resid_out) {
     const bool s_ok = (unsigned)s_in < (unsigned)n;   // a token outside the slice is rejected, never read
     const int s = s_ok ? s_in : 0;
     const float ls = qrow[s];                         // same address for every lane
-    double res[2] = {0.0, 0.0};
-    float lq[2];
-    int idx[2];
+    double res[kLH];
+    float lq[kLH];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int i = (int)threadIdx.x + h * NT;
-        idx[h] = i < Kp ? L.idx[i] : -1;
-        lq[h] = i < Kp ? qrow[idx[h]] : 0.f;
-    }
+    for (int h = 0; h < kLH; ++h) lq[h] = idx[h] >= 0 ? qrow[idx[h]] : 0.f;
     auto weight = [&](float l, int j) {
         if (qs.onehot >= 0) return j == qs.onehot ? 1.0 : 0.0;
         const float z = l * inv_t;
@@ -1257,19 +1365,21 @@ __device__ __forceinline__ bool walk_step(const CompactList& L, int Kp, double (
     };
     const double qd = s_ok ? weight(ls, s) / qs.total : 1.0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < kLH; ++h) {
+        res[h] = 0.0;
         if (idx[h] >= 0) {
             if (idx[h] == s) ws.pick = w[h];
             const double r = w[h] - weight(lq[h], idx[h]) / qs.total;
             res[h] = r > 0.0 ? r : 0.0;
         }
-    const double R = sum1(res[0] + res[1], ws.R[parity]);   // its barrier also publishes pick
+    }
+    const double R = sum1(sum3(res), ws.R[parity]);   // its barrier also publishes pick
     const double pd = s_ok ? ws.pick : 0.0;
     if (resid_out && threadIdx.x == 0) *resid_out = R;
     if ((double)u * qd < pd) return true;
     if (R > 0.0) {
-        w[0] = res[0] / R;
-        w[1] = res[1] / R;
+#pragma unroll
+        for (int h = 0; h < kLH; ++h) w[h] = res[h] / R;
     }
     __syncthreads();   // every thread has read pick
     if (threadIdx.x == 0) ws.pick = 0.0;   // p^(i)(s) if s has no mass left
@@ -1278,17 +1388,21 @@ __device__ __forceinline__ bool walk_step(const CompactList& L, int Kp, double (
 }
 
 // The end of a walk: the token of the accepted candidate, or a draw from the running target.
-__device__ __forceinline__ void walk_finish(const CompactList& L, int Kp, const double (&w)[2], int acc, int mr, int tok, float u,
+__device__ __forceinline__ void walk_finish(const int (&idx)[kLH], const double (&w)[kLH], int Kp, int acc, int mr, int tok, float u,
                                             int row, int m, Slots& sl, Shared& sh, int32_t* out_index, int32_t* out_token,
                                             double* out_resid) {
+    int at = -1;
     if (acc == mr) {
-        double c[2];
-        const double total = list_scan(w, Kp, c, sl.scan[0], sl.scan[1]);
-        tok = L.idx[list_pick(w, c, (double)u * total, sl, sh)];
+        double c[kLH];
+        const double total = list_scan(w, Kp, c, sl.scan[0]);
+        at = list_pick(w, c, (double)u * total, sl, sh);
     }
+#pragma unroll
+    for (int h = 0; h < kLH; ++h)
+        if (at == (int)threadIdx.x + h * NT) out_token[row] = idx[h];   // the drawn entry's owner
     if (threadIdx.x == 0) {
         out_index[row] = acc;
-        out_token[row] = tok;
+        if (at < 0) out_token[row] = tok;
         if (out_resid)
             for (int i = (acc == mr ? mr : acc + 1); i < m; ++i) out_resid[(size_t)row * m + i] = -1.0;   // steps not evaluated
     }
@@ -1301,12 +1415,13 @@ __global__ __launch_bounds__(NT) void multi_verify_list_kernel(const float* p_lo
                                                                int n, float inv_t, int top_k, int32_t* out_index,
                                                                int32_t* out_token, double* out_resid) {
     __shared__ FastShared fs;
-    __shared__ CompactList L, Q;    // kept entries of the target, of the proposal at hand
+    __shared__ CompactList L;    // kept entries of the row at hand
     __shared__ WalkShared ws;
     const int row = blockIdx.x;
     const int mr = row_candidates(m_rows, row, m);
     int Kp = 0, acc = mr, tok = -1;
-    double w[2] = {0.0, 0.0};
+    int idx[kLH];
+    double w[kLH];
     if (threadIdx.x == 0) ws.pick = 0.0;
     // One loop over the target row (i = -1) and the proposal rows, so that the top-k selection has
     // a single call site and is inlined with its LDS operands (a second copy would be called
@@ -1314,38 +1429,42 @@ __global__ __launch_bounds__(NT) void multi_verify_list_kernel(const float* p_lo
     for (int i = -1; i < mr; ++i) {
         const float* qrow = i < 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + i) * n;
         float z[E];
-        unsigned km = 0u;
         load_row<E>(qrow, nullptr, 0.f, inv_t, nullptr, n, z);
-        WarpStat qs = warp_select<E>(z, n, top_k, 0, fs, &km);
-        CompactList& G = i < 0 ? L : Q;
-        const int Kq = compact_row<E>(km, z, G, fs.s);
-        double wq[2];
-        list_weights(G, Kq, qs.zmax, wq);
-        qs.total = sum1(wq[0] + wq[1], fs.s.sum);
+        WarpStat qs;
+        Threshold t;
+        const int Kq = select_list<E>(z, n, top_k, fs, L, t, qs);
+        int iq[kLH];
+        double wq[kLH];
+        list_weights(L, Kq, qs.zmax, t, iq, wq);
+        qs.total = sum1(sum3(wq), fs.s.sum);
         if (i < 0) {   // p^(1): the kept entries of the target, normalised
             Kp = Kq;
-            w[0] = wq[0] / qs.total;
-            w[1] = wq[1] / qs.total;
+#pragma unroll
+            for (int h = 0; h < kLH; ++h) {
+                idx[h] = iq[h];
+                w[h] = wq[h] / qs.total;
+            }
             continue;
         }
         const int s = cand[(size_t)row * m + i];
-        if (walk_step(L, Kp, w, qs, qrow, inv_t, s, n, u_acc[(size_t)row * m + i], i & 1, ws,
+        if (walk_step(idx, w, qs, qrow, inv_t, s, n, u_acc[(size_t)row * m + i], i & 1, ws,
                       out_resid ? &out_resid[(size_t)row * m + i] : nullptr)) {
             acc = i;
             tok = s;
             break;
         }
     }
-    walk_finish(L, Kp, w, acc, mr, tok, u_final[row], row, m, fs.s, fs.sh, out_index, out_token, out_resid);
+    walk_finish(idx, w, Kp, acc, mr, tok, u_final[row], row, m, fs.s, fs.sh, out_index, out_token, out_resid);
 }
 
 // The same in two launches when the caller lends room for the rows' statistics: the top-k
 // selection of the target row and of every proposal row runs in a workgroup of its own (all of
-// them in parallel), and the walk over the candidates then only gathers.
+// them in parallel), and the walk over the candidates then only gathers.  With room for the target rows' lists
+// as well (llen != null) the walk starts from those instead of selecting the row's kept entries again.
 template <int E>
 __global__ __launch_bounds__(NT) void multi_row_stats_kernel(const float* p_logits, const float* q_logits,
                                                              const int32_t* m_rows, int m, int n, float inv_t,
-                                                             int top_k, WarpStat* stats) {
+                                                             int top_k, WarpStat* stats, int32_t* llen, int32_t* lidx, double* lw) {
     __shared__ FastShared fs;
     __shared__ CompactList L;
     const int j = blockIdx.x, row = blockIdx.y;   // j = 0: the target row, j >= 1: proposal j - 1
@@ -1353,7 +1472,9 @@ __global__ __launch_bounds__(NT) void multi_row_stats_kernel(const float* p_logi
     const float* l = j == 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + (j - 1)) * n;
     float z[E];
     load_row<E>(l, nullptr, 0.f, inv_t, nullptr, n, z);
-    const WarpStat st = warp_and_draw<E>(z, n, top_k, 0, fs, L, nullptr, nullptr);
+    ListStore store = list_at(llen, lidx, lw, row);
+    if (j > 0 || !llen) store.len = nullptr;
+    const WarpStat st = warp_and_draw<E>(z, n, top_k, 0, fs, L, nullptr, nullptr, store);
     if (threadIdx.x == 0) stats[(size_t)row * (m + 1) + j] = st;
 }
 
@@ -1361,9 +1482,9 @@ template <int E>
 __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_logits, const float* q_logits,
                                                                const int32_t* cand, const float* u_acc,
                                                                const float* u_final, const int32_t* m_rows, int m,
-                                                               int n, float inv_t, const WarpStat* stats,
-                                                               int32_t* out_index, int32_t* out_token,
-                                                               double* out_resid) {
+                                                               int n, float inv_t, const WarpStat* stats, int32_t* llen,
+                                                               int32_t* lidx, double* lw, int32_t* out_index,
+                                                               int32_t* out_token, double* out_resid) {
     __shared__ Slots sl;
     __shared__ Shared sh;
     __shared__ CompactList L;
@@ -1372,25 +1493,55 @@ __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_lo
     const int mr = row_candidates(m_rows, row, m);
     const WarpStat ps = stats[(size_t)row * (m + 1)];
     if (threadIdx.x == 0) { ws.pick = 0.0; sl.pick = 0x7FFFFFFF; }
-    float z[E];
-    load_row<E>(p_logits + (size_t)row * n, nullptr, 0.f, inv_t, nullptr, n, z);
-    const int Kp = compact_row<E>(kept_mask<E>(ps, z, n), z, L, sl);
-    double w[2];
-    list_weights(L, Kp, ps.zmax, w);
-    w[0] /= ps.total;
-    w[1] /= ps.total;
+    int idx[kLH], Kp;
+    double w[kLH];
+    if (llen) {
+        const ListStore src = list_at(llen, lidx, lw, row);
+        Kp = *src.len;
+#pragma unroll
+        for (int h = 0; h < kLH; ++h) {
+            const int i = (int)threadIdx.x + h * NT;
+            idx[h] = -1;
+            w[h] = 0.0;
+            if (i < Kp) { idx[h] = src.idx[i]; w[h] = src.w[i]; }
+        }
+        __syncthreads();
+    } else {
+        float z[E];
+        load_row<E>(p_logits + (size_t)row * n, nullptr, 0.f, inv_t, nullptr, n, z);
+        const Threshold t = {key_to_float(ps.tau), ps.tie_cut};
+        unsigned hi[E], lim = 1u;
+        if (ps.onehot < -1) {   // the list the selection had: everything from the threshold's bin up
+            float gmin = INFINITY;
+#pragma unroll
+            for (int e = 0; e < E; ++e) gmin = fminf(gmin, z[e]);
+            gmin = -block_max_f(-gmin, sh);
+            linear_bins<E>(z, gmin, ps.zmax, hi);
+            lim = (unsigned)(-2 - ps.onehot);
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e) hi[e] = keeps(t, z[e], entry<E>(e)) ? 1u : 0u;
+        }
+        count_entries<E>(hi, lim, sl);
+        __syncthreads();
+        Kp = place_entries<E>(hi, lim, z, L, sl);
+        __syncthreads();
+        list_weights(L, Kp, ps.zmax, t, idx, w);
+    }
+#pragma unroll
+    for (int h = 0; h < kLH; ++h) w[h] /= ps.total;
     int acc = mr, tok = -1;
     for (int i = 0; i < mr; ++i) {
         const WarpStat qs = stats[(size_t)row * (m + 1) + 1 + i];
         const int s = cand[(size_t)row * m + i];
-        if (walk_step(L, Kp, w, qs, q_logits + ((size_t)row * m + i) * n, inv_t, s, n, u_acc[(size_t)row * m + i], i & 1, ws,
+        if (walk_step(idx, w, qs, q_logits + ((size_t)row * m + i) * n, inv_t, s, n, u_acc[(size_t)row * m + i], i & 1, ws,
                       out_resid ? &out_resid[(size_t)row * m + i] : nullptr)) {
             acc = i;
             tok = s;
             break;
         }
     }
-    walk_finish(L, Kp, w, acc, mr, tok, u_final[row], row, m, sl, sh, out_index, out_token, out_resid);
+    walk_finish(idx, w, Kp, acc, mr, tok, u_final[row], row, m, sl, sh, out_index, out_token, out_resid);
 }
 
 template <int E>
@@ -1413,11 +1564,9 @@ __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits,
             pick[1] = 1.0;
         }
         float z[E];
-        unsigned km;
         load_row<E>(i < 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + i) * n, nullptr, 0.f, inv_t, nullptr, n, z);
-        WarpStat qs = warp_select<E>(z, n, top_k, greedy, fs, &km);
         double q[E];
-        dense_weights<E>(qs, z, q, fs.s);
+        const WarpStat qs = dense_row<E>(z, n, top_k, greedy, fs, q);
         __syncthreads();   // the sum's words are used again below; pick[] is initialised
         if (i < 0) {
 #pragma unroll
@@ -1437,7 +1586,7 @@ __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits,
             q[e] = r > 0.0 ? r : 0.0;   // q now holds max(0, p^(i) - q_i)
             rs += q[e];
         }
-        const double R = sum1(rs, fs.s.scan[0]);   // its barrier also publishes pick[]
+        const double R = sum1(rs, fs.s.scan[0][0]);   // its barrier also publishes pick[]
         const double pd = pick[0], qd = pick[1];
         if (out_resid && threadIdx.x == 0) out_resid[(size_t)row * m + i] = R;
         const bool accept = (double)u_acc[(size_t)row * m + i] * qd < pd;
@@ -1545,7 +1694,8 @@ void launch_verify_stats(hawk_ctx* c, int k) {
     if (fast_e(c)) {
         auto kern = fast_e(c) == 4 ? verify_stats_fast<4> : (fast_e(c) == 8 ? verify_stats_fast<8> : verify_stats_fast<16>);
         kern<<<dim3(k + 1, c->B), NT, 0, c->stream>>>(wsp<float>(c, c->off.logit_s), wsp<float>(c, c->off.logit_b),
-                                                      wsp<int32_t>(c, c->off.k_eff), wsp<WarpStat>(c, c->off.pstat), k,
+                                                      wsp<int32_t>(c, c->off.k_eff), wsp<WarpStat>(c, c->off.pstat),
+                                                      wsp<int32_t>(c, c->off.llen), wsp<int32_t>(c, c->off.lidx), wsp<double>(c, c->off.lw), k,
                                                       samp_params(c));
         return;
     }
@@ -1559,8 +1709,8 @@ void launch_accept_commit(hawk_ctx* c, int k, const UniformSrc& us) {
         auto kern = fast_e(c) == 4 ? accept_commit_fast<4> : (fast_e(c) == 8 ? accept_commit_fast<8> : accept_commit_fast<16>);
         kern<<<c->B, NT, 0, c->stream>>>(
             wsp<float>(c, c->off.logit_b), wsp<float>(c, c->off.dlogit_b), wsp<WarpStat>(c, c->off.pstat),
-            wsp<WarpStat>(c, c->off.qstat), wsp<int32_t>(c, c->off.k_eff), wsp<int32_t>(c, c->off.draft),
-            wsp<int32_t>(c, c->off.grid), wsp<int32_t>(c, c->off.n), wsp<uint32_t>(c, c->off.x),
+            wsp<WarpStat>(c, c->off.qstat), wsp<int32_t>(c, c->off.llen), wsp<int32_t>(c, c->off.lidx), wsp<double>(c, c->off.lw),
+            wsp<int32_t>(c, c->off.k_eff), wsp<int32_t>(c, c->off.draft), wsp<int32_t>(c, c->off.grid), wsp<int32_t>(c, c->off.n), wsp<uint32_t>(c, c->off.x),
             wsp<uint32_t>(c, c->off.hprev), (int)(c->d * c->asz / 4), wsp<int32_t>(c, c->off.out_na),
             wsp<int32_t>(c, c->off.out_tok), wsp<unsigned long long>(c, c->off.counters), k, c->S, samp_params(c), us);
         return;
@@ -1598,7 +1748,12 @@ int launch_sample_rows(const float* logits, const int32_t* skip, const float* u,
     return hipGetLastError() == hipSuccess ? HAWK_OK : HAWK_EDEVICE;
 }
 
-size_t multi_verify_workspace_bytes(int rows, int m) { return (size_t)rows * (m + 1) * sizeof(WarpStat); }
+// Statistics of every row; with the target rows' lists behind them (see ListStore).
+static size_t multi_stats_bytes(int rows, int m) { return ((size_t)rows * (m + 1) * sizeof(WarpStat) + 255) & ~(size_t)255; }
+size_t multi_verify_workspace_bytes(int rows, int m) { return multi_stats_bytes(rows, m) + (size_t)rows * ((size_t)kCap * 12 + 16); }
+size_t list_len_bytes(size_t rows) { return rows * sizeof(int32_t); }
+size_t list_idx_bytes(size_t rows) { return rows * kCap * sizeof(int32_t); }
+size_t list_w_bytes(size_t rows) { return rows * kCap * sizeof(double); }
 
 int launch_multi_verify(const float* p_logits, const float* q_logits, const int32_t* cand, const float* u_acc,
                         const float* u_final, const int32_t* m_rows, int rows, int m, int n, float temperature, int top_k,
@@ -1609,13 +1764,22 @@ int launch_multi_verify(const float* p_logits, const float* q_logits, const int3
     const int greedy = (temperature == 0.0f || top_k == 1) ? 1 : 0;
     const float inv_t = greedy ? 1.0f : 1.0f / temperature;
     const int tk = top_k < n ? top_k : n;
-    if (use_list(tk, n, greedy) && workspace && workspace_bytes >= multi_verify_workspace_bytes(rows, m)) {
+    const size_t stat_bytes = (size_t)rows * (m + 1) * sizeof(WarpStat);
+    if (use_list(tk, n, greedy) && workspace && workspace_bytes >= stat_bytes) {
         WarpStat* stats = static_cast<WarpStat*>(workspace);
+        // room for the lists too: weights first (8-byte entries), then indices and lengths
+        double* lw = nullptr;
+        int32_t *lidx = nullptr, *llen = nullptr;
+        if (workspace_bytes >= multi_verify_workspace_bytes(rows, m) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
+            lw = reinterpret_cast<double*>(static_cast<char*>(workspace) + multi_stats_bytes(rows, m));
+            lidx = reinterpret_cast<int32_t*>(lw + (size_t)rows * kCap);
+            llen = lidx + (size_t)rows * kCap;
+        }
         auto k1 = E == 4 ? multi_row_stats_kernel<4> : (E == 8 ? multi_row_stats_kernel<8> : multi_row_stats_kernel<16>);
         auto k2 = E == 4 ? multi_verify_walk_kernel<4> : (E == 8 ? multi_verify_walk_kernel<8> : multi_verify_walk_kernel<16>);
-        k1<<<dim3(m + 1, rows), NT, 0, stream>>>(p_logits, q_logits, m_rows, m, n, inv_t, tk, stats);
-        k2<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, stats, out_index, out_token,
-                                    out_resid);
+        k1<<<dim3(m + 1, rows), NT, 0, stream>>>(p_logits, q_logits, m_rows, m, n, inv_t, tk, stats, llen, lidx, lw);
+        k2<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, stats, llen, lidx, lw, out_index,
+                                    out_token, out_resid);
     } else if (use_list(tk, n, greedy)) {
         auto kern = E == 4 ? multi_verify_list_kernel<4> : (E == 8 ? multi_verify_list_kernel<8> : multi_verify_list_kernel<16>);
         kern<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, tk, out_index, out_token,
@@ -1663,7 +1827,7 @@ int launch_multi_verify_static(const float* p_logits, const float* q_logits, con
     // every record the second launch reads is written by the first launch of the same call, so
     // nothing in the array has to be cleared between calls
     return launch_multi_verify(p_logits, q_logits, cand, u_acc, u_final, m_rows, rows, m, n, temperature, top_k, out_index,
-                               out_token, out_resid, ws, multi_verify_workspace_bytes(rows, m), stream);
+                               out_token, out_resid, ws, (size_t)rows * (m + 1) * sizeof(WarpStat), stream);
 }
 
 }  // namespace hawk
