@@ -157,9 +157,12 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     o.tree = take(TreeArea(B).bytes);
     o.llen = take(list_len_bytes(B * ks)); o.lidx = take(list_idx_bytes(B * ks)); o.lw = take(list_w_bytes(B * ks));
     const size_t widest = 3 * d > m ? 3 * d : m;
-    c->split_bytes = g->dtype == HAWK_BF16 ? M * widest * 4 : 0;
+    const size_t M16 = (M + 15) & ~(size_t)15;   // planes come in tiles of 16 rows
+    c->split_bytes = g->dtype == HAWK_BF16 ? M16 * widest * 4 : 0;
     o.split = c->split_bytes ? take(c->split_bytes) : 0;
-    o.split2 = c->split_bytes ? take(M * m * 4) : 0;
+    o.split2 = c->split_bytes ? take(M16 * widest * 4) : 0;
+    o.rtab = c->split_bytes ? take((size_t)c->Tmax * (hd / 2) * 8) : 0;
+    o.ssq = c->split_bytes ? take(M16 * (d / 16 + 4) * 4) : 0;
     // Tile-major copy of every GEMM weight (16 x 32 tiles, 1 KB each, in MFMA operand order): the
     // MFMA kernels then fetch whole kilobytes per request instead of 64-byte pieces of 16 rows.
     c->n_gpk = 0;
@@ -200,16 +203,14 @@ void run_layers(hawk_ctx* c, const RowMap& map, int M) {
     const Offsets& o = c->off;
     const int d = c->d, m = c->m;
     for (int l = 0; l < c->L; ++l) {
-        launch_rmsnorm(c, o.x, d, c->w.g1[l], o.a, M, true);
+        launch_rmsnorm(c, o.x, d, c->w.g1[l], o.a, M);
         launch_gemm(c, o.a, d, c->w.Wqkv[l], 3 * d, d, o.qkv, 3 * d, M, false, false);
-        if (!attention_does_rope(c, map)) launch_rope_append(c, map, l, M);
+        launch_rope_append(c, map, l, M);
         launch_attention(c, map, l, M);
         launch_gemm(c, o.o, d, c->w.Wo[l], d, d, o.x, d, M, true, false);
-        launch_rmsnorm(c, o.x, d, c->w.g2[l], o.a, M, true);
-        if (!launch_gemm_swiglu(c, o.a, d, c->w.W13[l], m, d, o.u, M)) {
-            launch_gemm(c, o.a, d, c->w.W13[l], 2 * m, d, o.u, 2 * m, M, false, false);
-            launch_swiglu(c, M);
-        }
+        launch_rmsnorm(c, o.x, d, c->w.g2[l], o.a, M);
+        launch_gemm(c, o.a, d, c->w.W13[l], 2 * m, d, o.u, 2 * m, M, false, false);
+        launch_swiglu(c, M);
         launch_gemm(c, o.u, 2 * m, c->w.W2[l], d, m, o.x, d, M, true, false);
     }
 }
@@ -220,7 +221,7 @@ size_t slice_off(const hawk_ctx* c) { return c->w.W_out + (size_t)c->cfg.samp_lo
 void run_step_rows(hawk_ctx* c, int k) {
     const int M = c->S * (k + 1);
     RowMap map = step_map(c, k);
-    launch_embed_rows(c, map, M);
+    if (xcd_ok(c, k) || stream_ok(c, k) || !rows_ok(c)) launch_embed_rows(c, map, M);
     if (xcd_ok(c, k)) {  // one persistent kernel laid out on the XCDs: all layers and the output projection
         if (c->kev_a) (void)hipEventRecord(c->kev_a, c->stream);
         if (launch_verify_xcd(c, k) != 0) c->launch_failed = 1;
@@ -239,8 +240,12 @@ void run_step_rows(hawk_ctx* c, int k) {
     }
     c->last_path = 0;
     c->last_kernel = 0;
+    if (rows_ok(c)) {
+        rows_step_pass(c, map, M);
+        return;
+    }
     run_layers(c, map, M);
-    launch_rmsnorm(c, c->off.x, c->d, c->w.g_f, c->off.a, M, true);
+    launch_rmsnorm(c, c->off.x, c->d, c->w.g_f, c->off.a, M);
     launch_gemm(c, c->off.a, c->d, slice_off(c), c->Vs, c->d, c->off.logit_s, c->Vs, M, false, true);
 }
 
@@ -251,6 +256,12 @@ void enqueue_draft(hawk_ctx* c, int k, const UniformSrc& us, const DraftMode& dm
         if (stream_draft_ok(c)) {  // one persistent kernel: W_d, final norm, output projection
             const size_t prev = (i == 1) ? c->off.hprev : (((i - 1) & 1) ? c->off.g1 : c->off.g0);
             if (launch_draft_stream(c, i, prev, g) != 0) c->launch_failed = 1;
+            launch_draft_sample(c, i, k, us, dm);
+            continue;
+        }
+        if (rows_ok(c)) {
+            const size_t prev = (i == 1) ? c->off.hprev : (((i - 1) & 1) ? c->off.g1 : c->off.g0);
+            rows_draft_pass(c, i, prev, g);
             launch_draft_sample(c, i, k, us, dm);
             continue;
         }
@@ -300,6 +311,13 @@ int enqueue_prefill(hawk_ctx* c, const float* cond, const float* uncond, int bat
     RowMap map;
     map.mode = 0; map.rows_per_seq = n_cond; map.n_seq = c->S; map.batch = c->B; map.n_cond = n_cond;
     map.n = nullptr; map.k_eff = nullptr; map.tree_depth = nullptr; map.tree_anc = nullptr;
+    if (rows_ok(c)) {
+        rows_prompt_pass(c, map, M);
+        launch_keep_hprev_prefill(c);
+        launch_first_token(c, us);
+        HIP_TRY(c, hipGetLastError());
+        return HAWK_OK;
+    }
     launch_cond_rows(c, M);
     run_layers(c, map, M);
     launch_keep_hprev_prefill(c);
@@ -401,6 +419,10 @@ int hawk_create(const hawk_config* cfg, void* workspace, size_t workspace_bytes,
     for (int j = 0; j < c->hd / 2; ++j) f[j] = pow((double)c->cfg.rope_theta, -2.0 * j / (double)c->hd);
     if (hipMemcpyAsync(c->ws + c->off.inv_freq, f, (size_t)(c->hd / 2) * 8, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess) {
+        hawk_destroy(c);
+        return HAWK_EDEVICE;
+    }
+    if (rows_fill_rope(c) != 0) {
         hawk_destroy(c);
         return HAWK_EDEVICE;
     }
@@ -754,8 +776,8 @@ int hawk_verify_tree(hawk_ctx* c, int depth, const int32_t* m_depth, const int32
         map.tree_depth = wsp<int32_t>(c, t0 + ta.depth);
         map.tree_anc = wsp<unsigned long long>(c, t0 + ta.anc);
         const int M = c->S * n_nodes;
-        c->presplit_off = 0;
-        launch_embed_rows(c, map, M);
+        const bool persistent = xcd_ok(c, n_nodes - 1) || stream_tree_ok(c, n_nodes);
+        if (persistent || !rows_ok(c)) launch_embed_rows(c, map, M);
         if (xcd_ok(c, n_nodes - 1)) {       // one persistent kernel, laid out on the XCDs: all layers and the output projection
             if (launch_verify_xcd(c, n_nodes - 1, map.tree_depth, map.tree_anc) != 0) c->launch_failed = 1;
             c->last_path = 1;
@@ -767,9 +789,13 @@ int hawk_verify_tree(hawk_ctx* c, int depth, const int32_t* m_depth, const int32
         } else {                            // one kernel per operation
             c->last_path = 0;
             c->last_kernel = 0;
-            run_layers(c, map, M);
-            launch_rmsnorm(c, c->off.x, c->d, c->w.g_f, c->off.a, M, true);
-            launch_gemm(c, c->off.a, c->d, slice_off(c), c->Vs, c->d, c->off.logit_s, c->Vs, M, false, true);
+            if (rows_ok(c)) {
+                rows_step_pass(c, map, M);
+            } else {
+                run_layers(c, map, M);
+                launch_rmsnorm(c, c->off.x, c->d, c->w.g_f, c->off.a, M);
+                launch_gemm(c, c->off.a, c->d, slice_off(c), c->Vs, c->d, c->off.logit_s, c->Vs, M, false, true);
+            }
         }
         HIP_TRY(c, hipGetLastError());
         // The walk, on the device: per depth, the row of the node each prompt stands on is gathered as

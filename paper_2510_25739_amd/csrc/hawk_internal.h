@@ -61,7 +61,9 @@ struct Offsets {  // byte offsets into the workspace
     size_t u_draft, u_acc, u_fin, out_na, out_tok, inv_freq, replay, cond;
     size_t tree;    // candidate tree of a tree pass: int32 depth[64], then uint64 ancestors[64], then walk state
     size_t split;   // bf16 hi / lo planes of a GEMM input (batched shapes; 0: not present)
-    size_t split2;  // second pair of planes: written by a GEMM's own epilogue while it reads the first
+    size_t split2;  // second region of planes: written by a product's own epilogue while it reads the first
+    size_t rtab;    // rotary table [Tmax][hd / 2] (cos, sin) of the many-rows path (0: not present)
+    size_t ssq;     // partial sums of squares of the residual stream, [row][d / 16]
     size_t llen, lidx, lw;   // lists of the kept entries of the last verify pass's rows (sampling.hip: ListStore), [B][k_max + 1]
     size_t gpack;   // tile-major copy of the GEMM weights for the MFMA GEMM / GEMV kernels (0: not present)
     size_t total;
@@ -105,8 +107,6 @@ struct hawk_ctx {
     // matrices in the tile-major copy; pairs = m for W1|W3 stored with rows interleaved (W1 row f, W3 row f, ...)
     struct { size_t blob_off, pack_off; int N, K, pairs; } gpk[4 * 128 + 2];
     int n_gpk;
-    size_t presplit_off;  // activation buffer whose bf16 planes are current (presplit_M rows of presplit_K), 0: none
-    int presplit_M, presplit_K, presplit_buf;
     // per image
     int B, S, C, gh, gw, N, top_k, greedy;
     float temperature, inv_t, cfg_scale;
@@ -140,43 +140,50 @@ template <typename T> inline T* wsp(hawk_ctx* c, size_t off) { return reinterpre
 void launch_embed_rows(hawk_ctx*, const RowMap&, int M);
 void launch_cond_rows(hawk_ctx*, int M);                       // X <- condition vectors
 // out[r] = rmsnorm(in[r * in_stride ...]) * gain, r < M (in_stride in elements)
-// for_gemm: the next call is the GEMM that reads the output; its bf16 planes are written here too
-void launch_rmsnorm(hawk_ctx*, size_t off_in, size_t in_stride, size_t off_gain, size_t off_out, int M,
-                    bool for_gemm = false);
+void launch_rmsnorm(hawk_ctx*, size_t off_in, size_t in_stride, size_t off_gain, size_t off_out, int M);
 // Y[M][N] (+)= A[M][K] * W[N][K]^T ; out_f32: store fp32 (logits) instead of activations
 void launch_gemm(hawk_ctx*, size_t off_a, int lda, size_t w_off, int N, int K, size_t off_y,
                  int ldy, int M, bool accumulate, bool out_f32);
-// the same on the MFMA units (bf16, many rows); false if the shape is not covered (gemm.hip)
-bool launch_gemm_mfma(hawk_ctx*, size_t off_a, int lda, size_t w_off, int N, int K, size_t off_y, int ldy, int M,
-                      bool accumulate);
-// A kernel that produces the input of the next GEMM (M rows of K values at off_a) can write that
-// GEMM's bf16 hi / lo planes itself, [row][K] each: true and the planes if such a GEMM takes the
-// MFMA path; the planes then count as current until the next launch_gemm call.
-bool presplit_planes(hawk_ctx*, size_t off_a, int M, int K, uint16_t** hi, uint16_t** lo);
 // fills the tile-major weight copy from the blob (after hawk_load's upload); 0 or -1
 int gemm_pack_weights(hawk_ctx*);
 void launch_rope_append(hawk_ctx*, const RowMap&, int layer, int M);
 void launch_attention(hawk_ctx*, const RowMap&, int layer, int M);
-// true: launch_attention also rotates q, k and appends k, v for these rows (no launch_rope_append)
-bool attention_does_rope(const hawk_ctx*, const RowMap&);
-// U[:, 0..m) = SiLU(A W1^T) * (A W3^T) in one MFMA kernel (and the bf16 planes of the result for the W2
-// GEMM); false: not applicable, the caller runs the GEMM and launch_swiglu
-bool launch_gemm_swiglu(hawk_ctx*, size_t off_a, int lda, size_t w13_off, int m, int K, size_t off_u, int M);
-// Without a context: Y[M][N] = A W^T, A fp32 [M][K] (row stride lda), W bf16 row-major [N][K], on
-// the MFMA kernels.  planes: room for 2 M K bf16 values (the two bf16 planes of A); A == nullptr:
-// the planes are filled already (hi first, then lo).  false: the shape is not supported
-// (K % 64, N % 16, lda % 4, ldy % 4).
-bool gemm_rows_bf16(hipStream_t stream, const float* A, int lda, int M, int K, const uint16_t* W, int N, float* Y,
-                    int ldy, uint16_t* planes);
-// The draft heads' blocks in one launch (at most 16 rows, K % 128 == 0): W holds `blocks` square
-// [K][K] matrices one after the other; G[(r * blocks + j)][K] = A[r] + silu(W_j A[r]) as fp32 and as
-// the two bf16 planes the product that follows reads (planes_g: 2 M blocks K values; planes_a: 2 M K).
-// false: shape not covered, the caller runs the product and the activation separately.
-bool gemm_rows_heads(hipStream_t stream, const float* A, int M, int K, const uint16_t* W, int blocks, float* G,
-                     uint16_t* planes_a, uint16_t* planes_g);
 void launch_swiglu(hawk_ctx*, int M);
 void launch_draft_input(hawk_ctx*, int i);                     // [g | E[left] | E[up]]
 void launch_keep_hprev_prefill(hawk_ctx*);
+
+// ---- many rows of a bf16 context (and the draft heads' products), implemented in rows.hip ----
+// Activations as two bf16 planes, hi and lo, in MFMA operand order: 16 rows x 32 features are 512
+// consecutive values.  kts: features / 32.
+__host__ __device__ inline size_t plane_at(int row, int f, int kts) {
+    return ((size_t)(row >> 4) * kts + (f >> 5)) * 512 + (size_t)(((f >> 3) & 3) * 16 + (row & 15)) * 8 + (f & 7);
+}
+inline size_t plane_halves(int M, int K) { return (size_t)((M + 15) / 16) * 16 * K; }   // values of one plane
+enum { kGemmPlain = 0, kGemmResidual, kGemmSwiglu, kGemmHeads };
+struct RowsGemm {
+    const uint16_t *hi, *lo;   // planes of A
+    const uint16_t* W;         // tile-major copy (packed) or row-major [N][K]
+    int packed, mode, M, N, K; // N % 16 == 0, K % 32 == 0
+    const float* ssq;          // row r of the result is scaled by 1 / sqrt(sum_p ssq[r][p] / norm_d + eps) (ssq_n 0: not scaled)
+    int ssq_ld, ssq_n;
+    float norm_d, eps;
+    float* Y;                  // fp32 result (kGemmResidual: added to; kGemmHeads: may be null)
+    int ldy;
+    uint16_t *ohi, *olo;       // planes of the result (kGemmPlain / kGemmResidual: times gain; may be null)
+    int okts;
+    const uint16_t* gain;
+    float* ossq;               // sums of squares of the result per row and strip of 16 features (may be null)
+    int ossq_ld;
+    const float* resid;        // kGemmHeads: A as fp32 [M][K]
+    int blocks;
+};
+void launch_rows_gemm(hipStream_t, const RowsGemm&);
+void launch_rows_split(hipStream_t, const float* A, int lda, int M, int K, uint16_t* hi, uint16_t* lo);
+bool rows_ok(const hawk_ctx*);               // does the context's shape take this path?
+int rows_fill_rope(hawk_ctx*);               // once per context; 0 = ok
+void rows_step_pass(hawk_ctx*, const RowMap&, int M);     // step or tree rows: embedding, layers, logits to logit_s
+void rows_prompt_pass(hawk_ctx*, const RowMap&, int M);   // condition rows; logits of each sequence's last one
+void rows_draft_pass(hawk_ctx*, int i, size_t off_prev, size_t off_out);   // micro-step i up to its logits
 
 // ---- streaming path, implemented in stream.hip ----
 size_t stream_workspace(const hawk_ctx*, size_t base, StreamOffsets* out);  // extra workspace bytes
@@ -216,6 +223,7 @@ int launch_multi_verify(const float* p_logits, const float* q_logits, const int3
                         int32_t* out_index, int32_t* out_token, double* out_resid, void* workspace,
                         size_t workspace_bytes, hipStream_t stream);
 size_t multi_verify_workspace_bytes(int rows, int m);
+size_t multi_verify_list_workspace_bytes(int rows, int m);   // with room for the target rows' lists as well
 size_t list_len_bytes(size_t rows);   // workspace of the rows' lists: lengths, indices, weights
 size_t list_idx_bytes(size_t rows);
 size_t list_w_bytes(size_t rows);

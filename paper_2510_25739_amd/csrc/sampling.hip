@@ -1748,9 +1748,10 @@ int launch_sample_rows(const float* logits, const int32_t* skip, const float* u,
     return hipGetLastError() == hipSuccess ? HAWK_OK : HAWK_EDEVICE;
 }
 
-// Statistics of every row; with the target rows' lists behind them (see ListStore).
+// Statistics of every row; in a larger workspace the target rows' lists (see ListStore) behind them.
 static size_t multi_stats_bytes(int rows, int m) { return ((size_t)rows * (m + 1) * sizeof(WarpStat) + 255) & ~(size_t)255; }
-size_t multi_verify_workspace_bytes(int rows, int m) { return multi_stats_bytes(rows, m) + (size_t)rows * ((size_t)kCap * 12 + 16); }
+size_t multi_verify_workspace_bytes(int rows, int m) { return (size_t)rows * (m + 1) * sizeof(WarpStat); }
+size_t multi_verify_list_workspace_bytes(int rows, int m) { return multi_stats_bytes(rows, m) + (size_t)rows * ((size_t)kCap * 12 + 16); }
 size_t list_len_bytes(size_t rows) { return rows * sizeof(int32_t); }
 size_t list_idx_bytes(size_t rows) { return rows * kCap * sizeof(int32_t); }
 size_t list_w_bytes(size_t rows) { return rows * kCap * sizeof(double); }
@@ -1764,13 +1765,12 @@ int launch_multi_verify(const float* p_logits, const float* q_logits, const int3
     const int greedy = (temperature == 0.0f || top_k == 1) ? 1 : 0;
     const float inv_t = greedy ? 1.0f : 1.0f / temperature;
     const int tk = top_k < n ? top_k : n;
-    const size_t stat_bytes = (size_t)rows * (m + 1) * sizeof(WarpStat);
-    if (use_list(tk, n, greedy) && workspace && workspace_bytes >= stat_bytes) {
+    if (use_list(tk, n, greedy) && workspace && workspace_bytes >= multi_verify_workspace_bytes(rows, m)) {
         WarpStat* stats = static_cast<WarpStat*>(workspace);
         // room for the lists too: weights first (8-byte entries), then indices and lengths
         double* lw = nullptr;
         int32_t *lidx = nullptr, *llen = nullptr;
-        if (workspace_bytes >= multi_verify_workspace_bytes(rows, m) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
+        if (workspace_bytes >= multi_verify_list_workspace_bytes(rows, m) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
             lw = reinterpret_cast<double*>(static_cast<char*>(workspace) + multi_stats_bytes(rows, m));
             lidx = reinterpret_cast<int32_t*>(lw + (size_t)rows * kCap);
             llen = lidx + (size_t)rows * kCap;
@@ -1827,7 +1827,7 @@ int launch_multi_verify_static(const float* p_logits, const float* q_logits, con
     // every record the second launch reads is written by the first launch of the same call, so
     // nothing in the array has to be cleared between calls
     return launch_multi_verify(p_logits, q_logits, cand, u_acc, u_final, m_rows, rows, m, n, temperature, top_k, out_index,
-                               out_token, out_resid, ws, (size_t)rows * (m + 1) * sizeof(WarpStat), stream);
+                               out_token, out_resid, ws, multi_verify_workspace_bytes(rows, m), stream);
 }
 
 }  // namespace hawk

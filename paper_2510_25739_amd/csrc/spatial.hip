@@ -2,6 +2,8 @@
 // appendix "Draft Heads Structure and Memory Overhead"): the dual-direction heads on the MFMA
 // GEMM kernels, the speculation cache as a ring per (column, depth) in device memory, and the
 // gather of a position's sampling pool.  No context: every entry point takes device pointers.
+#include <string.h>
+
 #include "hawk_internal.h"
 
 namespace hawk {
@@ -10,34 +12,6 @@ namespace {
 
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
-
-// G[(r, j)] = h[r] + silu(Y[r][j d .. j d + d)), written as the two bf16 planes the output-layer
-// GEMM reads (row r * n_heads + j, so that the logits come out as [rows][n_heads][V_s]) and, if
-// asked for, as fp32.  One thread per four features.
-__global__ void head_act_kernel(const float* h, const float* Y, int rows, int n_heads, int d, uint16_t* ghi,
-                                uint16_t* glo, float* g_out) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int d4 = d / 4;
-    if (i >= (size_t)rows * n_heads * d4) return;
-    const size_t rj = i / d4;                 // r * n_heads + j
-    const int f = (int)(i - rj * d4) * 4;
-    const size_t r = rj / n_heads;
-    const float4 x = *reinterpret_cast<const float4*>(h + r * d + f);
-    const float4 y = *reinterpret_cast<const float4*>(Y + rj * d + f);   // Y is [rows][n_heads * d]
-    float4 g;
-    g.x = x.x + y.x / (1.0f + expf(-y.x));
-    g.y = x.y + y.y / (1.0f + expf(-y.y));
-    g.z = x.z + y.z / (1.0f + expf(-y.z));
-    g.w = x.w + y.w / (1.0f + expf(-y.w));
-    unsigned h0, h1, h2, h3, l0, l1, l2, l3;
-    bf16_split(g.x, h0, l0);
-    bf16_split(g.y, h1, l1);
-    bf16_split(g.z, h2, l2);
-    bf16_split(g.w, h3, l3);
-    *reinterpret_cast<uint2*>(ghi + rj * d + f) = make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
-    *reinterpret_cast<uint2*>(glo + rj * d + f) = make_uint2(l0 | (l1 << 16), l2 | (l3 << 16));
-    if (g_out) *reinterpret_cast<float4*>(g_out + rj * d + f) = g;
-}
 
 // ---- speculation cache ----
 // A prediction of depth dep for the position (row, col) waits in slot
@@ -135,9 +109,10 @@ bool cache_args_ok(int IW, int IH, int VSD, int Vs) {
 
 }  // namespace
 
+// planes of h, planes of g (and room for g itself, which the caller may want to look at)
 size_t spatial_heads_workspace_bytes(int rows, int n_heads, int d) {
     const size_t M = (size_t)rows * n_heads;
-    return align_up(M * d * sizeof(float)) + align_up(2 * (size_t)rows * d * 2) + align_up(2 * M * d * 2);
+    return align_up(M * d * sizeof(float)) + align_up(4 * plane_halves(rows, d)) + align_up(4 * plane_halves((int)M, d));
 }
 
 int launch_spatial_heads(const float* h, const uint16_t* W_heads, const uint16_t* W_out, int rows, int n_heads, int d,
@@ -149,22 +124,23 @@ int launch_spatial_heads(const float* h, const uint16_t* W_heads, const uint16_t
          reinterpret_cast<uintptr_t>(g_out) | reinterpret_cast<uintptr_t>(W_heads) | reinterpret_cast<uintptr_t>(W_out)) & 15)
         return HAWK_EINVAL;
     const int M = rows * n_heads;
-    char* w = static_cast<char*>(workspace);
-    float* Y = reinterpret_cast<float*>(w);
-    w += align_up((size_t)M * d * sizeof(float));
+    char* w = static_cast<char*>(workspace) + align_up((size_t)M * d * sizeof(float));
     uint16_t* hplanes = reinterpret_cast<uint16_t*>(w);
-    w += align_up(2 * (size_t)rows * d * 2);
+    w += align_up(4 * plane_halves(rows, d));
     uint16_t* gplanes = reinterpret_cast<uint16_t*>(w);
-    // every head's linear layer in one product, Y[r][j d + f] = (W_j h_r)[f], with the residual and
-    // the activation in its epilogue where the shape allows (the workspace's Y then holds g)
-    if (!gemm_rows_heads(stream, h, rows, d, W_heads, n_heads, g_out ? g_out : Y, hplanes, gplanes)) {
-        if (!gemm_rows_bf16(stream, h, d, rows, d, W_heads, n_heads * d, Y, n_heads * d, hplanes)) return HAWK_EINVAL;
-        const size_t total = (size_t)M * (d / 4);
-        head_act_kernel<<<(unsigned)((total + 255) / 256), 256, 0, stream>>>(h, Y, rows, n_heads, d, gplanes,
-                                                                            gplanes + (size_t)M * d, g_out);
-    }
-    // the shared output layer over all (row, head) pairs
-    if (!gemm_rows_bf16(stream, nullptr, d, M, d, W_out, Vs, q_logits, Vs, gplanes)) return HAWK_EINVAL;
+    launch_rows_split(stream, h, d, rows, d, hplanes, hplanes + plane_halves(rows, d));
+    // every head's linear layer in one product, with the residual and the activation in its epilogue: row
+    // (r, j) of g = h[r] + silu(W_j h[r]) leaves it as planes
+    RowsGemm g;
+    memset(&g, 0, sizeof g);
+    g.hi = hplanes; g.lo = hplanes + plane_halves(rows, d); g.W = W_heads; g.mode = kGemmHeads; g.M = rows; g.N = n_heads * d; g.K = d;
+    g.resid = h; g.blocks = n_heads; g.Y = g_out; g.ohi = gplanes; g.olo = gplanes + plane_halves(M, d); g.okts = d / 32;
+    launch_rows_gemm(stream, g);
+    // the shared output layer over all (row, head) pairs: the logits come out as [rows][n_heads][V_s]
+    memset(&g, 0, sizeof g);
+    g.hi = gplanes; g.lo = gplanes + plane_halves(M, d); g.W = W_out; g.mode = kGemmPlain; g.M = M; g.N = Vs; g.K = d;
+    g.Y = q_logits; g.ldy = Vs;
+    launch_rows_gemm(stream, g);
     return hipGetLastError() == hipSuccess ? HAWK_OK : HAWK_EDEVICE;
 }
 
