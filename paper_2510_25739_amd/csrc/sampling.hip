@@ -526,6 +526,7 @@ __global__ void force_commit_kernel(const int32_t* forced, int32_t* grid, int32_
 // A word of Slots may be written again once every thread has passed a barrier after reading it.
 
 constexpr int kBins = NT;    // bins of the first, linear cut of the value range
+constexpr float kMinRange = 1e-30f;   // narrower rows take the radix select: 1024 / range must be finite, or bins are not
 constexpr int kCand = 256;   // entries of the threshold's bin that are ranked directly
 constexpr int kTopCap = 2048;               // largest top-k that takes the list form
 constexpr int kCap = kTopCap + kCand;       // entries of a list: the kept ones and the rest of the threshold's bin
@@ -857,7 +858,7 @@ __device__ __forceinline__ void cut_row(const float (&z)[E], int n, int K, FastS
     row_minmax<E>(z, gmin, gmax, fs);
     pending = false;
     tag = -1;
-    if (gmax > gmin && gmin > -INFINITY && gmax < INFINITY) {
+    if (gmax - gmin > kMinRange && gmin > -INFINITY && gmax < INFINITY) {
         linear_bins<E>(z, gmin, gmax, hi);
 #pragma unroll
         for (int e = 0; e < E; ++e) atomicAdd(&fs.hist[hi[e]], 1u);
@@ -1130,7 +1131,8 @@ __device__ __forceinline__ WarpStat warp_and_draw(const float (&z)[E], int n, in
         }
         if (u) {
             st.total = list_scan(w, Kc, c, fs.s.scan[0]);
-            *drawn = L.e[list_pick(w, c, (double)*u * st.total, fs.s, fs.sh)].x;
+            const int at = list_pick(w, c, (double)*u * st.total, fs.s, fs.sh);
+            *drawn = Kc > 0 ? L.e[at].x : 0;   // NaN logits may leave nothing: still a token of the slice
         } else {
             st.total = sum1(sum3(w), fs.s.sum);
         }
@@ -1281,7 +1283,7 @@ __global__ __launch_bounds__(NT) void accept_commit_fast(
             (void)list_scan(w, Kc, c, sl.scan[1]);
             at = list_pick(w, c, (double)uf * ps.total, sl, sh);
         }
-        y = src.idx[at];
+        y = Kc > 0 ? src.idx[at] : 0;
     } else {
         double w[E];
 #pragma unroll

@@ -1,0 +1,127 @@
+"""GPU parity of the many-row passes (prompt rows and teacher-forced step rows of several sequences) against a
+plain float64 forward, at sizes that take each of the products' kernels, both attention kernels and ragged
+row counts; and of the sampling kernels' selection on rows whose value range it cannot cut linearly.
+
+The bound on hidden states: a cache entry is fp16 (2^-11 relative), activations travel as bf16 pairs (2^-17),
+sums are fp32.  The cache dominates: keys and values of relative error 2^-12 (round to nearest, on average half of it) and
+weights whose scores of order one shift by as much change an attention output by about 2^-11 of its size, and
+the output's share in the residual stream is below one: 2^-11 per layer, 1e-3 for the two layers here.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import torch
+    import paper_2510_25739_amd as H
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return H
+
+
+def reference(s, blob, x):
+    """Residual stream after all layers for rows x [sequence, position, d], causal, in float64."""
+    import torch
+    t = lambda name: torch.from_numpy(np.asarray(synth.blob_tensor(s, blob, name), dtype=np.float64))
+    x = torch.from_numpy(x.astype(np.float64))
+    S, T, d = x.shape
+    nh, hd = s.n_heads, s.head_dim
+    ang = torch.arange(T, dtype=torch.float64)[:, None] * s.rope_theta ** (-torch.arange(0, hd, 2, dtype=torch.float64) / hd)
+    cos, sin = torch.cos(ang), torch.sin(ang)
+    norm = lambda v, g: v / torch.sqrt((v * v).mean(-1, keepdim=True) + s.rms_eps) * g
+
+    def heads(v, rotate):
+        v = v.view(S, T, nh, hd).transpose(1, 2)
+        if not rotate:
+            return v
+        a, b = v[..., 0::2], v[..., 1::2]
+        return torch.stack((a * cos - b * sin, a * sin + b * cos), dim=-1).reshape(S, nh, T, hd)
+
+    hidden = torch.full((T, T), float("-inf"), dtype=torch.float64).triu(1)
+    for l in range(s.n_layers):
+        a = norm(x, t(f"l{l}.g1"))
+        q, k, v = (heads(a @ t(f"l{l}.{w}").T, w != "Wv") for w in ("Wq", "Wk", "Wv"))
+        p = torch.softmax(q @ k.transpose(2, 3) / hd ** 0.5 + hidden, dim=-1)
+        x = x + (p @ v).transpose(1, 2).reshape(S, T, d) @ t(f"l{l}.Wo").T
+        a = norm(x, t(f"l{l}.g2"))
+        x = x + (torch.nn.functional.silu(a @ t(f"l{l}.W1").T) * (a @ t(f"l{l}.W3").T)) @ t(f"l{l}.W2").T
+    return x.numpy()
+
+
+def relative(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def hidden_pair(H, s, chunk):
+    """Hidden states of the prompt rows and of a teacher-forced chunk of every sequence, and their reference."""
+    blob = synth.make_weights(s, seed=4, std=0.05)
+    hk = H.Hawk(H.HawkConfig.from_shape(s, k_max=max(chunk - 1, 0)))
+    hk.load(blob)
+    hk.set_path(0)
+    cond = synth.make_cond(s, seed=2)
+    unc = synth.make_cond(s, seed=3) if s.use_cfg else None
+    hk.prefill(cond, unc, s.grid_h, s.grid_w, 1.0, s.top_k, s.cfg_scale, np.full(s.batch, 0.5, np.float32))
+    got = [hk.last_hidden(s.n_cond).cpu().numpy().reshape(s.n_seq, s.n_cond, -1)]
+    tok = np.zeros((s.batch, chunk), np.int64)
+    tok[:, 0] = hk.grid()[:, 0]                  # the chunk's first row is the last committed token
+    forced = np.random.Generator(np.random.PCG64(5)).integers(0, s.vocab, size=(s.batch, chunk)).astype(np.int32)
+    tok[:, 1:] = forced[:, :-1]
+    hk.force([1] * s.batch, forced)
+    got.append(hk.last_hidden(chunk).cpu().numpy().reshape(s.n_seq, chunk, -1))
+    x0 = cond if unc is None else np.concatenate([cond, unc])
+    emb = np.asarray(synth.blob_tensor(s, blob, "E"))[np.tile(tok, (s.n_seq // s.batch, 1))]
+    return np.concatenate(got, axis=1), reference(s, blob, np.concatenate([x0, emb], axis=1))
+
+
+BASE = synth.HawkShape("rows", 2, 256, 4, 704, 1024, 16, 8, 8, 5, top_k=50)
+SHAPES = [
+    # d_model, heads, d_mlp, prompts, guidance, n_cond, chunk
+    (256, 4, 704, 1, 1.0, 1, 1),       # one row everywhere
+    (256, 2, 704, 1, 1.0, 65, 17),     # heads of 128; one row past a group of 64 keys and past a tile of 16 step rows
+    (256, 4, 704, 3, 1.0, 67, 33),     # ragged tiles of (1, 1), (2, 1), (4, 1); three tiles of step rows
+    (256, 4, 704, 10, 1.0, 50, 6),     # (2, 2), (4, 3)
+    (256, 4, 704, 32, 1.0, 63, 2),     # (4, 2), (4, 3) two to a unit
+    (512, 4, 1376, 13, 2.0, 50, 3),    # (4, 4), LDS-staged (8, 8); heads of 128
+    (512, 8, 1376, 32, 1.0, 63, 2),    # LDS-staged (16, 8) with a ragged last group
+    (768, 12, 2048, 16, 2.0, 100, 2),  # LDS-staged (20, 12)
+    (512, 8, 1376, 32, 1.0, 100, 2),   # LDS-staged (10, 8) for the projections and the MLP
+]
+
+
+@pytest.mark.parametrize("d,heads,mlp,batch,scale,n_cond,chunk", SHAPES)
+def test_many_row_passes_match_a_float64_forward(H, d, heads, mlp, batch, scale, n_cond, chunk):
+    s = BASE.replace(d_model=d, n_heads=heads, d_mlp=mlp, batch=batch, cfg_scale=scale, n_cond=n_cond, grid_w=max(8, chunk))
+    got, ref = hidden_pair(H, s, chunk)
+    prompt, step = relative(got[:, :n_cond], ref[:, :n_cond]), relative(got[:, n_cond:], ref[:, n_cond:])
+    print(f"rows {s.n_seq * n_cond} + {s.n_seq * chunk}: relative error prompt {prompt:.2e}, step {step:.2e}")
+    assert prompt < 1e-3 and step < 1e-3
+
+
+HARD_ROWS = {
+    "narrower than a bin can resolve": lambda rng, n: (rng.integers(0, 3, n) * 1e-38).astype(np.float32),
+    "all equal": lambda rng, n: np.zeros(n, np.float32),
+    "few values": lambda rng, n: rng.integers(0, 4, n).astype(np.float32),
+    "masked with -inf": lambda rng, n: np.where((rng.random(n) < 0.99) & (np.arange(n) > 3), -np.inf, rng.standard_normal(n)).astype(np.float32),
+    "masked with the lowest value": lambda rng, n: np.where((rng.random(n) < 0.99) & (np.arange(n) > 3), np.finfo(np.float32).min, rng.standard_normal(n)).astype(np.float32),
+    "one far outlier": lambda rng, n: np.concatenate([[1e6], rng.standard_normal(n - 1)]).astype(np.float32),
+}
+
+
+@pytest.mark.parametrize("n,top_k", [(257, 40), (4097, 64), (8192, 1000), (8193, 2048), (16384, 3000)])
+@pytest.mark.parametrize("kind", HARD_ROWS)
+def test_selection_on_rows_without_a_useful_linear_cut(H, kind, n, top_k):
+    import torch
+    rng = np.random.Generator(np.random.PCG64(n))
+    rows = np.stack([HARD_ROWS[kind](rng, n) for _ in range(4)])
+    u = np.array([0.0, 0.3, 0.77, 1.0 - 2.0 ** -24], np.float32)
+    got = H.sample_rows(torch.from_numpy(rows).cuda(), torch.from_numpy(u).cuda(), 1.0, top_k).cpu().numpy()
+    want = []
+    for r in range(4):
+        w, z = oracle.warp(rows[r], 1.0, top_k)
+        want.append(oracle.inv_cdf(w, z, float(u[r])))
+    np.testing.assert_array_equal(got, want)
