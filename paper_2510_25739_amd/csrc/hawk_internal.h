@@ -65,7 +65,7 @@ struct Offsets {  // byte offsets into the workspace
     size_t rtab;    // rotary table [Tmax][hd / 2] (cos, sin) of the many-rows path (0: not present)
     size_t ssq;     // partial sums of squares of the residual stream, [row][d / 16]
     size_t llen, lidx, lw;   // lists of the kept entries of the last verify pass's rows (sampling.hip: ListStore), [B][k_max + 1]
-    size_t gpack;   // tile-major copy of the GEMM weights for the MFMA GEMM / GEMV kernels (0: not present)
+    size_t gpack;   // tile-major copy of the GEMM weights for the products of rows.hip (0: not present)
     size_t total;
 };
 

@@ -779,8 +779,8 @@ template <int WN, int WM, int SR, int CT, int S, int MODE> static void launch_st
     constexpr int BS = WN * SR, BT = WM * CT, lds = S * (BS + 2 * BT) * 1024;
     const int strips = g.N / 16, tiles = (g.M + 15) / 16, total = ((strips + BS - 1) / BS) * ((tiles + BT - 1) / BT);
     auto k = rows_gemm_staged_kernel<WN, WM, SR, CT, S, MODE>;
-    static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    (void)once;   // a failure shows as a failed launch
+    // per launch: the attribute belongs to the current device; a failure shows as a failed launch
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     k<<<(total + 7) / 8 * 8, 64 * WN * WM, lds, stream>>>(g);
 }
 template <bool PACKED, int MODE> static void launch_rows_gemm_as(hipStream_t stream, const RowsGemm& g) {
