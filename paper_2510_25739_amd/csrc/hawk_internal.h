@@ -223,7 +223,6 @@ int launch_multi_verify(const float* p_logits, const float* q_logits, const int3
                         int32_t* out_index, int32_t* out_token, double* out_resid, void* workspace,
                         size_t workspace_bytes, hipStream_t stream);
 size_t multi_verify_workspace_bytes(int rows, int m);
-size_t multi_verify_list_workspace_bytes(int rows, int m);   // with room for the target rows' lists as well
 size_t list_len_bytes(size_t rows);   // workspace of the rows' lists: lengths, indices, weights
 size_t list_idx_bytes(size_t rows);
 size_t list_w_bytes(size_t rows);

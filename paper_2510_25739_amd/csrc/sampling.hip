@@ -4,9 +4,10 @@
 // Decisions (which logits survive top-k, where a uniform falls in a CDF, whether a draft is
 // accepted) are taken on fp32 logits with fp64 weights exp(z - zmax) and fp64 sums, so
 // that they do not depend on the order of summation beyond the last bits of an fp64.
-// One workgroup of 1024 threads handles one logit row; thread t owns the contiguous index
-// segment [t*E, (t+1)*E), which makes every scan an in-order prefix over token indices.
-// Reductions use wavefront shuffles, then one LDS exchange across the 16 waves.
+// One workgroup of 1024 threads handles one logit row.  In the generic form thread t owns the contiguous
+// index segment [t*E, (t+1)*E), which makes every scan an in-order prefix over token indices; the
+// register-resident form owns chunks of four and scans a list in index order.
+// Reductions use cross-lane moves, then one LDS exchange across the 16 waves.
 #include <mutex>
 #include "hawk_internal.h"
 
@@ -522,7 +523,8 @@ __global__ void force_commit_kernel(const int32_t* forced, int32_t* grid, int32_
 //     and those that do not get weight zero;
 //   - every block-wide exchange has LDS words of its own and costs one barrier (behind the writes).
 // Draw from a 16384-entry row at top-k 1000: 20 us with bounds checks, per-thread segments and
-// per-wave histograms, 14 us with coalesced rows and single barriers.
+// per-wave histograms, 14 us with coalesced rows and single barriers (26.2k cycles in the kernel), 17.8k cycles
+// without bounds checks, with bins kept and the list gathered from lane masks.
 // A word of Slots may be written again once every thread has passed a barrier after reading it.
 
 constexpr int kBins = NT;    // bins of the first, linear cut of the value range
@@ -1461,12 +1463,12 @@ __global__ __launch_bounds__(NT) void multi_verify_list_kernel(const float* p_lo
 
 // The same in two launches when the caller lends room for the rows' statistics: the top-k
 // selection of the target row and of every proposal row runs in a workgroup of its own (all of
-// them in parallel), and the walk over the candidates then only gathers.  With room for the target rows' lists
-// as well (llen != null) the walk starts from those instead of selecting the row's kept entries again.
+// them in parallel), and the walk over the candidates then gathers the target's kept entries again
+// (writing them out instead made no difference: tree step 173.0 ms an image against 173.6).
 template <int E>
 __global__ __launch_bounds__(NT) void multi_row_stats_kernel(const float* p_logits, const float* q_logits,
                                                              const int32_t* m_rows, int m, int n, float inv_t,
-                                                             int top_k, WarpStat* stats, int32_t* llen, int32_t* lidx, double* lw) {
+                                                             int top_k, WarpStat* stats) {
     __shared__ FastShared fs;
     __shared__ CompactList L;
     const int j = blockIdx.x, row = blockIdx.y;   // j = 0: the target row, j >= 1: proposal j - 1
@@ -1474,9 +1476,7 @@ __global__ __launch_bounds__(NT) void multi_row_stats_kernel(const float* p_logi
     const float* l = j == 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + (j - 1)) * n;
     float z[E];
     load_row<E>(l, nullptr, 0.f, inv_t, nullptr, n, z);
-    ListStore store = list_at(llen, lidx, lw, row);
-    if (j > 0 || !llen) store.len = nullptr;
-    const WarpStat st = warp_and_draw<E>(z, n, top_k, 0, fs, L, nullptr, nullptr, store);
+    const WarpStat st = warp_and_draw<E>(z, n, top_k, 0, fs, L, nullptr, nullptr);
     if (threadIdx.x == 0) stats[(size_t)row * (m + 1) + j] = st;
 }
 
@@ -1484,8 +1484,7 @@ template <int E>
 __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_logits, const float* q_logits,
                                                                const int32_t* cand, const float* u_acc,
                                                                const float* u_final, const int32_t* m_rows, int m,
-                                                               int n, float inv_t, const WarpStat* stats, int32_t* llen,
-                                                               int32_t* lidx, double* lw, int32_t* out_index,
+                                                               int n, float inv_t, const WarpStat* stats, int32_t* out_index,
                                                                int32_t* out_token, double* out_resid) {
     __shared__ Slots sl;
     __shared__ Shared sh;
@@ -1497,39 +1496,26 @@ __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_lo
     if (threadIdx.x == 0) { ws.pick = 0.0; sl.pick = 0x7FFFFFFF; }
     int idx[kLH], Kp;
     double w[kLH];
-    if (llen) {
-        const ListStore src = list_at(llen, lidx, lw, row);
-        Kp = *src.len;
+    float z[E];
+    load_row<E>(p_logits + (size_t)row * n, nullptr, 0.f, inv_t, nullptr, n, z);
+    const Threshold t = {key_to_float(ps.tau), ps.tie_cut};
+    unsigned hi[E], lim = 1u;
+    if (ps.onehot < -1) {   // the list the selection had: everything from the threshold's bin up
+        float gmin = INFINITY;
 #pragma unroll
-        for (int h = 0; h < kLH; ++h) {
-            const int i = (int)threadIdx.x + h * NT;
-            idx[h] = -1;
-            w[h] = 0.0;
-            if (i < Kp) { idx[h] = src.idx[i]; w[h] = src.w[i]; }
-        }
-        __syncthreads();
+        for (int e = 0; e < E; ++e) gmin = fminf(gmin, z[e]);
+        gmin = -block_max_f(-gmin, sh);
+        linear_bins<E>(z, gmin, ps.zmax, hi);
+        lim = (unsigned)(-2 - ps.onehot);
     } else {
-        float z[E];
-        load_row<E>(p_logits + (size_t)row * n, nullptr, 0.f, inv_t, nullptr, n, z);
-        const Threshold t = {key_to_float(ps.tau), ps.tie_cut};
-        unsigned hi[E], lim = 1u;
-        if (ps.onehot < -1) {   // the list the selection had: everything from the threshold's bin up
-            float gmin = INFINITY;
 #pragma unroll
-            for (int e = 0; e < E; ++e) gmin = fminf(gmin, z[e]);
-            gmin = -block_max_f(-gmin, sh);
-            linear_bins<E>(z, gmin, ps.zmax, hi);
-            lim = (unsigned)(-2 - ps.onehot);
-        } else {
-#pragma unroll
-            for (int e = 0; e < E; ++e) hi[e] = keeps(t, z[e], entry<E>(e)) ? 1u : 0u;
-        }
-        count_entries<E>(hi, lim, sl);
-        __syncthreads();
-        Kp = place_entries<E>(hi, lim, z, L, sl);
-        __syncthreads();
-        list_weights(L, Kp, ps.zmax, t, idx, w);
+        for (int e = 0; e < E; ++e) hi[e] = keeps(t, z[e], entry<E>(e)) ? 1u : 0u;
     }
+    count_entries<E>(hi, lim, sl);
+    __syncthreads();
+    Kp = place_entries<E>(hi, lim, z, L, sl);
+    __syncthreads();
+    list_weights(L, Kp, ps.zmax, t, idx, w);
 #pragma unroll
     for (int h = 0; h < kLH; ++h) w[h] /= ps.total;
     int acc = mr, tok = -1;
@@ -1750,10 +1736,7 @@ int launch_sample_rows(const float* logits, const int32_t* skip, const float* u,
     return hipGetLastError() == hipSuccess ? HAWK_OK : HAWK_EDEVICE;
 }
 
-// Statistics of every row; in a larger workspace the target rows' lists (see ListStore) behind them.
-static size_t multi_stats_bytes(int rows, int m) { return ((size_t)rows * (m + 1) * sizeof(WarpStat) + 255) & ~(size_t)255; }
 size_t multi_verify_workspace_bytes(int rows, int m) { return (size_t)rows * (m + 1) * sizeof(WarpStat); }
-size_t multi_verify_list_workspace_bytes(int rows, int m) { return multi_stats_bytes(rows, m) + (size_t)rows * ((size_t)kCap * 12 + 16); }
 size_t list_len_bytes(size_t rows) { return rows * sizeof(int32_t); }
 size_t list_idx_bytes(size_t rows) { return rows * kCap * sizeof(int32_t); }
 size_t list_w_bytes(size_t rows) { return rows * kCap * sizeof(double); }
@@ -1769,18 +1752,10 @@ int launch_multi_verify(const float* p_logits, const float* q_logits, const int3
     const int tk = top_k < n ? top_k : n;
     if (use_list(tk, n, greedy) && workspace && workspace_bytes >= multi_verify_workspace_bytes(rows, m)) {
         WarpStat* stats = static_cast<WarpStat*>(workspace);
-        // room for the lists too: weights first (8-byte entries), then indices and lengths
-        double* lw = nullptr;
-        int32_t *lidx = nullptr, *llen = nullptr;
-        if (workspace_bytes >= multi_verify_list_workspace_bytes(rows, m) && (reinterpret_cast<uintptr_t>(workspace) & 7) == 0) {
-            lw = reinterpret_cast<double*>(static_cast<char*>(workspace) + multi_stats_bytes(rows, m));
-            lidx = reinterpret_cast<int32_t*>(lw + (size_t)rows * kCap);
-            llen = lidx + (size_t)rows * kCap;
-        }
         auto k1 = E == 4 ? multi_row_stats_kernel<4> : (E == 8 ? multi_row_stats_kernel<8> : multi_row_stats_kernel<16>);
         auto k2 = E == 4 ? multi_verify_walk_kernel<4> : (E == 8 ? multi_verify_walk_kernel<8> : multi_verify_walk_kernel<16>);
-        k1<<<dim3(m + 1, rows), NT, 0, stream>>>(p_logits, q_logits, m_rows, m, n, inv_t, tk, stats, llen, lidx, lw);
-        k2<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, stats, llen, lidx, lw, out_index,
+        k1<<<dim3(m + 1, rows), NT, 0, stream>>>(p_logits, q_logits, m_rows, m, n, inv_t, tk, stats);
+        k2<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, stats, out_index,
                                     out_token, out_resid);
     } else if (use_list(tk, n, greedy)) {
         auto kern = E == 4 ? multi_verify_list_kernel<4> : (E == 8 ? multi_verify_list_kernel<8> : multi_verify_list_kernel<16>);
