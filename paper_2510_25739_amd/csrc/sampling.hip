@@ -516,7 +516,9 @@ __global__ void force_commit_kernel(const int32_t* forced, int32_t* grid, int32_
 // work of one wave.  So:
 //   - entry e of thread t is index (e / 4) * 4096 + 4 t + e % 4 (E / 4 chunks of 16 KB): a wave's
 //     request is one contiguous kilobyte;
-//   - places past the end of the row hold NaN, which no comparison keeps: no bounds checks per entry;
+//   - places past the end of the row hold NaN, which no comparison of values keeps, so that no entry needs a
+//     bounds check.  They share bin 0 with the smallest entries: find_bin takes them off its count, and a list
+//     cut at bin 0 ends at the row's n-th entry (place_entries; they come last in index order);
 //   - an entry's bin of the first, linear cut of the value range is computed once and kept; the entries
 //     at or above the threshold's bin go to a list in LDS with one comparison each, their places counted
 //     from lane masks; which of the few entries of the threshold's bin itself survive is settled meanwhile,
@@ -920,9 +922,10 @@ __device__ __forceinline__ void count_entries(const unsigned (&hi)[E], unsigned 
         if ((threadIdx.x & 63) == 0) sl.cnt[q * NW + (threadIdx.x >> 6)] = c;
     }
 }
-// Writes those entries into the list in index order; returns their number.
+// Writes those entries into the list in index order; returns their number without the places past the end of
+// the row (n entries): where lim is bin 0 these are counted too, behind every entry of the row.
 template <int E>
-__device__ __forceinline__ int place_entries(const unsigned (&hi)[E], unsigned lim, const float (&z)[E], CompactList& L, const Slots& sl) {
+__device__ __forceinline__ int place_entries(const unsigned (&hi)[E], unsigned lim, const float (&z)[E], int n, CompactList& L, const Slots& sl) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int v = lane < 4 * E ? sl.cnt[lane] : 0;   // chunk-major, wave-minor: the order of the indices
     const int inc = wave_incl_scan_i(v);
@@ -941,7 +944,7 @@ __device__ __forceinline__ int place_entries(const unsigned (&hi)[E], unsigned l
                 ++at;
             }
     }
-    return min(__builtin_amdgcn_readlane(inc, 4 * E - 1), kCap);
+    return min(__builtin_amdgcn_readlane(inc, 4 * E - 1), min(n, kCap));
 }
 
 // The list of a top-k row: its length, its largest entry and the exact threshold.
@@ -953,7 +956,7 @@ __device__ __forceinline__ int select_list(const float (&z)[E], int n, int K, Fa
     count_entries<E>(hi, lim, fs.s);
     __syncthreads();
     if (pending) rank_by_waves(fs, fs.count);
-    const int Kc = place_entries<E>(hi, lim, z, L, fs.s);
+    const int Kc = place_entries<E>(hi, lim, z, n, L, fs.s);
     __syncthreads();
     t = ranked_threshold(fs, pending);
     st.tau = fkey(t.tz);
@@ -1513,7 +1516,7 @@ __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_lo
     }
     count_entries<E>(hi, lim, sl);
     __syncthreads();
-    Kp = place_entries<E>(hi, lim, z, L, sl);
+    Kp = place_entries<E>(hi, lim, z, n, L, sl);
     __syncthreads();
     list_weights(L, Kp, ps.zmax, t, idx, w);
 #pragma unroll

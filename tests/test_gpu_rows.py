@@ -125,3 +125,71 @@ def test_selection_on_rows_without_a_useful_linear_cut(H, kind, n, top_k):
         w, z = oracle.warp(rows[r], 1.0, top_k)
         want.append(oracle.inv_cdf(w, z, float(u[r])))
     np.testing.assert_array_equal(got, want)
+
+
+def _uniforms(rng, *shape):
+    return (rng.integers(0, 1 << 24, size=shape).astype(np.float32) / np.float32(1 << 24)).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,top_k", [(64, 63), (257, 40), (257, 256), (1200, 1150), (2000, 1990), (2303, 2047), (8192, 1000), (16384, 3000)])
+@pytest.mark.parametrize("kind", HARD_ROWS)
+def test_candidates_on_rows_without_a_useful_linear_cut(H, kind, n, top_k):
+    # every list and dense form of the recursion on such rows; residual masses are sums of fp64 weights of one row's
+    # mass (1e-13: rounding of up to n additions of terms below one, in another order)
+    import torch
+    rng = np.random.Generator(np.random.PCG64(n + top_k))
+    rows, m = 4, 2
+    p = np.stack([HARD_ROWS[kind](rng, n) for _ in range(rows)])
+    q = np.stack([np.stack([HARD_ROWS[kind](rng, n) for _ in range(m)]) for _ in range(rows)])
+    cand = rng.integers(0, n, size=(rows, m)).astype(np.int32)
+    cand[0] = np.argmax(q[0], axis=1)
+    u_acc, u_fin = _uniforms(rng, rows, m), _uniforms(rng, rows)
+    want = [oracle.multi_verify(p[r], q[r], cand[r], u_acc[r], float(u_fin[r]), 1.0, top_k, want_resid=True) for r in range(rows)]
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    for ws in (None, torch.empty(H.multi_verify_workspace_bytes(rows, m), dtype=torch.uint8, device="cuda:0")):
+        idx, tok, resid = (x.cpu().numpy() for x in H.multi_verify(t(p), t(q), t(cand), t(u_acc), t(u_fin), 1.0, top_k, want_resid=True, workspace=ws))
+        np.testing.assert_array_equal(idx, [w[0] for w in want])
+        np.testing.assert_array_equal(tok, [w[1] for w in want])
+        np.testing.assert_allclose(resid, [w[2] for w in want], rtol=1e-11, atol=1e-13)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("vocab,top_k", [(200, 40), (200, 199), (256, 255)])
+def test_stored_lists_hold_entries_of_the_row_only(H, vocab, top_k, sign):
+    # One output row far larger than the others: its logit is the row's largest or smallest, and where it is the
+    # largest (one of the signs) all others share the lowest bin of the linear cut with the places past the row's
+    # end.  The lists a verify pass leaves are the last arrays of an fp32 context's workspace: lengths, indices, weights.
+    s = synth.CONFIGS[0].replace(vocab=vocab, top_k=top_k, k=3)
+    blob = synth.make_weights(s, seed=1)
+    off, shape = synth.blob_layout(s)["W_out"]
+    blob[off:off + 4 * shape[0] * shape[1]].view(np.float32).reshape(shape)[7] *= sign * 1e5
+    cfg = H.HawkConfig.from_shape(s)
+    hk = H.Hawk(cfg)
+    hk.load(blob)
+    cap, rows = 2048 + 256, s.k + 1                 # entries of a list, rows of a pass
+    up = lambda b: (b + 255) & ~255
+    end = H.workspace_bytes(cfg) + hk._ws_ptr - hk._ws.data_ptr()
+    lw = end - up(rows * cap * 8)
+    lidx = lw - up(rows * cap * 4)
+    llen = lidx - up(rows * 4)
+    rng = np.random.Generator(np.random.PCG64(3))
+    hk.prefill(synth.make_cond(s, seed=2), None, s.grid_h, s.grid_w, 1.0, top_k, 1.0, _uniforms(rng, 1))
+    whole = 0
+    for _ in range(6):
+        hk.draft(s.k, _uniforms(rng, 1, s.k))
+        hk.verify(s.k, _uniforms(rng, 1, s.k), _uniforms(rng, 1))
+        raw = hk._ws.cpu().numpy()
+        length = raw[llen:llen + rows * 4].view(np.int32)
+        idx = raw[lidx:lidx + rows * cap * 4].view(np.int32).reshape(rows, cap)
+        w = raw[lw:lw + rows * cap * 8].view(np.float64).reshape(rows, cap)
+        logits = hk.logits(rows)[0]
+        for r in range(rows):
+            n, low, high = int(length[r]), logits[r].min(), logits[r].max()
+            # without ties the list is everything from the cut's bin up: the whole row where that is the lowest bin
+            bins = ((logits[r] - low) * ((1024 - 0.01) / (high - low))).astype(int)
+            assert n == (bins >= np.sort(bins)[vocab - top_k]).sum() and n >= top_k
+            assert n == vocab or logits[r, 7] < high
+            assert (np.diff(idx[r, :n]) > 0).all() and idx[r, 0] >= 0 and idx[r, n - 1] < vocab
+            assert (w[r, :n] > 0).sum() <= top_k
+            whole += n == vocab
+    print("rows listed whole:", whole)
