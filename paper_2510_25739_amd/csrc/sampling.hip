@@ -562,7 +562,15 @@ struct Threshold { float tz; int cut; };
 __device__ __forceinline__ bool keeps(const Threshold& t, float z, int j) { return z > t.tz || (z == t.tz && j <= t.cut); }
 __device__ __forceinline__ float key_to_float(unsigned k) { return __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k); }
 
-template <int E> __device__ __forceinline__ int entry(int e) { return (e >> 2) * (4 * NT) + (int)threadIdx.x * 4 + (e & 3); }
+// Index of entry e of thread t.  The functions below take t from their caller: a kernel that runs them in a loop
+// over rows passes a value of that iteration (this_thread), or the compiler keeps every entry's address and bounds
+// check in registers across the loop, and spills.
+template <int E> __device__ __forceinline__ int entry(int e, int t) { return (e >> 2) * (4 * NT) + t * 4 + (e & 3); }
+__device__ __forceinline__ int this_thread() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
 
 // Sum over the block of one double per thread.  One barrier.
@@ -639,20 +647,20 @@ __device__ __forceinline__ void rank_candidates(FastShared& fs, unsigned cnt) {
 // The row's guided, scaled logits into registers (and the guided row to `out`); NaN past the end.
 template <int E>
 __device__ __forceinline__ void load_row(const float* lc, const float* lu, float scale, float inv_t, float* out, int n,
-                                         float (&z)[E]) {
+                                         float (&z)[E], int th = (int)threadIdx.x) {
     const float nan = __uint_as_float(0x7FC00000u);
     if ((n & 3) == 0 && ((reinterpret_cast<uintptr_t>(lc) | reinterpret_cast<uintptr_t>(lu) | reinterpret_cast<uintptr_t>(out)) & 15) == 0) {
         float4 a[E / 4], u[E / 4];
 #pragma unroll
         for (int q = 0; q < E / 4; ++q) {
-            const int j = entry<E>(4 * q);
+            const int j = entry<E>(4 * q, th);
             a[q] = make_float4(nan, nan, nan, nan);
             if (j < n) a[q] = *reinterpret_cast<const float4*>(lc + j);
             if (lu && j < n) u[q] = *reinterpret_cast<const float4*>(lu + j);
         }
 #pragma unroll
         for (int q = 0; q < E / 4; ++q) {
-            const int j = entry<E>(4 * q);
+            const int j = entry<E>(4 * q, th);
             if (lu && j < n) {
                 a[q].x = fmaf(scale, a[q].x - u[q].x, u[q].x); a[q].y = fmaf(scale, a[q].y - u[q].y, u[q].y);
                 a[q].z = fmaf(scale, a[q].z - u[q].z, u[q].z); a[q].w = fmaf(scale, a[q].w - u[q].w, u[q].w);
@@ -663,7 +671,7 @@ __device__ __forceinline__ void load_row(const float* lc, const float* lu, float
     } else {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int j = entry<E>(e);
+            const int j = entry<E>(e, th);
             z[e] = nan;
             if (j < n) {
                 const float l = lu ? fmaf(scale, lc[j] - lu[j], lu[j]) : lc[j];
@@ -678,7 +686,7 @@ __device__ __forceinline__ void load_row(const float* lc, const float* lu, float
 // odd distributions, infinite logits): the value of the K-th largest entry and up to which index entries
 // equal to it are kept (fs.tau_z, fs.tie_cut; ends with a barrier).
 template <int E>
-__device__ __forceinline__ void radix_select(const float (&z)[E], int n, int K, FastShared& fs) {
+__device__ __forceinline__ void radix_select(const float (&z)[E], int n, int K, FastShared& fs, int th) {
     Shared& sh = fs.sh;
     const int lane = threadIdx.x & 63, wave = wave_id();
     unsigned prefix = 0u, mask = 0u, remaining = (unsigned)K, count_eq = 0u;
@@ -689,7 +697,7 @@ __device__ __forceinline__ void radix_select(const float (&z)[E], int n, int K, 
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const unsigned k = fkey(z[e]);
-            if (entry<E>(e) < n && (k & mask) == prefix) atomicAdd(&fs.hist[(k >> shift) & 255u], 1u);
+            if (entry<E>(e, th) < n && (k & mask) == prefix) atomicAdd(&fs.hist[(k >> shift) & 255u], 1u);
         }
         __syncthreads();
         if (wave == 0) {  // lane owns bins 4*lane .. 4*lane+3; suffix sums from the top bin down
@@ -724,12 +732,12 @@ __device__ __forceinline__ void radix_select(const float (&z)[E], int n, int K, 
         for (int q = 0; q < E / 4; ++q) {
             int c = 0;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) c += (entry<E>(4 * q + e) < n && fkey(z[4 * q + e]) == prefix) ? 1 : 0;
+            for (int e = 0; e < 4; ++e) c += (entry<E>(4 * q + e, th) < n && fkey(z[4 * q + e]) == prefix) ? 1 : 0;
             const int at = before + block_excl_scan_i(c, sh);
             int seen = at;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (entry<E>(4 * q + e) < n && fkey(z[4 * q + e]) == prefix && ++seen == (int)remaining) fs.tie_cut = entry<E>(4 * q + e);
+                if (entry<E>(4 * q + e, th) < n && fkey(z[4 * q + e]) == prefix && ++seen == (int)remaining) fs.tie_cut = entry<E>(4 * q + e, th);
             __syncthreads();
             if (threadIdx.x == NT - 1) sh.b_int = at + c;
             __syncthreads();
@@ -741,12 +749,12 @@ __device__ __forceinline__ void radix_select(const float (&z)[E], int n, int K, 
 
 // Arg-max of the row, lowest index first: the largest (key, ~index).  One barrier.
 template <int E>
-__device__ __forceinline__ int arg_max(const float (&z)[E], int n, Slots& sl) {
+__device__ __forceinline__ int arg_max(const float (&z)[E], int n, unsigned long long (&slot)[NW], int th) {
     unsigned long long best = 0ull;
 #pragma unroll
     for (int e = 0; e < E; ++e)
-        if (entry<E>(e) < n) best = maxu64(best, ((unsigned long long)fkey(z[e]) << 32) | (0xFFFFFFFFu - (unsigned)entry<E>(e)));
-    best = max1(best, sl.key);
+        if (entry<E>(e, th) < n) best = maxu64(best, ((unsigned long long)fkey(z[e]) << 32) | (0xFFFFFFFFu - (unsigned)entry<E>(e, th)));
+    best = max1(best, slot);
     return (int)(0xFFFFFFFFu - (unsigned)best);
 }
 
@@ -857,7 +865,7 @@ __device__ __forceinline__ void linear_bins(const float (&z)[E], float gmin, flo
 // kernel gather the same list).
 template <int E>
 __device__ __forceinline__ void cut_row(const float (&z)[E], int n, int K, FastShared& fs, float& gmax, unsigned (&hi)[E],
-                                        unsigned& lim, bool& pending, int& tag) {
+                                        unsigned& lim, bool& pending, int& tag, int th) {
     float gmin;
     row_minmax<E>(z, gmin, gmax, fs);
     pending = false;
@@ -875,10 +883,10 @@ __device__ __forceinline__ void cut_row(const float (&z)[E], int n, int K, FastS
             tag = -2 - (int)lim;
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                if (hi[e] == lim && entry<E>(e) < n) {
+                if (hi[e] == lim && entry<E>(e, th) < n) {
                     const unsigned at = atomicAdd(&fs.cand_n, 1u);
                     fs.cand_z[at] = z[e];
-                    fs.cand_idx[at] = entry<E>(e);
+                    fs.cand_idx[at] = entry<E>(e, th);
                 }
             if (cnt <= 64) {
                 pending = true;
@@ -895,11 +903,11 @@ __device__ __forceinline__ void cut_row(const float (&z)[E], int n, int K, FastS
             return;
         }
     }
-    radix_select<E>(z, n, K, fs);
+    radix_select<E>(z, n, K, fs, th);
     const Threshold t = {fs.tau_z, fs.tie_cut};
     lim = 1u;
 #pragma unroll
-    for (int e = 0; e < E; ++e) hi[e] = keeps(t, z[e], entry<E>(e)) ? 1u : 0u;
+    for (int e = 0; e < E; ++e) hi[e] = keeps(t, z[e], entry<E>(e, th)) ? 1u : 0u;
 }
 
 // When top-k keeps at most kTopCap entries, they are gathered - in index order - into a list in LDS
@@ -925,7 +933,7 @@ __device__ __forceinline__ void count_entries(const unsigned (&hi)[E], unsigned 
 // Writes those entries into the list in index order; returns their number without the places past the end of
 // the row (n entries): where lim is bin 0 these are counted too, behind every entry of the row.
 template <int E>
-__device__ __forceinline__ int place_entries(const unsigned (&hi)[E], unsigned lim, const float (&z)[E], int n, CompactList& L, const Slots& sl) {
+__device__ __forceinline__ int place_entries(const unsigned (&hi)[E], unsigned lim, const float (&z)[E], int n, CompactList& L, const Slots& sl, int th) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int v = lane < 4 * E ? sl.cnt[lane] : 0;   // chunk-major, wave-minor: the order of the indices
     const int inc = wave_incl_scan_i(v);
@@ -940,7 +948,7 @@ __device__ __forceinline__ int place_entries(const unsigned (&hi)[E], unsigned l
 #pragma unroll
         for (int e = 4 * q; e < 4 * q + 4; ++e)
             if (hi[e] >= lim) {
-                if (at < kCap) L.e[at] = make_int2(entry<E>(e), __float_as_int(z[e]));
+                if (at < kCap) L.e[at] = make_int2(entry<E>(e, th), __float_as_int(z[e]));
                 ++at;
             }
     }
@@ -949,14 +957,15 @@ __device__ __forceinline__ int place_entries(const unsigned (&hi)[E], unsigned l
 
 // The list of a top-k row: its length, its largest entry and the exact threshold.
 template <int E>
-__device__ __forceinline__ int select_list(const float (&z)[E], int n, int K, FastShared& fs, CompactList& L, Threshold& t, WarpStat& st) {
+__device__ __forceinline__ int select_list(const float (&z)[E], int n, int K, FastShared& fs, CompactList& L, Threshold& t, WarpStat& st,
+                                           int th = (int)threadIdx.x) {
     unsigned hi[E], lim;
     bool pending;
-    cut_row<E>(z, n, K, fs, st.zmax, hi, lim, pending, st.onehot);
+    cut_row<E>(z, n, K, fs, st.zmax, hi, lim, pending, st.onehot, th);
     count_entries<E>(hi, lim, fs.s);
     __syncthreads();
     if (pending) rank_by_waves(fs, fs.count);
-    const int Kc = place_entries<E>(hi, lim, z, n, L, fs.s);
+    const int Kc = place_entries<E>(hi, lim, z, n, L, fs.s, th);
     __syncthreads();
     t = ranked_threshold(fs, pending);
     st.tau = fkey(t.tz);
@@ -1033,7 +1042,7 @@ __device__ __forceinline__ int list_pick(const double (&w)[kLH], const double (&
 
 // Inverse-CDF draw from the dense per-thread weights w (ascending index order).
 template <int E>
-__device__ __forceinline__ int inv_cdf_row(const double (&w)[E], double total, float u, Slots& sl, Shared& sh) {
+__device__ __forceinline__ int inv_cdf_row(const double (&w)[E], double total, float u, Slots& sl, Shared& sh, int th = (int)threadIdx.x) {
     const int lane = threadIdx.x & 63, wave = wave_id();
     double s[E / 4], inc[E / 4];
     __syncthreads();   // the slots may still be read by an earlier exchange
@@ -1058,8 +1067,8 @@ __device__ __forceinline__ int inv_cdf_row(const double (&w)[E], double total, f
         for (int e = 4 * q; e < 4 * q + 4; ++e)
             if (w[e] > 0.0) {
                 c += w[e];
-                last = entry<E>(e);
-                if (c > target && cand == 0x7FFFFFFF) cand = entry<E>(e);
+                last = entry<E>(e, th);
+                if (c > target && cand == 0x7FFFFFFF) cand = entry<E>(e, th);
             }
     }
     cand = wave_min_i(cand);
@@ -1073,13 +1082,14 @@ __device__ __forceinline__ int inv_cdf_row(const double (&w)[E], double total, f
 // The statistics (with total) of a row that does not take the list form - greedy, every entry kept, or more
 // than kTopCap kept - and the weight of every entry of the thread.
 template <int E>
-__device__ __forceinline__ WarpStat dense_row(const float (&z)[E], int n, int top_k, int greedy, FastShared& fs, double (&w)[E]) {
+__device__ __forceinline__ WarpStat dense_row(const float (&z)[E], int n, int top_k, int greedy, FastShared& fs, double (&w)[E],
+                                             int th = (int)threadIdx.x) {
     WarpStat st;
     st.total = 1.0; st.zmax = 0.f; st.tau = 0x007FFFFFu; st.tie_cut = -1; st.onehot = -1;  // keeps every finite entry
     if (greedy) {
-        st.onehot = arg_max<E>(z, n, fs.s);
+        st.onehot = arg_max<E>(z, n, fs.s.key, th);
 #pragma unroll
-        for (int e = 0; e < E; ++e) w[e] = (entry<E>(e) == st.onehot) ? 1.0 : 0.0;
+        for (int e = 0; e < E; ++e) w[e] = (entry<E>(e, th) == st.onehot) ? 1.0 : 0.0;
         return st;
     }
     Threshold t = {-INFINITY, -1};
@@ -1087,7 +1097,7 @@ __device__ __forceinline__ WarpStat dense_row(const float (&z)[E], int n, int to
         unsigned hi[E], lim;
         bool pending;
         int tag;
-        cut_row<E>(z, n, top_k, fs, st.zmax, hi, lim, pending, tag);
+        cut_row<E>(z, n, top_k, fs, st.zmax, hi, lim, pending, tag, th);
         __syncthreads();
         if (pending) rank_by_waves(fs, fs.count);
         __syncthreads();
@@ -1101,7 +1111,7 @@ __device__ __forceinline__ WarpStat dense_row(const float (&z)[E], int n, int to
     double s = 0.0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        w[e] = keeps(t, z[e], entry<E>(e)) ? exp((double)z[e] - (double)st.zmax) : 0.0;
+        w[e] = keeps(t, z[e], entry<E>(e, th)) ? exp((double)z[e] - (double)st.zmax) : 0.0;
         s += w[e];
         __builtin_amdgcn_sched_barrier(0);   // one exponential at a time: interleaved ones spill
     }
@@ -1225,7 +1235,7 @@ __global__ __launch_bounds__(NT) void accept_commit_fast(
     UniformSrc us) {
     __shared__ Slots sl;
     __shared__ Shared sh;
-    const int b = blockIdx.x, lane = threadIdx.x & 63;
+    const int b = blockIdx.x, lane = threadIdx.x & 63, th = (int)threadIdx.x;
     const int ke = k_eff[b];
     if (threadIdx.x <= k) out_tok[b * (k + 1) + threadIdx.x] = -1;
     if (ke < 0) {
@@ -1292,14 +1302,14 @@ __global__ __launch_bounds__(NT) void accept_commit_fast(
     } else {
         double w[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) w[e] = entry<E>(e) < P.Vs ? weight_of(ps, prow, P.inv_t, entry<E>(e)) : 0.0;
+        for (int e = 0; e < E; ++e) w[e] = entry<E>(e, th) < P.Vs ? weight_of(ps, prow, P.inv_t, entry<E>(e, th)) : 0.0;
         if (a < ke) {
             const float* qrow = dlogit_b + ((size_t)b * P.kstride + a) * P.Vs;
             const WarpStat qs = qstat[b * P.kstride + a];
             double res[E], s = 0.0;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                const double q = entry<E>(e) < P.Vs ? weight_of(qs, qrow, P.inv_t, entry<E>(e)) / qs.total : 0.0;
+                const double q = entry<E>(e, th) < P.Vs ? weight_of(qs, qrow, P.inv_t, entry<E>(e, th)) / qs.total : 0.0;
                 const double r = w[e] / ps.total - q;
                 res[e] = r > 0.0 ? r : 0.0;
                 s += res[e];
@@ -1435,11 +1445,12 @@ __global__ __launch_bounds__(NT) void multi_verify_list_kernel(const float* p_lo
     // through generic pointers).
     for (int i = -1; i < mr; ++i) {
         const float* qrow = i < 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + i) * n;
+        const int th = this_thread();
         float z[E];
-        load_row<E>(qrow, nullptr, 0.f, inv_t, nullptr, n, z);
+        load_row<E>(qrow, nullptr, 0.f, inv_t, nullptr, n, z, th);
         WarpStat qs;
         Threshold t;
-        const int Kq = select_list<E>(z, n, top_k, fs, L, t, qs);
+        const int Kq = select_list<E>(z, n, top_k, fs, L, t, qs, th);
         int iq[kLH];
         double wq[kLH];
         list_weights(L, Kq, qs.zmax, t, iq, wq);
@@ -1493,7 +1504,7 @@ __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_lo
     __shared__ Shared sh;
     __shared__ CompactList L;
     __shared__ WalkShared ws;
-    const int row = blockIdx.x;
+    const int row = blockIdx.x, th = (int)threadIdx.x;
     const int mr = row_candidates(m_rows, row, m);
     const WarpStat ps = stats[(size_t)row * (m + 1)];
     if (threadIdx.x == 0) { ws.pick = 0.0; sl.pick = 0x7FFFFFFF; }
@@ -1512,11 +1523,11 @@ __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_lo
         lim = (unsigned)(-2 - ps.onehot);
     } else {
 #pragma unroll
-        for (int e = 0; e < E; ++e) hi[e] = keeps(t, z[e], entry<E>(e)) ? 1u : 0u;
+        for (int e = 0; e < E; ++e) hi[e] = keeps(t, z[e], entry<E>(e, th)) ? 1u : 0u;
     }
     count_entries<E>(hi, lim, sl);
     __syncthreads();
-    Kp = place_entries<E>(hi, lim, z, n, L, sl);
+    Kp = place_entries<E>(hi, lim, z, n, L, sl, th);
     __syncthreads();
     list_weights(L, Kp, ps.zmax, t, idx, w);
 #pragma unroll
@@ -1535,33 +1546,40 @@ __global__ __launch_bounds__(NT) void multi_verify_walk_kernel(const float* p_lo
     walk_finish(idx, w, Kp, acc, mr, tok, u_final[row], row, m, sl, sh, out_index, out_token, out_resid);
 }
 
+// The same with every entry of the target kept, for rows that do not take the list form (top-k beyond
+// kTopCap, or all entries).  The running target lives in LDS (entry e of thread t at [e][t], read and written by
+// its owner only): as E more fp64 values in registers beside the selection's and the proposal's it spilled (326
+// registers at E = 16).  16384 entries, two candidates, top-k 16384 / 2500: 86.5 / 97.7 us with the target in
+// registers, 58.3 / 61.6 us here.
 template <int E>
 __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits, const float* q_logits,
                                                           const int32_t* cand, const float* u_acc,
                                                           const float* u_final, const int32_t* m_rows, int m, int n,
-                                                          float inv_t, int top_k, int greedy, int32_t* out_index,
+                                                          float inv_t, int top_k, int32_t* out_index,
                                                           int32_t* out_token, double* out_resid) {
     __shared__ FastShared fs;
     __shared__ double pick[2];
+    __shared__ double target[E][NT];
     const int row = blockIdx.x;
     const int mr = row_candidates(m_rows, row, m);
     int acc = mr, tok = -1;
-    double p[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) p[e] = 0.0;
     for (int i = -1; i < mr; ++i) {   // i = -1: the target row (one call site of the selection, see multi_verify_list_kernel)
+        const int th = this_thread();
         if (threadIdx.x == 0) {   // a candidate outside the slice has no owner: p = 0, q = 1 rejects it
             pick[0] = 0.0;
             pick[1] = 1.0;
         }
         float z[E];
-        load_row<E>(i < 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + i) * n, nullptr, 0.f, inv_t, nullptr, n, z);
+        load_row<E>(i < 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + i) * n, nullptr, 0.f, inv_t, nullptr, n, z, th);
         double q[E];
-        const WarpStat qs = dense_row<E>(z, n, top_k, greedy, fs, q);
+        const WarpStat qs = dense_row<E>(z, n, top_k, 0, fs, q, th);
         __syncthreads();   // the sum's words are used again below; pick[] is initialised
         if (i < 0) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) p[e] = q[e] / qs.total;
+            for (int e = 0; e < E; ++e) {
+                target[e][th] = q[e] / qs.total;
+                __builtin_amdgcn_sched_barrier(0);   // one division at a time, here and below: interleaved ones spill
+            }
             continue;
         }
         const int s = cand[(size_t)row * m + i];
@@ -1569,13 +1587,15 @@ __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits,
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             q[e] /= qs.total;
-            if (entry<E>(e) == s) {   // the owner of the candidate's entry publishes p^(i)(s), q_i(s)
-                pick[0] = p[e];
+            const double p = target[e][th];
+            if (entry<E>(e, th) == s) {   // the owner of the candidate's entry publishes p^(i)(s), q_i(s)
+                pick[0] = p;
                 pick[1] = q[e];
             }
-            const double r = p[e] - q[e];
+            const double r = p - q[e];
             q[e] = r > 0.0 ? r : 0.0;   // q now holds max(0, p^(i) - q_i)
             rs += q[e];
+            __builtin_amdgcn_sched_barrier(0);
         }
         const double R = sum1(rs, fs.s.scan[0][0]);   // its barrier also publishes pick[]
         const double pd = pick[0], qd = pick[1];
@@ -1589,13 +1609,19 @@ __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits,
         }
         if (R > 0.0) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) p[e] = q[e] / R;
+            for (int e = 0; e < E; ++e) {
+                target[e][th] = q[e] / R;
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
     if (acc == mr) {
-        double sp = 0.0;
+        double p[E], sp = 0.0;
 #pragma unroll
-        for (int e = 0; e < E; ++e) sp += p[e];
+        for (int e = 0; e < E; ++e) {
+            p[e] = target[e][threadIdx.x];
+            sp += p[e];
+        }
         __syncthreads();
         const double total = sum1(sp, fs.s.sum);
         tok = inv_cdf_row<E>(p, total, u_final[row], fs.s, fs.sh);
@@ -1603,6 +1629,44 @@ __global__ __launch_bounds__(NT) void multi_verify_kernel(const float* p_logits,
     if (threadIdx.x == 0) {
         out_index[row] = acc;
         out_token[row] = tok;
+        if (out_resid)
+            for (int i = (acc == mr ? mr : acc + 1); i < m; ++i) out_resid[(size_t)row * m + i] = -1.0;   // steps not evaluated
+    }
+}
+
+// The same where every row is the point mass on its arg-max (greedy): the target stays the point mass it
+// is - a proposal's point mass elsewhere leaves max(0, p - q) = p with mass 1, the same one leaves nothing -, so a
+// row costs its arg-max and the recursion is a comparison of indices.  16384 entries, two candidates: 93.2 us as fp64
+// weights per entry, 11.7 us here.
+template <int E>
+__global__ __launch_bounds__(NT) void multi_verify_greedy_kernel(const float* p_logits, const float* q_logits, const int32_t* cand,
+                                                                 const float* u_acc, const int32_t* m_rows, int m, int n, float inv_t,
+                                                                 int32_t* out_index, int32_t* out_token, double* out_resid) {
+    __shared__ unsigned long long key[2][NW];   // alternating: a row's exchange may be read while the next one is written
+    const int row = blockIdx.x;
+    const int mr = row_candidates(m_rows, row, m);
+    int acc = mr, best = 0;
+    for (int i = -1; i < mr; ++i) {
+        const int th = this_thread();
+        float z[E];
+        load_row<E>(i < 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + i) * n, nullptr, 0.f, inv_t, nullptr, n, z, th);
+        const int top = arg_max<E>(z, n, key[i & 1], th);
+        if (i < 0) {
+            best = top;
+            continue;
+        }
+        const int s = cand[(size_t)row * m + i];
+        // a candidate outside the slice: p = 0, q = 1 rejects it
+        const double pd = s == best ? 1.0 : 0.0, qd = (s == top || (unsigned)s >= (unsigned)n) ? 1.0 : 0.0;
+        if (out_resid && threadIdx.x == 0) out_resid[(size_t)row * m + i] = top == best ? 0.0 : 1.0;
+        if ((double)u_acc[(size_t)row * m + i] * qd < pd) {
+            acc = i;
+            break;
+        }
+    }
+    if (threadIdx.x == 0) {
+        out_index[row] = acc;
+        out_token[row] = acc < mr ? cand[(size_t)row * m + acc] : best;
         if (out_resid)
             for (int i = (acc == mr ? mr : acc + 1); i < m; ++i) out_resid[(size_t)row * m + i] = -1.0;   // steps not evaluated
     }
@@ -1764,10 +1828,13 @@ int launch_multi_verify(const float* p_logits, const float* q_logits, const int3
         auto kern = E == 4 ? multi_verify_list_kernel<4> : (E == 8 ? multi_verify_list_kernel<8> : multi_verify_list_kernel<16>);
         kern<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, tk, out_index, out_token,
                                       out_resid);
+    } else if (greedy) {
+        auto kern = E == 4 ? multi_verify_greedy_kernel<4> : (E == 8 ? multi_verify_greedy_kernel<8> : multi_verify_greedy_kernel<16>);
+        kern<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, m_rows, m, n, inv_t, out_index, out_token, out_resid);
     } else {
         auto kern = E == 4 ? multi_verify_kernel<4> : (E == 8 ? multi_verify_kernel<8> : multi_verify_kernel<16>);
-        kern<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, tk, greedy, out_index,
-                                      out_token, out_resid);
+        kern<<<rows, NT, 0, stream>>>(p_logits, q_logits, cand, u_acc, u_final, m_rows, m, n, inv_t, tk, out_index, out_token,
+                                      out_resid);
     }
     return hipGetLastError() == hipSuccess ? HAWK_OK : HAWK_EDEVICE;
 }

@@ -198,3 +198,34 @@ def test_rejection_probability_curve_matches_oracle(H):
     print("r(m), distinct proposals:", np.round(curves["distinct"], 4))
     assert np.all(curves["distinct"][1:] < curves["same"][1:])
     assert curves["same"][-1] / curves["same"][-2] > 0.97
+
+
+@pytest.mark.parametrize("n", [1, 63, 4096, 4097, 8193, 16383])
+def test_greedy_recursion_over_arg_max_indices(H, n):
+    # point masses: proposals that agree with the target and that do not, candidates on and off either arg-max, ties
+    # (lowest index), candidates outside the slice, short pools; all entries-per-thread forms and ragged ends
+    import torch
+    rows, m = 10, 3
+    p, q, cand, u_acc, u_fin = make_rows(n, rows, m, n, 0.0, n, 0.2)
+    q[0::3, 1] = p[0::3]                                      # the same arg-max
+    p[1, [0, n - 1]] = 50.0                                   # ties at both ends
+    cand[2::4, 0] = np.argmax(p[2::4], axis=1)
+    cand[3::4, 2] = 0
+    bad = cand.copy()
+    bad[5, 0], bad[6, 1] = n, -1
+    m_rows = np.array([m] * (rows - 2) + [1, 0], dtype=np.int32)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    idx, tok, resid = (x.cpu().numpy() for x in H.multi_verify(t(p), t(q), t(bad), t(u_acc), t(u_fin), 0.0, n, want_resid=True, m_rows=t(m_rows)))
+    for r in range(rows):
+        best = int(np.argmax(p[r]))
+        want_i, want_t, want_r = int(m_rows[r]), best, []
+        for i in range(int(m_rows[r])):
+            top = int(np.argmax(q[r, i]))
+            want_r.append(0.0 if top == best else 1.0)
+            if bad[r, i] == best and (top != best or u_acc[r, i] < 1.0):
+                want_i, want_t = i, best
+                break
+        if m_rows[r] == m and (bad[r] == cand[r]).all():
+            assert oracle.multi_verify(p[r], q[r], cand[r], u_acc[r], float(u_fin[r]), 0.0, n) == (want_i, want_t)
+        assert (idx[r], tok[r]) == (want_i, want_t)
+        np.testing.assert_array_equal(resid[r], want_r + [-1.0] * (m - len(want_r)))

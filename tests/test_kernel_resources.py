@@ -1,0 +1,24 @@
+"""What the compiler needs for the sampling kernels: registers kept in scratch memory.  A kernel of 1024 threads has
+128 registers per thread; the ones that loop over rows spill every address of the loop if it is left to the compiler,
+and the recursion over whole rows did so with the running target in registers (326 spilled, 1.7 times the time)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2510_25739_amd import build
+
+SPILLS = 64   # per-thread values that one row's pass reloads once; beyond that the entries themselves are spilled
+
+
+def test_sampling_kernels_keep_their_entries_in_registers(tmp_path):
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("no hipcc")
+    cmd = [build.HIPCC, *build.FLAGS, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
+           os.path.join(build.CSRC, "sampling.hip"), "-o", str(tmp_path / "sampling.o")]
+    report = subprocess.run(cmd, capture_output=True, text=True, check=True).stderr
+    spills = {name: int(n) for name, n in re.findall(r"Function Name: (\S+).*?VGPRs Spill: (\d+)", report, flags=re.S)}
+    assert any("multi_verify_kernel" in k for k in spills) and any("multi_verify_greedy_kernel" in k for k in spills)
+    assert {k: n for k, n in spills.items() if n > SPILLS} == {}
+    assert all(n <= 1 for k, n in spills.items() if "multi_verify_kernel" not in k), spills
