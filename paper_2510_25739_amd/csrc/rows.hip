@@ -436,8 +436,15 @@ __global__ void rope_table_kernel(const double* inv_freq, float2* tab, int pairs
 // weighted sum of the values (weights split hi / lo as well).  Its A operand is the transposed value tile,
 // which ds_read_b64_tr_b16 forms from row-major LDS: lane i of a group of 16 names 4 features of row
 // i / 4, and receives column i of the four rows.
+//
+// A pair of halves holds a fp32 value to one unit in its last place unless the low one is subnormal, so both are moved
+// up by powers of two first: a query row by its own (largest feature in [2^14, 2^15)), weights by 2^14.  Error of
+// the output against float64 on the same cache, before it becomes planes (2-norm; prompt / step rows): 32 sequences of
+// 120 + 6 rows, heads of 64: scalar fp32 1.9e-7 / 2.3e-7, here 1.2e-7 / 1.5e-7; heads of 128: 2.6e-7 / 2.9e-7, here
+// 1.3e-7 / 1.8e-7 (pairs without the powers of two: 3.8e-6 / 9.7e-6, and queries beyond 65504 were NaN).
+constexpr float kWeightScale = 16384.f;
 
-template <int HD> struct QRow { h8 hi[HD / 32], lo[HD / 32]; };
+template <int HD> struct QRow { h8 hi[HD / 32], lo[HD / 32]; float back; };   // back: what undoes the row's power of two
 
 // Eight consecutive features of a raw projection row after the rotary step (pairs (2 j, 2 j + 1)).
 __device__ __forceinline__ void rope8(const float* src, const float2* tab, float (&o)[8]) {
@@ -448,49 +455,6 @@ __device__ __forceinline__ void rope8(const float* src, const float2* tab, float
     o[4] = b.x * d.x - b.y * d.y; o[5] = b.x * d.y + b.y * d.x;
     o[6] = b.z * d.z - b.w * d.w; o[7] = b.z * d.w + b.w * d.z;
 }
-template <int HD>
-__device__ __forceinline__ void load_query(const float* row, const float2* tab, int kg, bool on, float scale, QRow<HD>& q) {
-#pragma unroll
-    for (int ks = 0; ks < HD / 32; ++ks) {
-        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        const int f = ks * 32 + kg * 8;
-        if (on) rope8(row + f, tab + f / 2, v);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float x = v[e] * scale;
-            q.hi[ks][e] = (_Float16)x;
-            q.lo[ks][e] = (_Float16)(x - (float)q.hi[ks][e]);
-        }
-    }
-}
-template <int HD> __device__ __forceinline__ f32x4 score_tile(const h8 (&k)[HD / 32], const QRow<HD>& q) {
-    f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < HD / 32; ++ks) {
-        s = __builtin_amdgcn_mfma_f32_16x16x32_f16(k[ks], q.hi[ks], s, 0, 0, 0);
-        s = __builtin_amdgcn_mfma_f32_16x16x32_f16(k[ks], q.lo[ks], s, 0, 0, 0);
-    }
-    return s;
-}
-// o += V^T P for one tile of 16 keys whose values sit row-major in LDS (row stride vs halves).
-template <int HD>
-__device__ __forceinline__ void value_tile(const _Float16* v, int vs, f32x4 p, int r16, int kg, f32x4 (&o)[HD / 16]) {
-    h4 ph, pl;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        ph[e] = (_Float16)p[e];
-        pl[e] = (_Float16)(p[e] - (float)ph[e]);
-    }
-    const _Float16* at = v + (size_t)(4 * kg + (r16 >> 2)) * vs + (r16 & 3) * 4;
-#pragma unroll
-    for (int ft = 0; ft < HD / 16; ++ft) {
-        const s4 raw = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s4*)const_cast<_Float16*>(at + ft * 16));
-        const h4 a = __builtin_bit_cast(h4, raw);
-        o[ft] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ph, o[ft], 0, 0, 0);
-        o[ft] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, pl, o[ft], 0, 0, 0);
-    }
-}
 __device__ __forceinline__ float row_max4(float v) {   // over the four lanes that share a row
     v = fmaxf(v, __shfl_xor(v, 16));
     return fmaxf(v, __shfl_xor(v, 32));
@@ -498,6 +462,68 @@ __device__ __forceinline__ float row_max4(float v) {   // over the four lanes th
 __device__ __forceinline__ float row_sum4(float v) {
     v += __shfl_xor(v, 16);
     return v + __shfl_xor(v, 32);
+}
+template <int HD>
+__device__ __forceinline__ void load_query(const float* row, const float2* tab, int kg, bool on, float scale, QRow<HD>& q) {
+    float v[HD / 32][8], top = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks) {
+        const int f = ks * 32 + kg * 8;
+        if (on) rope8(row + f, tab + f / 2, v[ks]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[ks][e] = on ? v[ks][e] * scale : 0.f;
+            top = fmaxf(top, fabsf(v[ks][e]));
+        }
+    }
+    // exponent of the largest feature; zero and subnormal rows move by 2^126, infinite ones as if they were finite
+    const int ex = (int)(__float_as_uint(row_max4(top)) >> 23);
+    const int shift = max(-113, min(126, 14 + 127 - ex));
+    const float up = __uint_as_float((unsigned)(127 + shift) << 23);
+    q.back = __uint_as_float((unsigned)(127 - shift) << 23);
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float x = v[ks][e] * up;
+            q.hi[ks][e] = (_Float16)x;
+            q.lo[ks][e] = (_Float16)(x - (float)q.hi[ks][e]);
+        }
+}
+template <int HD> __device__ __forceinline__ f32x4 score_tile(const h8 (&k)[HD / 32], const QRow<HD>& q) {
+    f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks) s = __builtin_amdgcn_mfma_f32_16x16x32_f16(k[ks], q.lo[ks], s, 0, 0, 0);
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks) s = __builtin_amdgcn_mfma_f32_16x16x32_f16(k[ks], q.hi[ks], s, 0, 0, 0);
+    return s * q.back;
+}
+// o += 2^14 V^T P for one tile of 16 keys whose values sit row-major in LDS (row stride vs halves).
+template <int HD>
+__device__ __forceinline__ void value_tile(const _Float16* v, int vs, f32x4 p, int r16, int kg, f32x4 (&o)[HD / 16]) {
+    h4 ph, pl;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float w = p[e] * kWeightScale;
+        ph[e] = (_Float16)w;
+        pl[e] = (_Float16)(w - (float)ph[e]);
+    }
+    const _Float16* at = v + (size_t)(4 * kg + (r16 >> 2)) * vs + (r16 & 3) * 4;
+#pragma unroll
+    for (int ft = 0; ft < HD / 16; ++ft) {
+        const s4 raw = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s4*)const_cast<_Float16*>(at + ft * 16));
+        const h4 a = __builtin_bit_cast(h4, raw);
+        o[ft] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, pl, o[ft], 0, 0, 0);
+        o[ft] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ph, o[ft], 0, 0, 0);
+    }
+}
+// v / d with r = 1 / d: the product's rounding is taken back once.
+__device__ __forceinline__ f32x4 divided(f32x4 v, float d, float r) {
+    f32x4 q = v * r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[e] = fmaf(fmaf(-q[e], d, v[e]), r, q[e]);
+    return q;
 }
 
 struct AttnArgs {
@@ -587,10 +613,11 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
     }
     den = row_sum4(den);
     if (row < C) {
-        const float r = 1.f / den;
+        den *= kWeightScale;
+        const float rden = 1.f / den;
 #pragma unroll
         for (int ft = 0; ft < HD / 16; ++ft)
-            store_planes4(a.hi, a.lo, (int)base + row, h * HD + ft * 16 + 4 * kg, a.d / 32, o[ft] * r);
+            store_planes4(a.hi, a.lo, (int)base + row, h * HD + ft * 16 + 4 * kg, a.d / 32, divided(o[ft], den, rden));
     }
 }
 
@@ -739,7 +766,7 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
                 t += e * ml[w][1][r];
                 v += *reinterpret_cast<const f32x4*>(&om[w][r][f]) * e;
             }
-            v *= 1.f / t;
+            v /= t * kWeightScale;
         }
         store_planes4(a.hi, a.lo, R0 + rr, h * HD + f, a.d / 32, v);
     }

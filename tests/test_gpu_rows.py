@@ -102,6 +102,34 @@ def test_many_row_passes_match_a_float64_forward(H, d, heads, mlp, batch, scale,
     assert prompt < 1e-3 and step < 1e-3
 
 
+def test_queries_beyond_the_range_of_a_half(H):
+    # The first feature pair of every head's queries is around 2^20 and meets keys of zero: the scores, and with them the
+    # hidden states, are those of the other features.  These are 2^-20 of the row's largest, where a pair of halves moved
+    # up to 2^14 still holds 2^-18 of them: within the bound above.
+    s = BASE.replace(n_heads=2, n_cond=20)
+    blob = synth.make_weights(s, seed=4, std=0.05)
+    import torch
+    lay = synth.blob_layout(s)
+    pairs = [h * s.head_dim + e for h in range(s.n_heads) for e in (0, 1)]
+    for l in range(s.n_layers):
+        for name, factor in (("Wq", 2.0 ** 21), ("Wk", 0.0)):
+            off, shape = lay[f"l{l}.{name}"]
+            w = torch.from_numpy(blob[off:off + 2 * shape[0] * shape[1]]).view(torch.bfloat16).view(shape)
+            w[pairs] *= factor
+    cond = synth.make_cond(s, seed=2)
+    hk = H.Hawk(H.HawkConfig.from_shape(s, k_max=3))
+    hk.load(blob)
+    hk.set_path(0)
+    hk.prefill(cond, None, s.grid_h, s.grid_w, 1.0, s.top_k, 1.0, np.full(1, 0.5, np.float32))
+    got = [hk.last_hidden(s.n_cond).cpu().numpy().reshape(1, s.n_cond, -1)]
+    tok = np.concatenate([hk.grid()[:, :1], [[7, 9, 11]]], axis=1)
+    hk.force([1], tok[:, 1:].astype(np.int32))
+    got.append(hk.last_hidden(3).cpu().numpy().reshape(1, 3, -1))
+    emb = np.asarray(synth.blob_tensor(s, blob, "E"))[tok[:, :3]]
+    ref = reference(s, blob, np.concatenate([cond, emb], axis=1))
+    assert relative(np.concatenate(got, axis=1), ref) < 1e-3
+
+
 HARD_ROWS = {
     "narrower than a bin can resolve": lambda rng, n: (rng.integers(0, 3, n) * 1e-38).astype(np.float32),
     "all equal": lambda rng, n: np.zeros(n, np.float32),
