@@ -518,6 +518,26 @@ __device__ __forceinline__ void value_tile(const _Float16* v, int vs, f32x4 p, i
         o[ft] = __builtin_amdgcn_mfma_f32_16x16x16f16(a, ph, o[ft], 0, 0, 0);
     }
 }
+// A value of the rows in flight that is infinite or NaN as a half goes to LDS as zero: in the product its weight of zero
+// would make NaN of rows that do not see it.  The rows that do get their NaN at the end (poison).
+__device__ __forceinline__ bool finite_half(float x) { return fabsf(x) < 65520.f; }
+__device__ __forceinline__ bool clear_not_finite(h8& v) {   // true: something was cleared
+    const v4u b = __builtin_bit_cast(v4u, v);
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bad = bad || (b[i] & 0x7C00u) == 0x7C00u || (b[i] & 0x7C000000u) == 0x7C000000u;
+    if (bad) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = finite_half((float)v[e]) ? v[e] : (_Float16)0.f;
+    }
+    return bad;
+}
+__device__ __forceinline__ void poison(f32x4& o, const float* v) {   // v: the four features of a row that is seen
+    const float4 x = *reinterpret_cast<const float4*>(v);
+    const float nan = __uint_as_float(0x7FC00000u);
+    o = (f32x4){finite_half(x.x) ? o[0] : nan, finite_half(x.y) ? o[1] : nan, finite_half(x.z) ? o[2] : nan, finite_half(x.w) ? o[3] : nan};
+}
+
 // v / d with r = 1 / d: the product's rounding is taken back once.
 __device__ __forceinline__ f32x4 divided(f32x4 v, float d, float r) {
     f32x4 q = v * r;
@@ -542,6 +562,7 @@ template <int HD>
 __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
     constexpr int KST = HD + 8, VST = HD + 16;
     __shared__ __attribute__((aligned(16))) _Float16 ks_[64 * KST], vs_[64 * VST];
+    __shared__ int cleared[4];   // per wave: values that are not finite, in the block on the diagonal
     const int rg = blockIdx.x, h = blockIdx.y, s = blockIdx.z, C = a.map.rows_per_seq;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r16 = lane & 15, kg = lane >> 4;
     const int row = rg * 64 + wave * 16 + r16;
@@ -560,6 +581,7 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
             const int pc = min(pos, C - 1);
             const float* kr = a.qkv + (base + pc) * 3 * a.d + a.d + (size_t)h * HD + f0;
             const float2* tab = a.rope + (size_t)pc * (HD / 2) + f0 / 2;
+            bool bad = false;
 #pragma unroll
             for (int c = 0; c < HD / 32; ++c) {
                 float k[8];
@@ -571,11 +593,18 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
                 vv[0] = (_Float16)v0.x; vv[1] = (_Float16)v0.y; vv[2] = (_Float16)v0.z; vv[3] = (_Float16)v0.w;
                 vv[4] = (_Float16)v1.x; vv[5] = (_Float16)v1.y; vv[6] = (_Float16)v1.z; vv[7] = (_Float16)v1.w;
                 *reinterpret_cast<h8*>(ks_ + key * KST + f0 + c * 8) = kk;
-                *reinterpret_cast<h8*>(vs_ + key * VST + f0 + c * 8) = vv;
-                if (kb == rg && pos < C) {
-                    *reinterpret_cast<h8*>(a.Kc + cbase + (size_t)pos * HD + f0 + c * 8) = kk;
-                    *reinterpret_cast<h8*>(a.Vc + cbase + (size_t)pos * HD + f0 + c * 8) = vv;
+                if (kb == rg) {
+                    if (pos < C) {
+                        *reinterpret_cast<h8*>(a.Kc + cbase + (size_t)pos * HD + f0 + c * 8) = kk;
+                        *reinterpret_cast<h8*>(a.Vc + cbase + (size_t)pos * HD + f0 + c * 8) = vv;
+                    }
+                    bad |= clear_not_finite(vv);
                 }
+                *reinterpret_cast<h8*>(vs_ + key * VST + f0 + c * 8) = vv;
+            }
+            if (kb == rg) {
+                const int any = __any(bad);
+                if (lane == 0) cleared[wave] = any;
             }
         }
         __syncthreads();
@@ -616,8 +645,15 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
         den *= kWeightScale;
         const float rden = 1.f / den;
 #pragma unroll
-        for (int ft = 0; ft < HD / 16; ++ft)
-            store_planes4(a.hi, a.lo, (int)base + row, h * HD + ft * 16 + 4 * kg, a.d / 32, divided(o[ft], den, rden));
+        for (int ft = 0; ft < HD / 16; ++ft) o[ft] = divided(o[ft], den, rden);
+        if (cleared[0] | cleared[1] | cleared[2] | cleared[3])
+            for (int key = rg * 64; key <= row; ++key) {
+                const float* v = a.qkv + (base + key) * 3 * a.d + 2 * a.d + (size_t)h * HD + 4 * kg;
+#pragma unroll
+                for (int ft = 0; ft < HD / 16; ++ft) poison(o[ft], v + ft * 16);
+            }
+#pragma unroll
+        for (int ft = 0; ft < HD / 16; ++ft) store_planes4(a.hi, a.lo, (int)base + row, h * HD + ft * 16 + 4 * kg, a.d / 32, o[ft]);
     }
 }
 
@@ -633,6 +669,7 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
     constexpr int VST = HD + 16, T = HD == 64 ? 3 : 2, CH = HD / 32;   // CH: 16-byte chunks per lane of a value tile
     __shared__ __attribute__((aligned(16))) _Float16 vbuf[NWV][16 * VST];
     __shared__ float om[NWV][16][HD + 4], ml[NWV][2][16];
+    __shared__ int cleared[NWV];
     const int s = blockIdx.x, h = blockIdx.y, rt = blockIdx.z, R = a.map.rows_per_seq;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, kg = lane >> 4;
     const int b = s % a.map.batch, ke = a.map.k_eff[b];
@@ -668,8 +705,9 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
     load_query<HD>(a.qkv + (size_t)(R0 + min(row, R - 1)) * 3 * a.d + (size_t)h * HD, a.rope + (size_t)min(qpos, a.Tmax - 1) * (HD / 2), kg,
                    row < nrows, 1.f / sqrtf((float)HD), q);
     // which of the pass's own entries the row attends, one bit each: its ancestors or the rows before it, and itself
-    unsigned long long sees = 0ull;
-    if (row < nrows) sees = (tree ? a.map.tree_anc[row] | (1ull << row) : (2ull << row) - 1ull);
+    auto visible = [&](int r) { return tree ? a.map.tree_anc[r] | (1ull << r) : (2ull << r) - 1ull; };
+    const unsigned long long sees = row < nrows ? visible(row) : 0ull;
+    bool bad = false;   // values that are not finite among the pass's own
     f32x4 o[HD / 16];
 #pragma unroll
     for (int ft = 0; ft < HD / 16; ++ft) o[ft] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -729,11 +767,12 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
             h8 vv;
             vv[0] = (_Float16)v0.x; vv[1] = (_Float16)v0.y; vv[2] = (_Float16)v0.z; vv[3] = (_Float16)v0.w;
             vv[4] = (_Float16)v1.x; vv[5] = (_Float16)v1.y; vv[6] = (_Float16)v1.z; vv[7] = (_Float16)v1.w;
-            *reinterpret_cast<h8*>(vb + r16 * VST + f) = vv;
             if (nt == rt && kr < nrows) {
                 *reinterpret_cast<h8*>(a.Kc + entry + f) = k[c];
                 *reinterpret_cast<h8*>(a.Vc + entry + f) = vv;
             }
+            bad |= clear_not_finite(vv);
+            *reinterpret_cast<h8*>(vb + r16 * VST + f) = vv;
         }
         f32x4 sc = score_tile<HD>(k, q);
 #pragma unroll
@@ -745,6 +784,8 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
     }
     // merge: every wave's maximum, sum and weighted values
     den = row_sum4(den);
+    const int any = __any(bad);
+    if (lane == 0) cleared[wave] = any;
     if (kg == 0) {
         ml[wave][0][r16] = mx;
         ml[wave][1][r16] = den;
@@ -752,6 +793,9 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
 #pragma unroll
     for (int ft = 0; ft < HD / 16; ++ft) *reinterpret_cast<f32x4*>(&om[wave][r16][ft * 16 + 4 * kg]) = o[ft];
     __syncthreads();
+    int poisoned = 0;
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) poisoned |= cleared[w];
     for (int i = threadIdx.x; i < 16 * (HD / 4); i += 64 * NWV) {
         const int r = i / (HD / 4), f = (i % (HD / 4)) * 4, rr = rt * 16 + r;
         if (rr >= R) continue;
@@ -767,6 +811,9 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
                 v += *reinterpret_cast<const f32x4*>(&om[w][r][f]) * e;
             }
             v /= t * kWeightScale;
+            if (poisoned)
+                for (int key = 0; key < nrows; ++key)
+                    if ((visible(rr) >> key) & 1ull) poison(v, a.qkv + (size_t)(R0 + key) * 3 * a.d + 2 * a.d + (size_t)h * HD + f);
         }
         store_planes4(a.hi, a.lo, R0 + rr, h * HD + f, a.d / 32, v);
     }

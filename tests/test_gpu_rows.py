@@ -130,6 +130,39 @@ def test_queries_beyond_the_range_of_a_half(H):
     assert relative(np.concatenate(got, axis=1), ref) < 1e-3
 
 
+@pytest.mark.parametrize("heads", [4, 2])   # of 64 and of 128
+def test_rows_do_not_feel_what_they_do_not_see(H, heads):
+    # a condition row, then a token of a chunk, that is NaN: the rows before it are the same to the bit as without it
+    s = BASE.replace(n_heads=heads, n_cond=70, batch=2)
+    blob = synth.make_weights(s, seed=4, std=0.05)
+    off, shape = synth.blob_layout(s)["E"]
+    forced = np.array([[3, 5, 900, 7], [2, 4, 900, 8]], np.int32)
+    u = np.full(2, 0.5, np.float32)
+
+    def run(cond, blob, feed):
+        hk = H.Hawk(H.HawkConfig.from_shape(s, k_max=3))
+        hk.load(blob)
+        hk.set_path(0)
+        hk.prefill(cond, None, s.grid_h, s.grid_w, 1.0, s.top_k, 1.0, u)
+        if not feed:
+            return hk.last_hidden(s.n_cond).cpu().numpy().reshape(2, s.n_cond, -1)
+        hk.force([1, 1], forced)     # rows: the last token of the prompt pass, then 3, 5, 900 and 2, 4, 900
+        return hk.last_hidden(4).cpu().numpy().reshape(2, 4, -1)
+
+    cond = synth.make_cond(s, seed=2)
+    clean, bad = run(cond, blob, False), cond.copy()
+    bad[0, 66], bad[1, 9] = np.nan, np.nan
+    got = run(bad, blob, False)
+    np.testing.assert_array_equal(got[0, :66], clean[0, :66])
+    np.testing.assert_array_equal(got[1, :9], clean[1, :9])
+    assert np.isnan(got[0, 66:]).all() and np.isnan(got[1, 9:]).all()
+    clean, holed = run(cond, blob, True), blob.copy()
+    holed[off:off + 2 * shape[0] * shape[1]].view(np.uint16).reshape(shape)[900] = 0x7FC0
+    got = run(cond, holed, True)
+    np.testing.assert_array_equal(got[:, :3], clean[:, :3])
+    assert np.isnan(got[:, 3]).all()
+
+
 HARD_ROWS = {
     "narrower than a bin can resolve": lambda rng, n: (rng.integers(0, 3, n) * 1e-38).astype(np.float32),
     "all equal": lambda rng, n: np.zeros(n, np.float32),
