@@ -242,10 +242,14 @@ __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
 // cores: 1920 cycles of MFMA per k-step of a 20 x 12 tile against 44 KB from L2 (23 B per cycle) and 136 KB
 // out of LDS (71 B per cycle).  The k-steps' loads are counted by hand (inline assembly): hipcc would wait for all of them
 // before every read of LDS.  The load reads M0 one wait state after it was written at the earliest; the compiler
-// does not look into the block, so the s_nop is ours.
+// does not look into the block, so the s_nop is ours, and M0 is named as changed.
 __device__ __forceinline__ void tile_to_lds(const uint16_t* src, const uint16_t* dst) {   // src per lane, dst wave-uniform
     const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const uint16_t*)dst;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane((int)at)), "v"(src) : "memory");
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // M0 is never allocated, only written before an instruction that reads it
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane((int)at)), "v"(src)
+                 : "memory", "m0");
+#pragma clang diagnostic pop
 }
 template <int WN, int WM, int SR, int CT, int S, int MODE>
 __global__ __launch_bounds__(64 * WN * WM) void rows_gemm_staged_kernel(RowsGemm g) {

@@ -22,3 +22,12 @@ def test_sampling_kernels_keep_their_entries_in_registers(tmp_path):
     assert any("multi_verify_kernel" in k for k in spills) and any("multi_verify_greedy_kernel" in k for k in spills)
     assert {k: n for k, n in spills.items() if n > SPILLS} == {}
     assert all(n <= 1 for k, n in spills.items() if "multi_verify_kernel" not in k), spills
+
+
+def test_assembly_that_writes_m0_says_so():
+    # the compiler does not look into an asm block: it has to be told that what it last put into M0 is gone
+    blocks = []
+    for src in build.SOURCES:
+        text = open(os.path.join(build.CSRC, src)).read()
+        blocks += [b for b in re.findall(r"asm(?: volatile)?\((.*?)\);\n", text, flags=re.S) if "_b32 m0" in b]
+    assert blocks and all('"m0"' in b.rpartition(":")[2] for b in blocks), blocks
