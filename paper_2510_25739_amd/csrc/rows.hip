@@ -156,12 +156,11 @@ __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
         }
     }
     rsrc_t rw[SR], rh[CT], rl[CT];
-    const uint16_t* wrow[SR];
+    const unsigned wl = (unsigned)(r16 * g.K + k0 * 32 + kg * 8) * 2u;   // row-major: the lane's first piece in a strip
 #pragma unroll
     for (int s = 0; s < SR; ++s) {
         const int strip = min(s_first + s, strips - 1);   // strips past the end repeat the last (never stored)
-        if (PACKED) rw[s] = bounded(g.W + ((size_t)strip * nk + k0) * 512, n * 1024);
-        else wrow[s] = g.W + (size_t)(strip * 16 + r16) * g.K + kg * 8;
+        rw[s] = PACKED ? bounded(g.W + ((size_t)strip * nk + k0) * 512, n * 1024) : bounded(g.W + (size_t)strip * 16 * g.K, (unsigned)g.K * 32u);
     }
 #pragma unroll
     for (int t = 0; t < CT; ++t) {
@@ -174,8 +173,7 @@ __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
         const unsigned at = (unsigned)lane * 16u + (unsigned)s * 1024u;
 #pragma unroll
         for (int i = 0; i < SR; ++i) {
-            if (PACKED) st.w[i] = __builtin_amdgcn_raw_buffer_load_b128(rw[i], at, 0, 0);
-            else st.w[i] = *reinterpret_cast<const v4u*>(wrow[i] + (size_t)min(k0 + s, nk - 1) * 32);
+            st.w[i] = __builtin_amdgcn_raw_buffer_load_b128(rw[i], PACKED ? at : s < n ? wl + (unsigned)s * 64u : 0x80000000u, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < CT; ++i) {
@@ -251,7 +249,7 @@ __device__ __forceinline__ void tile_to_lds(const uint16_t* src, const uint16_t*
                  : "memory", "m0");
 #pragma clang diagnostic pop
 }
-template <int WN, int WM, int SR, int CT, int S, int MODE>
+template <int WN, int WM, int SR, int CT, int S, bool PACKED, int MODE>
 __global__ __launch_bounds__(64 * WN * WM) void rows_gemm_staged_kernel(RowsGemm g) {
     constexpr int NWV = WN * WM, BS = WN * SR, BT = WM * CT, NTL = BS + 2 * BT, LPW = (NTL + NWV - 1) / NWV;
     extern __shared__ __attribute__((aligned(1024))) uint16_t stage[];   // [S][NTL][512]
@@ -268,7 +266,7 @@ __global__ __launch_bounds__(64 * WN * WM) void rows_gemm_staged_kernel(RowsGemm
 
     // this wave's tiles of a stage: numbers wave, wave + NWV, .. (past the end: the first ones again, same bytes)
     const uint16_t* src[LPW];
-    int slot[LPW];
+    int slot[LPW], step[LPW];
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
         int q = wave + i * NWV;
@@ -276,11 +274,16 @@ __global__ __launch_bounds__(64 * WN * WM) void rows_gemm_staged_kernel(RowsGemm
         slot[i] = q * 512;
         const int strip = min(s_first + q, strips - 1), tile = min(t_first + (q < BS + BT ? q - BS : q - BS - BT), tiles - 1);
         src[i] = (q < BS ? g.W + (size_t)strip * nk * 512 : (q < BS + BT ? g.hi : g.lo) + (size_t)tile * nk * 512) + lane * 8;
+        step[i] = 512;
+        if (!PACKED && q < BS) {   // row-major: the lane's own row of the strip
+            src[i] = g.W + (size_t)(strip * 16 + r16) * g.K + kg * 8;
+            step[i] = 32;
+        }
     }
     auto request = [&](int k) {   // k-steps past the end: the last one again, into a stage nobody reads any more
         const int kc = min(k, nk - 1), buf = (k % S) * NTL * 512;
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) tile_to_lds(src[i] + (size_t)kc * 512, stage + buf + slot[i]);
+        for (int i = 0; i < LPW; ++i) tile_to_lds(src[i] + (size_t)kc * step[i], stage + buf + slot[i]);
     };
     if (g.ssq_n > 0) {
         constexpr int RPW = 16 * BT / NWV;
@@ -416,12 +419,12 @@ __global__ __launch_bounds__(256) void rows_draft_input_kernel(const float* prev
     }
 }
 
-// Planes of the rows of A as they are.
+// Planes of the rows of A as they are.  Block (row, 1024 features).
 __global__ __launch_bounds__(256) void rows_split_kernel(const float* A, int lda, int K, uint16_t* hi, uint16_t* lo) {
-    for (int f = threadIdx.x * 4; f < K; f += 1024) {
-        const float4 a = *reinterpret_cast<const float4*>(A + (size_t)blockIdx.x * lda + f);
-        store_planes4(hi, lo, blockIdx.x, f, K / 32, (f32x4){a.x, a.y, a.z, a.w});
-    }
+    const int f = blockIdx.y * 1024 + threadIdx.x * 4;
+    if (f >= K) return;
+    const float4 a = *reinterpret_cast<const float4*>(A + (size_t)blockIdx.x * lda + f);
+    store_planes4(hi, lo, blockIdx.x, f, K / 32, (f32x4){a.x, a.y, a.z, a.w});
 }
 
 __global__ void rope_table_kernel(const double* inv_freq, float2* tab, int pairs, int positions) {
@@ -843,7 +846,7 @@ static int pick_kernel(const RowsGemm& g) {
     float cost = 1e30f;
     for (int i = 0; i < (int)(sizeof kRowsKernels / sizeof kRowsKernels[0]); ++i) {
         const RowsKernel& t = kRowsKernels[i];
-        if (t.staged && (!g.packed || tiles < 4)) continue;
+        if (t.staged && tiles < 4) continue;
         const long wgs = (long)((strips + t.SR - 1) / t.SR) * ((tiles + t.CT - 1) / t.CT);
         // small tiles share a unit, at 1.3 times the cost of having it alone
         const float rounds = t.slots == 1 ? (float)((wgs + 255) / 256)
@@ -854,51 +857,82 @@ static int pick_kernel(const RowsGemm& g) {
     return best;
 }
 
-template <int WN, int WM, int SR, int CT, int S, int MODE> static void launch_staged(hipStream_t stream, const RowsGemm& g) {
+// Row-major weights (the dual-direction heads, contexts without the tile-major copy) come as 64-byte pieces of 16 rows: a
+// round of 256 workgroups takes fixed + step microseconds per k-step, whether a unit holds one of them or two, and
+// kernels that draw the weights once for all rows win early.  Fitted to 45 products (K 768, 1280, 4096; 1 to 2048 rows;
+// weights in the last-level cache and not): the choice is the fastest of these nine for 44 of them and 5 % behind for one.
+// With the costs of the tile-major kernels, weights not in cache: 44 rows of 8192 x 4096 (4, 1) 50 us, (4, 3) here 35 us;
+// one row of 8192 x 4096 (2, 1) of eight waves 27 us, of four waves 17.6 us; 1024 rows of 16384 x 1280 (4, 4) 245 us,
+// (16, 8) 96 us.
+struct RowMajorKernel { int SR, CT; float fixed, step; };
+static const RowMajorKernel kRowMajorKernels[] = {{1, 1, 1.2f, 0.059f}, {2, 1, 1.5f, 0.094f}, {4, 1, 1.5f, 0.169f}, {2, 2, 1.9f, 0.11f}, {4, 3, 2.4f, 0.205f},
+                                                  {4, 4, 5.3f, 0.202f}, {8, 8, 5.5f, 0.462f}, {16, 8, 8.9f, 0.802f}, {20, 12, 14.2f, 1.278f}};
+static int pick_row_major(const RowsGemm& g) {
+    const int strips = g.N / 16, tiles = (g.M + 15) / 16;
+    int best = 0;
+    float cost = 1e30f;
+    for (int i = 0; i < (int)(sizeof kRowMajorKernels / sizeof kRowMajorKernels[0]); ++i) {
+        const RowMajorKernel& t = kRowMajorKernels[i];
+        const long wgs = (long)((strips + t.SR - 1) / t.SR) * ((tiles + t.CT - 1) / t.CT);
+        const float us = (float)((wgs + 255) / 256) * (t.fixed + t.step * (float)(g.K / 32));
+        if (us < cost) { cost = us; best = i; }
+    }
+    return best;
+}
+
+template <int WN, int WM, int SR, int CT, int S, bool PACKED, int MODE> static void launch_staged(hipStream_t stream, const RowsGemm& g) {
     constexpr int BS = WN * SR, BT = WM * CT, lds = S * (BS + 2 * BT) * 1024;
     const int strips = g.N / 16, tiles = (g.M + 15) / 16, total = ((strips + BS - 1) / BS) * ((tiles + BT - 1) / BT);
-    auto k = rows_gemm_staged_kernel<WN, WM, SR, CT, S, MODE>;
+    auto k = rows_gemm_staged_kernel<WN, WM, SR, CT, S, PACKED, MODE>;
     // per launch: the attribute belongs to the current device; a failure shows as a failed launch
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     k<<<(total + 7) / 8 * 8, 64 * WN * WM, lds, stream>>>(g);
 }
-template <bool PACKED, int MODE> static void launch_rows_gemm_as(hipStream_t stream, const RowsGemm& g) {
+template <int SR, int CT, int D, int KW, bool PACKED, int MODE> static void launch_direct(hipStream_t stream, const RowsGemm& g) {
     const int strips = g.N / 16, tiles = (g.M + 15) / 16;
-#define HAWK_ROWS_TILE(I, SRV, CTV, DV, KWV)                                                                           \
-    case I:                                                                                                            \
-        rows_gemm_kernel<SRV, CTV, DV, KWV, PACKED, MODE>                                                              \
-            <<<((strips + SRV - 1) / SRV + 7) / 8 * 8 * ((tiles + CTV - 1) / CTV), 64 * KWV, 0, stream>>>(g);          \
-        return;
+    rows_gemm_kernel<SR, CT, D, KW, PACKED, MODE><<<((strips + SR - 1) / SR + 7) / 8 * 8 * ((tiles + CT - 1) / CT), 64 * KW, 0, stream>>>(g);
+}
+template <int MODE> static void launch_packed(hipStream_t stream, const RowsGemm& g) {
     switch (pick_kernel(g)) {
-        HAWK_ROWS_TILE(0, 1, 1, 6, 8)
-        HAWK_ROWS_TILE(1, 2, 1, 5, 8)
-        HAWK_ROWS_TILE(2, 4, 1, 4, 8)
-        HAWK_ROWS_TILE(3, 2, 2, 6, 4)
-        HAWK_ROWS_TILE(4, 4, 2, 3, 8)
-        HAWK_ROWS_TILE(5, 4, 3, 2, 8)
-        HAWK_ROWS_TILE(6, 4, 3, 3, 4)
-        HAWK_ROWS_TILE(7, 4, 4, 2, 8)
+        case 0: return launch_direct<1, 1, 6, 8, true, MODE>(stream, g);
+        case 1: return launch_direct<2, 1, 5, 8, true, MODE>(stream, g);
+        case 2: return launch_direct<4, 1, 4, 8, true, MODE>(stream, g);
+        case 3: return launch_direct<2, 2, 6, 4, true, MODE>(stream, g);
+        case 4: return launch_direct<4, 2, 3, 8, true, MODE>(stream, g);
+        case 5: return launch_direct<4, 3, 2, 8, true, MODE>(stream, g);
+        case 6: return launch_direct<4, 3, 3, 4, true, MODE>(stream, g);
+        case 7: return launch_direct<4, 4, 2, 8, true, MODE>(stream, g);
+        case 8: return launch_staged<2, 4, 4, 2, 4, true, MODE>(stream, g);
+        case 9: return launch_staged<2, 4, 5, 2, 4, true, MODE>(stream, g);
+        case 10: return launch_staged<4, 2, 4, 4, 4, true, MODE>(stream, g);
+        default: return launch_staged<4, 2, 5, 6, 3, true, MODE>(stream, g);
     }
-#undef HAWK_ROWS_TILE
-    if constexpr (PACKED) switch (pick_kernel(g)) {
-        case 8: launch_staged<2, 4, 4, 2, 4, MODE>(stream, g); return;
-        case 9: launch_staged<2, 4, 5, 2, 4, MODE>(stream, g); return;
-        case 10: launch_staged<4, 2, 4, 4, 4, MODE>(stream, g); return;
-        default: launch_staged<4, 2, 5, 6, 3, MODE>(stream, g); return;
+}
+template <int MODE> static void launch_row_major(hipStream_t stream, const RowsGemm& g) {
+    switch (pick_row_major(g)) {
+        case 0: return launch_direct<1, 1, 6, 4, false, MODE>(stream, g);
+        case 1: return launch_direct<2, 1, 4, 4, false, MODE>(stream, g);
+        case 2: return launch_direct<4, 1, 3, 4, false, MODE>(stream, g);
+        case 3: return launch_direct<2, 2, 4, 4, false, MODE>(stream, g);
+        case 4: return launch_direct<4, 3, 3, 4, false, MODE>(stream, g);
+        case 5: return launch_direct<4, 4, 2, 8, false, MODE>(stream, g);
+        case 6: return launch_staged<2, 4, 4, 2, 4, false, MODE>(stream, g);
+        case 7: return launch_staged<4, 2, 4, 4, 4, false, MODE>(stream, g);
+        default: return launch_staged<4, 2, 5, 6, 3, false, MODE>(stream, g);
     }
 }
 
 void launch_rows_gemm(hipStream_t stream, const RowsGemm& g) {
     if (g.packed) {
         switch (g.mode) {
-            case kGemmPlain: launch_rows_gemm_as<true, kGemmPlain>(stream, g); return;
-            case kGemmResidual: launch_rows_gemm_as<true, kGemmResidual>(stream, g); return;
-            default: launch_rows_gemm_as<true, kGemmSwiglu>(stream, g); return;
+            case kGemmPlain: launch_packed<kGemmPlain>(stream, g); return;
+            case kGemmResidual: launch_packed<kGemmResidual>(stream, g); return;
+            default: launch_packed<kGemmSwiglu>(stream, g); return;
         }
     }
-    if (g.mode == kGemmHeads) launch_rows_gemm_as<false, kGemmHeads>(stream, g);
-    else if (g.mode == kGemmResidual) launch_rows_gemm_as<false, kGemmResidual>(stream, g);
-    else launch_rows_gemm_as<false, kGemmPlain>(stream, g);
+    if (g.mode == kGemmHeads) launch_row_major<kGemmHeads>(stream, g);
+    else if (g.mode == kGemmResidual) launch_row_major<kGemmResidual>(stream, g);
+    else launch_row_major<kGemmPlain>(stream, g);
 }
 
 int gemm_pack_weights(hawk_ctx* c) {
@@ -915,7 +949,7 @@ int gemm_pack_weights(hawk_ctx* c) {
 }
 
 void launch_rows_split(hipStream_t stream, const float* A, int lda, int M, int K, uint16_t* hi, uint16_t* lo) {
-    rows_split_kernel<<<M, 256, 0, stream>>>(A, lda, K, hi, lo);
+    rows_split_kernel<<<dim3(M, (K + 1023) / 1024), 256, 0, stream>>>(A, lda, K, hi, lo);
 }
 
 // Shapes of the whole path: bf16 with the tile-major weight copy, heads of 64 or 128.

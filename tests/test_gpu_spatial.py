@@ -44,6 +44,11 @@ HEAD_CASES = [
     (5, 3, 192, 4096),      # d a multiple of 64 only
     (7, 4, 512, 2000),      # more than sixteen (row, head) pairs, ragged output layer
     (12, 4, 4096, 8192),    # the 7B shape: twelve rows (two guidance streams), 8192-entry slice
+    (16, 4, 768, 16384),    # 64 (row, head) pairs over a full slice, each weight drawn once
+    (24, 4, 1280, 4096),    # two row tiles a weight: (2, 2)
+    (65, 4, 256, 16400),    # LDS-staged with row-major weights, ragged both ways: (16, 8)
+    (64, 4, 512, 16384),    # (8, 8)
+    (150, 4, 512, 16384),   # (20, 12)
 ]
 
 
