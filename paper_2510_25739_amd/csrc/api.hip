@@ -156,7 +156,8 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     o.replay = take(B * c->Nmax * 4); o.cond = take(S * (size_t)g->max_cond * d * 4);
     o.tree = take(TreeArea(B).bytes);
     o.llen = take(list_len_bytes(B * ks)); o.lidx = take(list_idx_bytes(B * ks)); o.lw = take(list_w_bytes(B * ks));
-    const size_t widest = 3 * d > m ? 3 * d : m;
+    const size_t m32 = (m + 31) & ~(size_t)31;   // hidden features in whole k-tiles
+    const size_t widest = 3 * d > m32 ? 3 * d : m32;
     const size_t M16 = (M + 15) & ~(size_t)15;   // planes come in tiles of 16 rows
     c->split_bytes = g->dtype == HAWK_BF16 ? M16 * widest * 4 : 0;
     o.split = c->split_bytes ? take(c->split_bytes) : 0;
@@ -167,21 +168,21 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     // MFMA kernels then fetch whole kilobytes per request instead of 64-byte pieces of 16 rows.
     c->n_gpk = 0;
     o.gpack = 0;
-    if (g->dtype == HAWK_BF16 && d % 32 == 0 && m % 32 == 0 && Vs % 16 == 0) {
+    if (g->dtype == HAWK_BF16 && d % 32 == 0) {
         size_t q = 0;
-        auto reg = [&](size_t blob_off, size_t N, size_t K, int pairs = 0) {
+        auto reg = [&](size_t blob_off, size_t N, size_t K, size_t cols, int pairs = 0) {
             auto& e2 = c->gpk[c->n_gpk++];
-            e2.blob_off = blob_off; e2.pack_off = q; e2.N = (int)N; e2.K = (int)K; e2.pairs = pairs;
+            e2.blob_off = blob_off; e2.pack_off = q; e2.N = (int)N; e2.K = (int)K; e2.cols = (int)cols; e2.pairs = pairs;
             q += N * K * 2;
         };
         for (int l = 0; l < c->L; ++l) {
-            reg(c->w.Wqkv[l], 3 * d, d);
-            reg(c->w.Wo[l], d, d);
-            reg(c->w.W13[l], 2 * m, d, (int)m);   // W1 and W3 rows interleaved: SwiGLU in the GEMM's epilogue
-            reg(c->w.W2[l], d, m);
+            reg(c->w.Wqkv[l], 3 * d, d, d);
+            reg(c->w.Wo[l], d, d, d);
+            reg(c->w.W13[l], 2 * m32, d, d, (int)m);   // W1 and W3 rows interleaved: SwiGLU in the GEMM's epilogue
+            reg(c->w.W2[l], d, m32, m);
         }
-        reg(c->w.W_out + (size_t)g->samp_lo * d * e, Vs, d);
-        reg(c->w.W_d, d, 3 * d);
+        reg(c->w.W_d, d, 3 * d, 3 * d);
+        if (Vs % 16 == 0) reg(c->w.W_out + (size_t)g->samp_lo * d * e, Vs, d, d);
         o.gpack = take(q);
     }
     p += stream_workspace(c, p, &c->soff);

@@ -410,7 +410,8 @@ void launch_rmsnorm(hawk_ctx* c, size_t off_in, size_t in_stride, size_t off_gai
 
 void launch_gemm(hawk_ctx* c, size_t off_a, int lda, size_t w_off, int N, int K, size_t off_y, int ldy,
                  int M, bool accumulate, bool out_f32) {
-    // bf16 shapes whose product the matrix cores take although the context as a whole does not run in rows.hip
+    // bf16 products that the matrix cores take although the context as a whole does not run in rows.hip (d no multiple of 32),
+    // or that have no tile-major weights there
     if (c->off.split && K % 32 == 0 && N % 16 == 0 && ldy % 4 == 0 && lda % 4 == 0 && 4 * plane_halves(M, K) <= c->split_bytes) {
         RowsGemm g;
         memset(&g, 0, sizeof g);

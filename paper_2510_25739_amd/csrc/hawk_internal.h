@@ -105,7 +105,7 @@ struct hawk_ctx {
     size_t blob_bytes;
     size_t split_bytes;
     // matrices in the tile-major copy; pairs = m for W1|W3 stored with rows interleaved (W1 row f, W3 row f, ...)
-    struct { size_t blob_off, pack_off; int N, K, pairs; } gpk[4 * 128 + 2];
+    struct { size_t blob_off, pack_off; int N, K, cols, pairs; } gpk[4 * 128 + 2];
     int n_gpk;
     // per image
     int B, S, C, gh, gw, N, top_k, greedy;

@@ -38,14 +38,17 @@ __device__ __forceinline__ rsrc_t bounded(const void* base, unsigned bytes) {
 // s * 16 + l % 16, columns kt * 32 + (l / 16) * 8 .. + 7: one MFMA A operand per tile.
 // pairs > 0 (W1|W3, pairs = m): strip s holds W1 rows 8 s .. 8 s + 7 and the matching W3 rows
 // interleaved (row 2 j = W1 row 8 s + j, row 2 j + 1 = W3 row 8 s + j), so that an MFMA result lane
-// holds both halves of a SwiGLU pair.
-__global__ void pack_tiles_kernel(const uint16_t* W, int K, v4u* dst, size_t total, int pairs) {
+// holds both halves of a SwiGLU pair.  Hidden features come in whole k-tiles: rows of W1|W3 and columns of W2 from m up
+// to the next multiple of 32 are zeros, and so are the features between them.  cols: columns of W (m for W2, else K).
+__global__ void pack_tiles_kernel(const uint16_t* W, int K, int cols, v4u* dst, size_t total, int pairs) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= total) return;
     const int lane = (int)(i & 63), r = lane & 15;
     const size_t tile = i >> 6, kts = (size_t)K / 32, s = tile / kts, kt = tile - s * kts;
     const size_t row = pairs ? (size_t)(r & 1) * pairs + s * 8 + (r >> 1) : s * 16 + r;
-    dst[i] = *reinterpret_cast<const v4u*>(W + row * (size_t)K + kt * 32 + (lane >> 4) * 8);
+    const size_t col = kt * 32 + (lane >> 4) * 8;
+    const bool inside = col < (size_t)cols && (!pairs || s * 8 + (r >> 1) < (size_t)pairs);
+    dst[i] = inside ? *reinterpret_cast<const v4u*>(W + row * (size_t)cols + col) : (v4u){0u, 0u, 0u, 0u};
 }
 
 // Sum over the wave's 64 lanes, the same value in every lane.
@@ -79,6 +82,15 @@ __device__ __forceinline__ f32x4 gains4(const uint16_t* g) {
 }
 
 // ------------------------------------------------------------------------------------------ products
+
+// Lane's share of a row's partial sums of squares: the four it loaded before, and those past the first 256 (d > 4096).
+__device__ __forceinline__ float ssq_share(const RowsGemm& g, int row, int lane, f32x4 first) {
+    float v = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v += lane * 4 + e < g.ssq_n ? first[e] : 0.f;
+    for (int p = 256 + lane; p < g.ssq_n; p += 64) v += g.ssq[(size_t)row * g.ssq_ld + p];
+    return v;
+}
 
 // What follows a product, for one result lane: features f .. f + 3 of a row (lane group kg of the strip).
 template <int MODE>
@@ -150,7 +162,7 @@ __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
     if (g.ssq_n > 0) {
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
-            // straight-line (a loop per row would wait for each row in turn); a row has at most 256 partial sums
+            // straight-line: a loop per row would wait for each row in turn
             const int r = min(t_first * 16 + wave + i * KW, g.M - 1);
             sq[i] = *reinterpret_cast<const f32x4*>(g.ssq + (size_t)r * g.ssq_ld + min(lane * 4, g.ssq_ld - 4));
         }
@@ -204,10 +216,7 @@ __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
     if (g.ssq_n > 0) {
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
-            float v = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v += lane * 4 + e < g.ssq_n ? sq[i][e] : 0.f;
-            v = wave_total(v);
+            const float v = wave_total(ssq_share(g, min(t_first * 16 + wave + i * KW, g.M - 1), lane, sq[i]));
             if (lane == 0 && wave + i * KW < 16 * CT) rscale[wave + i * KW] = 1.0f / sqrtf(v / g.norm_d + g.eps);
         }
     }
@@ -293,10 +302,7 @@ __global__ __launch_bounds__(64 * WN * WM) void rows_gemm_staged_kernel(RowsGemm
             sq[i] = *reinterpret_cast<const f32x4*>(g.ssq + (size_t)min(t_first * 16 + wave * RPW + i, g.M - 1) * g.ssq_ld + min(lane * 4, g.ssq_ld - 4));
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
-            float v = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v += lane * 4 + e < g.ssq_n ? sq[i][e] : 0.f;
-            v = wave_total(v);
+            const float v = wave_total(ssq_share(g, min(t_first * 16 + wave * RPW + i, g.M - 1), lane, sq[i]));
             if (lane == 0) rscale[wave * RPW + i] = 1.0f / sqrtf(v / g.norm_d + g.eps);
         }
     }
@@ -941,7 +947,7 @@ int gemm_pack_weights(hawk_ctx* c) {
         const auto& e = c->gpk[i];
         const size_t total = (size_t)e.N * e.K / 8;   // 16-byte chunks
         pack_tiles_kernel<<<(unsigned)((total + 255) / 256), 256, 0, c->stream>>>(
-            reinterpret_cast<const uint16_t*>(c->ws + c->off.blob + e.blob_off), e.K,
+            reinterpret_cast<const uint16_t*>(c->ws + c->off.blob + e.blob_off), e.K, e.cols,
             reinterpret_cast<v4u*>(c->ws + c->off.gpack + e.pack_off), total, e.pairs);
     }
     if (hipGetLastError() != hipSuccess) return -1;
@@ -952,10 +958,8 @@ void launch_rows_split(hipStream_t stream, const float* A, int lda, int M, int K
     rows_split_kernel<<<dim3(M, (K + 1023) / 1024), 256, 0, stream>>>(A, lda, K, hi, lo);
 }
 
-// Shapes of the whole path: bf16 with the tile-major weight copy, heads of 64 or 128.
-bool rows_ok(const hawk_ctx* c) {
-    return c->cfg.dtype == HAWK_BF16 && c->off.gpack && (c->hd == 64 || c->hd == 128) && c->d % 32 == 0 && c->d <= 4096 && c->m % 32 == 0;
-}
+// Contexts that take this path: those with the tile-major copy of their weights (bf16, d a multiple of 32).
+bool rows_ok(const hawk_ctx* c) { return c->off.gpack != 0; }
 
 int rows_fill_rope(hawk_ctx* c) {
     if (!c->off.rtab) return 0;
@@ -990,9 +994,14 @@ void scaled_by_rms(hawk_ctx* c, RowsGemm& g, int partials) {
 
 }  // namespace
 
-// The output layer over the rows whose planes (of x * g_f) and sums of squares are current.
-static void rows_output_layer(hawk_ctx* c, int M, int partials, size_t off_logits) {
-    RowsGemm g = product(c, plane_pair(c, c->off.split, M, c->d), M, c->d, 4 * c->L, kGemmPlain);
+// The output layer over the rows of x (`stride` values apart), whose planes (of x * g_f) and sums of squares are current.
+static void rows_output_layer(hawk_ctx* c, int M, int partials, size_t off_x, size_t stride, size_t off_logits) {
+    if (c->Vs % 16) {   // no whole strips: row by row
+        launch_rmsnorm(c, off_x, stride, c->w.g_f, c->off.a, M);
+        launch_gemm(c, c->off.a, c->d, c->w.W_out + (size_t)c->cfg.samp_lo * c->d * c->esz, c->Vs, c->d, off_logits, c->Vs, M, false, true);
+        return;
+    }
+    RowsGemm g = product(c, plane_pair(c, c->off.split, M, c->d), M, c->d, 4 * c->L + 1, kGemmPlain);
     scaled_by_rms(c, g, partials);
     g.Y = wsp<float>(c, off_logits); g.ldy = c->Vs;
     launch_rows_gemm(c->stream, g);
@@ -1001,7 +1010,7 @@ static void rows_output_layer(hawk_ctx* c, int M, int partials, size_t off_logit
 // All decoder layers over M rows (mode 0: condition rows, 1: step rows, 2: tree rows), from their embedding or
 // condition vectors; leaves x and, for the output layer, the planes of x * g_f with the sums of squares.
 static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
-    const int d = c->d, m = c->m;
+    const int d = c->d, m = (c->m + 31) & ~31;   // hidden features as the tile-major copies have them
     const PlanePtr pa = plane_pair(c, c->off.split, M, d), po = plane_pair(c, c->off.split + 2 * sizeof(uint16_t) * plane_halves(M, d), M, d),
                    pu = plane_pair(c, c->off.split2, M, m);
     float *x = wsp<float>(c, c->off.x), *ssq = wsp<float>(c, c->off.ssq);
@@ -1021,7 +1030,11 @@ static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
         a.qkv = wsp<float>(c, c->off.qkv); a.Kc = wsp<_Float16>(c, c->off.kc) + layer; a.Vc = wsp<_Float16>(c, c->off.vc) + layer;
         a.rope = wsp<float2>(c, c->off.rtab); a.map = map; a.d = d; a.H = c->H; a.Tmax = c->Tmax; a.hi = po.hi; a.lo = po.lo;
         const int R = map.rows_per_seq;
-        if (map.mode == 0) {
+        if (c->hd != 64 && c->hd != 128) {   // heads that the kernels above have no tiles for
+            launch_rope_append(c, map, l, M);
+            launch_attention(c, map, l, M);
+            launch_rows_split(c->stream, wsp<float>(c, c->off.o), d, M, d, po.hi, po.lo);
+        } else if (map.mode == 0) {
             auto k = c->hd == 64 ? attn_prompt_kernel<64> : attn_prompt_kernel<128>;
             k<<<dim3((R + 63) / 64, c->H, c->S), 256, 0, c->stream>>>(a);
         } else {
@@ -1051,16 +1064,17 @@ static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
 
 void rows_step_pass(hawk_ctx* c, const RowMap& map, int M) {
     rows_layers(c, map, M);
-    rows_output_layer(c, M, c->d / 16, c->off.logit_s);
+    rows_output_layer(c, M, c->d / 16, c->off.x, c->d, c->off.logit_s);
 }
 
 // Condition rows; logits of the last one of every sequence.
 void rows_prompt_pass(hawk_ctx* c, const RowMap& map, int M) {
     rows_layers(c, map, M);
     const PlanePtr p = plane_pair(c, c->off.split, c->S, c->d);
-    rows_pick_kernel<<<c->S, 256, 0, c->stream>>>(wsp<float>(c, c->off.x) + (size_t)(c->C - 1) * c->d, (size_t)c->C * c->d, c->d,
-                                                  blob16(c, c->w.g_f), p.hi, p.lo, wsp<float>(c, c->off.ssq), ssq_ld(c));
-    rows_output_layer(c, c->S, 1, c->off.logit_s);
+    const size_t last = c->off.x + (size_t)(c->C - 1) * c->d * sizeof(float), stride = (size_t)c->C * c->d;
+    rows_pick_kernel<<<c->S, 256, 0, c->stream>>>(wsp<float>(c, last), stride, c->d, blob16(c, c->w.g_f), p.hi, p.lo,
+                                                  wsp<float>(c, c->off.ssq), ssq_ld(c));
+    rows_output_layer(c, c->S, 1, last, stride, c->off.logit_s);
 }
 
 // Draft micro-step i up to its logits: head output to off_out ([S][d] fp32), reading the previous one from off_prev.
@@ -1070,11 +1084,11 @@ void rows_draft_pass(hawk_ctx* c, int i, size_t off_prev, size_t off_out) {
     rows_draft_input_kernel<<<dim3(3, S), 256, 0, c->stream>>>(wsp<float>(c, off_prev), blob16(c, c->w.E), wsp<int32_t>(c, c->off.n),
                                                                wsp<int32_t>(c, c->off.k_eff), wsp<int32_t>(c, c->off.grid),
                                                                wsp<int32_t>(c, c->off.draft), i, c->B, c->N, c->gw, c->kmax + 1, d, pin.hi, pin.lo);
-    RowsGemm g = product(c, pin, S, 3 * d, 4 * c->L + 1, kGemmPlain);
+    RowsGemm g = product(c, pin, S, 3 * d, 4 * c->L, kGemmPlain);
     g.Y = wsp<float>(c, off_out); g.ldy = d; g.ohi = pa.hi; g.olo = pa.lo; g.okts = d / 32; g.gain = blob16(c, c->w.g_f);
     g.ossq = wsp<float>(c, c->off.ssq); g.ossq_ld = ssq_ld(c);
     launch_rows_gemm(c->stream, g);
-    rows_output_layer(c, S, d / 16, c->off.dlogit_s);
+    rows_output_layer(c, S, d / 16, off_out, d, c->off.dlogit_s);
 }
 
 }  // namespace hawk

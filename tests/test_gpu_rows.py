@@ -57,9 +57,9 @@ def relative(a, b):
     return float(np.linalg.norm(a - b) / np.linalg.norm(b))
 
 
-def hidden_pair(H, s, chunk):
+def hidden_pair(H, s, chunk, want_logits=False, std=0.05):
     """Hidden states of the prompt rows and of a teacher-forced chunk of every sequence, and their reference."""
-    blob = synth.make_weights(s, seed=4, std=0.05)
+    blob = synth.make_weights(s, seed=4, std=std)
     hk = H.Hawk(H.HawkConfig.from_shape(s, k_max=max(chunk - 1, 0)))
     hk.load(blob)
     hk.set_path(0)
@@ -75,7 +75,8 @@ def hidden_pair(H, s, chunk):
     got.append(hk.last_hidden(chunk).cpu().numpy().reshape(s.n_seq, chunk, -1))
     x0 = cond if unc is None else np.concatenate([cond, unc])
     emb = np.asarray(synth.blob_tensor(s, blob, "E"))[np.tile(tok, (s.n_seq // s.batch, 1))]
-    return np.concatenate(got, axis=1), reference(s, blob, np.concatenate([x0, emb], axis=1))
+    pair = np.concatenate(got, axis=1), reference(s, blob, np.concatenate([x0, emb], axis=1))
+    return pair + (hk.logits(chunk), blob) if want_logits else pair
 
 
 BASE = synth.HawkShape("rows", 2, 256, 4, 704, 1024, 16, 8, 8, 5, top_k=50)
@@ -100,6 +101,23 @@ def test_many_row_passes_match_a_float64_forward(H, d, heads, mlp, batch, scale,
     prompt, step = relative(got[:, :n_cond], ref[:, :n_cond]), relative(got[:, n_cond:], ref[:, n_cond:])
     print(f"rows {s.n_seq * n_cond} + {s.n_seq * chunk}: relative error prompt {prompt:.2e}, step {step:.2e}")
     assert prompt < 1e-3 and step < 1e-3
+
+
+@pytest.mark.parametrize("d,heads,mlp,vocab,batch", [
+    (256, 8, 704, 1024, 5),       # heads of 32
+    (288, 9, 488, 1000, 3),       # hidden features and vocabulary slice in no whole tiles
+    (4352, 17, 352, 1008, 2),     # heads of 256, more than 256 partial sums of squares a row
+])
+def test_other_shapes_match_a_float64_forward(H, d, heads, mlp, vocab, batch):
+    # Weights of deviation 0.8 / sqrt(d), as 0.05 is at 256: queries and keys of size 0.8 and so scores of order one, which
+    # the bound above rests on (0.05 at 4352 gives scores of order ten: 1.5e-3).  Logits, of size 0.8, carry the hidden
+    # states' relative error.
+    s = BASE.replace(d_model=d, n_heads=heads, d_mlp=mlp, vocab=vocab, batch=batch, n_cond=21)
+    got, ref, logits, blob = hidden_pair(H, s, 6, want_logits=True, std=0.8 / d ** 0.5)
+    assert relative(got, ref) < 1e-3
+    x = ref[:, -6:]
+    want = x / np.sqrt((x * x).mean(-1, keepdims=True) + s.rms_eps) * synth.blob_tensor(s, blob, "g_f") @ synth.blob_tensor(s, blob, "W_out").T.astype(np.float64)
+    assert relative(logits, want) < 1e-3
 
 
 def test_queries_beyond_the_range_of_a_half(H):
