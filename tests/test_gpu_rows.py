@@ -91,6 +91,12 @@ SHAPES = [
     (512, 8, 1376, 32, 1.0, 63, 2),    # LDS-staged (16, 8) with a ragged last group
     (768, 12, 2048, 16, 2.0, 100, 2),  # LDS-staged (20, 12)
     (512, 8, 1376, 32, 1.0, 100, 2),   # LDS-staged (10, 8) for the projections and the MLP
+    # step attention with more cached positions than its waves request at once: eight waves, then four (from 256
+    # workgroups on), heads of 64 (three tiles of 16 a wave) and of 128 (two)
+    (256, 4, 704, 1, 1.0, 400, 5),
+    (256, 2, 704, 1, 1.0, 270, 5),
+    (256, 4, 704, 64, 1.0, 210, 2),
+    (256, 2, 704, 128, 1.0, 140, 2),
 ]
 
 
