@@ -155,7 +155,8 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     o.out_na = take(B * 4); o.out_tok = take(B * ks * 4); o.inv_freq = take((size_t)(hd / 2) * 8);
     o.replay = take(B * c->Nmax * 4); o.cond = take(S * (size_t)g->max_cond * d * 4);
     o.tree = take(TreeArea(B).bytes);
-    o.llen = take(list_len_bytes(B * ks)); o.lidx = take(list_idx_bytes(B * ks)); o.lw = take(list_w_bytes(B * ks));
+    const size_t lists = Vs <= 16 * (size_t)kSampThreads ? B * ks : 0;   // larger rows are not sampled from lists
+    o.llen = take(list_len_bytes(lists)); o.lidx = take(list_idx_bytes(lists)); o.lw = take(list_w_bytes(lists));
     const size_t m32 = (m + 31) & ~(size_t)31;   // hidden features in whole k-tiles
     const size_t widest = 3 * d > m32 ? 3 * d : m32;
     const size_t M16 = (M + 15) & ~(size_t)15;   // planes come in tiles of 16 rows

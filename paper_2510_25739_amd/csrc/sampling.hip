@@ -23,11 +23,9 @@ struct Shared {
     double dred[NW];
     int ired[NW];
     float fred[NW];
-    unsigned ukred[NW];
     // broadcast slots
     unsigned b_prefix, b_remaining, b_count_eq;
     int b_int;
-    double b_dbl;
 };
 
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {
@@ -148,17 +146,6 @@ __device__ float block_max_f(float v, Shared& sh) {
 #pragma unroll
     for (int w = 1; w < NW; ++w) t = fmaxf(t, sh.fred[w]);
     return t;
-}
-// Minimum and maximum over the block in one exchange.
-__device__ void block_minmax_f(float& lo, float& hi, Shared& sh) {
-    lo = wave_min_f(lo);
-    hi = wave_max_f(hi);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) { sh.fred[threadIdx.x >> 6] = lo; sh.dred[threadIdx.x >> 6] = (double)hi; }
-    __syncthreads();
-    lo = sh.fred[0]; hi = (float)sh.dred[0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) { lo = fminf(lo, sh.fred[w]); hi = fmaxf(hi, (float)sh.dred[w]); }
 }
 __device__ int block_min_i(int v, Shared& sh) {
     v = wave_min_i(v);

@@ -109,7 +109,8 @@ bool cache_args_ok(int IW, int IH, int VSD, int Vs) {
 
 }  // namespace
 
-// planes of h, planes of g (and room for g itself, which the caller may want to look at)
+// Planes of h, planes of g, and before them room for g as fp32 that nothing uses any more: callers size their buffers by
+// what this function has always asked for at least.
 size_t spatial_heads_workspace_bytes(int rows, int n_heads, int d) {
     const size_t M = (size_t)rows * n_heads;
     return align_up(M * d * sizeof(float)) + align_up(4 * plane_halves(rows, d)) + align_up(4 * plane_halves((int)M, d));
