@@ -141,9 +141,10 @@ __device__ __forceinline__ void gemm_epilogue(const RowsGemm& g, f32x4 v, int ro
 // rows; its KW waves split K and work alone - weight tiles and plane tiles straight into registers in operand
 // order, D k-steps of 32 in flight, no LDS and no barrier in the loop - and add their partial results
 // through LDS at the end, where each takes its share of the tiles through the epilogue.
-// Bound by what one compute unit draws from L2 (64 bytes per cycle): SR + 2 CT kilobytes per k-step, every
-// byte fetched once per workgroup; the tile is chosen per shape (pick_kernel).  Workgroups that
-// share weights follow each other on one XCD, so that the second finds them in its L2.
+// A k-step draws SR + 2 CT kilobytes from L2 for SR CT tiles of 2 MFMAs, every byte fetched once per workgroup; the
+// tile is chosen per shape (pick_kernel).  Workgroups that share weights follow each other on one XCD, so that the second
+// finds them in its L2.  Bound by the latency of the loads in flight: at 192 rows of the XL widths (17.5 us for W1|W3,
+// 10.8 us for QKV) 9 to 14 bytes per cycle reach a compute unit from L2 (of 64) and its matrix cores are 8 to 13 % busy.
 template <int SR, int CT, int D, int KW, bool PACKED, int MODE>
 __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
     __shared__ f32x4 part[KW][SR * CT][64];
@@ -245,9 +246,10 @@ __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
 // The same product where the rows are many enough to be a contraction (the prompt pass): a workgroup of WN x WM
 // waves owns (WN SR) strips x (WM CT) row tiles; weight and plane tiles of a k-step go to LDS - whole tiles of 1 KB
 // in operand order, moved by the load unit itself (no registers, no address arithmetic, no bank conflicts) - S
-// stages deep, and every wave reads the SR + 2 CT tiles of its part for 2 SR CT MFMAs.  Bound by the matrix
-// cores: 1920 cycles of MFMA per k-step of a 20 x 12 tile against 44 KB from L2 (23 B per cycle) and 136 KB
-// out of LDS (71 B per cycle).  The k-steps' loads are counted by hand (inline assembly): hipcc would wait for all of them
+// stages deep, and every wave reads the SR + 2 CT tiles of its part for 2 SR CT MFMAs.  A k-step of a 20 x 12 tile is
+// 1920 cycles of MFMA, 44 KB from L2 and 136 KB out of LDS.  Measured at 3840 rows of 3840 x 1280 (73 us): matrix cores
+// 41 % busy, 11 bytes per cycle from L2, no bank conflicts; with one workgroup to a unit its waves meet at a
+// barrier per k-step and nothing else runs meanwhile.  The k-steps' loads are counted by hand (inline assembly): hipcc would wait for all of them
 // before every read of LDS.  The load reads M0 one wait state after it was written at the earliest; the compiler
 // does not look into the block, so the s_nop is ours, and M0 is named as changed.
 __device__ __forceinline__ void tile_to_lds(const uint16_t* src, const uint16_t* dst) {   // src per lane, dst wave-uniform

@@ -511,9 +511,8 @@ __global__ void force_commit_kernel(const int32_t* forced, int32_t* grid, int32_
 //     from lane masks; which of the few entries of the threshold's bin itself survive is settled meanwhile,
 //     and those that do not get weight zero;
 //   - every block-wide exchange has LDS words of its own and costs one barrier (behind the writes).
-// Draw from a 16384-entry row at top-k 1000: 20 us with bounds checks, per-thread segments and
-// per-wave histograms, 14 us with coalesced rows and single barriers (26.2k cycles in the kernel), 17.8k cycles
-// without bounds checks, with bins kept and the list gathered from lane masks.
+// Draw from a 16384-entry row at top-k 1000 (sample_rows_kernel, kernel trace): 19.3 us with bounds checks, per-thread
+// segments and per-wave histograms, 9.4 us like this.
 // A word of Slots may be written again once every thread has passed a barrier after reading it.
 
 constexpr int kBins = NT;    // bins of the first, linear cut of the value range
