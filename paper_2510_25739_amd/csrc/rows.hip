@@ -307,6 +307,7 @@ __global__ __launch_bounds__(64 * WN * WM) void rows_gemm_staged_kernel(RowsGemm
             const float v = wave_total(ssq_share(g, min(t_first * 16 + wave * RPW + i, g.M - 1), lane, sq[i]));
             if (lane == 0) rscale[wave * RPW + i] = 1.0f / sqrtf(v / g.norm_d + g.eps);
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // written before the first barrier below, the only one where K is 32
     }
 #pragma unroll
     for (int k = 0; k < S - 1; ++k) request(k);

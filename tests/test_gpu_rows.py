@@ -113,6 +113,7 @@ def test_many_row_passes_match_a_float64_forward(H, d, heads, mlp, batch, scale,
     (256, 8, 704, 1024, 5),       # heads of 32
     (288, 9, 488, 1000, 3),       # hidden features and vocabulary slice in no whole tiles
     (4352, 17, 352, 1008, 2),     # heads of 256, more than 256 partial sums of squares a row
+    (32, 2, 2048, 1024, 30),      # one k-step of 32, W1|W3 LDS-staged; heads of 16
 ])
 def test_other_shapes_match_a_float64_forward(H, d, heads, mlp, vocab, batch):
     # Weights of deviation 0.8 / sqrt(d), as 0.05 is at 256: queries and keys of size 0.8 and so scores of order one, which
