@@ -338,16 +338,32 @@ __device__ __forceinline__ void mfma_store(const XP& p, int kind, const GJob& g,
     // strip, so that a strip's store goes out while the next one is multiplied.
     const rsrc_t out = make_rsrc(p.part[kind]);
     const unsigned at8 = (unsigned)((((size_t)ring * kXcd + c.x) * p.nstrips[kind] + s0) * 16 + col) * 64u + kg * 16u;
+    // The input's fragments are read KB k-tiles at a time, all requests ahead of the products: left to itself the compiler
+    // keeps two in flight and every product waits for LDS (W2's 28 products 0.90 -> 0.47 us, the XL shape 888 -> 874 us a
+    // launch; all 14 k-tiles at once spilled 71 registers, 979 us).
+    constexpr int KB = KTM <= 8 ? KTM : (KTM + 1) / 2;
+    v4u h[KB], l[KB];
 #pragma unroll
     for (int si = 0; si < NSW; ++si) {
         f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f}, acl = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kt = 0; kt < KTM; ++kt) {   // k-tiles beyond the XCD's slice: zero weights (their LDS columns are in bounds)
-            const bf16x8 h = __builtin_bit_cast(bf16x8, *reinterpret_cast<const v4u*>(act_hi + at + kt * 32));
-            const bf16x8 l = __builtin_bit_cast(bf16x8, *reinterpret_cast<const v4u*>(act_lo + at + kt * 32));
-            const bf16x8 a = __builtin_bit_cast(bf16x8, w[si * KTM + kt]);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, h, acc, 0, 0, 0);
-            acl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, l, acl, 0, 0, 0);
+        for (int k0 = 0; k0 < KTM; k0 += KB) {
+            if (KTM > KB || si == 0) {
+#pragma unroll
+                for (int kt = 0; kt < KB; ++kt)
+                    if (k0 + kt < KTM) {   // k-tiles beyond the XCD's slice: zero weights (their LDS columns are in bounds)
+                        h[kt] = *reinterpret_cast<const v4u*>(act_hi + at + (k0 + kt) * 32);
+                        l[kt] = *reinterpret_cast<const v4u*>(act_lo + at + (k0 + kt) * 32);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int kt = 0; kt < KB; ++kt)
+                if (k0 + kt < KTM) {
+                    const bf16x8 a = __builtin_bit_cast(bf16x8, w[si * KTM + k0 + kt]);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, h[kt]), acc, 0, 0, 0);
+                    acl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, l[kt]), acl, 0, 0, 0);
+                }
         }
         if (c.dbg && si == NSW - 1) {   // when tracing: the products are done (the stamp follows them in program order only through this)
             asm volatile("" :: "v"(acc), "v"(acl));
