@@ -581,10 +581,14 @@ template <int HD>
 __device__ __forceinline__ IoJobs load_io_jobs(const XP& p, const Ctx& c, int io, int lane) {
     IoJobs j;
     auto entry = [&](int k) { return p.rtab + ((((size_t)k * kXcd + c.x) * kPer + c.j) * kNIO + io) * 3; };
-    j.sA = entry(X_A)[0]; j.tA = entry(X_A)[1];
-    j.sC = entry(X_C)[0]; j.tC = entry(X_C)[1];
-    j.sD = entry(X_D)[0]; j.tD = entry(X_D)[1]; j.sD2 = HD == 64 ? -1 : entry(X_D)[2];   // (second strips: the wide shape only)
-    j.sE = entry(X_E)[0]; j.tE = entry(X_E)[1];
+    // All of it is the same in every lane.  Scalar registers are short as well and spill to lanes of vector registers, so
+    // the narrow heads keep the values in vector registers of their own (XL shape 860 us a launch, moved to scalar
+    // registers 871 us); the wide heads have none left for that (8 to 32 spilled to scratch: 3.18 ms, scalar 3.11 ms).
+    auto uni = [](int v) { return HD == 64 ? v : __builtin_amdgcn_readfirstlane(v); };
+    j.sA = uni(entry(X_A)[0]); j.tA = uni(entry(X_A)[1]);
+    j.sC = uni(entry(X_C)[0]); j.tC = uni(entry(X_C)[1]);
+    j.sD = uni(entry(X_D)[0]); j.tD = uni(entry(X_D)[1]); j.sD2 = HD == 64 ? -1 : uni(entry(X_D)[2]);   // (second strips: the wide shape only)
+    j.sE = uni(entry(X_E)[0]); j.tE = uni(entry(X_E)[1]);
     const int col = lane & 15, quad = lane >> 4;
     j.rp = col < p.MR ? row_pos(p, col) : RowPos{0, 0, 0, 0, false};
     j.rot0 = j.rot1 = make_float2(1.f, 0.f);
@@ -599,14 +603,14 @@ __device__ __forceinline__ IoJobs load_io_jobs(const XP& p, const Ctx& c, int io
     j.nA = p.njobs[F_A][c.x]; j.nB = p.njobs[F_B][c.x]; j.nC = p.njobs[F_C][c.x]; j.nD = p.njobs[F_D][c.x];
     j.nE = p.njobs[F_E][c.x];
     const int16_t* a = p.atab + ((size_t)c.x * kPer + c.j) * 4;
-    j.a_seq = a[0]; j.a_h = a[1]; j.a_rg = a[2]; j.a_slot = a[3];
-    j.pA = j.sA >= 0 ? p.ptab[p.poff[X_A] + j.sA] : 0;
-    j.pD = j.sD >= 0 ? p.ptab[p.poff[X_D] + j.sD] : 0;
+    j.a_seq = uni(a[0]); j.a_h = uni(a[1]); j.a_rg = uni(a[2]); j.a_slot = uni(a[3]);
+    j.pA = uni(j.sA >= 0 ? p.ptab[p.poff[X_A] + j.sA] : 0);
+    j.pD = uni(j.sD >= 0 ? p.ptab[p.poff[X_D] + j.sD] : 0);
     j.a_ke = -1; j.a_kv0 = 0;
     if (j.a_rg >= 0) {
         const int b = j.a_seq % p.B;
-        j.a_ke = p.k_eff[b];
-        j.a_kv0 = j.a_ke >= 0 ? p.C + p.n[b] - 1 : 0;
+        j.a_ke = uni(p.k_eff[b]);
+        j.a_kv0 = uni(j.a_ke >= 0 ? p.C + p.n[b] - 1 : 0);
     }
     return j;
 }
@@ -617,11 +621,13 @@ __device__ __forceinline__ IoJobs load_io_jobs(const XP& p, const Ctx& c, int io
 template <int HD>
 __device__ __forceinline__ void reduce_job(const XP& p, Ctx& c, const IoJobs& jb, int kind, int layer, int lane, f32x4& resid,
                                            unsigned stage) {
-    // (selects, not indexing with a run-time value: that would move the structure into memory)
-    const int s = kind == X_A ? jb.sA : kind == X_C ? jb.sC : kind == X_D ? jb.sD : jb.sE;
-    const int slot = kind == X_A ? jb.tA : kind == X_C ? jb.tC : kind == X_D ? jb.tD : jb.tE;
+    // (selects between values read beforehand: a select between members becomes a select between their addresses, and
+    // the structure moves into scratch memory, whose loads queue behind the unit's weight requests)
+    const int sA = jb.sA, sC = jb.sC, sD = jb.sD, sE = jb.sE, tA = jb.tA, tC = jb.tC, tD = jb.tD, tE = jb.tE, pA = jb.pA, pD = jb.pD, sD2 = jb.sD2;
+    const int s = kind == X_A ? sA : kind == X_C ? sC : kind == X_D ? sD : sE;
+    const int slot = kind == X_A ? tA : kind == X_C ? tC : kind == X_D ? tD : tE;
     // the wide shape has more W1|W3 strips than IO waves: a wave's second strip is gathered along with its first
-    const int s2 = (HD != 64 && kind == X_D) ? jb.sD2 : -1;
+    const int s2 = (HD != 64 && kind == X_D) ? sD2 : -1;
     if (s < 0) return;
     const int col = lane & 15, quad = lane >> 4, d = p.d, ring = layer & 1;
     const bool live = col < p.MR;
@@ -638,10 +644,10 @@ __device__ __forceinline__ void reduce_job(const XP& p, Ctx& c, const IoJobs& jb
     float rn = 1.f;
     f32x4 v, vb = (f32x4){0.f, 0.f, 0.f, 0.f};
     if (HD != 64 && kind == X_D)
-        v = gather_partials<true>(p, c, kind, s, jb.pD, ring, tag, parity_bit(c, kind, layer, col), lane, scaled, &rn,
+        v = gather_partials<true>(p, c, kind, s, pD, ring, tag, parity_bit(c, kind, layer, col), lane, scaled, &rn,
                                   stage, s2, &vb);
     else
-        v = gather_partials(p, c, kind, s, kind == X_A ? jb.pA : kind == X_D ? jb.pD : 0, ring, tag, parity_bit(c, kind, layer, col), lane,
+        v = gather_partials(p, c, kind, s, kind == X_A ? pA : kind == X_D ? pD : 0, ring, tag, parity_bit(c, kind, layer, col), lane,
                             scaled, &rn, stage);
     stamp(c, stage, 4);
     v *= rn;
@@ -1165,7 +1171,8 @@ __device__ __forceinline__ void io_stage(const XP& p, Ctx& c, const IoJobs& jb, 
     const unsigned wait_tag = tag_of(c, (kind == X_A || kind == X_LM) ? layer - 1 : layer, wait_flag);
     const u64 region = (kind == X_A || kind == X_LM) ? p.o_a : kind == X_C ? p.o_o : kind == X_D ? p.o_x2 : p.o_h;
     const int Kp = kind == X_C ? p.KpO : kind == X_E ? p.KpH : p.KpA;
-    const int nwait = wait_flag == F_E ? jb.nE : wait_flag == F_B ? jb.nB : wait_flag == F_C ? jb.nC : jb.nD;
+    const int nB = jb.nB, nC = jb.nC, nD = jb.nD, nE = jb.nE;
+    const int nwait = wait_flag == F_E ? nE : wait_flag == F_B ? nB : wait_flag == F_C ? nC : nD;
     stamp(c, stage, 0);
     wait_flags(p, c, wait_flag, nwait, wait_tag);
     unsigned* const go = HD != 64 ? s.go : nullptr;   // every IO wave announces once per product stage
