@@ -64,38 +64,49 @@ constexpr int kMaxJobs = 128;                    // flag words of one XCD and st
 enum XKind { X_A = 0, X_C, X_D, X_E, X_LM, X_NK };   // QKV, Wo, W1|W3, W2, output projection
 enum XFlag { F_A = 0, F_B, F_C, F_D, F_E, F_NF };    // who raised a flag: reduce of A, attention, reduce of C, D, E
 
+// A pointer of the parameter block.  The block is read from memory, so the compiler cannot know that its pointers are to
+// global memory and would access through them with FLAT instructions: slower to issue, and counted as LDS accesses as
+// well, so that waits for LDS became waits for the weight tiles in flight (XL shape 860 -> 848 us a launch, 7B 3.10 ->
+// 3.06 ms).
+template <class T>
+struct G {
+    uintptr_t at;   // (an integer: a cast of a generic pointer to global and back is folded away)
+    G& operator=(T* q) { at = reinterpret_cast<uintptr_t>(q); return *this; }
+    __device__ __forceinline__ operator T*() const { return (T*)(__attribute__((address_space(1))) T*)at; }
+};
+
 struct XP {
-    const uint4* wpack;
-    const uint4* zero_tile;     // 1 KB of zeros: what absent strips / k-tiles of a wave's job read
+    G<const uint4> wpack;
+    G<const uint4> zero_tile;     // 1 KB of zeros: what absent strips / k-tiles of a wave's job read
     u64 layer_tiles;            // tiles of one layer
     u64 xbase[X_NK][kXcd];      // first tile of (kind, XCD) inside a layer (output projection: after all layers)
     int32_t KT[X_NK][kXcd];     // k-tiles of the XCD's slice of the kind's input
     int32_t nstrips[X_NK];
     int32_t hd0[kXcd + 1];      // heads of XCD c: hd0[c] .. hd0[c + 1] - 1
     int32_t ke0[kXcd + 1];      // k-tiles of the MLP's hidden vector of XCD c
-    const int16_t* gtab;        // [kind][32][kCW][2]: first strip and strip count of (unit j, compute wave w)
-    const int16_t* ptab;        // [poff[kind] + strip]: producer of the strip, (unit * kCW + wave) * 2 + round
+    G<const int16_t> gtab;       // [kind][32][kCW][2]: first strip and strip count of (unit j, compute wave w)
+    G<const int16_t> ptab;       // [poff[kind] + strip]: producer of the strip, (unit * kCW + wave) * 2 + round
     int poff[X_NK];
-    const int16_t* rtab;        // [kind][8][32][kNIO][3]: strip (-1: none), flag slot, second strip (-1: none) of (XCD, unit, IO wave)
-    const int16_t* atab;        // [8][32][4]: sequence, head, row group (-1: none), flag slot
+    G<const int16_t> rtab;       // [kind][8][32][kNIO][3]: strip (-1: none), flag slot, second strip (-1: none) of (XCD, unit, IO wave)
+    G<const int16_t> atab;       // [8][32][4]: sequence, head, row group (-1: none), flag slot
     int32_t njobs[F_NF][kXcd];  // flag slots a consumer of that stage waits for
-    u64* part[X_NK];            // partial sums: [ring][8 source XCDs][strip][16 rows][16 features] fp32, parity in the lowest bit
-    u64* pss[X_NK];             // per-XCD sums of squares that ride along (products after a norm): [ring][8][unit][wave][round][16 rows] {value, tag}
-    uint8_t* xbuf;              // per-XCD buffers: [8][ring][xcd_bytes]
+    G<u64> part[X_NK];           // partial sums: [ring][8 source XCDs][strip][16 rows][16 features] fp32, parity in the lowest bit
+    G<u64> pss[X_NK];            // per-XCD sums of squares that ride along (products after a norm): [ring][8][unit][wave][round][16 rows] {value, tag}
+    G<uint8_t> xbuf;             // per-XCD buffers: [8][ring][xcd_bytes]
     u64 xcd_bytes, o_a, o_q, o_kv, o_o, o_x2, o_h, o_ss;   // regions of one XCD buffer (bytes)
-    unsigned* lflag;            // [8][F_NF][kMaxJobs]
-    const uint16_t* blob;
+    G<unsigned> lflag;           // [8][F_NF][kMaxJobs]
+    G<const uint16_t> blob;
     u64 g1_off, g2_off, layer_bytes, gf_off;
-    const float2* rope;
-    _Float16* Kc;
-    _Float16* Vc;
-    float* X;                   // embedded rows in, final hidden rows out ([MR][d] fp32)
-    float* logit_s;
-    unsigned* err;
-    const int32_t* n;
-    const int32_t* k_eff;
-    const int32_t* tdepth;      // rows of a candidate tree (null: a chain): depth of node r, and bit a of tanc[r] set iff node a
-    const u64* tanc;            //   is an ancestor of node r; node r sits at the root's position + depth, in cache entry root + r
+    G<const float2> rope;
+    G<_Float16> Kc;
+    G<_Float16> Vc;
+    G<float> X;                  // embedded rows in, final hidden rows out ([MR][d] fp32)
+    G<float> logit_s;
+    G<unsigned> err;
+    G<const int32_t> n;
+    G<const int32_t> k_eff;
+    G<const int32_t> tdepth;     // rows of a candidate tree (null: a chain): depth of node r, and bit a of tanc[r] set iff node a
+    G<const u64> tanc;           //   is an ancestor of node r; node r sits at the root's position + depth, in cache entry root + r
     int32_t L, d, H, m, Vs, S, B, C, RS, MR, RPJ, Smax, Tmax;
     int32_t hd;                 // head dimension (64 or 128)
     float qscale;               // 1 / sqrt(hd)
@@ -119,14 +130,6 @@ __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
     return ((unsigned long long)hi << 32) | (unsigned long long)lo;
 }
 __device__ __forceinline__ void compiler_fence() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
-// A pointer the compiler must treat as new: addresses derived from it are computed where they are used
-// instead of once before the layer loop (dozens of 64-bit addresses kept alive across the whole kernel).
-template <typename T>
-__device__ __forceinline__ T* fresh(T* ptr) {
-    asm volatile("" : "+v"(ptr));
-    return ptr;
-}
-
 // Loads that must see what another unit of the same XCD stored (they skip the unit's own L1 and are
 // served by the XCD's L2), or what another XCD wrote through to memory: device scope.  The 16-byte forms
 // go through a buffer resource (32-bit byte offsets from a wave-uniform base), which the compiler tracks
@@ -296,7 +299,7 @@ __device__ __forceinline__ void issue_tiles(const XP& p, const GJob& g, u64 laye
                                             int round = 0) {
     const int ns = min(max(g.ns - round * NSW, 0), NSW), KT = g.KT;
     const v4u* src = reinterpret_cast<const v4u*>(p.wpack + (layer_base + g.tile0 + (u64)round * NSW * KT) * 64 + lane);
-    const v4u* zero = reinterpret_cast<const v4u*>(p.zero_tile) + lane;
+    const v4u* zero = reinterpret_cast<const v4u*>(p.zero_tile + 0) + lane;
 #pragma unroll
     for (int t = T0; t < T1; ++t) {   // (a sub-range of the wave's tiles: a request can be spread over several stages)
         const int si = t / KTM, kt = t % KTM;
@@ -1272,7 +1275,7 @@ __device__ __forceinline__ void issue_item(const XP& p, const GJob& g, u64 layer
     asm volatile("" : "+s"(ns), "+s"(KT));   // worked out per item, not for every item of the layer ahead of the loop
     const int have = SI < ns ? min(max(KT - KC * 16, 0), 16) : 0;
     // (the job's fields are in scalar registers - see compute_main_stream - and so is everything here)
-    const char* base = reinterpret_cast<const char*>(p.wpack) + (layer_base + g.tile0 + (u64)SI * KT + KC * 16) * 1024;
+    const char* base = reinterpret_cast<const char*>(p.wpack + 0) + (layer_base + g.tile0 + (u64)SI * KT + KC * 16) * 1024;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {   // four tiles per resource: their offsets fit the instruction's immediate field
         if (KC * 16 + q * 4 < KTM) {
