@@ -324,7 +324,7 @@ __device__ __forceinline__ void issue_paced(const XP& p, const GJob& g, u64 laye
 
 // The wave's products of a stage from the staged K-slice (LDS planes [16][Kp]) and the partial sums
 // out as tagged words: part[ring][XCD][strip][row][quad][4].  No branches up to the stores (see above).
-template <int NSW, int KTM>
+template <int NSW, int KTM, bool HALF>
 __device__ __forceinline__ void mfma_store(const XP& p, int kind, const GJob& g, const Ctx& c, int lane, const v4u (&w)[NSW * KTM],
                                            const uint16_t* act_hi, const uint16_t* act_lo, const float* ssrow, int Kp, int ring,
                                            unsigned tag, unsigned pbit, int round = 0, unsigned dbg_stage = 0) {
@@ -339,8 +339,13 @@ __device__ __forceinline__ void mfma_store(const XP& p, int kind, const GJob& g,
     // value with the word's parity in its lowest bit (see parity_bit); one store instruction per strip.  A
     // write-through store occupies the wave for ~0.3 us, several times the products of a strip: strip by
     // strip, so that a strip's store goes out while the next one is multiplied.
+    // HALF (at most eight rows in flight): two strips a store, the second one's rows in the lanes of columns 8 .. 15.  What
+    // bounds the exchange is the number of requests a unit's waves make, not their bytes: with this and the halved looks
+    // of gather_partials the XL shape went 848 -> 802 us a launch, the B shape 259 -> 236.
     const rsrc_t out = make_rsrc(p.part[kind]);
-    const unsigned at8 = (unsigned)((((size_t)ring * kXcd + c.x) * p.nstrips[kind] + s0) * 16 + col) * 64u + kg * 16u;
+    const int row = HALF ? col & 7 : col, upper = HALF ? col >> 3 : 0;
+    const unsigned at8 = (unsigned)((((size_t)ring * kXcd + c.x) * p.nstrips[kind] + s0 + upper) * 16 + row) * 64u + kg * 16u;
+    f32x4 held = (f32x4){0.f, 0.f, 0.f, 0.f};
     // The input's fragments are read KB k-tiles at a time, all requests ahead of the products: left to itself the compiler
     // keeps two in flight and every product waits for LDS (W2's 28 products 0.90 -> 0.47 us, the XL shape 888 -> 874 us a
     // launch; all 14 k-tiles at once spilled 71 registers, 979 us).
@@ -372,9 +377,19 @@ __device__ __forceinline__ void mfma_store(const XP& p, int kind, const GJob& g,
             asm volatile("" :: "v"(acc), "v"(acl));
             stamp(c, dbg_stage, 3);
         }
-        const f32x4 v = acc + acl;
-        if (si < ns && col < p.MR)
-            st_16(out, at8 + si * 1024u, (v4u){(__float_as_uint(v[0]) & ~1u) | pbit, (__float_as_uint(v[1]) & ~1u) | pbit,
+        f32x4 v = acc + acl;
+        if constexpr (HALF) {
+            if (si % 2 == 0 && si + 1 < NSW) { held = v; continue; }
+            if (si % 2) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float moved = lane_xor8(v[e]);
+                    v[e] = upper ? moved : held[e];
+                }
+            }
+        }
+        if ((HALF ? (si & ~1) + upper : si) < ns && row < p.MR)
+            st_16(out, at8 + (HALF ? si & ~1 : si) * 1024u, (v4u){(__float_as_uint(v[0]) & ~1u) | pbit, (__float_as_uint(v[1]) & ~1u) | pbit,
                                                (__float_as_uint(v[2]) & ~1u) | pbit, (__float_as_uint(v[3]) & ~1u) | pbit});
     }
 }
@@ -446,16 +461,20 @@ __device__ __forceinline__ void stage_copy_cols(rsrc_t r, unsigned src, int MR, 
 // and *rn receives 1/rms of the lane's row.
 // TWO: the partials of a second strip s2 (same product, -1: none) are polled along with the first's and
 // their sum goes to *v2.
-template <bool TWO = false>
+// HALF (at most eight rows in flight): lanes of columns 8 .. 15 look at XCDs 4 .. 7 for the rows 0 .. 7, so that a look is
+// half as many requests; the sums are those of columns 0 .. 7.
+template <bool TWO, bool HALF>
 __device__ __forceinline__ f32x4 gather_partials(const XP& p, Ctx& c, int kind, int s, int prod, int ring, unsigned tag, unsigned pbit,
                                                  int lane, bool scaled, float* rn, unsigned dbg_stage = 1000u, int s2 = -1,
                                                  f32x4* v2 = nullptr) {
-    const int col = lane & 15, quad = lane >> 4;
-    const bool live = col < p.MR;
-    f32x4 val[kXcd];
+    static_assert(!(TWO && HALF), "");
+    constexpr int NX = HALF ? kXcd / 2 : kXcd, NSQ = HALF ? 1 : 2;   // words and sums of squares a lane looks at
+    const int quad = lane >> 4, upper = HALF ? (lane >> 3) & 1 : 0, row = HALF ? lane & 7 : lane & 15;
+    const bool live = row < p.MR;
+    f32x4 val[NX];
 #pragma unroll
-    for (int x = 0; x < kXcd; ++x) val[x] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    unsigned need = live ? 0xFFu : 0u;
+    for (int x = 0; x < NX; ++x) val[x] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    unsigned need = live ? (1u << NX) - 1u : 0u;
     f32x4 val2[TWO ? kXcd : 1];
     unsigned need2 = (TWO && live && s2 >= 0) ? 0xFFu : 0u;
     if (TWO) {
@@ -469,23 +488,25 @@ __device__ __forceinline__ f32x4 gather_partials(const XP& p, Ctx& c, int kind, 
     const int nstr = kind == X_A ? p.nstrips[X_A] : kind == X_C ? p.nstrips[X_C] : kind == X_D ? p.nstrips[X_D]
                                                                                : kind == X_E ? p.nstrips[X_E] : p.nstrips[X_LM];
     const rsrc_t in = make_rsrc(part);
-    const unsigned at8 = (unsigned)(((size_t)ring * kXcd * nstr + s) * 16 + col) * 64u + quad * 16u;
+    const unsigned at8 = (unsigned)((((size_t)ring * kXcd + upper * NX) * nstr + s) * 16 + row) * 64u + quad * 16u;
     const unsigned xstride = (unsigned)nstr * 1024u;
     const unsigned at8b = at8 + (unsigned)((TWO ? s2 : s) - s) * 1024u;   // (the second strip's words)
     const unsigned pb = pbit * 0x1u;
-    // sums of squares: the lane's quarter looks at XCDs 2 * quad and 2 * quad + 1; `prod` = the strip's
-    // producer (unit * kCW + wave) * 2 + round, the same on every XCD
-    const u64* pss = pssb + (((size_t)ring * kXcd + 2 * quad) * kPer * kCW * 2 + prod) * 16 + col;
-    unsigned need_ss = (live && scaled) ? 3u : 0u;
-    float ssv[2] = {0.f, 0.f};
+    // sums of squares: the lane's quarter looks at XCDs 2 * quad and 2 * quad + 1 (HALF: its half of the columns at one of
+    // them); `prod` = the strip's producer (unit * kCW + wave) * 2 + round, the same on every XCD
+    const u64* pss = pssb + (((size_t)ring * kXcd + 2 * quad + upper) * kPer * kCW * 2 + prod) * 16 + row;
+    unsigned need_ss = (live && scaled) ? (1u << NSQ) - 1u : 0u;
+    float ssv[NSQ];
+#pragma unroll
+    for (int i = 0; i < NSQ; ++i) ssv[i] = 0.f;
     bool ok = c.dead;
     unsigned nspin = 0;
     for (unsigned spins = 0; spins < kSpinLimit && !ok; ++spins) {
         ++nspin;
-        v4u w[kXcd], w2[TWO ? kXcd : 1];
-        u64 sw[2] = {0ull, 0ull};
+        v4u w[NX], w2[TWO ? kXcd : 1];
+        u64 sw[NSQ];
 #pragma unroll
-        for (int x = 0; x < kXcd; ++x)
+        for (int x = 0; x < NX; ++x)
             if ((need >> x) & 1u) w[x] = ld_16(in, at8 + x * xstride);
         if (TWO) {
 #pragma unroll
@@ -493,10 +514,10 @@ __device__ __forceinline__ f32x4 gather_partials(const XP& p, Ctx& c, int kind, 
                 if ((need2 >> x) & 1u) w2[x] = ld_16(in, at8b + x * xstride);
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < NSQ; ++i)
             if ((need_ss >> i) & 1u) sw[i] = ld_u64(pss + (size_t)i * kPer * kCW * 2 * 16);
 #pragma unroll
-        for (int x = 0; x < kXcd; ++x)
+        for (int x = 0; x < NX; ++x)
             if ((need >> x) & 1u) {
                 if (((w[x][0] & w[x][1] & w[x][2] & w[x][3]) & 1u) == pb && ((w[x][0] | w[x][1] | w[x][2] | w[x][3]) & 1u) == pb) {
                     val[x] = (f32x4){__uint_as_float(w[x][0] & ~1u), __uint_as_float(w[x][1] & ~1u), __uint_as_float(w[x][2] & ~1u),
@@ -505,7 +526,7 @@ __device__ __forceinline__ f32x4 gather_partials(const XP& p, Ctx& c, int kind, 
                 }
             }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < NSQ; ++i)
             if (((need_ss >> i) & 1u) && (unsigned)(sw[i] >> 32) == tag) {
                 ssv[i] = __uint_as_float((unsigned)sw[i]);
                 need_ss &= ~(1u << i);
@@ -528,14 +549,20 @@ __device__ __forceinline__ f32x4 gather_partials(const XP& p, Ctx& c, int kind, 
     if (c.dbg && (threadIdx.x & 63) == 0 && (blockIdx.x == 0 || blockIdx.x == 248) && dbg_stage < 512u)
         c.dbg[((size_t)(blockIdx.x ? 1 : 0) * 512 + dbg_stage) * 16 + 14] = nspin;
     if (scaled) {
-        float a = ssv[0] + ssv[1];
+        float a = ssv[0] + (HALF ? lane_xor8(ssv[0]) : ssv[NSQ - 1]);
         a = sum_xor16(a);
         a = sum_xor32(a);
         *rn = 1.0f / sqrtf(a / (float)p.d + p.eps);
     }
     f32x4 v = val[0];
 #pragma unroll
-    for (int x = 1; x < kXcd; ++x) v += val[x];
+    for (int x = 1; x < NX; ++x) v += val[x];
+    if (HALF) {
+#pragma unroll
+        for (int x = 0; x < NX; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += lane_xor8(val[x][e]);
+    }
     if (TWO) {
         f32x4 u = val2[0];
 #pragma unroll
@@ -621,7 +648,7 @@ __device__ __forceinline__ IoJobs load_io_jobs(const XP& p, const Ctx& c, int io
 // The reduce job of an IO wave for product `kind` (X_A .. X_E, a run-time value: the four products share
 // one copy of this code, which keeps the kernel inside the instruction cache) of `layer`; none: returns
 // at once.  resid: the wave's strip of the residual stream (owners of Wo / W2 strips).
-template <int HD>
+template <int HD, bool HALF>
 __device__ __forceinline__ void reduce_job(const XP& p, Ctx& c, const IoJobs& jb, int kind, int layer, int lane, f32x4& resid,
                                            unsigned stage) {
     // (selects between values read beforehand: a select between members becomes a select between their addresses, and
@@ -647,10 +674,10 @@ __device__ __forceinline__ void reduce_job(const XP& p, Ctx& c, const IoJobs& jb
     float rn = 1.f;
     f32x4 v, vb = (f32x4){0.f, 0.f, 0.f, 0.f};
     if (HD != 64 && kind == X_D)
-        v = gather_partials<true>(p, c, kind, s, pD, ring, tag, parity_bit(c, kind, layer, col), lane, scaled, &rn,
+        v = gather_partials<true, false>(p, c, kind, s, pD, ring, tag, parity_bit(c, kind, layer, col), lane, scaled, &rn,
                                   stage, s2, &vb);
     else
-        v = gather_partials(p, c, kind, s, kind == X_A ? pA : kind == X_D ? pD : 0, ring, tag, parity_bit(c, kind, layer, col), lane,
+        v = gather_partials<false, HALF>(p, c, kind, s, kind == X_A ? pA : kind == X_D ? pD : 0, ring, tag, parity_bit(c, kind, layer, HALF ? col & 7 : col), lane,
                             scaled, &rn, stage);
     stamp(c, stage, 4);
     v *= rn;
@@ -708,6 +735,7 @@ __device__ __forceinline__ void reduce_job(const XP& p, Ctx& c, const IoJobs& jb
 }
 
 // Output projection: logits of the strip's 16 vocabulary entries for every row.
+template <bool HALF>
 __device__ __forceinline__ void reduce_logits(const XP& p, Ctx& c, int io, int lane) {
     const int col = lane & 15, quad = lane >> 4;
     const unsigned tag = tag_of(c, p.L, F_A);
@@ -715,7 +743,7 @@ __device__ __forceinline__ void reduce_logits(const XP& p, Ctx& c, int io, int l
         const int s = ((i * kPer + (int)c.j) * kNIO + io) * kXcd + (int)c.x;
         if (s >= p.nstrips[X_LM]) break;
         float rn = 1.f;
-        const f32x4 v = gather_partials(p, c, X_LM, s, p.ptab[p.poff[X_LM] + s], 0, tag, parity_bit(c, X_LM, 0, col), lane, true, &rn) * rn;
+        const f32x4 v = gather_partials<false, HALF>(p, c, X_LM, s, p.ptab[p.poff[X_LM] + s], 0, tag, parity_bit(c, X_LM, 0, HALF ? col & 7 : col), lane, true, &rn) * rn;
         if (col < p.MR) *reinterpret_cast<f32x4*>(p.logit_s + (size_t)col * p.Vs + s * 16 + 4 * quad) = v;
     }
 }
@@ -1127,7 +1155,7 @@ __device__ __forceinline__ unsigned product_tag(const XP& p, const Ctx& c, int k
 
 // Compute waves.  KIND: which matrix; NSW: strips per wave and round; KTM: most k-tiles an XCD's slice
 // has.  w holds this stage's tiles, requested one or two stages ago.
-template <int KIND, int NSW, int KTM, class Prefetch>
+template <int KIND, int NSW, int KTM, bool HALF, class Prefetch>
 __device__ __forceinline__ void compute_stage(const XP& p, const Ctx& c, const GJob& g, const Lds& s, int layer, unsigned stage,
                                               int Kp, v4u (&w)[NSW * KTM], Prefetch&& prefetch) {
     const int lane = threadIdx.x & 63;
@@ -1139,8 +1167,8 @@ __device__ __forceinline__ void compute_stage(const XP& p, const Ctx& c, const G
     lds_barrier();   // the XCD's slice of the stage input is in LDS
     stamp(c, stage, 1);
     const float* ssrow = (KIND == X_C || KIND == X_E) ? nullptr : s.ss0 + (stage & 1u) * 16;
-    const unsigned pbit = parity_bit(c, KIND, layer, lane & 15);
-    mfma_store<NSW, KTM>(p, KIND, g, c, lane, w, act_hi, act_lo, ssrow, Kp, ring, tag, pbit, 0, stage);
+    const unsigned pbit = parity_bit(c, KIND, layer, lane & (HALF ? 7 : 15));
+    mfma_store<NSW, KTM, HALF>(p, KIND, g, c, lane, w, act_hi, act_lo, ssrow, Kp, ring, tag, pbit, 0, stage);
     stamp(c, stage, 2);
     // Loads and stores share one counter and complete out of order among each other: with stores
     // pending, "wait for the first n loads" is not expressible and every wait becomes "wait for
@@ -1156,7 +1184,7 @@ __device__ __forceinline__ void compute_stage(const XP& p, const Ctx& c, const G
     if (KIND == X_LM) {   // further rounds of the output projection: same staged input
         for (int r = 1; r < p.lm_rounds; ++r) {
             issue_tiles<NSW, KTM>(p, g, 0, lane, w, r);
-            mfma_store<NSW, KTM>(p, KIND, g, c, lane, w, act_hi, act_lo, ssrow, Kp, ring, tag, pbit, r);
+            mfma_store<NSW, KTM, HALF>(p, KIND, g, c, lane, w, act_hi, act_lo, ssrow, Kp, ring, tag, pbit, r);
         }
     }
 }
@@ -1164,7 +1192,7 @@ __device__ __forceinline__ void compute_stage(const XP& p, const Ctx& c, const G
 // IO waves: wait for the producers of the stage input on this XCD, stage the XCD's slice in LDS, then -
 // while the compute waves multiply - do the wave's reduce job of this stage.  kind is a run-time value
 // (X_A .. X_LM): one copy of this code serves every product.
-template <int HD>
+template <int HD, bool HALF>
 __device__ __forceinline__ void io_stage(const XP& p, Ctx& c, const IoJobs& jb, const Lds& s, int kind, int layer, unsigned stage,
                                          f32x4& resid) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1209,9 +1237,9 @@ __device__ __forceinline__ void io_stage(const XP& p, Ctx& c, const IoJobs& jb, 
                    s.act0 + (size_t)(stage & 1u) * s.act_elems, threadIdx.x - kCW * 64, normed ? kIOThreads - 64 : kIOThreads, go);
     stamp(c, stage, 2);
     lds_barrier();
-    if (kind == X_LM) reduce_logits(p, c, wave - kCW, lane);
+    if (kind == X_LM) reduce_logits<HALF>(p, c, wave - kCW, lane);
     else {
-        reduce_job<HD>(p, c, jb, kind, layer, lane, resid, stage);
+        reduce_job<HD, HALF>(p, c, jb, kind, layer, lane, resid, stage);
     }
     stamp(c, stage, 3);
 }
@@ -1220,7 +1248,7 @@ __device__ __forceinline__ void io_stage(const XP& p, Ctx& c, const IoJobs& jb, 
 // W2; strips per wave and round of the output projection.  Weights are requested one or two stages
 // ahead: Wo and W1|W3 behind QKV's products (they arrive while the attention runs), W2 and the next
 // layer's QKV behind W1|W3's.
-template <int NA, int KA, int NC, int KC, int ND, int KD, int NE, int KE, int NL>
+template <int NA, int KA, int NC, int KC, int ND, int KD, int NE, int KE, int NL, bool HALF>
 __device__ __forceinline__ void compute_main(const XP& p, const Ctx& c, const Lds& s) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const GJob gA = load_gjob(p, X_A, c, wave), gC = load_gjob(p, X_C, c, wave), gD = load_gjob(p, X_D, c, wave);
@@ -1237,22 +1265,22 @@ __device__ __forceinline__ void compute_main(const XP& p, const Ctx& c, const Ld
     for (int l = 0; l < p.L; ++l) {
         const u64 lb = (u64)l * p.layer_tiles;
         const bool more = l + 1 < p.L;
-        compute_stage<X_A, NA, KA>(p, c, gA, s, l, stage++, p.KpA, wA, [&] {
+        compute_stage<X_A, NA, KA, HALF>(p, c, gA, s, l, stage++, p.KpA, wA, [&] {
             issue_paced<ND, KD, NDh, ND * KD, CH>(p, gD, lb, lane, wD);
             issue_paced<NC, KC, 0, NC * KC, CH>(p, gC, lb, lane, wC);
         });
         ++stage;   // attention: the IO waves' business
-        compute_stage<X_C, NC, KC>(p, c, gC, s, l, stage++, p.KpO, wC, [&] {
+        compute_stage<X_C, NC, KC, HALF>(p, c, gC, s, l, stage++, p.KpO, wC, [&] {
             if (more) issue_paced<NA, KA, 0, NA * KA, CH>(p, gA, lb + p.layer_tiles, lane, wA);
         });
-        compute_stage<X_D, ND, KD>(p, c, gD, s, l, stage++, p.KpA, wD, [&] { issue_paced<NE, KE, 0, NE * KE, CH>(p, gE, lb, lane, wE); });
-        compute_stage<X_E, NE, KE>(p, c, gE, s, l, stage++, p.KpH, wE, [&] {
+        compute_stage<X_D, ND, KD, HALF>(p, c, gD, s, l, stage++, p.KpA, wD, [&] { issue_paced<NE, KE, 0, NE * KE, CH>(p, gE, lb, lane, wE); });
+        compute_stage<X_E, NE, KE, HALF>(p, c, gE, s, l, stage++, p.KpH, wE, [&] {
             if (more) issue_paced<ND, KD, 0, NDh, CH>(p, gD, lb + p.layer_tiles, lane, wD);
         });
     }
     v4u wL[NL * KA];
     issue_tiles<NL, KA>(p, gL, 0, lane, wL);
-    compute_stage<X_LM, NL, KA>(p, c, gL, s, p.L, stage++, p.KpA, wL, [] {});
+    compute_stage<X_LM, NL, KA, HALF>(p, c, gL, s, p.L, stage++, p.KpA, wL, [] {});
 }
 
 // ------------------------------------------------------------------------- compute waves, streamed
@@ -1408,7 +1436,7 @@ __device__ __forceinline__ void compute_main_stream(const XP& p, const Ctx& c, c
     stream_stage<X_LM, NL, 1, 16>(p, c, gL, s, p.L, stage++, p.KpA, 0, b0, b1, NextItem<16>{p, none, 0, lane});
 }
 
-template <int RPJ, int HD>
+template <int RPJ, int HD, bool HALF>
 __device__ __forceinline__ void io_main(const XP& p, Ctx& c, const Lds& s) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const IoJobs jb = load_io_jobs<HD>(p, c, wave - kCW, lane);
@@ -1430,11 +1458,11 @@ __device__ __forceinline__ void io_main(const XP& p, Ctx& c, const Lds& s) {
     for (unsigned stage = 0; stage < nstages; ++stage) {
         const int l = (int)(stage / 5u), st = (int)(stage - 5u * (unsigned)l);
         if (st == 1) attn_io<RPJ, HD>(p, c, jb, s, l, stage, joins);
-        else io_stage<HD>(p, c, jb, s, l == p.L ? X_LM : st == 0 ? X_A : st == 2 ? X_C : st == 3 ? X_D : X_E, l, stage, resid);
+        else io_stage<HD, HALF>(p, c, jb, s, l == p.L ? X_LM : st == 0 ? X_A : st == 2 ? X_C : st == 3 ? X_D : X_E, l, stage, resid);
     }
 }
 
-template <int NA, int KA, int NC, int KC, int ND, int KD, int NE, int KE, int NL, int RPJ, int HD = 64>
+template <int NA, int KA, int NC, int KC, int ND, int KD, int NE, int KE, int NL, int RPJ, bool HALF, int HD = 64>
 __global__ __launch_bounds__(kThreads, 1) void verify_xcd_kernel(const XP* __restrict__ params, unsigned epoch0, unsigned par, unsigned par_lm, u64* dbg) {
     // The parameter block lives in device memory (written when the step shape changes): tables in it are
     // indexed with run-time values, which a by-value kernel argument would answer with a private copy.
@@ -1457,8 +1485,8 @@ __global__ __launch_bounds__(kThreads, 1) void verify_xcd_kernel(const XP* __res
     // The two kinds of waves run separate code (and cross the same workgroup barriers), so that neither
     // carries the other's registers: compute waves the weights in flight, IO waves the attention's keys
     // and values and the partial sums of a reduce job.
-    if ((threadIdx.x >> 6) >= kCW) io_main<RPJ, HD>(p, c, s);
-    else compute_main<NA, KA, NC, KC, ND, KD, NE, KE, NL>(p, c, s);
+    if ((threadIdx.x >> 6) >= kCW) io_main<RPJ, HD, HALF>(p, c, s);
+    else compute_main<NA, KA, NC, KC, ND, KD, NE, KE, NL, HALF>(p, c, s);
 }
 
 // The same pass for the wide shape: the compute waves stream their tiles (see compute_main_stream).
@@ -1481,7 +1509,7 @@ __global__ __launch_bounds__(kThreads, 1) void verify_xcd_stream_kernel(const XP
     Ctx c;
     c.x = blockIdx.x % kXcd; c.j = blockIdx.x / kXcd; c.epoch0 = epoch0; c.par = par; c.par_lm = par_lm; c.dead = false; c.err = p.err; c.dbg = dbg;
     if (xcc_id() != c.x) give_up(c);
-    if ((threadIdx.x >> 6) >= kCW) io_main<RPJ, HD>(p, c, s);
+    if ((threadIdx.x >> 6) >= kCW) io_main<RPJ, HD, false>(p, c, s);
     else compute_main_stream<NA, NC, ND, NE, KE, NL>(p, c, s);
 }
 
@@ -1868,8 +1896,9 @@ int launch_verify_xcd(hawk_ctx* c, int k, const int32_t* tree_depth, const unsig
     if (c->d == 1280) {
         // strips per compute wave: QKV 240 / 128 -> 2, Wo 80 / 128 -> 1, W1|W3 432 / 128 -> 4, W2 -> 1, output 1024 / 128 -> 8
         p.lm_rounds = 2;
-        kern = RPJ == 1 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 5, 1, 6, 4, 5, 1, 14, 4, 1>)
-                        : reinterpret_cast<const void*>(verify_xcd_kernel<2, 5, 1, 6, 4, 5, 1, 14, 4, 2>);
+        kern = RPJ == 2 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 5, 1, 6, 4, 5, 1, 14, 4, 2, false>)
+             : p.MR > 8 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 5, 1, 6, 4, 5, 1, 14, 4, 1, false>)
+                        : reinterpret_cast<const void*>(verify_xcd_kernel<2, 5, 1, 6, 4, 5, 1, 14, 4, 1, true>);
         if (P->NSW[X_A] > 2 || P->NSW[X_C] > 1 || P->NSW[X_D] > 4 || P->NSW[X_E] > 1 || P->NSW[X_LM] > 8) return -1;
     } else if (c->d == 4096) {
         // streamed: QKV 768 strips / 128 waves -> 6, Wo 256 -> 2, W1|W3 1376 -> 11 (12 with an empty one), W2 256 -> 2 x 3 chunks
@@ -1883,8 +1912,9 @@ int launch_verify_xcd(hawk_ctx* c, int k, const int32_t* tree_depth, const unsig
     } else {
         // d = 768: QKV 144 -> 2, Wo 48 -> 1, W1|W3 256 -> 2, W2 48 -> 1, output 8 in two rounds of 4
         p.lm_rounds = 2;
-        kern = RPJ == 1 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 1>)
-                        : reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 2>);
+        kern = RPJ == 2 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 2, false>)
+             : p.MR > 8 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 1, false>)
+                        : reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 1, true>);
         if (P->NSW[X_A] > 2 || P->NSW[X_C] > 1 || P->NSW[X_D] > 2 || P->NSW[X_E] > 1 || P->NSW[X_LM] > 8) return -1;
     }
     // the parameter block and the attention job table of this step shape: uploaded when they change
