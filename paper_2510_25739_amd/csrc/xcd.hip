@@ -1094,18 +1094,20 @@ __device__ __forceinline__ void attn_io(const XP& p, Ctx& c, const IoJobs& jb, c
         }
         if (io == 0) stamp(c, stage, 5);
 #pragma unroll
-        for (int r = 0; r < RPJ; ++r) {
+        for (int r = 0; r < RPJ; ++r) {   // the lane groups' maximum first: one rescaling, then plain sums (803 -> 796 us)
+            float mn = fmaxf(A[r].mx, lane_xor8(A[r].mx));
+            mn = fmaxf(mn, lane_xor16(mn));
+            mn = fmaxf(mn, lane_xor32(mn));
+            const float f0 = __expf(A[r].mx - mn);
+            auto total = [&](float xx) {
+                xx *= f0;
+                xx += lane_xor8(xx);
+                return sum_xor32(sum_xor16(xx));
+            };
+            A[r].mx = mn;
+            A[r].den = total(A[r].den);
 #pragma unroll
-            for (int o = LPP; o < 64; o <<= 1) {
-                auto other = [&](float xx) { return o == 8 ? lane_xor8(xx) : (o == 16 ? lane_xor16(xx) : lane_xor32(xx)); };
-                const float omx = other(A[r].mx), oden = other(A[r].den);
-                const float mn = fmaxf(A[r].mx, omx);
-                const float f0 = __expf(A[r].mx - mn), f1 = __expf(omx - mn);
-                A[r].den = A[r].den * f0 + oden * f1;
-#pragma unroll
-                for (int e = 0; e < 8 * NCH; ++e) A[r].acc[e] = A[r].acc[e] * f0 + other(A[r].acc[e]) * f1;
-                A[r].mx = mn;
-            }
+            for (int e = 0; e < 8 * NCH; ++e) A[r].acc[e] = total(A[r].acc[e]);
             if (pg == 0) {
                 float* mine = s.part + ((size_t)io * RPJ + r) * PS;
 #pragma unroll
