@@ -850,6 +850,7 @@ __device__ __forceinline__ void attend_round(const float (&q)[RPJ][8 * NCH], int
 
 struct Lds {
     unsigned* join;     // arrivals of the IO waves at their own barrier (only ever grows)
+    unsigned* sent;     // compute waves that have sent off their partial sums, counted over the launch
     unsigned* go;       // streamed kind: IO waves that have requested a stage input, counted over the launch (a hint, see stream_stage)
     uint16_t* act0;     // staged K-slices, alternating between stages: hi plane, lo plane behind it; odd stages use
     unsigned act_elems; //   the buffer act_elems elements further on (an offset, not a second pointer to choose from: a
@@ -1171,6 +1172,7 @@ __device__ __forceinline__ void compute_stage(const XP& p, const Ctx& c, const G
     const float* ssrow = (KIND == X_C || KIND == X_E) ? nullptr : s.ss0 + (stage & 1u) * 16;
     const unsigned pbit = parity_bit(c, KIND, layer, lane & (HALF ? 7 : 15));
     mfma_store<NSW, KTM, HALF>(p, KIND, g, c, lane, w, act_hi, act_lo, ssrow, Kp, ring, tag, pbit, 0, stage);
+    if (lane == 0) atomicAdd(s.sent, 1u);
     stamp(c, stage, 2);
     // Loads and stores share one counter and complete out of order among each other: with stores
     // pending, "wait for the first n loads" is not expressible and every wait becomes "wait for
@@ -1239,6 +1241,17 @@ __device__ __forceinline__ void io_stage(const XP& p, Ctx& c, const IoJobs& jb, 
                    s.act0 + (size_t)(stage & 1u) * s.act_elems, threadIdx.x - kCW * 64, normed ? kIOThreads - 64 : kIOThreads, go);
     stamp(c, stage, 2);
     lds_barrier();
+    // No look at the partial sums before the unit's own are on their way (its compute waves count themselves in LDS):
+    // looks cannot find anything earlier, and a unit serves its waves' requests in order, so each of them held up the
+    // stores of the partial sums.  XL shape 796 -> 785 us a launch, 780 with the pause (narrow heads), 7B shape 3.04 ->
+    // 2.97 ms (3.02 with a pause); waiting for the stores' acknowledgement instead 798, looks spaced by pauses 796.
+    // The wait is bounded and running out of it changes nothing but the timing.
+    const unsigned l5 = stage / 5u, st5 = stage - 5u * l5, want = kCW * (4u * l5 + (st5 ? st5 - 1u : 0u) + 1u);
+    for (unsigned spins = 0; spins < 8192u; ++spins) {
+        if ((int)(__hip_atomic_load(s.sent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) - want) >= 0) break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    if (HD == 64) __builtin_amdgcn_s_sleep(8);
     if (kind == X_LM) reduce_logits<HALF>(p, c, wave - kCW, lane);
     else {
         reduce_job<HD, HALF>(p, c, jb, kind, layer, lane, resid, stage);
@@ -1403,6 +1416,7 @@ __device__ __forceinline__ void stream_stage(const XP& p, const Ctx& c, const GJ
             st_16(out, at8 + si * 1024u, (v4u){(__float_as_uint(v[0]) & ~1u) | pbit, (__float_as_uint(v[1]) & ~1u) | pbit,
                                                (__float_as_uint(v[2]) & ~1u) | pbit, (__float_as_uint(v[3]) & ~1u) | pbit});
     }
+    if (lane == 0) atomicAdd(s.sent, 1u);
     stamp(c, stage, 2);
     stamp(c, stage, 4);
 }
@@ -1474,12 +1488,13 @@ __global__ __launch_bounds__(kThreads, 1) void verify_xcd_kernel(const XP* __res
     const size_t act_elems = (size_t)2 * p.MR * max(max(p.KpA, p.KpO), p.KpH);
     s.join = reinterpret_cast<unsigned*>(smem_raw);
     s.go = s.join + 1;
+    s.sent = s.join + 2;
     s.act0 = reinterpret_cast<uint16_t*>(smem_raw + 1);
     s.act_elems = (unsigned)act_elems;
     s.part = reinterpret_cast<float*>(s.act0 + 2 * act_elems);
     s.qs = s.part + kNIO * RPJ * (HD + 4);
     s.ss0 = s.qs + RPJ * HD;
-    if (threadIdx.x == 0) { *s.join = 0u; *s.go = 0u; }
+    if (threadIdx.x == 0) { *s.join = 0u; *s.go = 0u; *s.sent = 0u; }
     __syncthreads();
     Ctx c;
     c.x = blockIdx.x % kXcd; c.j = blockIdx.x / kXcd; c.epoch0 = epoch0; c.par = par; c.par_lm = par_lm; c.dead = false; c.err = p.err; c.dbg = dbg;
@@ -1501,12 +1516,13 @@ __global__ __launch_bounds__(kThreads, 1) void verify_xcd_stream_kernel(const XP
     const size_t act_elems = (size_t)2 * p.MR * max(max(p.KpA, p.KpO), p.KpH);
     s.join = reinterpret_cast<unsigned*>(smem_raw);
     s.go = s.join + 1;
+    s.sent = s.join + 2;
     s.act0 = reinterpret_cast<uint16_t*>(smem_raw + 1);
     s.act_elems = (unsigned)act_elems;
     s.part = reinterpret_cast<float*>(s.act0 + 2 * act_elems);
     s.qs = s.part + kNIO * RPJ * (HD + 4);
     s.ss0 = s.qs + RPJ * HD;
-    if (threadIdx.x == 0) { *s.join = 0u; *s.go = 0u; }
+    if (threadIdx.x == 0) { *s.join = 0u; *s.go = 0u; *s.sent = 0u; }
     __syncthreads();
     Ctx c;
     c.x = blockIdx.x % kXcd; c.j = blockIdx.x / kXcd; c.epoch0 = epoch0; c.par = par; c.par_lm = par_lm; c.dead = false; c.err = p.err; c.dbg = dbg;
