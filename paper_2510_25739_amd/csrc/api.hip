@@ -163,7 +163,7 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     c->split_bytes = g->dtype == HAWK_BF16 ? M16 * widest * 4 : 0;
     o.split = c->split_bytes ? take(c->split_bytes) : 0;
     o.split2 = c->split_bytes ? take(M16 * widest * 4) : 0;
-    o.rtab = c->split_bytes ? take((size_t)c->Tmax * (hd / 2) * 8) : 0;
+    o.rtab = take((size_t)c->Tmax * (hd / 2) * (c->split_bytes ? 8 : 16));
     o.ssq = c->split_bytes ? take(M16 * (d / 16 + 4) * 4) : 0;
     // Tile-major copy of every GEMM weight (16 x 32 tiles, 1 KB each, in MFMA operand order): the
     // MFMA kernels then fetch whole kilobytes per request instead of 64-byte pieces of 16 rows.
@@ -200,8 +200,9 @@ RowMap step_map(hawk_ctx* c, int k) {
     return m;
 }
 
-// All decoder layers over M rows held in x (residual stream, updated in place).
+// All decoder layers over M rows held in x (residual stream, updated in place), of contexts that rows.hip does not take.
 void run_layers(hawk_ctx* c, const RowMap& map, int M) {
+    if (c->cfg.dtype == HAWK_FP32) return f32_layers(c, map, M);
     const Offsets& o = c->off;
     const int d = c->d, m = c->m;
     for (int l = 0; l < c->L; ++l) {
@@ -218,6 +219,13 @@ void run_layers(hawk_ctx* c, const RowMap& map, int M) {
 }
 
 size_t slice_off(const hawk_ctx* c) { return c->w.W_out + (size_t)c->cfg.samp_lo * c->d * c->esz; }
+
+// Final norm and output layer over M rows of x, `stride` values apart; normalised to off_norm on the way (bf16).
+void run_output_layer(hawk_ctx* c, size_t off_x, size_t stride, size_t off_norm, size_t off_logits, int M) {
+    if (c->cfg.dtype == HAWK_FP32) return f32_output_layer(c, off_x, stride, off_logits, M);
+    launch_rmsnorm(c, off_x, stride, c->w.g_f, off_norm, M);
+    launch_gemm(c, off_norm, c->d, slice_off(c), c->Vs, c->d, off_logits, c->Vs, M, false, true);
+}
 
 // Target pass over the step rows [last committed | drafts] and logits of every row.
 void run_step_rows(hawk_ctx* c, int k) {
@@ -247,8 +255,7 @@ void run_step_rows(hawk_ctx* c, int k) {
         return;
     }
     run_layers(c, map, M);
-    launch_rmsnorm(c, c->off.x, c->d, c->w.g_f, c->off.a, M);
-    launch_gemm(c, c->off.a, c->d, slice_off(c), c->Vs, c->d, c->off.logit_s, c->Vs, M, false, true);
+    run_output_layer(c, c->off.x, c->d, c->off.a, c->off.logit_s, M);
 }
 
 void enqueue_draft(hawk_ctx* c, int k, const UniformSrc& us, const DraftMode& dm) {
@@ -267,10 +274,14 @@ void enqueue_draft(hawk_ctx* c, int k, const UniformSrc& us, const DraftMode& dm
             launch_draft_sample(c, i, k, us, dm);
             continue;
         }
+        if (c->cfg.dtype == HAWK_FP32) {
+            f32_draft_pass(c, i, i == 1 ? c->off.hprev : ((i - 1) & 1) ? c->off.g1 : c->off.g0, g);
+            launch_draft_sample(c, i, k, us, dm);
+            continue;
+        }
         launch_draft_input(c, i);
         launch_gemm(c, c->off.din, 3 * c->d, c->w.W_d, c->d, 3 * c->d, g, c->d, c->S, false, false);
-        launch_rmsnorm(c, g, c->d, c->w.g_f, c->off.ga, c->S);
-        launch_gemm(c, c->off.ga, c->d, slice_off(c), c->Vs, c->d, c->off.dlogit_s, c->Vs, c->S, false, true);
+        run_output_layer(c, g, c->d, c->off.ga, c->off.dlogit_s, c->S);
         launch_draft_sample(c, i, k, us, dm);
     }
 }
@@ -324,9 +335,7 @@ int enqueue_prefill(hawk_ctx* c, const float* cond, const float* uncond, int bat
     run_layers(c, map, M);
     launch_keep_hprev_prefill(c);
     // final norm + output projection of the last condition row of every sequence
-    launch_rmsnorm(c, c->off.x + (size_t)(n_cond - 1) * c->d * c->asz, (size_t)n_cond * c->d, c->w.g_f, c->off.a,
-                   c->S);
-    launch_gemm(c, c->off.a, c->d, slice_off(c), c->Vs, c->d, c->off.logit_s, c->Vs, c->S, false, true);
+    run_output_layer(c, c->off.x + (size_t)(n_cond - 1) * c->d * c->asz, (size_t)n_cond * c->d, c->off.a, c->off.logit_s, c->S);
     launch_first_token(c, us);
     HIP_TRY(c, hipGetLastError());
     return HAWK_OK;
@@ -424,7 +433,7 @@ int hawk_create(const hawk_config* cfg, void* workspace, size_t workspace_bytes,
         hawk_destroy(c);
         return HAWK_EDEVICE;
     }
-    if (rows_fill_rope(c) != 0) {
+    if ((c->cfg.dtype == HAWK_FP32 ? f32_fill_rope(c) : rows_fill_rope(c)) != 0) {
         hawk_destroy(c);
         return HAWK_EDEVICE;
     }
@@ -795,8 +804,7 @@ int hawk_verify_tree(hawk_ctx* c, int depth, const int32_t* m_depth, const int32
                 rows_step_pass(c, map, M);
             } else {
                 run_layers(c, map, M);
-                launch_rmsnorm(c, c->off.x, c->d, c->w.g_f, c->off.a, M);
-                launch_gemm(c, c->off.a, c->d, slice_off(c), c->Vs, c->d, c->off.logit_s, c->Vs, M, false, true);
+                run_output_layer(c, c->off.x, c->d, c->off.a, c->off.logit_s, M);
             }
         }
         HIP_TRY(c, hipGetLastError());

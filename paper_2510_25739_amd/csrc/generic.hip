@@ -1,13 +1,14 @@
 // Generic (any-shape) kernels of the target decoder and the draft head.
 //
 // Two arithmetic configurations, selected by the weight dtype of the context:
-//   fp32 blobs: fp32 weights, fp64 activations / accumulators / KV cache (exact-parity set);
+//   fp32 blobs: fp32 weights, fp64 activations / accumulators / KV cache (exact-parity set); products and the attention
+//               over heads of 32, 64 and 128 are in fp32.hip;
 //   bf16 blobs: bf16 weights, fp16 KV cache (same bytes as bf16, 3 more mantissa bits: the
 //               cache's rounding is what dominates the logit error), fp32 activations and
 //               accumulators.
 // One wave computes one output column of a skinny GEMM for up to RT rows, streaming its
-// weight row with 16-byte loads; this is the fallback path and the only path of the
-// fp32 configuration.  bf16 contexts run in xcd.hip, stream.hip and rows.hip.
+// weight row with 16-byte loads; this is the fallback path of bf16 contexts, which otherwise run in xcd.hip,
+// stream.hip and rows.hip.
 #include <string.h>
 
 #include "hawk_internal.h"
@@ -16,7 +17,6 @@ namespace hawk {
 
 struct CfgF32 {
     using WT = float; using AT = double; using KT = double;
-    static constexpr int VE = 4;
 };
 struct CfgBF16 {
     using WT = uint16_t; using AT = float; using KT = _Float16;
@@ -29,10 +29,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {  // round to nearest 
     return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 
-__device__ __forceinline__ void load_w(const float* p, double* out) {
-    float4 v = *reinterpret_cast<const float4*>(p);
-    out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
-}
 __device__ __forceinline__ void load_w(const uint16_t* p, float* out) {
     uint4 v = *reinterpret_cast<const uint4*>(p);
     out[0] = bf16_to_f32(v.x & 0xFFFFu); out[1] = bf16_to_f32(v.x >> 16);
@@ -390,7 +386,8 @@ void launch_cond_rows(hawk_ctx* c, int M) {
 }
 
 void launch_rmsnorm(hawk_ctx* c, size_t off_in, size_t in_stride, size_t off_gain, size_t off_out, int M) {
-    if (c->cfg.dtype == HAWK_BF16 && c->d % 4 == 0 && in_stride % 4 == 0 && off_in % 16 == 0 && off_out % 16 == 0 && (c->off.blob + off_gain) % 8 == 0 &&
+    using Cfg = CfgBF16;
+    if (c->d % 4 == 0 && in_stride % 4 == 0 && off_in % 16 == 0 && off_out % 16 == 0 && (c->off.blob + off_gain) % 8 == 0 &&
         c->d <= 8192) {
         const float* X = wsp<float>(c, off_in);
         const uint16_t* g = reinterpret_cast<const uint16_t*>(c->ws + c->off.blob + off_gain);
@@ -403,9 +400,9 @@ void launch_rmsnorm(hawk_ctx* c, size_t off_in, size_t in_stride, size_t off_gai
             rmsnorm_rows_kernel<8><<<M, 256, 0, c->stream>>>(X, g, out, c->d, in_stride, c->cfg.rms_eps);
         return;
     }
-    DISPATCH(c, (rmsnorm_kernel<Cfg><<<M, 256, 0, c->stream>>>(
+    rmsnorm_kernel<Cfg><<<M, 256, 0, c->stream>>>(
                     wsp<typename Cfg::AT>(c, off_in), wptr<Cfg>(c, off_gain), wsp<typename Cfg::AT>(c, off_out),
-                    c->d, in_stride, c->cfg.rms_eps)));
+                    c->d, in_stride, c->cfg.rms_eps);
 }
 
 void launch_gemm(hawk_ctx* c, size_t off_a, int lda, size_t w_off, int N, int K, size_t off_y, int ldy,
@@ -423,16 +420,17 @@ void launch_gemm(hawk_ctx* c, size_t off_a, int lda, size_t w_off, int N, int K,
         launch_rows_gemm(c->stream, g);
         return;
     }
+    using Cfg = CfgBF16;
     constexpr int RT = 8;
     dim3 grid((N + 3) / 4, (M + RT - 1) / RT);
     if (out_f32) {
-        DISPATCH(c, (gemm_rows_kernel<Cfg, RT, float><<<grid, 256, 0, c->stream>>>(
+        gemm_rows_kernel<Cfg, RT, float><<<grid, 256, 0, c->stream>>>(
                         wsp<typename Cfg::AT>(c, off_a), lda, wptr<Cfg>(c, w_off), N, K, wsp<float>(c, off_y), ldy,
-                        M, accumulate ? 1 : 0)));
+                        M, accumulate ? 1 : 0);
     } else {
-        DISPATCH(c, (gemm_rows_kernel<Cfg, RT, typename Cfg::AT><<<grid, 256, 0, c->stream>>>(
+        gemm_rows_kernel<Cfg, RT, typename Cfg::AT><<<grid, 256, 0, c->stream>>>(
                         wsp<typename Cfg::AT>(c, off_a), lda, wptr<Cfg>(c, w_off), N, K,
-                        wsp<typename Cfg::AT>(c, off_y), ldy, M, accumulate ? 1 : 0)));
+                        wsp<typename Cfg::AT>(c, off_y), ldy, M, accumulate ? 1 : 0);
     }
 }
 
@@ -453,18 +451,20 @@ void launch_attention(hawk_ctx* c, const RowMap& map, int layer, int M) {
 }
 
 void launch_swiglu(hawk_ctx* c, int M) {
+    using Cfg = CfgBF16;
     size_t total = (size_t)M * c->m;
-    DISPATCH(c, (swiglu_kernel<Cfg><<<(unsigned)((total + 255) / 256), 256, 0, c->stream>>>(
-                    wsp<typename Cfg::AT>(c, c->off.u), c->m, total)));
+    swiglu_kernel<Cfg><<<(unsigned)((total + 255) / 256), 256, 0, c->stream>>>(
+                    wsp<typename Cfg::AT>(c, c->off.u), c->m, total);
 }
 
 void launch_draft_input(hawk_ctx* c, int i) {
+    using Cfg = CfgBF16;
     // draft i writes its head output to g1 (i odd) / g0 (i even); draft i > 1 reads draft i-1's
     size_t prev = (i == 1) ? c->off.hprev : (((i - 1) & 1) ? c->off.g1 : c->off.g0);
-    DISPATCH(c, (draft_input_kernel<Cfg><<<c->S, 256, 0, c->stream>>>(
+    draft_input_kernel<Cfg><<<c->S, 256, 0, c->stream>>>(
                     wsp<typename Cfg::AT>(c, c->off.din), wsp<typename Cfg::AT>(c, prev), wptr<Cfg>(c, c->w.E),
                     wsp<int32_t>(c, c->off.n), wsp<int32_t>(c, c->off.k_eff), wsp<int32_t>(c, c->off.grid),
-                    wsp<int32_t>(c, c->off.draft), i, c->B, c->N, c->gw, c->kmax + 1, c->d)));
+                    wsp<int32_t>(c, c->off.draft), i, c->B, c->N, c->gw, c->kmax + 1, c->d);
 }
 
 void launch_keep_hprev_prefill(hawk_ctx* c) {

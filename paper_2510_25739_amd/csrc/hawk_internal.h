@@ -62,7 +62,7 @@ struct Offsets {  // byte offsets into the workspace
     size_t tree;    // candidate tree of a tree pass: int32 depth[64], then uint64 ancestors[64], then walk state
     size_t split;   // bf16 hi / lo planes of a GEMM input (batched shapes; 0: not present)
     size_t split2;  // second region of planes: written by a product's own epilogue while it reads the first
-    size_t rtab;    // rotary table [Tmax][hd / 2] (cos, sin) of the many-rows path (0: not present)
+    size_t rtab;    // rotary table [Tmax][hd / 2] (cos, sin) of the many-rows path, in double of the fp32 configuration
     size_t ssq;     // partial sums of squares of the residual stream, [row][d / 16]
     size_t llen, lidx, lw;   // lists of the kept entries of the last verify pass's rows (sampling.hip: ListStore), [B][k_max + 1]
     size_t gpack;   // tile-major copy of the GEMM weights for the products of rows.hip (0: not present)
@@ -139,6 +139,7 @@ template <typename T> inline T* wsp(hawk_ctx* c, size_t off) { return reinterpre
 // ---- launchers implemented in generic.hip (dtype chosen from ctx->cfg.dtype) ----
 void launch_embed_rows(hawk_ctx*, const RowMap&, int M);
 void launch_cond_rows(hawk_ctx*, int M);                       // X <- condition vectors
+// the next ones: bf16 contexts only
 // out[r] = rmsnorm(in[r * in_stride ...]) * gain, r < M (in_stride in elements)
 void launch_rmsnorm(hawk_ctx*, size_t off_in, size_t in_stride, size_t off_gain, size_t off_out, int M);
 // Y[M][N] (+)= A[M][K] * W[N][K]^T ; out_f32: store fp32 (logits) instead of activations
@@ -151,6 +152,12 @@ void launch_attention(hawk_ctx*, const RowMap&, int layer, int M);
 void launch_swiglu(hawk_ctx*, int M);
 void launch_draft_input(hawk_ctx*, int i);                     // [g | E[left] | E[up]]
 void launch_keep_hprev_prefill(hawk_ctx*);
+
+// ---- the fp32 configuration, implemented in fp32.hip ----
+int f32_fill_rope(hawk_ctx*);                             // once per context; 0 = ok
+void f32_layers(hawk_ctx*, const RowMap&, int M);         // x -> x
+void f32_output_layer(hawk_ctx*, size_t off_x, size_t stride, size_t off_logits, int M);
+void f32_draft_pass(hawk_ctx*, int i, size_t off_prev, size_t off_out);   // micro-step i up to its logits
 
 // ---- many rows of a bf16 context (and the draft heads' products), implemented in rows.hip ----
 // Activations as two bf16 planes, hi and lo, in MFMA operand order: 16 rows x 32 features are 512

@@ -586,6 +586,38 @@ def test_streaming_kernel_row_counts_and_batches(H, cfg, k, batch, scale, path):
     assert_bf16(total, 12)
 
 
+@pytest.mark.parametrize("cfg,ks", [(2, [7, 8, 6, 9]), (1, [7, 8, 0, 9])])
+def test_xcd_kernel_on_either_side_of_eight_rows(H, cfg, ks):
+    # up to eight rows the partial sums cross two strips a store and two XCDs a look, beyond that one: launches of both
+    # kinds in turn on one context (the words' parities carry over)
+    s = synth.CONFIGS[cfg].replace(n_layers=3, n_cond=20, grid_h=10, grid_w=10, k=max(ks))
+    blob = synth.make_weights(s, seed=0)
+    hk, orc = H.Hawk(H.HawkConfig.from_shape(s)), oracle.Oracle.from_shape(s, blob)
+    hk.load(blob)
+    cond = synth.make_cond(s, seed=2)
+    hk.prefill(cond, None, s.grid_h, s.grid_w, 0.0, s.top_k, 1.0, [0.25])
+    orc.prefill(cond, None, 0.0, s.top_k, 1.0, [0.25])
+    assert np.array_equal(hk.grid()[:, 0], orc.grid()[:, 0])
+    rng = np.random.Generator(np.random.PCG64(7))
+    worst = 0.0
+    for k in ks * 2:
+        n0 = int(orc.n()[0])
+        toks = rng.integers(s.samp_lo, s.samp_lo + s.v_s, size=(1, max(k, 1))).astype(np.int32)[:, :k]
+        hk.draft_forced(k, toks, False)
+        orc.draft_forced(k, toks, False)
+        ua = np.zeros((1, max(k, 1)), np.float32)[:, :k]
+        na_g, t_g = hk.verify(k, ua, [0.5])
+        na_o, t_o = orc.verify(k, ua, [0.5])
+        assert hk.last_path() == 1 and hk.last_kernel() == 2
+        worst = max(worst, float(np.abs(hk.logits(k + 1) - orc.logits()).max()))
+        if not (np.array_equal(na_g, na_o) and np.array_equal(t_g, t_o)):
+            hk.force([n0], orc.grid()[:, n0:n0 + int(na_o[0]) + 1])
+        assert np.array_equal(hk.n(), orc.n())
+    print("either side of eight rows", cfg, worst)
+    assert worst <= 2e-2
+    hk.close()
+
+
 @pytest.mark.parametrize("path", [1, 2])
 def test_streaming_kernel_to_the_end_of_the_image_and_changing_draft_lengths(H, path):
     # one context, steps of different row counts in turn (the kernels' per-launch state - stage tags,
