@@ -171,6 +171,19 @@ def test_fp32_other_draft_lengths(H, k):
     assert_exact(res)
 
 
+@pytest.mark.parametrize("d,heads,m,n_cond,batch,k", [(256, 8, 1000, 3, 1, 2), (256, 2, 264, 21, 2, 6), (72, 9, 40, 5, 1, 4), (520, 65, 24, 9, 1, 1),
+                                                      (384, 3, 776, 70, 3, 3), (64, 1, 8, 1, 1, 7)])
+def test_fp32_widths_heads_and_row_counts(H, d, heads, m, n_cond, batch, k):
+    # heads of 32, 64 and 128 in the attention of this configuration and others, widths that leave a wave's last look at
+    # K partly empty, columns that fill no whole wave, 1 to 210 rows, more cached positions than four looks take
+    s = synth.HawkShape("odd", 2, d, heads, m, 203, n_cond, 6, 7, k, dtype="fp32", top_k=50, batch=batch)
+    blob, hk, orc = make_pair(H, s, std=0.05)
+    res = lockstep(s, hk, orc, k, u_seed=3)
+    if batch == 1:
+        assert_exact(res)
+    assert res["first_same"] and res["stage_bad"] == 0 and res["max_logit_err"] < 1e-5 and res["max_draft_logit_err"] < 1e-5
+
+
 @pytest.mark.parametrize("vocab,samp,top_k", [(16384, (0, 0), 1000), (16001, (0, 0), 16001), (9000, (4, 8192), 2000),
                                               (4096, (0, 0), 1), (70, (3, 50), 7)])
 def test_fp32_sampling_stage_over_vocab_sizes(H, vocab, samp, top_k):
