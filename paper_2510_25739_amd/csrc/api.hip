@@ -155,6 +155,7 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     o.out_na = take(B * 4); o.out_tok = take(B * ks * 4); o.inv_freq = take((size_t)(hd / 2) * 8);
     o.replay = take(B * c->Nmax * 4); o.cond = take(S * (size_t)g->max_cond * d * 4);
     o.tree = take(TreeArea(B).bytes);
+    o.rtab = take((size_t)c->Tmax * (hd / 2) * (g->dtype == HAWK_BF16 ? 8 : 16));
     const size_t lists = Vs <= 16 * (size_t)kSampThreads ? B * ks : 0;   // larger rows are not sampled from lists
     o.llen = take(list_len_bytes(lists)); o.lidx = take(list_idx_bytes(lists)); o.lw = take(list_w_bytes(lists));
     const size_t m32 = (m + 31) & ~(size_t)31;   // hidden features in whole k-tiles
@@ -163,7 +164,6 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     c->split_bytes = g->dtype == HAWK_BF16 ? M16 * widest * 4 : 0;
     o.split = c->split_bytes ? take(c->split_bytes) : 0;
     o.split2 = c->split_bytes ? take(M16 * widest * 4) : 0;
-    o.rtab = take((size_t)c->Tmax * (hd / 2) * (c->split_bytes ? 8 : 16));
     o.ssq = c->split_bytes ? take(M16 * (d / 16 + 4) * 4) : 0;
     // Tile-major copy of every GEMM weight (16 x 32 tiles, 1 KB each, in MFMA operand order): the
     // MFMA kernels then fetch whole kilobytes per request instead of 64-byte pieces of 16 rows.
