@@ -839,16 +839,19 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
 
 // ------------------------------------------------------------------------------------------ launchers
 
-// The kernels a product can take.  us: microseconds a workgroup spends on a k-step of 32 with the chip full
-// (measured at the XL and 7B widths, weights not in cache); slots: workgroups a compute unit holds at a time.
-// pick_kernel takes the one with the smallest rounds x k-steps x us: small tiles while one round of workgroups
-// covers the output, wider ones as the rows grow and the planes are drawn more often, the LDS-staged
-// ones once they are a contraction.
-struct RowsKernel { int SR, CT; float us; int slots; bool staged; };
+// The kernels a product with tile-major weights can take.  A round of workgroups takes fixed + step microseconds per k-step
+// of 32, and an XCD's compute units take its workgroups (see the kernels' mapping) 32 at a time, the small (4, 3) kernel's
+// 64.  Smaller tiles draw fewer bytes into a unit, so the smallest that covers the output in one round wins; the staged
+// ones once the rows are a contraction.  Fitted to 3900 times of these kernels (17 products of the B, XL and 7B widths, 2 to
+// 512 rows, weights from memory): the choice is 1.1 % behind the fastest on average.  Counting workgroups over the whole
+// chip, with a time per k-step alone, was 9.3 % behind: W1|W3 of 48 rows at the XL widths (2, 2) 14.5 us, (4, 2) 9.8 us, QKV
+// of 72 rows 13.3 and 9.1 us; 384 rows of W2 (4, 2) 26.0 us, since two XCDs had 36 workgroups, (4, 3) 17.6 us.
+struct RowsKernel { int SR, CT; float fixed, step; int slots; bool staged; };
 static const RowsKernel kRowsKernels[] = {
-    {1, 1, 0.028f, 2, false}, {2, 1, 0.037f, 2, false}, {4, 1, 0.064f, 2, false}, {2, 2, 0.062f, 2, false}, {4, 2, 0.125f, 1, false},
-    {4, 3, 0.138f, 1, false}, {4, 3, 0.270f, 2, false}, {4, 4, 0.200f, 1, false}, {8, 8, 0.52f, 1, true},   {10, 8, 0.64f, 1, true},
-    {16, 8, 0.95f, 1, true},  {20, 12, 1.65f, 1, true}};
+    {1, 1, 0.9f, 0.038f, 32, false}, {2, 1, 1.5f, 0.049f, 32, false}, {4, 1, 1.8f, 0.09f, 32, false},   {2, 2, 1.2f, 0.080f, 32, false},
+    {3, 2, 1.9f, 0.093f, 32, false}, {4, 2, 1.5f, 0.116f, 32, false}, {6, 2, 2.5f, 0.143f, 32, false},  {4, 3, 2.6f, 0.129f, 32, false},
+    {4, 3, 3.9f, 0.243f, 64, false}, {4, 4, 3.3f, 0.146f, 32, false}, {7, 3, 6.5f, 0.182f, 32, false},  {8, 8, 7.5f, 0.398f, 32, true},
+    {10, 8, 7.9f, 0.481f, 32, true}, {16, 8, 10.2f, 0.65f, 32, true}, {20, 12, 15.9f, 1.101f, 32, true}};
 static int pick_kernel(const RowsGemm& g) {
     const int strips = g.N / 16, tiles = (g.M + 15) / 16;
     int best = 0;
@@ -856,12 +859,10 @@ static int pick_kernel(const RowsGemm& g) {
     for (int i = 0; i < (int)(sizeof kRowsKernels / sizeof kRowsKernels[0]); ++i) {
         const RowsKernel& t = kRowsKernels[i];
         if (t.staged && tiles < 4) continue;
-        const long wgs = (long)((strips + t.SR - 1) / t.SR) * ((tiles + t.CT - 1) / t.CT);
-        // small tiles share a unit, at 1.3 times the cost of having it alone
-        const float rounds = t.slots == 1 ? (float)((wgs + 255) / 256)
-                           : i == 6 ? (float)((wgs + 511) / 512)   // (4, 3) in its two-per-unit form: us is that of the pair
-                           : (wgs <= 256 ? 1.f : (float)wgs / 197.f);
-        if (rounds * t.us < cost) { cost = rounds * t.us; best = i; }
+        const long sg = (strips + t.SR - 1) / t.SR, tg = (tiles + t.CT - 1) / t.CT;
+        const long per_xcd = t.staged ? (sg * tg + 7) / 8 : (sg + 7) / 8 * tg;
+        const float us = (float)((per_xcd + t.slots - 1) / t.slots) * (t.fixed + t.step * (float)(g.K / 32));
+        if (us < cost) { cost = us; best = i; }
     }
     return best;
 }
@@ -903,17 +904,20 @@ template <int SR, int CT, int D, int KW, bool PACKED, int MODE> static void laun
 }
 template <int MODE> static void launch_packed(hipStream_t stream, const RowsGemm& g) {
     switch (pick_kernel(g)) {
-        case 0: return launch_direct<1, 1, 6, 8, true, MODE>(stream, g);
+        case 0: return launch_direct<1, 1, 8, 4, true, MODE>(stream, g);
         case 1: return launch_direct<2, 1, 5, 8, true, MODE>(stream, g);
         case 2: return launch_direct<4, 1, 4, 8, true, MODE>(stream, g);
         case 3: return launch_direct<2, 2, 6, 4, true, MODE>(stream, g);
-        case 4: return launch_direct<4, 2, 3, 8, true, MODE>(stream, g);
-        case 5: return launch_direct<4, 3, 2, 8, true, MODE>(stream, g);
-        case 6: return launch_direct<4, 3, 3, 4, true, MODE>(stream, g);
-        case 7: return launch_direct<4, 4, 2, 8, true, MODE>(stream, g);
-        case 8: return launch_staged<2, 4, 4, 2, 4, true, MODE>(stream, g);
-        case 9: return launch_staged<2, 4, 5, 2, 4, true, MODE>(stream, g);
-        case 10: return launch_staged<4, 2, 4, 4, 4, true, MODE>(stream, g);
+        case 4: return launch_direct<3, 2, 6, 4, true, MODE>(stream, g);
+        case 5: return launch_direct<4, 2, 3, 8, true, MODE>(stream, g);
+        case 6: return launch_direct<6, 2, 4, 4, true, MODE>(stream, g);
+        case 7: return launch_direct<4, 3, 2, 8, true, MODE>(stream, g);
+        case 8: return launch_direct<4, 3, 3, 4, true, MODE>(stream, g);
+        case 9: return launch_direct<4, 4, 2, 8, true, MODE>(stream, g);
+        case 10: return launch_direct<7, 3, 5, 4, true, MODE>(stream, g);
+        case 11: return launch_staged<2, 4, 4, 2, 4, true, MODE>(stream, g);
+        case 12: return launch_staged<2, 4, 5, 2, 4, true, MODE>(stream, g);
+        case 13: return launch_staged<4, 2, 4, 4, 4, true, MODE>(stream, g);
         default: return launch_staged<4, 2, 5, 6, 3, true, MODE>(stream, g);
     }
 }
