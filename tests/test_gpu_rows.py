@@ -84,13 +84,16 @@ SHAPES = [
     # d_model, heads, d_mlp, prompts, guidance, n_cond, chunk
     (256, 4, 704, 1, 1.0, 1, 1),       # one row everywhere
     (256, 2, 704, 1, 1.0, 65, 17),     # heads of 128; one row past a group of 64 keys and past a tile of 16 step rows
-    (256, 4, 704, 3, 1.0, 67, 33),     # ragged tiles of (1, 1), (2, 1), (4, 1); three tiles of step rows
-    (256, 4, 704, 10, 1.0, 50, 6),     # (2, 2), (4, 3)
-    (256, 4, 704, 32, 1.0, 63, 2),     # (4, 2), (4, 3) two to a unit
-    (512, 4, 1376, 13, 2.0, 50, 3),    # (4, 4), LDS-staged (8, 8); heads of 128
+    (256, 4, 704, 3, 1.0, 67, 33),     # ragged tiles of (1, 1), (2, 2), (4, 2); three tiles of step rows
+    (256, 4, 704, 10, 1.0, 50, 6),     # (2, 1), (4, 2), (6, 2)
+    (256, 4, 704, 32, 1.0, 63, 2),     # (6, 2), LDS-staged (8, 8)
+    (512, 4, 1376, 13, 2.0, 50, 3),    # (4, 1), (4, 3), (4, 4), LDS-staged (8, 8); heads of 128
     (512, 8, 1376, 32, 1.0, 63, 2),    # LDS-staged (16, 8) with a ragged last group
     (768, 12, 2048, 16, 2.0, 100, 2),  # LDS-staged (20, 12)
-    (512, 8, 1376, 32, 1.0, 100, 2),   # LDS-staged (10, 8) for the projections and the MLP
+    (512, 8, 1376, 32, 1.0, 100, 2),   # LDS-staged (10, 8) for the MLP
+    (256, 4, 1376, 4, 1.0, 84, 5),     # (4, 3) two to a unit for W1|W3
+    (768, 12, 704, 2, 1.0, 56, 9),     # (3, 2) for QKV
+    (768, 12, 1376, 13, 1.0, 80, 5),   # (7, 3) for W2
     # step attention with more cached positions than its waves request at once: eight waves, then four (from 256
     # workgroups on), heads of 64 (three tiles of 16 a wave) and of 128 (two)
     (256, 4, 704, 1, 1.0, 400, 5),
