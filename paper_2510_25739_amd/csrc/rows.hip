@@ -64,6 +64,19 @@ __device__ __forceinline__ float wave_total(float v) {
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
+// Lane ^ 16 and lane ^ 32 by lane swaps (a shuffle goes through the LDS crossbar).
+#define HAWK_SWAP(NAME, WIDTH, OP)                                                                                       \
+    __device__ __forceinline__ float NAME(float v) {                                                                    \
+        const auto r = __builtin_amdgcn_permlane##WIDTH##_swap(__float_as_uint(v), __float_as_uint(v), false, false);   \
+        return OP(__uint_as_float(r[0]), __uint_as_float(r[1]));                                                        \
+    }
+__device__ __forceinline__ float addf(float a, float b) { return a + b; }
+HAWK_SWAP(sum16, 16, addf)
+HAWK_SWAP(sum32, 32, addf)
+HAWK_SWAP(max16, 16, fmaxf)
+HAWK_SWAP(max32, 32, fmaxf)
+#undef HAWK_SWAP
+
 // Four consecutive features f .. f + 3 (f % 4 == 0) of a row into the two planes.
 __device__ __forceinline__ void store_planes4(uint16_t* hi, uint16_t* lo, int row, int f, int kts, f32x4 v) {
     unsigned h0, h1, h2, h3, l0, l1, l2, l3;
@@ -131,8 +144,7 @@ __device__ __forceinline__ void gemm_epilogue(const RowsGemm& g, f32x4 v, int ro
     }
     if (g.ossq) {   // the strip's share of the row's sum of squares
         float p = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
-        p += __shfl_xor(p, 16);
-        p += __shfl_xor(p, 32);
+        p = sum32(sum16(p));
         if (live && kg == 0) g.ossq[(size_t)row * g.ossq_ld + (f >> 4)] = p;
     }
 }
@@ -462,30 +474,38 @@ constexpr float kWeightScale = 16384.f;
 
 template <int HD> struct QRow { h8 hi[HD / 32], lo[HD / 32]; float back; };   // back: what undoes the row's power of two
 
-// Eight consecutive features of a raw projection row after the rotary step (pairs (2 j, 2 j + 1)).
-__device__ __forceinline__ void rope8(const float* src, const float2* tab, float (&o)[8]) {
-    const float4 a = *reinterpret_cast<const float4*>(src), b = *reinterpret_cast<const float4*>(src + 4);
-    const float4 c = *reinterpret_cast<const float4*>(tab), d = *reinterpret_cast<const float4*>(tab + 2);
+// Eight consecutive features of a raw projection row, and after the rotary step (pairs (2 j, 2 j + 1)).
+struct Raw8 { float4 a, b, c, d; };
+__device__ __forceinline__ Raw8 load_raw8(const float* src, const float2* tab) {
+    return {*reinterpret_cast<const float4*>(src), *reinterpret_cast<const float4*>(src + 4), *reinterpret_cast<const float4*>(tab),
+            *reinterpret_cast<const float4*>(tab + 2)};
+}
+__device__ __forceinline__ void rope8(const Raw8& r, float (&o)[8]) {
+    const float4 a = r.a, b = r.b, c = r.c, d = r.d;
     o[0] = a.x * c.x - a.y * c.y; o[1] = a.x * c.y + a.y * c.x;
     o[2] = a.z * c.z - a.w * c.w; o[3] = a.z * c.w + a.w * c.z;
     o[4] = b.x * d.x - b.y * d.y; o[5] = b.x * d.y + b.y * d.x;
     o[6] = b.z * d.z - b.w * d.w; o[7] = b.z * d.w + b.w * d.z;
 }
 __device__ __forceinline__ float row_max4(float v) {   // over the four lanes that share a row
-    v = fmaxf(v, __shfl_xor(v, 16));
-    return fmaxf(v, __shfl_xor(v, 32));
+    v = max16(v);
+    return max32(v);
 }
 __device__ __forceinline__ float row_sum4(float v) {
-    v += __shfl_xor(v, 16);
-    return v + __shfl_xor(v, 32);
+    v = sum16(v);
+    return sum32(v);
 }
 template <int HD>
-__device__ __forceinline__ void load_query(const float* row, const float2* tab, int kg, bool on, float scale, QRow<HD>& q) {
+__device__ __forceinline__ void load_query(const float* row, const float2* tab, int kg, Raw8 (&raw)[HD / 32]) {
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks) raw[ks] = load_raw8(row + ks * 32 + kg * 8, tab + ks * 16 + kg * 4);
+}
+template <int HD>
+__device__ __forceinline__ void split_query(const Raw8 (&raw)[HD / 32], bool on, float scale, QRow<HD>& q) {
     float v[HD / 32][8], top = 0.f;
 #pragma unroll
     for (int ks = 0; ks < HD / 32; ++ks) {
-        const int f = ks * 32 + kg * 8;
-        if (on) rope8(row + f, tab + f / 2, v[ks]);
+        rope8(raw[ks], v[ks]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             v[ks][e] = on ? v[ks][e] * scale : 0.f;
@@ -585,7 +605,11 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
     const size_t base = (size_t)s * C;
     const float scale = 1.f / sqrtf((float)HD);
     QRow<HD> q;
-    load_query<HD>(a.qkv + (base + min(row, C - 1)) * 3 * a.d + (size_t)h * HD, a.rope + (size_t)min(row, C - 1) * (HD / 2), kg, row < C, scale, q);
+    {
+        Raw8 raw[HD / 32];
+        load_query<HD>(a.qkv + (base + min(row, C - 1)) * 3 * a.d + (size_t)h * HD, a.rope + (size_t)min(row, C - 1) * (HD / 2), kg, raw);
+        split_query<HD>(raw, row < C, scale, q);
+    }
     f32x4 o[HD / 16];
 #pragma unroll
     for (int ft = 0; ft < HD / 16; ++ft) o[ft] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -601,7 +625,7 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
 #pragma unroll
             for (int c = 0; c < HD / 32; ++c) {
                 float k[8];
-                rope8(kr + c * 8, tab + c * 4, k);
+                rope8(load_raw8(kr + c * 8, tab + c * 4), k);
                 const float4 v0 = *reinterpret_cast<const float4*>(kr + a.d + c * 8), v1 = *reinterpret_cast<const float4*>(kr + a.d + c * 8 + 4);
                 h8 kk, vv;
 #pragma unroll
@@ -712,14 +736,34 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
 #pragma unroll
         for (int c = 0; c < CH; ++c) t.v[c] = __builtin_amdgcn_raw_buffer_load_b128(rv, (unsigned)(tile * 16 * HD) * 2u + (unsigned)(c * 64 + lane) * 16u, 0, 0);
     };
+    // Requested in the order of need, since a unit answers in order: the query, without which no tile can be used, ahead of
+    // the cached tiles.
+    const int qpos = pos0 + (tree ? a.map.tree_depth[min(row, R - 1)] : row);
+    Raw8 qraw[HD / 32];
+    load_query<HD>(a.qkv + (size_t)(R0 + min(row, R - 1)) * 3 * a.d + (size_t)h * HD, a.rope + (size_t)min(qpos, a.Tmax - 1) * (HD / 2), kg, qraw);
+    struct Own { Raw8 k; float4 v0, v1; };
+    auto load_own = [&](int nt, Own (&t)[HD / 32]) {
+        const int krc = min(nt * 16 + r16, nrows - 1);    // this lane's key row (A operand)
+        const float* src = a.qkv + (size_t)(R0 + krc) * 3 * a.d + a.d + (size_t)h * HD + kg * 8;
+        const float2* tab = a.rope + (size_t)(pos0 + (tree ? a.map.tree_depth[krc] : krc)) * (HD / 2) + kg * 4;
+#pragma unroll
+        for (int c = 0; c < HD / 32; ++c) {
+            t[c].k = load_raw8(src + c * 32, tab + c * 16);
+            t[c].v0 = *reinterpret_cast<const float4*>(src + a.d + c * 32);
+            t[c].v1 = *reinterpret_cast<const float4*>(src + a.d + c * 32 + 4);
+        }
+    };
+    Own own[HD / 32];
+    int nt = NWV - 1 - wave;                              // own tile of this wave: the last waves have the first ones
     Tile ring[T];
 #pragma unroll
     for (int j = 0; j < T; ++j) request(wave + j * NWV, ring[j]);
-
-    const int qpos = pos0 + (tree ? a.map.tree_depth[min(row, R - 1)] : row);
     QRow<HD> q;
-    load_query<HD>(a.qkv + (size_t)(R0 + min(row, R - 1)) * 3 * a.d + (size_t)h * HD, a.rope + (size_t)min(qpos, a.Tmax - 1) * (HD / 2), kg,
-                   row < nrows, 1.f / sqrtf((float)HD), q);
+    split_query<HD>(qraw, row < nrows, 1.f / sqrtf((float)HD), q);
+    // The own keys and values come in behind the cached ones.  Not where four workgroups should share a unit, nor with wide
+    // heads: it takes 40 registers (14.1 us instead of 13.4 with four waves, since two workgroups fewer fit).
+    constexpr bool EARLY = HD == 64 && NWV == 8;
+    if (EARLY && nt * 16 < nrows) load_own(nt, own);
     // which of the pass's own entries the row attends, one bit each: its ancestors or the rows before it, and itself
     auto visible = [&](int r) { return tree ? a.map.tree_anc[r] | (1ull << r) : (2ull << r) - 1ull; };
     const unsigned long long sees = row < nrows ? visible(row) : 0ull;
@@ -765,21 +809,19 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
         }
     }
     // the pass's own entries: tile nt of 16 rows for wave NWV - 1 - nt % NWV
-    for (int nt = NWV - 1 - wave; nt * 16 < nrows; nt += NWV) {
-        const int kr = nt * 16 + r16;                     // this lane's key row (A operand)
-        const int krc = min(kr, nrows - 1);
-        const float* src = a.qkv + (size_t)(R0 + krc) * 3 * a.d + a.d + (size_t)h * HD;
-        const int kpos = pos0 + (tree ? a.map.tree_depth[krc] : krc);
+    for (; nt * 16 < nrows; nt += NWV) {
+        const int kr = nt * 16 + r16;
         const size_t entry = cbase + (size_t)(pos0 + kr) * HD;
+        if (!EARLY || nt >= NWV) load_own(nt, own);
         h8 k[HD / 32];
 #pragma unroll
         for (int c = 0; c < HD / 32; ++c) {
             const int f = c * 32 + kg * 8;
             float v[8];
-            rope8(src + f, a.rope + (size_t)kpos * (HD / 2) + f / 2, v);
+            rope8(own[c].k, v);
 #pragma unroll
             for (int e = 0; e < 8; ++e) k[c][e] = (_Float16)v[e];
-            const float4 v0 = *reinterpret_cast<const float4*>(src + a.d + f), v1 = *reinterpret_cast<const float4*>(src + a.d + f + 4);
+            const float4 v0 = own[c].v0, v1 = own[c].v1;
             h8 vv;
             vv[0] = (_Float16)v0.x; vv[1] = (_Float16)v0.y; vv[2] = (_Float16)v0.z; vv[3] = (_Float16)v0.w;
             vv[4] = (_Float16)v1.x; vv[5] = (_Float16)v1.y; vv[6] = (_Float16)v1.z; vv[7] = (_Float16)v1.w;
