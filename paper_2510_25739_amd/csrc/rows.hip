@@ -155,11 +155,14 @@ __device__ __forceinline__ void gemm_epilogue(const RowsGemm& g, f32x4 v, int ro
 // through LDS at the end, where each takes its share of the tiles through the epilogue.
 // A k-step draws SR + 2 CT kilobytes from L2 for SR CT tiles of 2 MFMAs, every byte fetched once per workgroup; the
 // tile is chosen per shape (pick_kernel).  Workgroups that share weights follow each other on one XCD, so that the second
-// finds them in its L2.  Bound by the latency of the loads in flight: at 192 rows of the XL widths (17.5 us for W1|W3,
-// 10.8 us for QKV) 9 to 14 bytes per cycle reach a compute unit from L2 (of 64) and its matrix cores are 8 to 13 % busy.
+// finds them in its L2.  Bound by what a compute unit takes in: every shape draws 70 to 80 KB a microsecond and unit (the
+// slopes of the table beside pick_kernel), a unit alone as well as all of them, so the tile with the fewest bytes for a
+// unit's share of the output is the fastest; eight waves rather than four shorten what comes before and after (W1|W3 of 192
+// rows at the XL widths: two (4, 3) workgroups to a unit 17.2 us, (7, 3) of four waves 17.1 us, of eight 15.1 us).
 template <int SR, int CT, int D, int KW, bool PACKED, int MODE>
 __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
-    __shared__ f32x4 part[KW][SR * CT][64];
+    constexpr int PW = KW * SR * CT > 128 ? KW / 2 : KW;   // waves whose partial results LDS holds at a time
+    __shared__ f32x4 part[PW][SR * CT][64];
     __shared__ float rscale[16 * CT];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int r16 = lane & 15, kg = lane >> 4;
@@ -240,17 +243,34 @@ __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
             load(s + j + D, ring[j]);
         }
     }
+    if (PW < KW) {   // the upper waves' first, added by the lower ones
+        if (wave >= PW) {
 #pragma unroll
-    for (int s = 0; s < SR; ++s)
+            for (int s = 0; s < SR; ++s)
 #pragma unroll
-        for (int t = 0; t < CT; ++t) part[wave][s * CT + t][lane] = acc[s][t];
+                for (int t = 0; t < CT; ++t) part[wave - PW][s * CT + t][lane] = acc[s][t];
+        }
+        __syncthreads();
+        if (wave < PW) {
+#pragma unroll
+            for (int s = 0; s < SR; ++s)
+#pragma unroll
+                for (int t = 0; t < CT; ++t) acc[s][t] += part[wave][s * CT + t][lane];
+        }
+    }
+    if (wave < PW) {
+#pragma unroll
+        for (int s = 0; s < SR; ++s)
+#pragma unroll
+            for (int t = 0; t < CT; ++t) part[wave][s * CT + t][lane] = acc[s][t];
+    }
     __syncthreads();
     // lane holds features 16 (s_first + s) + 4 kg .. + 3 of row 16 (t_first + t) + r16
     for (int q = wave; q < SR * CT; q += KW) {
         const int s = q / CT, t = q - s * CT, strip = s_first + s, row = (t_first + t) * 16 + r16, f = strip * 16 + 4 * kg;
         f32x4 v = part[0][q][lane];
 #pragma unroll
-        for (int w = 1; w < KW; ++w) v += part[w][q][lane];
+        for (int w = 1; w < PW; ++w) v += part[w][q][lane];
         gemm_epilogue<MODE>(g, v, row, f, strip < strips, kg, rscale[t * 16 + r16]);
     }
 }
@@ -885,14 +905,14 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
 // of 32, and an XCD's compute units take its workgroups (see the kernels' mapping) 32 at a time, the small (4, 3) kernel's
 // 64.  Smaller tiles draw fewer bytes into a unit, so the smallest that covers the output in one round wins; the staged
 // ones once the rows are a contraction.  Fitted to 3900 times of these kernels (17 products of the B, XL and 7B widths, 2 to
-// 512 rows, weights from memory): the choice is 1.1 % behind the fastest on average.  Counting workgroups over the whole
+// 512 rows, weights from memory): the choice is 0.9 % behind the fastest on average.  Counting workgroups over the whole
 // chip, with a time per k-step alone, was 9.3 % behind: W1|W3 of 48 rows at the XL widths (2, 2) 14.5 us, (4, 2) 9.8 us, QKV
 // of 72 rows 13.3 and 9.1 us; 384 rows of W2 (4, 2) 26.0 us, since two XCDs had 36 workgroups, (4, 3) 17.6 us.
 struct RowsKernel { int SR, CT; float fixed, step; int slots; bool staged; };
 static const RowsKernel kRowsKernels[] = {
     {1, 1, 0.9f, 0.038f, 32, false}, {2, 1, 1.5f, 0.049f, 32, false}, {4, 1, 1.8f, 0.09f, 32, false},   {2, 2, 1.2f, 0.080f, 32, false},
     {3, 2, 1.9f, 0.093f, 32, false}, {4, 2, 1.5f, 0.116f, 32, false}, {6, 2, 2.5f, 0.143f, 32, false},  {4, 3, 2.6f, 0.129f, 32, false},
-    {4, 3, 3.9f, 0.243f, 64, false}, {4, 4, 3.3f, 0.146f, 32, false}, {7, 3, 6.5f, 0.182f, 32, false},  {8, 8, 7.5f, 0.398f, 32, true},
+    {4, 3, 3.9f, 0.243f, 64, false}, {4, 4, 3.3f, 0.146f, 32, false}, {7, 3, 3.9f, 0.179f, 32, false},  {8, 8, 7.5f, 0.398f, 32, true},
     {10, 8, 7.9f, 0.481f, 32, true}, {16, 8, 10.2f, 0.65f, 32, true}, {20, 12, 15.9f, 1.101f, 32, true}};
 static int pick_kernel(const RowsGemm& g) {
     const int strips = g.N / 16, tiles = (g.M + 15) / 16;
@@ -956,7 +976,7 @@ template <int MODE> static void launch_packed(hipStream_t stream, const RowsGemm
         case 7: return launch_direct<4, 3, 2, 8, true, MODE>(stream, g);
         case 8: return launch_direct<4, 3, 3, 4, true, MODE>(stream, g);
         case 9: return launch_direct<4, 4, 2, 8, true, MODE>(stream, g);
-        case 10: return launch_direct<7, 3, 5, 4, true, MODE>(stream, g);
+        case 10: return launch_direct<7, 3, 2, 8, true, MODE>(stream, g);
         case 11: return launch_staged<2, 4, 4, 2, 4, true, MODE>(stream, g);
         case 12: return launch_staged<2, 4, 5, 2, 4, true, MODE>(stream, g);
         case 13: return launch_staged<4, 2, 4, 4, 4, true, MODE>(stream, g);
