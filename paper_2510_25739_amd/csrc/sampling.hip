@@ -1465,8 +1465,9 @@ __global__ __launch_bounds__(NT) void multi_verify_list_kernel(const float* p_lo
 // selection of the target row and of every proposal row runs in a workgroup of its own (all of
 // them in parallel), and the walk over the candidates then gathers the target's kept entries again
 // (writing them out instead made no difference: tree step 173.0 ms an image against 173.6).
+// 64 registers, so that two rows share a compute unit and one's barriers and loads are covered by the other.
 template <int E>
-__global__ __launch_bounds__(NT) void multi_row_stats_kernel(const float* p_logits, const float* q_logits,
+__global__ __launch_bounds__(NT, 8) void multi_row_stats_kernel(const float* p_logits, const float* q_logits,
                                                              const int32_t* m_rows, int m, int n, float inv_t,
                                                              int top_k, WarpStat* stats) {
     __shared__ FastShared fs;
@@ -1476,7 +1477,13 @@ __global__ __launch_bounds__(NT) void multi_row_stats_kernel(const float* p_logi
     const float* l = j == 0 ? p_logits + (size_t)row * n : q_logits + ((size_t)row * m + (j - 1)) * n;
     float z[E];
     load_row<E>(l, nullptr, 0.f, inv_t, nullptr, n, z);
-    const WarpStat st = warp_and_draw<E>(z, n, top_k, 0, fs, L, nullptr, nullptr);
+    WarpStat st;
+    Threshold t;
+    const int Kc = select_list<E>(z, n, top_k, fs, L, t, st);
+    int idx[kLH];
+    double w[kLH];
+    list_weights(L, Kc, st.zmax, t, idx, w);
+    st.total = sum1(sum3(w), fs.s.sum);
     if (threadIdx.x == 0) stats[(size_t)row * (m + 1) + j] = st;
 }
 
