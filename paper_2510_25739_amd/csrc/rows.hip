@@ -723,7 +723,9 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
 // and are appended to the cache by the workgroup of the same row tile.  The waves meet once, at the end.
 // Bound by memory latency: one dependent chain (projection rows, then the merge), all cache requests in flight
 // beside it.  Eight waves when few workgroups share the chip; four from one workgroup per compute unit on, where
-// four workgroups then fit a unit (32 sequences of 20 heads, 190 cached positions: 17.4 us with eight).
+// four workgroups then fit a unit (32 sequences of 20 heads, 190 cached positions: 12.0 us, with eight 17.4).
+// The query is asked for ahead of the cached tiles, so that its rotation does not wait for them, and sums over the lanes
+// go by lane swaps, not through LDS (13.2 -> 12.0 us there, three sequences of 20 heads on eight waves 8.6 -> 7.9).
 template <int HD, int NWV>
 __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
     constexpr int VST = HD + 16, T = HD == 64 ? 3 : 2, CH = HD / 32;   // CH: 16-byte chunks per lane of a value tile

@@ -1157,8 +1157,6 @@ __global__ __launch_bounds__(kThreads, 1) void verify_stream_kernel(SP p) {
                                                 slot(p, p.L) + p.o_ssx, p.d, p.Kpd, resid);
 }
 
-// One draft micro-step up to the logits (the sampling kernel follows): stage W (three column
-// blocks of W_d over 3 d/16 strips), one grid barrier, then the output projection.
 // The draft head's output projection, two rounds of jobs at a time: the weights of both are requested ahead of the grid
 // barrier, which a launch has registers for here (one round at a time, the second one's whole latency is exposed: five
 // drafts with their draws 145.6 -> 143.2 us at the XL shape, 120.5 -> 116.5 at the B shape).
@@ -1216,6 +1214,8 @@ __device__ __forceinline__ void draft_logits(const SP& p, const Lds& s, Barrier&
     __syncthreads();   // (a further pair's partial results go where these were read)
 }
 
+// One draft micro-step up to the logits (the sampling kernel follows): stage W (three column
+// blocks of W_d over 3 d/16 strips), one grid barrier, then the output projection.
 template <int TPS_D, int KREG_D, int RSMAX>
 __global__ __launch_bounds__(kThreads, 1) void draft_stream_kernel(SP p) {
     extern __shared__ uint4 smem_raw[];

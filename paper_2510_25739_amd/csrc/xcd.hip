@@ -29,9 +29,8 @@
 //
 // In the loaded kernel the latencies are two to three times the idle ones (a partial sum is in its
 // owner's registers 1.3 - 2.7 us after its store was issued, a local flag is seen after ~0.4 us, the
-// staging copy takes ~0.55 us), which is what bounds a stage at 4.4 - 5.5 us at the XL shape (see the
-// stage table that hawk_phase_trace gives); the weight stream itself accounts for ~5 % of that kernel's
-// time.  Two forms of the compute side: verify_xcd_kernel keeps a layer's tiles in registers, requested
+// staging copy takes ~0.5 us), which is what bounds a stage at 4.2 - 5.2 us at the XL shape (see the
+// stage table that hawk_phase_trace gives; 4.4 - 5.5 us before the steps measured below).  Two forms of the compute side: verify_xcd_kernel keeps a layer's tiles in registers, requested
 // a fifth of a layer per stage (d_model 768 / 1280); verify_xcd_stream_kernel streams them through two
 // register buffers (d_model 4096, where the stream is two thirds of the time).  The IO side is shared.
 #include <math.h>

@@ -599,6 +599,16 @@ def test_streaming_kernel_row_counts_and_batches(H, cfg, k, batch, scale, path):
     assert_bf16(total, 12)
 
 
+@pytest.mark.parametrize("vocab", [2048, 12304, 16384, 24576])
+def test_draft_output_projection_over_rounds(H, vocab):
+    # the draft kernel takes its output projection's jobs two rounds at a time: one round with idle workgroups, a second
+    # one that few have, two whole ones, and an odd third
+    s = synth.CONFIGS[1].replace(n_layers=1, vocab=vocab, n_cond=16, grid_h=6, grid_w=8, k=3, top_k=500)
+    total = accumulate_lockstep(H, s, s.k, 1, 12, expect_path=1)
+    print("draft rounds", vocab, total)
+    assert_bf16(total, 12)
+
+
 @pytest.mark.parametrize("cfg,ks", [(2, [7, 8, 6, 9]), (1, [7, 8, 0, 9])])
 def test_xcd_kernel_on_either_side_of_eight_rows(H, cfg, ks):
     # up to eight rows the partial sums cross two strips a store and two XCDs a look, beyond that one: launches of both
