@@ -1557,7 +1557,6 @@ struct XcdPlan {
     size_t xbase[X_NK][kXcd], layer_tiles, total_tiles;
     int njobs[F_NF][kXcd];
     int NSW[X_NK];                 // strips per compute wave and round the plan needs
-    int lm_rounds;
     int KpA, KpO, KpH;
     unsigned par, par_lm;          // parities of the partial-sum words (see parity_bit), per row
     std::vector<int16_t> gtab, rtab, ptab;
@@ -1577,6 +1576,16 @@ bool xcd_shape_ok(const hawk_ctx* c) {
         return false;
     if (c->Vs % (16 * kXcd) || c->d % (32 * kXcd) || c->H < kXcd) return false;
     return true;
+}
+
+// Strips per compute wave that the kernels of a width take: all of them follow from the width but those of the output
+// projection (rounds of four), so a slice of more entries than kPer * kCW * 16 times that has no plan: 16384 at the narrow
+// widths, 8192 at 4096.
+int most_strips(int d, int kind) {
+    static const int most[3][X_NK] = {{2, 1, 2, 1, 8},     // 768: 144, 48, 256, 48 strips over 128 waves
+                                      {2, 1, 4, 1, 8},     // 1280: 240, 80, 432, 80
+                                      {6, 2, 12, 2, 4}};   // 4096: 768, 256, 1376 (11, 12 with an empty one), 256
+    return most[d == 768 ? 0 : d == 1280 ? 1 : 2][kind];
 }
 
 // Contiguous split of n items into `parts` ranges; the first `n % parts` ranges (or the last, if
@@ -1627,9 +1636,10 @@ void build_xcd_plan(const hawk_ctx* c, XcdPlan* P) {
                 need = std::max(need, ws[w + 1] - ws[w]);
             }
         }
+        if (need > most_strips(d, k)) P->ok = false;
         P->NSW[k] = need;
-        if (P->nstrips[k] > 32767) P->ok = false;
     }
+    if (!P->ok) return;
     for (int k = 0; k < X_NK; ++k) {   // producer of every strip (the output projection takes two rounds of half the strips)
         P->poff[k] = (int)P->ptab.size();
         P->ptab.resize(P->ptab.size() + P->nstrips[k], 0);
@@ -1699,9 +1709,6 @@ void build_xcd_plan(const hawk_ctx* c, XcdPlan* P) {
         }
         for (int x = 0; x < kXcd; ++x) P->njobs[flag_of[k]][x] = k == X_D ? std::min(count[x], kPer * (kNIO - 1)) : count[x];
     }
-    const int per_round = kPer * kCW * P->NSW[X_LM];
-    (void)per_round;
-    P->lm_rounds = 1;
 }
 
 // Attention jobs of a step with RS rows per sequence: (sequence, head, row group) per unit of the XCD
@@ -1911,28 +1918,20 @@ int launch_verify_xcd(hawk_ctx* c, int k, const int32_t* tree_depth, const unsig
     p.eps = c->cfg.rms_eps;
     const void* kern = nullptr;
     if (c->d == 1280) {
-        // strips per compute wave: QKV 240 / 128 -> 2, Wo 80 / 128 -> 1, W1|W3 432 / 128 -> 4, W2 -> 1, output 1024 / 128 -> 8
         p.lm_rounds = 2;
         kern = RPJ == 2 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 5, 1, 6, 4, 5, 1, 14, 4, 2, false>)
              : p.MR > 8 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 5, 1, 6, 4, 5, 1, 14, 4, 1, false>)
                         : reinterpret_cast<const void*>(verify_xcd_kernel<2, 5, 1, 6, 4, 5, 1, 14, 4, 1, true>);
-        if (P->NSW[X_A] > 2 || P->NSW[X_C] > 1 || P->NSW[X_D] > 4 || P->NSW[X_E] > 1 || P->NSW[X_LM] > 8) return -1;
     } else if (c->d == 4096) {
-        // streamed: QKV 768 strips / 128 waves -> 6, Wo 256 -> 2, W1|W3 1376 -> 11 (12 with an empty one), W2 256 -> 2 x 3 chunks
-        // of its 43 k-tiles, output 512 -> 4
+        // streamed; 16 k-tiles an XCD and product, W2 three chunks of its 43
         p.lm_rounds = 1;
         kern = RPJ == 1 ? reinterpret_cast<const void*>(verify_xcd_stream_kernel<6, 2, 12, 2, 43, 4, 1, 128>)
                         : reinterpret_cast<const void*>(verify_xcd_stream_kernel<6, 2, 12, 2, 43, 4, 2, 128>);
-        if (P->NSW[X_A] > 6 || P->NSW[X_C] > 2 || P->NSW[X_D] > 12 || P->NSW[X_E] > 2 || P->NSW[X_LM] > 4) return -1;
-        for (int x = 0; x < kXcd; ++x)
-            if (P->KT[X_A][x] != 16 || P->KT[X_C][x] != 16 || P->KT[X_E][x] != 43) return -1;   // (three parts of the W2 input on both sides)
     } else {
-        // d = 768: QKV 144 -> 2, Wo 48 -> 1, W1|W3 256 -> 2, W2 48 -> 1, output 8 in two rounds of 4
         p.lm_rounds = 2;
         kern = RPJ == 2 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 2, false>)
              : p.MR > 8 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 1, false>)
                         : reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 1, true>);
-        if (P->NSW[X_A] > 2 || P->NSW[X_C] > 1 || P->NSW[X_D] > 2 || P->NSW[X_E] > 1 || P->NSW[X_LM] > 8) return -1;
     }
     // the parameter block and the attention job table of this step shape: uploaded when they change
     static_assert(sizeof(XP) <= 4096, "parameter block larger than its workspace region");

@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import synth
+from oracle import tree
 
 pytestmark = pytest.mark.gpu
 
@@ -607,6 +608,32 @@ def test_draft_output_projection_over_rounds(H, vocab, path):
     total = accumulate_lockstep(H, s, s.k, path, 12, expect_path=1)
     print("draft rounds", vocab, total)
     assert_bf16(total, 12)
+
+
+@pytest.mark.parametrize("cfg,vocab,kernel", [(1, 16384, 2), (1, 16512, 1), (2, 24576, 1), (4, 16384, 0)])
+def test_slices_that_the_xcd_kernel_has_no_room_for(H, cfg, vocab, kernel):
+    # The kernel laid out on the XCDs takes output projections of up to 16384 entries, 8192 at the 7B widths; larger ones
+    # were once accepted for it and then refused at the launch.  By default they run on the grid-barrier kernel or one
+    # kernel per operation: a chain's steps, and a tree's with the walk on the pass's own rows.
+    import torch
+    s = synth.CONFIGS[cfg].replace(n_layers=1, vocab=vocab, samp_lo=0, samp_n=0, cfg_scale=1.0, n_cond=8, grid_h=4, grid_w=8, k=3, top_k=500)
+    blob = synth.make_weights(s, seed=0)
+    steps = 0
+    for u_seed in range(1, 9):
+        _, hk, orc = make_pair(H, s, blob=blob)
+        res = lockstep(s, hk, orc, s.k, u_seed=u_seed, max_steps=5)
+        assert res["stage_bad"] == 0 and res["max_logit_err"] <= 2e-2 and res["max_draft_logit_err"] <= 2e-2, res
+        steps = res["steps"]
+        if steps:   # (the first tokens may differ in bf16: nothing ran then)
+            break
+    assert steps and hk.last_kernel() == kernel and hk.last_path() == (1 if kernel else 0)
+    if vocab <= 16384:   # (tree verification takes no larger slices)
+        q, cand, u = synth.make_logit_rows(4, (1, 1, 3, s.v_s)), [5, 9, 700], np.full(3, 0.5, np.float32)
+        na, toks = hk.verify_tree((3,), np.array([[cand]], np.int32), torch.from_numpy(q).to("cuda:0"), u.reshape(1, 1, 3), np.full((2, 1), 0.5, np.float32))
+        assert hk.last_kernel() == kernel
+        a, t, _ = tree.tree_walk(hk.tree_logits(4)[0], (3,), [q[0, 0]], [cand], [u], np.full(2, 0.5, np.float32), 1.0, s.top_k)
+        assert a == na[0] and list(toks[0, :a + 1]) == t
+    hk.close()
 
 
 @pytest.mark.parametrize("cfg,ks", [(2, [7, 8, 6, 9]), (1, [7, 8, 0, 9])])
