@@ -1157,21 +1157,22 @@ __global__ __launch_bounds__(kThreads, 1) void verify_stream_kernel(SP p) {
                                                 slot(p, p.L) + p.o_ssx, p.d, p.Kpd, resid);
 }
 
-// The draft head's output projection, two rounds of jobs at a time: the weights of both are requested ahead of the grid
-// barrier, which a launch has registers for here (one round at a time, the second one's whole latency is exposed: five
-// drafts with their draws 145.6 -> 143.2 us at the XL shape, 120.5 -> 116.5 at the B shape).
-template <int TPS, int KREG>
+// The draft head's output projection, two rounds of jobs at a time (JOBS; an odd last one alone): the weights of both are
+// requested ahead of the grid barrier, which a launch has registers for here (one round at a time, the second one's whole
+// latency is exposed: five drafts with their draws 145.6 -> 143.2 us at the XL shape, 120.5 -> 116.5 at the B shape).
+template <int TPS, int KREG, int JOBS>
 __device__ __forceinline__ void draft_logits(const SP& p, const Lds& s, Barrier& bar, int round) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const bool is_io = wave >= kCW;
     const unsigned ph = bar.id - bar.first + round;
     constexpr int NS = kTMax / TPS < kMaxStrips ? kTMax / TPS : kMaxStrips;
-    Job job[2] = {load_job(p, K_LM, round, 0), {}};
-    if (round + 1 < p.rounds[K_LM]) job[1] = load_job(p, K_LM, round + 1, 0);
-    v4u w0[NS * TPS], w1[NS * TPS];
+    Job job[JOBS];
+    v4u w[JOBS][NS * TPS];
+#pragma unroll
+    for (int j = 0; j < JOBS; ++j) job[j] = load_job(p, K_LM, round + j, 0);
     if (!is_io) {
-        issue_tiles<TPS, NS>(p, job[0], wave, lane, w0);
-        issue_tiles<TPS, NS>(p, job[1], wave, lane, w1);
+#pragma unroll
+        for (int j = 0; j < JOBS; ++j) issue_tiles<TPS, NS>(p, job[j], wave, lane, w[j]);
     } else {
         stamp(p, ph, 0);
         if (round == 0) {   // all rounds share one input
@@ -1200,23 +1201,29 @@ __device__ __forceinline__ void draft_logits(const SP& p, const Lds& s, Barrier&
         epilogue<K_LM, false>(p, s, 0, i == 0 ? s0 : i == 1 ? s1 : s2, v, lane, pre, resid);
     };
     if (!is_io && job[0].nstrips) {
-        mfma_job<TPS, NS>(w0, wave, lane, p.MR, s.act_hi, s.act_lo, p.Kpd, acc);
+        mfma_job<TPS, NS>(w[0], wave, lane, p.MR, s.act_hi, s.act_lo, p.Kpd, acc);
         put();
     }
     __syncthreads();
+    if (JOBS == 1) stamp(p, ph, 4);
     if (is_io) finish(job[0]);
-    else if (job[1].nstrips) mfma_job<TPS, NS>(w1, wave, lane, p.MR, s.act_hi, s.act_lo, p.Kpd, acc);
-    __syncthreads();
-    if (!is_io && job[1].nstrips) put();
-    __syncthreads();
-    stamp(p, ph, 4);
-    if (is_io) finish(job[1]);
-    __syncthreads();   // (a further pair's partial results go where these were read)
+    if constexpr (JOBS == 2) {
+        if (!is_io && job[1].nstrips) mfma_job<TPS, NS>(w[1], wave, lane, p.MR, s.act_hi, s.act_lo, p.Kpd, acc);
+        __syncthreads();
+        if (!is_io && job[1].nstrips) put();
+        __syncthreads();
+        stamp(p, ph, 4);
+        if (is_io) finish(job[1]);
+        __syncthreads();   // (a further round's partial results go where these were read)
+    }
 }
 
 // One draft micro-step up to the logits (the sampling kernel follows): stage W (three column
 // blocks of W_d over 3 d/16 strips), one grid barrier, then the output projection.
-template <int TPS_D, int KREG_D, int RSMAX>
+// PAIRS: more than one round of the output projection.  One round (slices of up to 8192 entries at the XL widths, 12288 at
+// the B widths) has a kernel of its own: with an empty second job five micro-steps of 16 sequences and their draws took
+// 189.7 us instead of 184.8 at XL (4096 entries), 153.8 instead of 150.1 at B (8192).
+template <int TPS_D, int KREG_D, int RSMAX, bool PAIRS>
 __global__ __launch_bounds__(kThreads, 1) void draft_stream_kernel(SP p) {
     extern __shared__ uint4 smem_raw[];
     Lds s;
@@ -1264,7 +1271,10 @@ __global__ __launch_bounds__(kThreads, 1) void draft_stream_kernel(SP p) {
         if (is_io) io_finish(p, s, bar, ph, wave, lane);
         else compute_finish(bar);
     }
-    for (int r = 0; r < p.rounds[K_LM]; r += 2) draft_logits<TPS_D, KREG_D>(p, s, bar, r);
+    int r = 0;
+    if constexpr (PAIRS)
+        for (; r + 1 < p.rounds[K_LM]; r += 2) draft_logits<TPS_D, KREG_D, 2>(p, s, bar, r);
+    if (r < p.rounds[K_LM]) draft_logits<TPS_D, KREG_D, 1>(p, s, bar, r);
 }
 
 // Copies one matrix into the tile order of its kind: tile T of the packed stream is
@@ -1738,8 +1748,11 @@ int launch_draft_stream(hawk_ctx* c, int i, size_t off_prev, size_t off_out) {
     p.draft = wsp<int32_t>(c, c->off.draft);
     p.E_off = c->w.E;
     p.step_i = i; p.N = c->N; p.IW = c->gw; p.kstride = c->kmax + 1;
-    const void* kern = c->d == 1280 ? reinterpret_cast<const void*>(draft_stream_kernel<10, 5, 6>)
-                                    : reinterpret_cast<const void*>(draft_stream_kernel<6, 3, 6>);
+    const bool pairs = p.rounds[K_LM] > 1;
+    const void* kern = c->d == 1280 ? (pairs ? reinterpret_cast<const void*>(draft_stream_kernel<10, 5, 6, true>)
+                                             : reinterpret_cast<const void*>(draft_stream_kernel<10, 5, 6, false>))
+                                    : (pairs ? reinterpret_cast<const void*>(draft_stream_kernel<6, 3, 6, true>)
+                                             : reinterpret_cast<const void*>(draft_stream_kernel<6, 3, 6, false>));
     return launch_persistent(c, kern, p, 1u);
 }
 
