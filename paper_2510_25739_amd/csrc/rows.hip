@@ -722,8 +722,10 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
 // maximum - and the last waves the tiles of the pass's own rows, which come rotated from the raw projections
 // and are appended to the cache by the workgroup of the same row tile.  The waves meet once, at the end.
 // Bound by memory latency: one dependent chain (projection rows, then the merge), all cache requests in flight
-// beside it.  Eight waves when few workgroups share the chip; four from one workgroup per compute unit on, where
-// four workgroups then fit a unit (32 sequences of 20 heads, 190 cached positions: 12.0 us, with eight 17.4).
+// beside it.  Eight waves while every workgroup has a compute unit to itself, which they fill (157 registers); four, of
+// which three workgroups fit a unit, from 256 workgroups on (32 sequences of 20 heads, 190 cached positions: 12.0 us, with
+// eight 17.4) - counted with their row tiles: 16 layers of ten XL sequences of 34 rows, 600 workgroups, 1399 us a pass with
+// four waves and 1495 with eight.  Below that eight are 10 % of a pass ahead at 4000 cached positions, four 1 to 4 % at up to 500.
 // The query is asked for ahead of the cached tiles, so that its rotation does not wait for them, and sums over the lanes
 // go by lane swaps, not through LDS (13.2 -> 12.0 us there, three sequences of 20 heads on eight waves 8.6 -> 7.9).
 template <int HD, int NWV>
@@ -782,8 +784,8 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
     for (int j = 0; j < T; ++j) request(wave + j * NWV, ring[j]);
     QRow<HD> q;
     split_query<HD>(qraw, row < nrows, 1.f / sqrtf((float)HD), q);
-    // The own keys and values come in behind the cached ones.  Not where four workgroups should share a unit, nor with wide
-    // heads: it takes 40 registers (14.1 us instead of 13.4 with four waves, since two workgroups fewer fit).
+    // The own keys and values come in behind the cached ones.  Not where workgroups should share a unit, nor with wide heads:
+    // it takes 40 registers (14.1 us instead of 13.4 with four waves, since two workgroups fit a unit instead of three).
     constexpr bool EARLY = HD == 64 && NWV == 8;
     if (EARLY && nt * 16 < nrows) load_own(nt, own);
     // which of the pass's own entries the row attends, one bit each: its ancestors or the rows before it, and itself
@@ -999,6 +1001,9 @@ template <int MODE> static void launch_row_major(hipStream_t stream, const RowsG
     }
 }
 
+// Waves of a step attention workgroup: see the kernel.
+extern "C" int hawk_rows_attn_waves(int sequences, int heads, int rows) { return sequences * heads * ((rows + 15) / 16) >= 256 ? 4 : 8; }
+
 void launch_rows_gemm(hipStream_t stream, const RowsGemm& g) {
     if (g.packed) {
         switch (g.mode) {
@@ -1109,7 +1114,7 @@ static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
             auto k = c->hd == 64 ? attn_prompt_kernel<64> : attn_prompt_kernel<128>;
             k<<<dim3((R + 63) / 64, c->H, c->S), 256, 0, c->stream>>>(a);
         } else {
-            const int nw = c->S * c->H >= 256 ? 4 : 8;
+            const int nw = hawk_rows_attn_waves(c->S, c->H, R);
             auto k = c->hd == 64 ? (nw == 4 ? attn_step_kernel<64, 4> : attn_step_kernel<64, 8>)
                                  : (nw == 4 ? attn_step_kernel<128, 4> : attn_step_kernel<128, 8>);
             k<<<dim3(c->S, c->H, (R + 15) / 16), 64 * nw, 0, c->stream>>>(a);
