@@ -74,19 +74,19 @@ struct Product {
     int i, B, cells, IW, kstride;
 };
 
-// One wave: NC columns (kSwiglu: one column of W1 and the matching one of W3) over up to RT rows; KW waves of a
-// workgroup split K.  A normalised row's factor commutes with the product: the sum of squares is taken on the way.
+// One wave: NC columns (kSwiglu: NC / 2 of W1 and the matching ones of W3) over up to RT rows; KW waves of a workgroup
+// split K.  A normalised row's factor commutes with the product: the sum of squares is taken on the way.
 template <int MODE, int RT, int NC, int KW>
 __global__ __launch_bounds__(256) void product_kernel(Product g) {
     __shared__ double part[4][(RT + 3) / 4 * 4 * NC];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int kw = wave % KW, r0 = blockIdx.y * RT;
-    const int n0 = (blockIdx.x * (4 / KW) + wave / KW) * (MODE == kSwiglu ? 1 : NC);
+    constexpr int OUT = MODE == kSwiglu ? NC / 2 : NC;   // results of a row
+    const int n0 = (blockIdx.x * (4 / KW) + wave / KW) * OUT;
     constexpr bool NORM = MODE == kNormed || MODE == kLogits || MODE == kSwiglu;
     const float* w[NC];
 #pragma unroll
-    for (int j = 0; j < NC; ++j)
-        w[j] = g.W + (size_t)(MODE == kSwiglu ? j * g.N + min(n0, g.N - 1) : min(n0 + j, g.N - 1)) * g.K;
+    for (int j = 0; j < NC; ++j) w[j] = g.W + (size_t)(j / OUT * g.N + min(n0 + j % OUT, g.N - 1)) * g.K;
     const double* a[RT];
     const float *left[RT], *up[RT];   // kDraft (null: zeros)
     bool on[RT];
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void product_kernel(Product g) {
     // lane (g, q NC + j) finishes column j of row 4 q + quad_of(g)
     constexpr int RQ = (RT + 3) / 4;
     const int sub = lane & 15, mq = sub / NC, mj = sub % NC, rr = 4 * mq + quad_of(lane >> 4);
-    double mine = 0.0, other = 0.0, mss = 0.0;   // (other: kSwiglu, the W3 column)
+    double mine = 0.0, other = 0.0, mss = 0.0;   // (other: kSwiglu, W3's columns)
 #pragma unroll
     for (int q = 0; q < RQ; ++q) {
         auto quad = [&](const double (&v)[RT]) {
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void product_kernel(Product g) {
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
             const double t = quad(acc[j]);
-            if (MODE == kSwiglu && j == 1) other = mq == q ? t : other;
+            if (j >= OUT) other = mq == q && mj == j - OUT ? t : other;
             else mine = mq == q && mj == j ? t : mine;
         }
     }
@@ -182,8 +182,8 @@ __global__ __launch_bounds__(256) void product_kernel(Product g) {
             for (int w2 = 1; w2 < KW; ++w2) mine += part[wave + w2][rr * NC + mj];
         }
     }
-    const int row = r0 + rr, col = n0 + (MODE == kSwiglu ? 0 : mj);
-    if (sub >= RQ * NC || rr >= RT || row >= g.M || col >= g.N || (MODE == kSwiglu && mj != 0)) return;
+    const int row = r0 + rr, col = n0 + mj;
+    if (sub >= RQ * NC || rr >= RT || row >= g.M || col >= g.N || mj >= OUT) return;
     const double scale = NORM ? 1.0 / sqrt(mss / (double)g.K + g.eps) : 1.0;
     if (MODE == kSwiglu) {
         const double p = mine * scale, q = other * scale;
@@ -193,15 +193,43 @@ __global__ __launch_bounds__(256) void product_kernel(Product g) {
     else g.Y[(size_t)row * g.ldy + col] = mine * scale;
 }
 
-// Four columns a wave where they are many (the output layer: the rows' activations, 2 KB each, would be drawn once per
-// column of 1 KB), K over four waves where the columns are few.
-template <int MODE, int NC, int KW> void launch_product(hipStream_t stream, const Product& g) {
-    const int cols = (4 / KW) * (MODE == kSwiglu ? 1 : NC), nb = (g.N + cols - 1) / cols;
-    if (g.M == 1) product_kernel<MODE, 1, NC, KW><<<dim3(nb, 1), 256, 0, stream>>>(g);
-    else if (g.M == 2) product_kernel<MODE, 2, NC, KW><<<dim3(nb, 1), 256, 0, stream>>>(g);
-    else if (g.M <= 4) product_kernel<MODE, 4, NC, KW><<<dim3(nb, 1), 256, 0, stream>>>(g);
-    else if (g.M <= 6) product_kernel<MODE, 6, NC, KW><<<dim3(nb, 1), 256, 0, stream>>>(g);
-    else product_kernel<MODE, 8, NC, KW><<<dim3(nb, (g.M + 7) / 8), 256, 0, stream>>>(g);
+template <int MODE, int RT, int NC, int KW> void launch_tile(hipStream_t stream, const Product& g) {
+    const int cols = (4 / KW) * (MODE == kSwiglu ? NC / 2 : NC);
+    product_kernel<MODE, RT, NC, KW><<<dim3((g.N + cols - 1) / cols, (g.M + RT - 1) / RT), 256, 0, stream>>>(g);
+}
+// Few rows are chains of launches near their latency: one result a wave (four where the columns are many, the output layer:
+// the rows' activations, 2 KB each, would be drawn once per column of 1 KB), K over four waves where the columns are few.
+template <int MODE, int NC, int KW> bool launch_few(hipStream_t stream, const Product& g) {
+    if (g.M == 1) launch_tile<MODE, 1, NC, KW>(stream, g);
+    else if (g.M == 2) launch_tile<MODE, 2, NC, KW>(stream, g);
+    else if (g.M <= 4) launch_tile<MODE, 4, NC, KW>(stream, g);
+    else if (g.M <= 6) launch_tile<MODE, 6, NC, KW>(stream, g);
+    else return false;
+    return true;
+}
+// More rows are bound by fp64 issue and by the activations' way through L1 (8 bytes a value against 4 of a weight): several
+// columns share a row's sum of squares, its gain and its loads, once one column a wave would be more waves than the units
+// hold a few of.  Microseconds of one column (one of W1|W3; K over four waves where it is long) -> of the choice: QKV of 256
+// wide, 24 rows 4.3 -> 3.9, of 2048 wide, 400 rows 1419 -> 567 (N * rows / 8 = 2304, 307200; at 1536 3.75 and 3.81); W1|W3
+// of 256 wide, 16 rows 4.5 -> 4.0, 2048 wide, 400 rows 1553 -> 1048 (1408 pairs of waves; at 880 3.7 and 4.1); Wo, W2 with K
+// over four waves: two columns 768 wide, 16 rows 15.6 -> 7.6, 2048 wide, 16 rows 100 -> 43, and from 4096 waves on four columns
+// without the split, 1024 wide, 64 rows 80.6 -> 24.1 (two 31.9; at 3072 19.5 and 14.7), 2048 wide, 400 rows 2225 -> 594.
+void launch_normed(hipStream_t stream, const Product& g) {
+    if (launch_few<kNormed, 1, 1>(stream, g)) return;
+    if ((long)g.N * ((g.M + 7) / 8) > 1536) launch_tile<kNormed, 8, 4, 1>(stream, g);
+    else launch_tile<kNormed, 8, 1, 1>(stream, g);
+}
+void launch_swiglu_product(hipStream_t stream, const Product& g) {
+    if (launch_few<kSwiglu, 2, 1>(stream, g)) return;
+    if ((long)g.N * ((g.M + 7) / 8) > 1280) launch_tile<kSwiglu, 8, 4, 1>(stream, g);
+    else launch_tile<kSwiglu, 8, 2, 1>(stream, g);
+}
+void launch_residual(hipStream_t stream, const Product& g) {
+    const bool split = g.K > 256;
+    if (split ? launch_few<kResidual, 1, 4>(stream, g) : launch_few<kResidual, 1, 1>(stream, g)) return;
+    if ((long)g.N * ((g.M + 7) / 8) > (split ? 4096 : 1280)) launch_tile<kResidual, 8, 4, 1>(stream, g);
+    else if (split) launch_tile<kResidual, 8, 2, 4>(stream, g);
+    else launch_tile<kResidual, 8, 1, 1>(stream, g);
 }
 
 // ------------------------------------------------------------------------------------------ attention
@@ -341,8 +369,7 @@ void add_product(hawk_ctx* c, size_t off_a, int K, size_t W, int M) {   // x += 
     Product g;
     memset(&g, 0, sizeof g);
     g.A = wsp<double>(c, off_a); g.lda = K; g.W = w32(c, W); g.N = c->d; g.K = K; g.M = M; g.Y = wsp<double>(c, c->off.x); g.ldy = c->d;
-    if (K > 256) launch_product<kResidual, 1, 4>(c->stream, g);
-    else launch_product<kResidual, 1, 1>(c->stream, g);
+    launch_residual(c->stream, g);
 }
 
 }  // namespace
@@ -359,7 +386,7 @@ void f32_layers(hawk_ctx* c, const RowMap& map, int M) {
     for (int l = 0; l < c->L; ++l) {
         Product g = normed(c, c->off.x, d, c->w.g1[l], c->w.Wqkv[l], 3 * d, M);
         g.Y = wsp<double>(c, c->off.qkv); g.ldy = 3 * d;
-        launch_product<kNormed, 1, 1>(c->stream, g);
+        launch_normed(c->stream, g);
 
         if (c->hd == 32 || c->hd == 64 || c->hd == 128) {
             Attn a;
@@ -376,7 +403,7 @@ void f32_layers(hawk_ctx* c, const RowMap& map, int M) {
 
         g = normed(c, c->off.x, d, c->w.g2[l], c->w.W13[l], m, M);
         g.Y = wsp<double>(c, c->off.u); g.ldy = m;
-        launch_product<kSwiglu, 2, 1>(c->stream, g);
+        launch_swiglu_product(c->stream, g);
         add_product(c, c->off.u, m, c->w.W2[l], M);
     }
 }
@@ -385,7 +412,7 @@ void f32_layers(hawk_ctx* c, const RowMap& map, int M) {
 void f32_output_layer(hawk_ctx* c, size_t off_x, size_t stride, size_t off_logits, int M) {
     Product g = normed(c, off_x, stride, c->w.g_f, c->w.W_out + (size_t)c->cfg.samp_lo * c->d * c->esz, c->Vs, M);
     g.logits = wsp<float>(c, off_logits); g.ldy = c->Vs;
-    launch_product<kLogits, 4, 1>(c->stream, g);
+    if (!launch_few<kLogits, 4, 1>(c->stream, g)) launch_tile<kLogits, 8, 4, 1>(c->stream, g);
 }
 
 // Draft micro-step i up to its logits: head output to off_out ([S][d]), reading the previous one from off_prev.
@@ -396,7 +423,7 @@ void f32_draft_pass(hawk_ctx* c, int i, size_t off_prev, size_t off_out) {
     g.Y = wsp<double>(c, off_out); g.ldy = c->d;
     g.E = w32(c, c->w.E); g.n = wsp<int32_t>(c, c->off.n); g.k_eff = wsp<int32_t>(c, c->off.k_eff); g.grid = wsp<int32_t>(c, c->off.grid);
     g.draft = wsp<int32_t>(c, c->off.draft); g.i = i; g.B = c->B; g.cells = c->N; g.IW = c->gw; g.kstride = c->kmax + 1;
-    launch_product<kDraft, 1, 4>(c->stream, g);
+    if (!launch_few<kDraft, 1, 4>(c->stream, g)) launch_tile<kDraft, 8, 1, 4>(c->stream, g);
     f32_output_layer(c, off_out, c->d, c->off.dlogit_s, c->S);
 }
 

@@ -173,10 +173,11 @@ def test_fp32_other_draft_lengths(H, k):
 
 
 @pytest.mark.parametrize("d,heads,m,n_cond,batch,k", [(256, 8, 1000, 3, 1, 2), (256, 2, 264, 21, 2, 6), (72, 9, 40, 5, 1, 4), (520, 65, 24, 9, 1, 1),
-                                                      (384, 3, 776, 70, 3, 3), (64, 1, 8, 1, 1, 7)])
+                                                      (384, 3, 776, 70, 3, 3), (64, 1, 8, 1, 1, 7), (72, 9, 200, 130, 2, 3), (1032, 129, 1096, 12, 2, 5)])
 def test_fp32_widths_heads_and_row_counts(H, d, heads, m, n_cond, batch, k):
     # heads of 32, 64 and 128 in the attention of this configuration and others, widths that leave a wave's last look at
-    # K partly empty, columns that fill no whole wave, 1 to 210 rows, more cached positions than four looks take
+    # K partly empty, columns that fill no whole wave, 1 to 260 rows, more cached positions than four looks take; from seven
+    # rows on two or four columns a wave, in workgroups that the columns do not fill (d 72), K over four waves or not
     s = synth.HawkShape("odd", 2, d, heads, m, 203, n_cond, 6, 7, k, dtype="fp32", top_k=50, batch=batch)
     blob, hk, orc = make_pair(H, s, std=0.05)
     res = lockstep(s, hk, orc, k, u_seed=3)
