@@ -1929,8 +1929,8 @@ int launch_verify_xcd(hawk_ctx* c, int k, const int32_t* tree_depth, const unsig
                         : reinterpret_cast<const void*>(verify_xcd_stream_kernel<6, 2, 12, 2, 43, 4, 2, 128>);
     } else {
         p.lm_rounds = 2;
-        kern = RPJ == 2 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 2, false>)
-             : p.MR > 8 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 1, false>)
+        if (RPJ != 1) return -1;   // (an XCD's two heads at most times 16 rows: never more jobs than its units)
+        kern = p.MR > 8 ? reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 1, false>)
                         : reinterpret_cast<const void*>(verify_xcd_kernel<2, 3, 1, 4, 2, 3, 1, 8, 4, 1, true>);
     }
     // the parameter block and the attention job table of this step shape: uploaded when they change
