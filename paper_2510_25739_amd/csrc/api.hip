@@ -146,9 +146,11 @@ bool derive(const hawk_config* g, hawk_ctx* c) {
     o.n = take(B * 4); o.k_eff = take(B * 4); o.step = take(4); o.done = take(4); o.counters = take(4 * 8);
     o.grid = take(B * c->Nmax * 4); o.draft = take(B * ks * 4); o.forced = take(B * ks * 4 + B * 4);
     o.hprev = take(S * d * a); o.qstat = take(B * ks * sizeof(WarpStat)); o.pstat = take(B * ks * sizeof(WarpStat));
-    o.x = take(M * d * a); o.a = take(M * d * a); o.qkv = take(M * 3 * d * a); o.o = take(M * d * a);
-    o.u = take(M * 2 * m * a); o.din = take(S * 3 * d * a); o.g0 = take(S * d * a); o.g1 = take(S * d * a);
-    o.ga = take(S * d * a);
+    // fp32 contexts have norms, gate and the draft head's gather inside their products: a, din and ga are not there, u is half
+    const size_t apart = g->dtype == HAWK_BF16 ? 1 : 0;
+    o.x = take(M * d * a); o.a = take(apart * M * d * a); o.qkv = take(M * 3 * d * a); o.o = take(M * d * a);
+    o.u = take(M * (1 + apart) * m * a); o.din = take(apart * S * 3 * d * a); o.g0 = take(S * d * a); o.g1 = take(S * d * a);
+    o.ga = take(apart * S * d * a);
     o.logit_s = take(S * ks * Vs * 4); o.logit_b = take(B * ks * Vs * 4);
     o.dlogit_s = take(S * Vs * 4); o.dlogit_b = take(B * ks * Vs * 4);
     o.u_draft = take(B * ks * 4); o.u_acc = take(B * ks * 4); o.u_fin = take(B * 4);

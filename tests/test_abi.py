@@ -46,6 +46,17 @@ def test_workspace_bytes_and_bad_configs(H):
         assert H.workspace_bytes(cfg) == 0, field
 
 
+def test_fp32_workspace_holds_what_its_kernels_use(H):
+    # per condition row: keys and values, the vector itself, its place in the rotary table, and in fp64 the residual stream,
+    # the projections, the attention's output and the gated hidden features - no normalised rows, no W1|W3 outputs
+    s = synth.CONFIGS[0].replace(n_cond=64)
+    more = s.replace(n_cond=64 + 4096)
+    d, m = s.d_model, s.d_mlp
+    row = 2 * s.n_layers * d * 8 + d * 4 + s.head_dim // 2 * 16 + (d + 3 * d + d + m) * 8
+    n0, n1 = (H.workspace_bytes(H.HawkConfig.from_shape(x)) for x in (s, more))
+    assert abs(n1 - n0 - 4096 * row) < 64 * 256, (n1 - n0) / 4096 - row
+
+
 def test_create_rejects_bad_arguments_without_touching_the_device(H):
     lib = H.load_library()
     cfg = H.HawkConfig.from_shape(synth.CONFIGS[0])
