@@ -191,7 +191,8 @@ int rows_fill_rope(hawk_ctx*);               // once per context; 0 = ok
 void rows_step_pass(hawk_ctx*, const RowMap&, int M);     // step or tree rows: embedding, layers, logits to logit_s
 void rows_prompt_pass(hawk_ctx*, const RowMap&, int M);   // condition rows; logits of each sequence's last one
 void rows_draft_pass(hawk_ctx*, int i, size_t off_prev, size_t off_out);   // micro-step i up to its logits
-extern "C" int hawk_rows_attn_waves(int sequences, int heads, int rows);      // the rule of a dispatch, for the tests
+extern "C" int hawk_rows_attn_waves(int sequences, int heads, int rows);      // rules of the dispatch, for the tests as well
+extern "C" int hawk_rows_kernel(int M, int N, int K);                        // entry of kRowsKernels for a tile-major product
 
 // ---- streaming path, implemented in stream.hip ----
 size_t stream_workspace(const hawk_ctx*, size_t base, StreamOffsets* out);  // extra workspace bytes

@@ -933,6 +933,13 @@ static int pick_kernel(const RowsGemm& g) {
     return best;
 }
 
+extern "C" int hawk_rows_kernel(int M, int N, int K) {
+    RowsGemm g;
+    memset(&g, 0, sizeof g);
+    g.M = M; g.N = N; g.K = K;
+    return pick_kernel(g);
+}
+
 // Row-major weights (the dual-direction heads, contexts without the tile-major copy) come as 64-byte pieces of 16 rows: a
 // round of 256 workgroups takes fixed + step microseconds per k-step, whether a unit holds one of them or two, and
 // kernels that draw the weights once for all rows win early.  Fitted to 45 products (K 768, 1280, 4096; 1 to 2048 rows;

@@ -91,9 +91,9 @@ SHAPES = [
     (512, 8, 1376, 32, 1.0, 63, 2),    # LDS-staged (16, 8) with a ragged last group
     (768, 12, 2048, 16, 2.0, 100, 2),  # LDS-staged (20, 12)
     (512, 8, 1376, 32, 1.0, 100, 2),   # LDS-staged (10, 8) for the MLP
-    (256, 4, 1376, 4, 1.0, 84, 5),     # (4, 3) two to a unit for W1|W3
+    (256, 4, 1376, 4, 1.0, 84, 5),     # (7, 3) for W1|W3
     (768, 12, 704, 2, 1.0, 56, 9),     # (3, 2) for QKV
-    (768, 12, 1376, 13, 1.0, 80, 5),   # (7, 3) for W2
+    (768, 12, 1376, 13, 1.0, 80, 5),   # (7, 3) for Wo and W2
     # step attention with more cached positions than its waves request at once: eight waves, then four (from 256
     # workgroups on), heads of 64 (three tiles of 16 a wave) and of 128 (two)
     (256, 4, 704, 1, 1.0, 400, 5),
@@ -107,6 +107,27 @@ SHAPES = [
 def test_many_row_passes_match_a_float64_forward(H, d, heads, mlp, batch, scale, n_cond, chunk):
     s = BASE.replace(d_model=d, n_heads=heads, d_mlp=mlp, batch=batch, cfg_scale=scale, n_cond=n_cond, grid_w=max(8, chunk))
     got, ref = hidden_pair(H, s, chunk)
+    prompt, step = relative(got[:, :n_cond], ref[:, :n_cond]), relative(got[:, n_cond:], ref[:, n_cond:])
+    print(f"rows {s.n_seq * n_cond} + {s.n_seq * chunk}: relative error prompt {prompt:.2e}, step {step:.2e}")
+    assert prompt < 1e-3 and step < 1e-3
+
+
+# With the shapes above: every product kernel with every epilogue that the B, XL and 7B widths take it with, up to 4100 rows
+# (asserted, with the library's own choice, in test_rows_dispatch.py).
+KERNEL_SHAPES = [
+    (768, 12, 352, 13, 1.0, 60, 37),   # (4, 3) two to a unit and (7, 3) for QKV; (3, 2), (4, 2), (6, 2) for Wo and W2
+    (128, 2, 704, 20, 1.0, 53, 40),    # (4, 3) for QKV, (4, 3) two to a unit and (4, 4) for W1|W3
+    (1024, 16, 704, 8, 1.0, 129, 9),   # (4, 1) for QKV, (2, 1) for W1|W3, (4, 3) two to a unit for Wo and W2
+    (1280, 20, 352, 32, 1.0, 103, 4),  # LDS-staged (10, 8) for Wo and W2
+    (512, 8, 352, 128, 1.0, 129, 1),   # LDS-staged (20, 12) for Wo and W2
+]
+
+
+@pytest.mark.parametrize("d,heads,mlp,batch,scale,n_cond,chunk", KERNEL_SHAPES)
+def test_every_product_kernel_and_epilogue(H, d, heads, mlp, batch, scale, n_cond, chunk):
+    # weights of deviation 0.8 / sqrt(d): scores of order one, which the bound rests on (see the next test)
+    s = BASE.replace(d_model=d, n_heads=heads, d_mlp=mlp, batch=batch, cfg_scale=scale, n_cond=n_cond, grid_w=max(8, chunk))
+    got, ref = hidden_pair(H, s, chunk, std=0.8 / d ** 0.5)
     prompt, step = relative(got[:, :n_cond], ref[:, :n_cond]), relative(got[:, n_cond:], ref[:, n_cond:])
     print(f"rows {s.n_seq * n_cond} + {s.n_seq * chunk}: relative error prompt {prompt:.2e}, step {step:.2e}")
     assert prompt < 1e-3 and step < 1e-3
