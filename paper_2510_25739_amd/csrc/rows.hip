@@ -153,12 +153,13 @@ __device__ __forceinline__ void gemm_epilogue(const RowsGemm& g, f32x4 v, int ro
 // rows; its KW waves split K and work alone - weight tiles and plane tiles straight into registers in operand
 // order, D k-steps of 32 in flight, no LDS and no barrier in the loop - and add their partial results
 // through LDS at the end, where each takes its share of the tiles through the epilogue.
-// A k-step draws SR + 2 CT kilobytes from L2 for SR CT tiles of 2 MFMAs, every byte fetched once per workgroup; the
-// tile is chosen per shape (pick_kernel).  Workgroups that share weights follow each other on one XCD, so that the second
-// finds them in its L2.  Bound by what a compute unit takes in: every shape draws 70 to 80 KB a microsecond and unit (the
-// slopes of the table beside pick_kernel), a unit alone as well as all of them, so the tile with the fewest bytes for a
-// unit's share of the output is the fastest; eight waves rather than four shorten what comes before and after (W1|W3 of 192
-// rows at the XL widths: two (4, 3) workgroups to a unit 17.2 us, (7, 3) of four waves 17.1 us, of eight 15.1 us).
+// A k-step draws SR + 2 CT kilobytes for SR CT tiles of 2 MFMAs, every byte fetched once per workgroup; the tile is chosen per
+// shape (pick_kernel).  Workgroups that share weights follow each other on one XCD, so that the second finds them in its L2.
+// Bound by the weights' way from memory: 64 groups of strips by 4 of rows take in 60 to 115 KB a microsecond and unit over a
+// k-step (79 with (7, 3) tiles, 2.8 TB/s of weights), 110 to 150 when the weights are in L2 already, and one workgroup alone
+// 130 to 240; so the tile with the fewest bytes for a unit's share of the output is the fastest.  Eight waves rather than four
+// shorten what comes before and after (W1|W3 of 192 rows at the XL widths: two (4, 3) workgroups to a unit 17.2 us, (7, 3) of
+// four waves 17.1 us, of eight 15.1 us).
 template <int SR, int CT, int D, int KW, bool PACKED, int MODE>
 __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
     constexpr int PW = KW * SR * CT > 128 ? KW / 2 : KW;   // waves whose partial results LDS holds at a time

@@ -56,7 +56,8 @@ constexpr int kThreads = (kCW + kNIO) * 64, kIOThreads = kNIO * 64;
 constexpr int kXcd = 8, kPer = kNWG / kXcd;      // workgroup i runs on XCD i % 8 (checked by every workgroup)
 constexpr unsigned kSpinLimit = 1u << 20;
 constexpr int kNIT = 4;                          // cache positions per lane group and register buffer
-constexpr int kPaceGap = 0, kPaceTiles = 6;   // weight requests go out six tiles per wave at a time (see issue_paced)
+constexpr int kPaceGap = 0, kPaceTiles = 6;   // weight requests go out six tiles per wave at a time (see issue_paced); XL shape 780 us a
+                                             //   launch, four at a time 802, eight 801, fourteen 836 (B shape 235, 236, 238, 237)
 constexpr int kRing = 2;                         // partial-sum areas and XCD buffers alternate between layers
 constexpr int kMaxJobs = 128;                    // flag words of one XCD and stage that others wait for (one per IO wave with a job)
 
@@ -1181,8 +1182,8 @@ __device__ __forceinline__ void compute_stage(const XP& p, const Ctx& c, const G
     // A compute unit answers its waves' memory requests in the order they were made: what the IO waves
     // ask for behind a batch of weight tiles waits until the batch has come in (with every unit asking
     // at once, ~0.15 us per KB and wave).  So every stage requests about a fifth of a layer, in small
-    // parts, here - where the unit's IO waves are between their first look at the partial sums and the
-    // look that finds them.
+    // parts, here: behind the stage's own stores, ahead of which the IO waves do not look (io_stage), and
+    // while the other XCDs' partial sums, which their first looks wait for, are still on the way.
     prefetch();
     if (KIND == X_LM) {   // further rounds of the output projection: same staged input
         for (int r = 1; r < p.lm_rounds; ++r) {
