@@ -8,7 +8,7 @@
 
 #include <new>
 
-#include "hawk_internal.h"
+#include "chain.h"
 
 #include <vector>
 
@@ -261,6 +261,10 @@ void run_step_rows(hawk_ctx* c, int k) {
 }
 
 void enqueue_draft(hawk_ctx* c, int k, const UniformSrc& us, const DraftMode& dm) {
+    if (chain_ok(c, k)) {   // one launch for all micro-steps
+        if (launch_draft_chain(c, k, samp_params(c), us, forced_src(c, k, dm)) != 0) c->launch_failed = 1;
+        return;
+    }
     launch_plan(c, k);
     for (int i = 1; i <= k; ++i) {
         const size_t g = (i & 1) ? c->off.g1 : c->off.g0;

@@ -31,16 +31,12 @@
 #include <algorithm>
 #include <vector>
 
-#include "hawk_internal.h"
+#include "chain.h"
+#include "exchange.h"
 
 namespace hawk {
 
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned long long u64;
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kCW = 4;                          // compute waves per workgroup
 constexpr int kNIO = 4;                         // IO waves per workgroup
@@ -96,23 +92,6 @@ struct SP {
 
 // ------------------------------------------------------------------------- device helpers
 
-// Exchange data is written once per launch, with stores that go through to memory, into a slot
-// that no cache has seen in this launch; after the barrier ordinary cached loads return it and
-// the 32 workgroups of an XCD share one L2 fill.
-__device__ __forceinline__ void st_u32(void* p, unsigned v) {
-    __hip_atomic_store(reinterpret_cast<unsigned*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_u64(void* p, unsigned lo, unsigned hi) {
-    __hip_atomic_store(reinterpret_cast<u64*>(p), (u64)lo | ((u64)hi << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_f32(float* p, float v) { st_u32(p, __float_as_uint(v)); }
-__device__ __forceinline__ void st_f32x2(float* p, float a, float b) { st_u64(p, __float_as_uint(a), __float_as_uint(b)); }
-__device__ __forceinline__ void st_f32x4(float* p, f32x4 v) {
-    st_f32x2(p, v[0], v[1]);
-    st_f32x2(p + 2, v[2], v[3]);
-}
-__device__ __forceinline__ void compiler_fence() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
-
 // Cross-row lane exchanges in the VALU (gfx950 lane swaps; a shuffle would go through the LDS
 // crossbar).  swap16(v, v) returns {rows 0,0,2,2 | rows 1,1,3,3} of v, swap32(v, v) returns
 // {lower half twice | upper half twice}: their sum is v[l] + v[l ^ 16] (resp. v[l ^ 32]) in every
@@ -139,28 +118,6 @@ __device__ __forceinline__ float lane_xor8(float v) {   // row_ror:8 - the other
 __device__ __forceinline__ float* slot(const SP& p, int l) { return p.arena + (u64)l * p.slot_floats; }
 __device__ __forceinline__ uint16_t* plane(const SP& p, int l, u64 off) {
     return reinterpret_cast<uint16_t*>(slot(p, l) + off);
-}
-
-__device__ __forceinline__ unsigned bf16_rne(float f) {
-    unsigned u = __float_as_uint(f);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ __forceinline__ float bf16_f32(unsigned b) { return __uint_as_float(b << 16); }
-
-// Writes four consecutive elements of a split vector: bf16 hi and lo halves, 8 bytes each.
-__device__ __forceinline__ void st_split4(uint16_t* hi, uint16_t* lo, f32x4 v) {
-    const unsigned h0 = bf16_rne(v[0]), h1 = bf16_rne(v[1]), h2 = bf16_rne(v[2]), h3 = bf16_rne(v[3]);
-    const unsigned l0 = bf16_rne(v[0] - bf16_f32(h0)), l1 = bf16_rne(v[1] - bf16_f32(h1));
-    const unsigned l2 = bf16_rne(v[2] - bf16_f32(h2)), l3 = bf16_rne(v[3] - bf16_f32(h3));
-    st_u64(hi, h0 | (h1 << 16), h2 | (h3 << 16));
-    st_u64(lo, l0 | (l1 << 16), l2 | (l3 << 16));
-}
-__device__ __forceinline__ void put_split(float4 v, uint16_t* hi, uint16_t* lo) {  // LDS destination
-    const unsigned h0 = bf16_rne(v.x), h1 = bf16_rne(v.y), h2 = bf16_rne(v.z), h3 = bf16_rne(v.w);
-    const unsigned l0 = bf16_rne(v.x - bf16_f32(h0)), l1 = bf16_rne(v.y - bf16_f32(h1));
-    const unsigned l2 = bf16_rne(v.z - bf16_f32(h2)), l3 = bf16_rne(v.w - bf16_f32(h3));
-    *reinterpret_cast<uint2*>(hi) = make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
-    *reinterpret_cast<uint2*>(lo) = make_uint2(l0 | (l1 << 16), l2 | (l3 << 16));
 }
 
 // Grid barrier.  Counters only ever grow (epochs continue across launches), so nothing is
@@ -1314,6 +1271,7 @@ struct StreamPlan {
     std::vector<uint32_t> desc;
     unsigned epoch;     // grid barriers completed by all launches so far
     unsigned launches;
+    unsigned chain_epoch;   // draft micro-steps of all chain launches so far
     bool err_word_ready;   // the error word (shared with the kernel laid out on the XCDs) has been cleared
 };
 
@@ -1437,6 +1395,7 @@ void build_plan(const hawk_ctx* c, StreamPlan* P) {
 }
 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+size_t up64(size_t x) { return (x + 63) & ~(size_t)63; }
 
 // Regions of an exchange slot, in floats: split planes are uint16 [16][K + 8] (hi, lo), sums of
 // squares [d / 16][16], queries [16][d], attention chunk partials.  Returns the slot size.
@@ -1474,6 +1433,8 @@ size_t stream_workspace(const hawk_ctx* c, size_t base, StreamOffsets* o) {
     o->slot_bytes = up256(slot_layout(c, nullptr) * 4);
     o->arena = take(o->slot_bytes * (L + 1) * kRing);
     o->bar = take((size_t)(kGroups + 1 + kReplicas) * 4096);
+    o->chain = take(kChainBarBytes);
+    o->left = take(chain_entries(c->Vs) ? (size_t)c->Vs * d * 4 : 0);
     o->err = take(256);
     o->dbg = take((4 * 4096 * 8 + 2 * 256 * kNWG) * 8);
     o->rope = take((size_t)c->Tmax * (c->hd / 2) * 8);
@@ -1485,6 +1446,7 @@ StreamPlan* stream_create(hawk_ctx* c) {
     build_plan(c, P);
     P->epoch = 0;
     P->launches = 0;
+    P->chain_epoch = 0;
     P->err_word_ready = false;
     if (!P->ok) return P;
     {   // the grid barrier needs all kNWG workgroups resident at once: one per compute unit
@@ -1515,6 +1477,7 @@ StreamPlan* stream_create(hawk_ctx* c) {
     up(o.tab, P->tab.data(), P->tab.size() * 4);
     up(o.desc, P->desc.data(), P->desc.size() * 4);
     fill(o.bar, 0, (size_t)(kGroups + 1 + kReplicas) * 4096);
+    fill(o.chain, 0, kChainBarBytes);
     // every word of the exchange arenas starts as the "not written yet" pattern the W2 stage polls for
     fill(o.arena, 0xFF, o.slot_bytes * (size_t)(c->L + 1) * kRing);
     fill(o.err, 0, 256);
@@ -1608,6 +1571,13 @@ bool stream_ok(const hawk_ctx* c, int k) {
     return stream_lds_bytes(c, MR) <= 150 * 1024;
 }
 
+// Does the draft chain take the slice?
+static bool chain_shape_ok(const hawk_ctx* c) {
+    const KindPlan &lm = c->plan->kind[K_LM], &wd = c->plan->kind[K_WD];
+    const int per_unit = ((lm.nstrips + lm.rounds - 1) / lm.rounds + kNWG - 1) / kNWG;   // strips of a workgroup in one round
+    return chain_entries(c->Vs) && lm.rounds <= 2 && lm.rounds * per_unit <= 4 && wd.rounds == 1 && wd.nstrips <= kNWG - 16;
+}
+
 // Re-tiles every matrix of the loaded blob into the streaming order (after hawk_load).
 int stream_repack(hawk_ctx* c) {
     StreamPlan* P = c->plan;
@@ -1629,6 +1599,9 @@ int stream_repack(hawk_ctx* c) {
     }
     run(c->w.W_out, c->d, K_LM, P->lm_base, c->cfg.samp_lo);
     run(c->w.W_d, 3 * c->d, K_WD, P->wd_base, c->d);
+    if (chain_shape_ok(c))
+        launch_left_table(c->stream, c->d, wp + P->wd_base * 64, wsp<int32_t>(c, c->soff.tab) + P->kind[K_WD].tab_index,
+                          blob + c->w.E / 2 + (size_t)c->cfg.samp_lo * c->d, wsp<float>(c, c->soff.left), c->Vs);
     if (hipGetLastError() != hipSuccess) return -1;
     return hipStreamSynchronize(c->stream) == hipSuccess ? 0 : -1;
 }
@@ -1754,6 +1727,48 @@ int launch_draft_stream(hawk_ctx* c, int i, size_t off_prev, size_t off_out) {
                                     : (pairs ? reinterpret_cast<const void*>(draft_stream_kernel<6, 3, 6, true>)
                                              : reinterpret_cast<const void*>(draft_stream_kernel<6, 3, 6, false>));
     return launch_persistent(c, kern, p, 1u);
+}
+
+// The draft chain in one launch: micro-steps whose partial products have places of their own in the exchange slots.
+static int chain_per_slot(const hawk_ctx* c) { return (int)((size_t)kNWG * 8 * kPS / up64((size_t)2 * c->S * c->d)); }
+
+// Can the k micro-steps of a step run as one launch?  Slices that one workgroup draws from and whose strips fit four to a
+// workgroup (both end at 16384 entries), and no more micro-steps than there are places for partial products.
+bool chain_ok(const hawk_ctx* c, int k) {
+    return k >= 1 && stream_draft_ok(c) && chain_shape_ok(c) && k <= chain_per_slot(c) * (c->L + 1);
+}
+
+// Enqueues the step's plan (drafts in flight, counters) and its k draft micro-steps, draws included.
+int launch_draft_chain(hawk_ctx* c, int k, const SampParams& sp, const UniformSrc& us, const ForcedSrc& fs) {
+    StreamPlan* P = c->plan;
+    const StreamOffsets& o = c->soff;
+    SP s;
+    fill_params(c, s, c->S);
+    ChainP p;
+    memset(&p, 0, sizeof p);
+    p.wpack = s.wpack; p.lm_base = s.lm_base; p.wd_base = s.wd_base;
+    p.tab_lm = s.tab[K_LM]; p.tab_wd = s.tab[K_WD]; p.lm_rounds = s.rounds[K_LM];
+    p.blob = s.blob; p.E_off = c->w.E; p.gf_off = c->w.g_f;
+    p.part = s.arena + s.o_p; p.slot_floats = s.slot_floats;
+    p.per_slot = chain_per_slot(c); p.part_floats = up64((size_t)2 * c->S * c->d);
+    p.left = wsp<float>(c, o.left);
+    p.hprev = wsp<float>(c, c->off.hprev);
+    p.grid = wsp<int32_t>(c, c->off.grid); p.n = s.n;
+    p.k_eff = wsp<int32_t>(c, c->off.k_eff); p.draft = wsp<int32_t>(c, c->off.draft); p.step = wsp<int32_t>(c, c->off.step);
+    p.counters = wsp<unsigned long long>(c, c->off.counters);
+    p.logit_s = wsp<float>(c, c->off.dlogit_s); p.dlogit_b = wsp<float>(c, c->off.dlogit_b);
+    p.qstat = wsp<WarpStat>(c, c->off.qstat);
+    p.bar = wsp<unsigned>(c, o.chain); p.err = s.err; p.epoch0 = P->chain_epoch;
+    p.S = c->S; p.B = c->B; p.N = c->N; p.IW = c->gw; p.k = k; p.eps = c->cfg.rms_eps;
+    p.sp = sp; p.us = us; p.fs = fs; p.us_draft = us.draft; p.fs_table = fs.table;
+    const void* kern = chain_kernel(c->d, c->Vs);
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess) return -1;
+    void* args[] = {&p};
+    // as launch_persistent: the grid is the number of compute units, and two workgroups do not fit one
+    if (hipLaunchKernel(kern, dim3(kNWG), dim3(kSampThreads), args, chain_lds_bytes(c->S, c->d), c->stream) != hipSuccess) return -1;
+    P->chain_epoch += (unsigned)k;
+    P->launches += 1;
+    return 0;
 }
 
 // The persistent kernels' error word exists and has been cleared (its region is part of the workspace
