@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 
 #include "chain.h"
@@ -911,21 +912,24 @@ int hawk_generate(hawk_ctx* c, const float* cond, const float* uncond, int batch
     rc = enqueue_prefill(c, cond, uncond, batch, n_cond, grid_h, grid_w, temperature, top_k, cfg_scale, us);
     if (rc) return rc;
     HIP_TRY(c, hipEventRecord(c->ev[1], c->stream));
-    // Every iteration commits at least one token per unfinished prompt, so N-1 iterations
-    // always suffice; the committed counts are polled every few iterations to stop early.
+    // Every iteration commits at least one token per unfinished prompt, so N-1 iterations always suffice, and at most
+    // k + 1.  The committed counts are read to stop early, but not before the prompt that is furthest behind can have
+    // finished: a look leaves the queue empty for about 45 us, and an iteration that nobody needed takes longer still
+    // (0.1 ms on the fp32 shape, 0.38 on the B, 0.9 on the XL one).  Looking at every fourth iteration had a third more
+    // looks over an image and up to three iterations too many.
     int32_t* nb = static_cast<int32_t*>(c->pinned);
     const DraftMode dm = {replay_tokens ? 2 : 0, replay_tokens ? 1 : 0};
-    const int poll = 4;
-    bool done = N <= 1;
-    for (int it = 0; it < N - 1 && !done; ++it) {
+    int left = N - 1;   // tokens the last prompt is short of
+    for (int it = 0, look = 0; it < N - 1 && left > 0; ++it) {
+        if (it == look) look = it + (left + k) / (k + 1);
         enqueue_draft(c, k, us, dm);
         enqueue_verify(c, k, us);
-        if ((it + 1) % poll == 0 || it == N - 2) {
+        if (it + 1 == look || it == N - 2) {
             HIP_TRY(c, hipGetLastError());
             rc = download(c, nb, c->off.n, (size_t)batch * 4);
             if (rc) return rc;
-            done = true;
-            for (int b = 0; b < batch; ++b) done = done && nb[b] >= N;
+            left = 0;
+            for (int b = 0; b < batch; ++b) left = std::max(left, N - nb[b]);
         }
     }
     HIP_TRY(c, hipEventRecord(c->ev[2], c->stream));
