@@ -167,6 +167,11 @@ __host__ __device__ inline size_t plane_at(int row, int f, int kts) {
 }
 inline size_t plane_halves(int M, int K) { return (size_t)((M + 15) / 16) * 16 * K; }   // values of one plane
 enum { kGemmPlain = 0, kGemmResidual, kGemmSwiglu, kGemmHeads };
+// Tile-major weights that launches behind this one read, for workgroups past its own to bring into the L2s they are read from.
+struct Ahead {
+    struct { const uint16_t* W; int kb, groups, total_kb; } of[2];   // kilobytes of a strip group of that launch's tiles, strip groups, kilobytes in all
+    int n, grid, extra;                                             // matrices; workgroups of the launch, and those behind them (a multiple of 8)
+};
 struct RowsGemm {
     const uint16_t *hi, *lo;   // planes of A
     const uint16_t* W;         // tile-major copy (packed) or row-major [N][K]
@@ -184,7 +189,7 @@ struct RowsGemm {
     const float* resid;        // kGemmHeads: A as fp32 [M][K]
     int blocks;
 };
-void launch_rows_gemm(hipStream_t, const RowsGemm&);
+void launch_rows_gemm(hipStream_t, const RowsGemm&, const Ahead* = nullptr);   // ahead: tile-major weights, kGemmResidual only
 void launch_rows_split(hipStream_t, const float* A, int lda, int M, int K, uint16_t* hi, uint16_t* lo);
 bool rows_ok(const hawk_ctx*);               // does the context's shape take this path?
 int rows_fill_rope(hawk_ctx*);               // once per context; 0 = ok

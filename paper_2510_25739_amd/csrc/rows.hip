@@ -11,6 +11,8 @@
 // row's 1 / rms (a row's factor commutes with the product).
 #include <string.h>
 
+#include <algorithm>
+
 #include "hawk_internal.h"
 
 namespace hawk {
@@ -105,6 +107,28 @@ __device__ __forceinline__ float ssq_share(const RowsGemm& g, int row, int lane,
     return v;
 }
 
+// A workgroup past a launch's own: brings its share of what the next launches read into the L2 it will be read from.  Their
+// workgroup i runs on XCD i % 8 and so do strip group i % 8, + 8, .. of its weights; so do the workgroups here.
+// (Kernels have an instance without this: the parameters and the look at them cost 0.2 us a launch.)
+__device__ __forceinline__ void bring_ahead(const Ahead& a, int wave, int waves, int lane) {
+    const int x = blockIdx.x & 7, all = (a.extra >> 3) * waves, mine = (((int)blockIdx.x - a.grid) >> 3) * waves + wave;
+    for (int i = 0; i < a.n; ++i) {
+        const int kb = a.of[i].kb, share = max(0, (a.of[i].groups - x + 7) >> 3) * kb;
+        const rsrc_t r = bounded(a.of[i].W, (unsigned)a.of[i].total_kb * 1024u);
+        for (int u = mine; u < share; u += 8 * all) {
+            v4u v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int k = u + j * all, g = k / kb;
+                const unsigned at = k < share ? (unsigned)(((g << 3) + x) * kb + (k - g * kb)) * 1024u + (unsigned)lane * 16u : 0x80000000u;
+                v[j] = __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) asm volatile("" ::"v"(v[j]));
+        }
+    }
+}
+
 // What follows a product, for one result lane: features f .. f + 3 of a row (lane group kg of the strip).
 template <int MODE>
 __device__ __forceinline__ void gemm_epilogue(const RowsGemm& g, f32x4 v, int row, int f, bool strip_ok, int kg, float scale) {
@@ -161,7 +185,7 @@ __device__ __forceinline__ void gemm_epilogue(const RowsGemm& g, f32x4 v, int ro
 // shorten what comes before and after (W1|W3 of 192 rows at the XL widths: two (4, 3) workgroups to a unit 17.2 us, (7, 3) of
 // four waves 17.1 us, of eight 15.1 us).
 template <int SR, int CT, int D, int KW, bool PACKED, int MODE>
-__global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
+__device__ __forceinline__ void rows_gemm(const RowsGemm& g) {
     constexpr int PW = KW * SR * CT > 128 ? KW / 2 : KW;   // waves whose partial results LDS holds at a time
     __shared__ f32x4 part[PW][SR * CT][64];
     __shared__ float rscale[16 * CT];
@@ -274,6 +298,14 @@ __global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) {
         for (int w = 1; w < PW; ++w) v += part[w][q][lane];
         gemm_epilogue<MODE>(g, v, row, f, strip < strips, kg, rscale[t * 16 + r16]);
     }
+}
+
+template <int SR, int CT, int D, int KW, bool PACKED, int MODE>
+__global__ __launch_bounds__(64 * KW) void rows_gemm_kernel(RowsGemm g) { rows_gemm<SR, CT, D, KW, PACKED, MODE>(g); }
+template <int SR, int CT, int D, int KW, int MODE>
+__global__ __launch_bounds__(64 * KW) void rows_gemm_ahead_kernel(RowsGemm g, Ahead a) {
+    if ((int)blockIdx.x >= a.grid) bring_ahead(a, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), KW, threadIdx.x & 63);
+    else rows_gemm<SR, CT, D, KW, true, MODE>(g);
 }
 
 // The same product where the rows are many enough to be a contraction (the prompt pass): a workgroup of WN x WM
@@ -729,14 +761,25 @@ __global__ __launch_bounds__(256) void attn_prompt_kernel(AttnArgs a) {
 // four waves and 1495 with eight.  Below that eight are 10 % of a pass ahead at 4000 cached positions, four 1 to 4 % at up to 500.
 // The query is asked for ahead of the cached tiles, so that its rotation does not wait for them, and sums over the lanes
 // go by lane swaps, not through LDS (13.2 -> 12.0 us there, three sequences of 20 heads on eight waves 8.6 -> 7.9).
-template <int HD, int NWV>
-__global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a) {
+struct Nothing {};
+// W: Ahead, or Nothing and a grid of sequences x heads x row tiles.
+template <int HD, int NWV, class W>
+__global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a, W ahead) {
     constexpr int VST = HD + 16, T = HD == 64 ? 3 : 2, CH = HD / 32;   // CH: 16-byte chunks per lane of a value tile
     __shared__ __attribute__((aligned(16))) _Float16 vbuf[NWV][16 * VST];
     __shared__ float om[NWV][16][HD + 4], ml[NWV][2][16];
     __shared__ int cleared[NWV];
-    const int s = blockIdx.x, h = blockIdx.y, rt = blockIdx.z, R = a.map.rows_per_seq;
+    int s = blockIdx.x, h = blockIdx.y, rt = blockIdx.z;
+    const int R = a.map.rows_per_seq;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, r16 = lane & 15, kg = lane >> 4;
+    if constexpr (sizeof(W) == sizeof(Ahead)) {
+        if ((int)blockIdx.x >= ahead.grid) {
+            bring_ahead(ahead, wave, NWV, lane);
+            return;
+        }
+        const int rest = blockIdx.x / a.map.n_seq;
+        s = (int)blockIdx.x - rest * a.map.n_seq; rt = rest / a.H; h = rest - rt * a.H;
+    }
     const int b = s % a.map.batch, ke = a.map.k_eff[b];
     const int R0 = s * R, row = rt * 16 + r16;
     if (ke < rt * 16) {   // no row of this tile is in flight: defined planes, nothing else reads them
@@ -974,23 +1017,29 @@ template <int WN, int WM, int SR, int CT, int S, bool PACKED, int MODE> static v
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     k<<<(total + 7) / 8 * 8, 64 * WN * WM, lds, stream>>>(g);
 }
-template <int SR, int CT, int D, int KW, bool PACKED, int MODE> static void launch_direct(hipStream_t stream, const RowsGemm& g) {
+template <int SR, int CT, int D, int KW, bool PACKED, int MODE> static void launch_direct(hipStream_t stream, const RowsGemm& g, const Ahead* ahead = nullptr) {
     const int strips = g.N / 16, tiles = (g.M + 15) / 16;
-    rows_gemm_kernel<SR, CT, D, KW, PACKED, MODE><<<((strips + SR - 1) / SR + 7) / 8 * 8 * ((tiles + CT - 1) / CT), 64 * KW, 0, stream>>>(g);
+    const int grid = ((strips + SR - 1) / SR + 7) / 8 * 8 * ((tiles + CT - 1) / CT);
+    if constexpr (PACKED && MODE == kGemmResidual)
+        if (ahead) {
+            rows_gemm_ahead_kernel<SR, CT, D, KW, MODE><<<grid + ahead->extra, 64 * KW, 0, stream>>>(g, *ahead);
+            return;
+        }
+    rows_gemm_kernel<SR, CT, D, KW, PACKED, MODE><<<grid, 64 * KW, 0, stream>>>(g);
 }
-template <int MODE> static void launch_packed(hipStream_t stream, const RowsGemm& g) {
+template <int MODE> static void launch_packed(hipStream_t stream, const RowsGemm& g, const Ahead* ahead) {
     switch (pick_kernel(g)) {
-        case 0: return launch_direct<1, 1, 8, 4, true, MODE>(stream, g);
-        case 1: return launch_direct<2, 1, 5, 8, true, MODE>(stream, g);
-        case 2: return launch_direct<4, 1, 4, 8, true, MODE>(stream, g);
-        case 3: return launch_direct<2, 2, 6, 4, true, MODE>(stream, g);
-        case 4: return launch_direct<3, 2, 6, 4, true, MODE>(stream, g);
-        case 5: return launch_direct<4, 2, 3, 8, true, MODE>(stream, g);
-        case 6: return launch_direct<6, 2, 4, 4, true, MODE>(stream, g);
-        case 7: return launch_direct<4, 3, 2, 8, true, MODE>(stream, g);
-        case 8: return launch_direct<4, 3, 3, 4, true, MODE>(stream, g);
-        case 9: return launch_direct<4, 4, 2, 8, true, MODE>(stream, g);
-        case 10: return launch_direct<7, 3, 2, 8, true, MODE>(stream, g);
+        case 0: return launch_direct<1, 1, 8, 4, true, MODE>(stream, g, ahead);
+        case 1: return launch_direct<2, 1, 5, 8, true, MODE>(stream, g, ahead);
+        case 2: return launch_direct<4, 1, 4, 8, true, MODE>(stream, g, ahead);
+        case 3: return launch_direct<2, 2, 6, 4, true, MODE>(stream, g, ahead);
+        case 4: return launch_direct<3, 2, 6, 4, true, MODE>(stream, g, ahead);
+        case 5: return launch_direct<4, 2, 3, 8, true, MODE>(stream, g, ahead);
+        case 6: return launch_direct<6, 2, 4, 4, true, MODE>(stream, g, ahead);
+        case 7: return launch_direct<4, 3, 2, 8, true, MODE>(stream, g, ahead);
+        case 8: return launch_direct<4, 3, 3, 4, true, MODE>(stream, g, ahead);
+        case 9: return launch_direct<4, 4, 2, 8, true, MODE>(stream, g, ahead);
+        case 10: return launch_direct<7, 3, 2, 8, true, MODE>(stream, g, ahead);
         case 11: return launch_staged<2, 4, 4, 2, 4, true, MODE>(stream, g);
         case 12: return launch_staged<2, 4, 5, 2, 4, true, MODE>(stream, g);
         case 13: return launch_staged<4, 2, 4, 4, 4, true, MODE>(stream, g);
@@ -1014,12 +1063,12 @@ template <int MODE> static void launch_row_major(hipStream_t stream, const RowsG
 // Waves of a step attention workgroup: see the kernel.
 extern "C" int hawk_rows_attn_waves(int sequences, int heads, int rows) { return sequences * heads * ((rows + 15) / 16) >= 256 ? 4 : 8; }
 
-void launch_rows_gemm(hipStream_t stream, const RowsGemm& g) {
+void launch_rows_gemm(hipStream_t stream, const RowsGemm& g, const Ahead* ahead) {
     if (g.packed) {
         switch (g.mode) {
-            case kGemmPlain: launch_packed<kGemmPlain>(stream, g); return;
-            case kGemmResidual: launch_packed<kGemmResidual>(stream, g); return;
-            default: launch_packed<kGemmSwiglu>(stream, g); return;
+            case kGemmPlain: launch_packed<kGemmPlain>(stream, g, nullptr); return;
+            case kGemmResidual: launch_packed<kGemmResidual>(stream, g, ahead); return;
+            default: launch_packed<kGemmSwiglu>(stream, g, nullptr); return;
         }
     }
     if (g.mode == kGemmHeads) launch_row_major<kGemmHeads>(stream, g);
@@ -1093,6 +1142,45 @@ static void rows_output_layer(hawk_ctx* c, int M, int partials, size_t off_x, si
     launch_rows_gemm(c->stream, g);
 }
 
+// Units a launch leaves idle bring the weights of a launch behind it into the L2s they will be read from (bring_ahead): an
+// attention launch those of Wo and W1|W3, which it has time for, Wo's those of W2, W2's those of the next QKV.  A launch of
+// few rows starts with its first weights a memory latency away and ends before the memory system is at its rate; from L2
+// QKV of 18 rows at the XL widths takes 5.4 us instead of 6.6, Wo and W2 12.7 instead of 15.2, W1|W3 7.6 instead of 9.2 and
+// the attention, with the transfer beside it, 9.4 instead of 8.2 (images of three prompts 126.4 -> 116.9 ms); 192 rows, where
+// only the attention has units to spare, W1|W3 13.1 instead of 15.0 and the attention 15.2 instead of 14.1 (211.2 -> 206.5 ms).
+// Not where a workgroup would have more to bring than the launch lasts (16 units for W2 of 192 rows 222 -> 246 ms, for QKV 240),
+// nor for weights that do not fit; nor where all layers' weights stay in the last-level cache (B shape, 170 MB) and the rows
+// are few: 24 rows 19.4 -> 19.7 ms an image, while 96 rows gain, 26.6 -> 26.1; nor for prompt rows (B shape, 91 rows: 475 -> 482 us,
+// XL shape, 80 rows: the same).
+constexpr int kL2Kb = 24 * 1024;   // of 32 MB: the rows' own data has the rest
+static Ahead plan_ahead(hawk_ctx* c, int M, int grid, int idle, int kb_each, const int* packs, int n) {
+    Ahead a;
+    memset(&a, 0, sizeof a);
+    a.grid = grid;
+    a.extra = std::max(idle, 0) / 8 * 8;
+    int kb = 0;
+    for (int i = 0; i < n; ++i) {
+        RowsGemm g;
+        memset(&g, 0, sizeof g);
+        g.M = M; g.N = c->gpk[packs[i]].N; g.K = c->gpk[packs[i]].K;
+        const RowsKernel& t = kRowsKernels[pick_kernel(g)];
+        kb += g.N / 16 * (g.K / 32);
+        if (t.staged || kb > kL2Kb || kb > a.extra * kb_each) break;   // (the staged kernels take strips in another order)
+        a.of[a.n].kb = t.SR * (g.K / 32); a.of[a.n].groups = (g.N / 16 + t.SR - 1) / t.SR; a.of[a.n].total_kb = g.N / 16 * (g.K / 32);
+        a.n += 1;
+    }
+    return a;
+}
+// ... beside the product with matrix `pack`
+static Ahead product_ahead(hawk_ctx* c, int M, int pack, int next) {
+    RowsGemm g;
+    memset(&g, 0, sizeof g);
+    g.M = M; g.N = c->gpk[pack].N; g.K = c->gpk[pack].K;
+    const RowsKernel& t = kRowsKernels[pick_kernel(g)];
+    const int grid = ((g.N / 16 + t.SR - 1) / t.SR + 7) / 8 * 8 * (((M + 15) / 16 + t.CT - 1) / t.CT);
+    return plan_ahead(c, M, grid, t.staged ? 0 : kNWG - grid, 128, &next, 1);
+}
+
 // All decoder layers over M rows (mode 0: condition rows, 1: step rows, 2: tree rows), from their embedding or
 // condition vectors; leaves x and, for the output layer, the planes of x * g_f with the sums of squares.
 static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
@@ -1105,6 +1193,16 @@ static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
     else
         rows_embed_kernel<<<M, 256, 0, c->stream>>>(x, blob16(c, c->w.E), map, wsp<int32_t>(c, c->off.grid), wsp<int32_t>(c, c->off.draft),
                                                     c->N, c->kmax + 1, d, blob16(c, c->w.g1[0]), pa.hi, pa.lo, ssq, ssq_ld(c));
+    const int R = map.rows_per_seq, nw = hawk_rows_attn_waves(c->S, c->H, R), attn_grid = c->S * c->H * ((R + 15) / 16), packs[2] = {1, 2};
+    const bool step = map.mode != 0 && (c->hd == 64 || c->hd == 128), bring = step && (M >= 64 || c->L * (4.0 * d + 3.0 * m) * d * 2 > 256e6);
+    // eight waves fill a unit; of four three workgroups fit, two with heads of 128
+    const int idle = bring ? std::min(kNWG * (nw == 8 ? 1 : c->hd == 64 ? 3 : 2) - attn_grid, 192) : 0;
+    Ahead attn = plan_ahead(c, M, attn_grid, idle, 192, packs, 2), after_o = attn, after_2 = attn;
+    after_o.n = after_2.n = 0;
+    if (bring) {
+        after_o = product_ahead(c, M, 1, 3);
+        after_2 = product_ahead(c, M, 3, 0);
+    }
     for (int l = 0; l < c->L; ++l) {
         RowsGemm g = product(c, pa, M, d, 4 * l, kGemmPlain);
         scaled_by_rms(c, g, l == 0 ? 1 : d / 16);
@@ -1115,7 +1213,6 @@ static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
         const size_t layer = (size_t)l * c->Smax * c->Tmax * d;
         a.qkv = wsp<float>(c, c->off.qkv); a.Kc = wsp<_Float16>(c, c->off.kc) + layer; a.Vc = wsp<_Float16>(c, c->off.vc) + layer;
         a.rope = wsp<float2>(c, c->off.rtab); a.map = map; a.d = d; a.H = c->H; a.Tmax = c->Tmax; a.hi = po.hi; a.lo = po.lo;
-        const int R = map.rows_per_seq;
         if (c->hd != 64 && c->hd != 128) {   // heads that the kernels above have no tiles for
             launch_rope_append(c, map, l, M);
             launch_attention(c, map, l, M);
@@ -1124,16 +1221,23 @@ static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
             auto k = c->hd == 64 ? attn_prompt_kernel<64> : attn_prompt_kernel<128>;
             k<<<dim3((R + 63) / 64, c->H, c->S), 256, 0, c->stream>>>(a);
         } else {
-            const int nw = hawk_rows_attn_waves(c->S, c->H, R);
-            auto k = c->hd == 64 ? (nw == 4 ? attn_step_kernel<64, 4> : attn_step_kernel<64, 8>)
-                                 : (nw == 4 ? attn_step_kernel<128, 4> : attn_step_kernel<128, 8>);
-            k<<<dim3(c->S, c->H, (R + 15) / 16), 64 * nw, 0, c->stream>>>(a);
+            if (attn.n) {
+                for (int i = 0; i < attn.n; ++i) attn.of[i].W = packed_weights(c, 4 * l + packs[i]);
+                auto k = c->hd == 64 ? (nw == 4 ? attn_step_kernel<64, 4, Ahead> : attn_step_kernel<64, 8, Ahead>)
+                                     : (nw == 4 ? attn_step_kernel<128, 4, Ahead> : attn_step_kernel<128, 8, Ahead>);
+                k<<<attn.grid + attn.extra, 64 * nw, 0, c->stream>>>(a, attn);
+            } else {
+                auto k = c->hd == 64 ? (nw == 4 ? attn_step_kernel<64, 4, Nothing> : attn_step_kernel<64, 8, Nothing>)
+                                     : (nw == 4 ? attn_step_kernel<128, 4, Nothing> : attn_step_kernel<128, 8, Nothing>);
+                k<<<dim3(c->S, c->H, (R + 15) / 16), 64 * nw, 0, c->stream>>>(a, Nothing());
+            }
         }
 
         g = product(c, po, M, d, 4 * l + 1, kGemmResidual);
         g.Y = x; g.ldy = d; g.ohi = pa.hi; g.olo = pa.lo; g.okts = d / 32; g.gain = blob16(c, c->w.g2[l]);
         g.ossq = ssq; g.ossq_ld = ssq_ld(c);
-        launch_rows_gemm(c->stream, g);
+        after_o.of[0].W = packed_weights(c, 4 * l + 3);
+        launch_rows_gemm(c->stream, g, after_o.n ? &after_o : nullptr);
 
         g = product(c, pa, M, d, 4 * l + 2, kGemmSwiglu);
         scaled_by_rms(c, g, d / 16);
@@ -1144,7 +1248,9 @@ static void rows_layers(hawk_ctx* c, const RowMap& map, int M) {
         g.Y = x; g.ldy = d; g.ohi = pa.hi; g.olo = pa.lo; g.okts = d / 32;
         g.gain = blob16(c, l + 1 < c->L ? c->w.g1[l + 1] : c->w.g_f);
         g.ossq = ssq; g.ossq_ld = ssq_ld(c);
-        launch_rows_gemm(c->stream, g);
+        const bool more = l + 1 < c->L;
+        after_2.of[0].W = packed_weights(c, more ? 4 * l + 4 : 0);
+        launch_rows_gemm(c->stream, g, more && after_2.n ? &after_2 : nullptr);
     }
 }
 
