@@ -418,6 +418,116 @@ __global__ __launch_bounds__(64 * WN * WM) void rows_gemm_staged_kernel(RowsGemm
         }
 }
 
+// The same with tile-major weights that go straight into registers, two k-steps ahead (three sets: the compiler waits for a
+// set as if no plane tiles were in flight behind it, so for what was requested up to a k-step before), and only the planes
+// through LDS, three stages deep.  Of a k-step of a 20 x 12 tile 24 KB are written to LDS and 96 KB read instead of 44 and 136,
+// 1.0 us of LDS time beside 0.9 us of MFMA time at 1.95 GHz; and tiles that LDS has no stages for become possible, such as 18 x 12 on twelve
+// waves (three to a SIMD cover each other's barriers) and 16 x 16.  3840 rows at the XL widths: W1|W3 148.4 us staged (20, 12),
+// 140.1 this way, 129.8 with (18, 12), whose rounds are full; QKV 74.7 and 71.6.  Weight tiles that several waves share come
+// from L1; the smaller (8, 8) and (10, 8) tiles stay staged, where a wave's weights would be most of its requests (Wo of 3200
+// rows 30.2 and 30.7 us).
+template <int WN, int WM, int SR, int CT, int MODE>
+__global__ __launch_bounds__(64 * WN * WM) void rows_gemm_wide_kernel(RowsGemm g) {
+    constexpr int S = 3, NWV = WN * WM, BS = WN * SR, BT = WM * CT, NTL = 2 * BT, LPW = (NTL + NWV - 1) / NWV;
+    extern __shared__ __attribute__((aligned(1024))) uint16_t stage[];   // [S][NTL][512]
+    __shared__ float rscale[16 * BT];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int r16 = lane & 15, kg = lane >> 4, wn = wave / WM, wm = wave - wn * WM;
+    const int strips = g.N / 16, tiles = (g.M + 15) / 16, nk = g.K / 32;
+    const int sg = (strips + BS - 1) / BS, total = sg * ((tiles + BT - 1) / BT);
+    const int per = (total + 7) / 8, id = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || id >= total) return;
+    const int s_first = (id % sg) * BS, t_first = (id / sg) * BT;
+    const uint16_t* src[LPW];
+    int slot[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        int q = wave + i * NWV;
+        if (q >= NTL) q -= NTL;   // (past the end: the first ones again, same bytes)
+        const int tile = min(t_first + (q < BT ? q : q - BT), tiles - 1);
+        slot[i] = q * 512;
+        src[i] = (q < BT ? g.hi : g.lo) + (size_t)tile * nk * 512 + lane * 8;
+    }
+    auto request = [&](int k) {   // k-steps past the end: the last one again, into a stage nobody reads any more
+        const int kc = min(k, nk - 1), buf = (k % S) * NTL * 512;
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) tile_to_lds(src[i] + (size_t)kc * 512, stage + buf + slot[i]);
+    };
+    const rsrc_t rw = bounded(g.W, (unsigned)strips * (unsigned)nk * 1024u);
+    unsigned first[SR];
+#pragma unroll
+    for (int s = 0; s < SR; ++s) first[s] = (unsigned)min(s_first + wn * SR + s, strips - 1) * (unsigned)nk * 1024u;
+    auto load = [&](int k, v4u (&w)[SR]) {
+        const unsigned at = (unsigned)min(k, nk - 1) * 1024u;
+#pragma unroll
+        for (int s = 0; s < SR; ++s) w[s] = __builtin_amdgcn_raw_buffer_load_b128(rw, (unsigned)lane * 16u, first[s] + at, 0);
+    };
+    if (g.ssq_n > 0) {
+        constexpr int RPW = 16 * BT / NWV;
+        f32x4 sq[RPW];
+#pragma unroll
+        for (int i = 0; i < RPW; ++i)
+            sq[i] = *reinterpret_cast<const f32x4*>(g.ssq + (size_t)min(t_first * 16 + wave * RPW + i, g.M - 1) * g.ssq_ld + min(lane * 4, g.ssq_ld - 4));
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            const float v = wave_total(ssq_share(g, min(t_first * 16 + wave * RPW + i, g.M - 1), lane, sq[i]));
+            if (lane == 0) rscale[wave * RPW + i] = 1.0f / sqrtf(v / g.norm_d + g.eps);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // written before the first barrier below, the only one where K is 32
+    }
+    v4u w[3][SR];
+    load(0, w[0]);
+    request(0);
+    load(1, w[1]);
+    request(1);
+    f32x4 acc[SR][CT];
+#pragma unroll
+    for (int s = 0; s < SR; ++s)
+#pragma unroll
+        for (int t = 0; t < CT; ++t) acc[s][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto step = [&](int k, int j) {   // j = k % 3
+        // own requests of k-step k are done when at most those of the next one are outstanding
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(SR + LPW) : "memory");
+        load(k + 2, w[(j + 2) % 3]);
+        request(k + 2);
+        const uint16_t* sh = stage + j * NTL * 512 + wm * CT * 512 + lane * 8;
+        const uint16_t* sl = sh + BT * 512;
+        bf16x8 h[2], l[2];
+        h[0] = *reinterpret_cast<const bf16x8*>(sh);
+        l[0] = *reinterpret_cast<const bf16x8*>(sl);
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {   // the next row tile's planes are on their way while this one's are multiplied
+            if (t + 1 < CT) {
+                h[(t + 1) & 1] = *reinterpret_cast<const bf16x8*>(sh + (t + 1) * 512);
+                l[(t + 1) & 1] = *reinterpret_cast<const bf16x8*>(sl + (t + 1) * 512);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int s = 0; s < SR; ++s) acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j][s]), h[t & 1], acc[s][t], 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < SR; ++s) acc[s][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j][s]), l[t & 1], acc[s][t], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage's reads are done before the next barrier lets it be overwritten
+    };
+    int k = 0;
+    for (; k + 3 <= nk; k += 3) {
+        step(k, 0);
+        step(k + 1, 1);
+        step(k + 2, 2);
+    }
+    if (k < nk) step(k, 0);
+    if (k + 1 < nk) step(k + 1, 1);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < SR; ++s)
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+            const int strip = s_first + wn * SR + s, tr = wm * CT + t;
+            gemm_epilogue<MODE>(g, acc[s][t], (t_first + tr) * 16 + r16, strip * 16 + 4 * kg, strip < strips, kg, g.ssq_n > 0 ? rscale[tr * 16 + r16] : 1.f);
+        }
+}
+
 // ------------------------------------------------------------------------------------------ rows in
 
 // One row per workgroup: x (fp32), the planes of x * gain and the row's sum of squares (one partial sum).
@@ -956,14 +1066,17 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a, W ahead
 // 512 rows, weights from memory): the choice is 0.9 % behind the fastest on average.  Counting workgroups over the whole
 // chip, with a time per k-step alone, was 9.3 % behind: W1|W3 of 48 rows at the XL widths (2, 2) 14.5 us, (4, 2) 9.8 us, QKV
 // of 72 rows 13.3 and 9.1 us; 384 rows of W2 (4, 2) 26.0 us, since two XCDs had 36 workgroups, (4, 3) 17.6 us.
-// Beyond the fitted rows, 560 sizes up to 4112: 1.3 % behind on average, the largest gap Wo of 3000 rows at the B widths, (7, 3)
-// 26.8 us and the staged (8, 8) 20.4.
+// From 200 rows on the entries behind (10, 8) are fitted to 372 products of the same widths, 70 to 4100 rows: the choice is 1.1 %
+// behind the fastest of these kernels on average and 3.6 % ahead of the choice among the staged forms alone (5.3 % behind); it is
+// slower than that one for four sizes, by 5 % at most (W1|W3 of 1000 rows at the 7B widths, 330 us instead of 314).
 struct RowsKernel { int SR, CT; float fixed, step; int slots; bool staged; };
 static const RowsKernel kRowsKernels[] = {
     {1, 1, 0.9f, 0.038f, 32, false}, {2, 1, 1.5f, 0.049f, 32, false}, {4, 1, 1.8f, 0.09f, 32, false},   {2, 2, 1.2f, 0.080f, 32, false},
     {3, 2, 1.9f, 0.093f, 32, false}, {4, 2, 1.5f, 0.116f, 32, false}, {6, 2, 2.5f, 0.143f, 32, false},  {4, 3, 2.6f, 0.129f, 32, false},
     {4, 3, 3.9f, 0.243f, 64, false}, {4, 4, 3.3f, 0.146f, 32, false}, {7, 3, 3.9f, 0.179f, 32, false},  {8, 8, 7.5f, 0.398f, 32, true},
-    {10, 8, 7.9f, 0.481f, 32, true}, {16, 8, 10.2f, 0.65f, 32, true}, {20, 12, 15.9f, 1.101f, 32, true}};
+    {10, 8, 7.9f, 0.481f, 32, true}, {16, 8, 12.0f, 0.674f, 32, true}, {20, 12, 18.3f, 1.135f, 32, true},
+    // further tiles of the kernel of (20, 12) and, the last one, of (16, 8)
+    {16, 12, 16.6f, 0.927f, 32, true}, {18, 12, 15.9f, 0.987f, 32, true}, {16, 16, 21.3f, 1.19f, 32, true}, {8, 12, 11.3f, 0.539f, 32, true}};
 static int pick_kernel(const RowsGemm& g) {
     const int strips = g.N / 16, tiles = (g.M + 15) / 16;
     int best = 0;
@@ -983,7 +1096,16 @@ extern "C" int hawk_rows_kernel(int M, int N, int K) {
     RowsGemm g;
     memset(&g, 0, sizeof g);
     g.M = M; g.N = N; g.K = K;
-    return pick_kernel(g);
+    const int i = pick_kernel(g);
+    return i < 15 ? i : i < 18 ? 14 : 13;
+}
+// The tile of that product's kernel, strips * 100 + row tiles.
+extern "C" int hawk_rows_tile(int M, int N, int K) {
+    RowsGemm g;
+    memset(&g, 0, sizeof g);
+    g.M = M; g.N = N; g.K = K;
+    const RowsKernel& t = kRowsKernels[pick_kernel(g)];
+    return t.SR * 100 + t.CT;
 }
 
 // Row-major weights (the dual-direction heads, contexts without the tile-major copy) come as 64-byte pieces of 16 rows: a
@@ -1017,6 +1139,13 @@ template <int WN, int WM, int SR, int CT, int S, bool PACKED, int MODE> static v
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     k<<<(total + 7) / 8 * 8, 64 * WN * WM, lds, stream>>>(g);
 }
+template <int WN, int WM, int SR, int CT, int MODE> static void launch_wide(hipStream_t stream, const RowsGemm& g) {
+    constexpr int BS = WN * SR, BT = WM * CT, lds = 3 * 2 * BT * 1024;
+    const int strips = g.N / 16, tiles = (g.M + 15) / 16, total = ((strips + BS - 1) / BS) * ((tiles + BT - 1) / BT);
+    auto k = rows_gemm_wide_kernel<WN, WM, SR, CT, MODE>;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    k<<<(total + 7) / 8 * 8, 64 * WN * WM, lds, stream>>>(g);
+}
 template <int SR, int CT, int D, int KW, bool PACKED, int MODE> static void launch_direct(hipStream_t stream, const RowsGemm& g, const Ahead* ahead = nullptr) {
     const int strips = g.N / 16, tiles = (g.M + 15) / 16;
     const int grid = ((strips + SR - 1) / SR + 7) / 8 * 8 * ((tiles + CT - 1) / CT);
@@ -1042,8 +1171,12 @@ template <int MODE> static void launch_packed(hipStream_t stream, const RowsGemm
         case 10: return launch_direct<7, 3, 2, 8, true, MODE>(stream, g, ahead);
         case 11: return launch_staged<2, 4, 4, 2, 4, true, MODE>(stream, g);
         case 12: return launch_staged<2, 4, 5, 2, 4, true, MODE>(stream, g);
-        case 13: return launch_staged<4, 2, 4, 4, 4, true, MODE>(stream, g);
-        default: return launch_staged<4, 2, 5, 6, 3, true, MODE>(stream, g);
+        case 13: return launch_wide<4, 2, 4, 4, MODE>(stream, g);
+        case 14: return launch_wide<4, 2, 5, 6, MODE>(stream, g);
+        case 15: return launch_wide<4, 2, 4, 6, MODE>(stream, g);
+        case 16: return launch_wide<6, 2, 3, 6, MODE>(stream, g);
+        case 17: return launch_wide<4, 2, 4, 8, MODE>(stream, g);
+        default: return launch_wide<2, 4, 4, 3, MODE>(stream, g);
     }
 }
 template <int MODE> static void launch_row_major(hipStream_t stream, const RowsGemm& g) {
