@@ -1278,8 +1278,8 @@ static void rows_output_layer(hawk_ctx* c, int M, int partials, size_t off_x, si
 // Units a launch leaves idle bring the weights of a launch behind it into the L2s they will be read from (bring_ahead): an
 // attention launch those of Wo and W1|W3, which it has time for, Wo's those of W2, W2's those of the next QKV.  A launch of
 // few rows starts with its first weights a memory latency away and ends before the memory system is at its rate; from L2
-// QKV of 18 rows at the XL widths takes 5.4 us instead of 6.6, Wo and W2 12.7 instead of 15.2, W1|W3 7.6 instead of 9.2 and
-// the attention, with the transfer beside it, 9.4 instead of 8.2 (images of three prompts 126.4 -> 116.9 ms); 192 rows, where
+// QKV of 18 rows at the XL widths takes 5.1 us instead of 6.6, Wo and W2 12.8 instead of 15.3, W1|W3 7.8 instead of 9.7 and
+// the attention, with the transfer beside it, 9.6 instead of 7.7 (images of three prompts 126.4 -> 116.9 ms); 192 rows, where
 // only the attention has units to spare, W1|W3 13.1 instead of 15.0 and the attention 15.2 instead of 14.1 (211.2 -> 206.5 ms).
 // Not where a workgroup would have more to bring than the launch lasts (16 units for W2 of 192 rows 222 -> 246 ms, for QKV 240),
 // nor for weights that do not fit; nor where all layers' weights stay in the last-level cache (B shape, 170 MB) and the rows

@@ -1176,7 +1176,8 @@ __device__ __forceinline__ void draft_logits(const SP& p, const Lds& s, Barrier&
 }
 
 // One draft micro-step up to the logits (the sampling kernel follows): stage W (three column
-// blocks of W_d over 3 d/16 strips), one grid barrier, then the output projection.
+// blocks of W_d over 3 d/16 strips), one grid barrier, then the output projection.  For slices of more than 16384 entries and
+// more micro-steps than the exchange slots have places for; the others are one launch for all of them (chain.hip).
 // PAIRS: more than one round of the output projection.  One round (slices of up to 8192 entries at the XL widths, 12288 at
 // the B widths) has a kernel of its own: with an empty second job five micro-steps of 16 sequences and their draws took
 // 189.7 us instead of 184.8 at XL (4096 entries), 153.8 instead of 150.1 at B (8192).
