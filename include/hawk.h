@@ -188,7 +188,7 @@ int hawk_force(hawk_ctx* ctx, const int32_t* n_from, const int32_t* tokens, int 
 
 /* State read-back (all host outputs, each synchronises the stream). */
 int hawk_get_n(hawk_ctx* ctx, int32_t* n /*[batch]*/);
-int hawk_get_grid(hawk_ctx* ctx, int32_t* grid /*[batch, N]*/);
+int hawk_get_grid(hawk_ctx* ctx, int32_t* grid /*[batch, N]; positions that the image has never come to are 0*/);
 /* guided target logits of the last verify/force, [batch, rows, samp_n], rows = k+1 or cnt */
 int hawk_get_logits(hawk_ctx* ctx, float* out, int rows);
 /* guided draft logits of the last draft, [batch, k, samp_n] */

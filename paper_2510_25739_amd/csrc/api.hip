@@ -322,7 +322,9 @@ int enqueue_prefill(hawk_ctx* c, const float* cond, const float* uncond, int bat
     c->greedy = (temperature == 0.f || top_k == 1) ? 1 : 0;
     c->inv_t = c->greedy ? 1.0f : 1.0f / temperature;
     const size_t per = (size_t)batch * n_cond * c->d * 4;
-    HIP_TRY(c, hipMemsetAsync(c->ws + c->off.n, 0, c->off.grid - c->off.n, c->stream));
+    // counts, counters and the grid behind them: hawk_get_grid hands out the whole grid, and what lies past n would be
+    // the image before or whatever the workspace held
+    HIP_TRY(c, hipMemsetAsync(c->ws + c->off.n, 0, c->off.grid - c->off.n + (size_t)batch * c->N * 4, c->stream));
     HIP_TRY(c, hipMemcpyAsync(c->ws + c->off.cond, cond, per, hipMemcpyHostToDevice, c->stream));
     if (c->cfg.use_cfg)
         HIP_TRY(c, hipMemcpyAsync(c->ws + c->off.cond + per, uncond, per, hipMemcpyHostToDevice, c->stream));

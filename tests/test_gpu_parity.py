@@ -384,6 +384,24 @@ def test_two_contexts_on_the_same_inputs_give_identical_bits(H, path):
         assert a.tobytes() == b.tobytes()
 
 
+@pytest.mark.parametrize("cfg", [0, 1])
+def test_a_prefill_leaves_nothing_of_the_image_before(H, cfg):
+    # positions past n are 0, as the oracle has them, also on a context that has had another image (and another grid size)
+    s = synth.CONFIGS[cfg].replace(n_layers=1, n_cond=6, grid_h=4, grid_w=8, batch=2)
+    hk = H.Hawk(H.HawkConfig.from_shape(s))
+    hk.load(synth.make_weights(s, seed=0))
+    cond = synth.make_cond(s, seed=2)
+    full = np.full((2, s.k + 1), s.vocab - 1, np.int32)
+    for h, w in ((4, 8), (4, 8), (3, 8), (4, 8)):
+        hk.prefill(cond, None, h, w, 1.0, s.top_k, 1.0, [0.25, 0.75])
+        assert (hk.n() == 1).all() and (hk.grid()[:, 1:] == 0).all()
+        while hk.n()[0] < h * w:
+            at = int(hk.n()[0])
+            hk.force([at, at], full[:, :min(s.k + 1, h * w - at)])
+        assert (hk.grid()[:, 1:] == s.vocab - 1).all()
+    hk.close()
+
+
 # ----------------------------------------------------------------------------- bf16: tolerance
 
 def bf16_case(H, shape, k, path, steps, u_seed=1, **kw):
