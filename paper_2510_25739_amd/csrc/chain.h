@@ -33,6 +33,7 @@ inline ForcedSrc forced_src(hawk_ctx* c, int k, const DraftMode& dm) {
     return fs;
 }
 
+constexpr int kChainRows = 16;                 // sequences of a launch
 constexpr size_t kChainBarBytes = 26 * 4096;   // counters, release words and tokens (cleared once per context)
 
 // A pointer of the parameter block, which the kernel reads anew in every micro-step: read from memory, the compiler cannot
@@ -56,6 +57,7 @@ struct ChainP {
     Global<float> part;                        // partial products: per_slot micro-steps of part_floats each in every exchange slot
     unsigned long long slot_floats, part_floats;
     Global<const float> left;                  // [Vs][d]: products of W_d's left-neighbour block with the slice's embeddings
+    Global<float> outside;                     // [S][d]: the same with committed tokens from outside the slice
     Global<const float> hprev;                 // [S][d]
     Global<const int32_t> grid, n;
     Global<int32_t> k_eff, draft, step;

@@ -15,7 +15,9 @@
 //
 // Only the left neighbour is the token just drawn, so its block's products with every embedding of the slice are a table
 // made once, when the weights are loaded (left_table_kernel; 84 MB at the XL shape): the token's row is read where its
-// embedding, a product and a barrier came before.  The other blocks' products of micro-step i + 1 are made while micro-step
+// embedding, a product and a barrier came before.  (A committed token from outside the slice, which only forcing brings, has
+// no row: in the first micro-step the workgroups of that block's strips, which have nothing to do otherwise, make its
+// products as the other blocks' are made.)  The other blocks' products of micro-step i + 1 are made while micro-step
 // i is drawn.  So A and B count on sets of their own: a workgroup may arrive at A(i + 1) before
 // another one has arrived at B(i).  It cannot arrive at A(i + 1) before all have arrived at A(i), which it waits for, nor at
 // B(i + 1) before all have arrived at B(i), since it waits for A(i + 1) and they arrive there later.
@@ -37,7 +39,8 @@ namespace {
 constexpr int kGroups = 8, kReplicas = 8;       // one group of arrivals per XCD; copies of the release words
 constexpr unsigned kSpinLimit = 1u << 21;
 constexpr int kTokReplicas = 32;                // copies of the tokens
-constexpr int kRowsMax = 16;
+constexpr int kRowsMax = kChainRows;
+constexpr int kNone = -1, kOutside = -2;        // left neighbours without a row: no draft there; a token from outside the slice
 // 4 KB pages of the chain's barrier memory (kChainBarBytes): counters and release words of A, of B, tokens
 constexpr int kPageA = 0, kPageRelA = 8, kPageB = 16, kPageRelB = 24, kPageTok = 25;
 
@@ -145,7 +148,7 @@ __global__ __launch_bounds__(NT, 1) void draft_chain_kernel(ChainP p) {
     constexpr int Kp = D + 8;
     extern __shared__ uint4 smem[];
     __shared__ float ssp[kRowsMax][8];      // sums of squares of a row's pieces
-    __shared__ int s_n[kRowsMax], s_ke[kRowsMax], s_left[2][kRowsMax];   // s_left: table row of a micro-step's left neighbour
+    __shared__ int s_n[kRowsMax], s_ke[kRowsMax], s_left[2][kRowsMax];   // s_left: table row of a micro-step's left neighbour, kNone or kOutside
     uint16_t* const hi = reinterpret_cast<uint16_t*>(smem);
     uint16_t* const lo = hi + (size_t)p.S * Kp;
     f32x4* const red = reinterpret_cast<f32x4*>(lo + (size_t)p.S * Kp);   // [16 waves][64]
@@ -203,14 +206,55 @@ __global__ __launch_bounds__(NT, 1) void draft_chain_kernel(ChainP p) {
     int most = -1;
     for (int b = 0; b < B; ++b) most = max(most, s_ke[b]);
     most = __builtin_amdgcn_readfirstlane(most);
+    if (wave == NW - 1 && lane < B) {   // the first left neighbours, read in LM(1) behind W's barriers or the one below
+        int left = kNone;
+        if (s_ke[lane] > 0) {
+            left = p.grid[(size_t)lane * p.N + s_n[lane] - 1] - p.sp.samp_lo;
+            if (left < 0 || left >= p.sp.Vs) left = kOutside;
+        }
+        s_left[1][lane] = left;
+    }
+    int least_left = kNone;
+    if (!has_w) {
+        __syncthreads();
+        for (int b = 0; b < B; ++b) least_left = min(least_left, s_left[1][b]);
+    }
+    if (ew[1] > 0 && __builtin_amdgcn_readfirstlane(least_left) == kOutside) {   // tokens that the table has no row of
+        const uint16_t* const Emb = p.blob + p.E_off / 2;
+        for (int it = wave; it < S * EH; it += NW) {
+            const int c = it / EH, j = (it - c * EH) * 512 + lane * 8, b = c % B;
+            const bool there = s_left[1][b] == kOutside;
+            const int tok = there ? p.grid[(size_t)b * p.N + s_n[b] - 1] : 0;
+            if (j < D) *reinterpret_cast<v4u*>(hi + (size_t)c * Kp + j) = there ? *reinterpret_cast<const v4u*>(Emb + (size_t)tok * D + j) : (v4u){0u, 0u, 0u, 0u};
+        }
+        __syncthreads();
+        const int col = lane & 15, kg = lane >> 4;
+        const v4u* src = reinterpret_cast<const v4u*>(p.wpack + (p.wd_base + (u64)(unsigned)ew[0]) * 64) + lane;
+        const uint16_t* from = hi + (size_t)(col < S ? col : 0) * Kp + kg * 8;
+        f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int kt = wave; kt < KT; kt += NW)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, src[(size_t)kt * 64]), *reinterpret_cast<const bf16x8*>(from + kt * 32), acc, 0, 0, 0);
+        red[wave * 64 + lane] = acc;
+        __syncthreads();
+        if (wave == 0) {   // (which arrives at A(1) with these stores done)
+            f32x4 v = red[lane];
+#pragma unroll 1
+            for (int w = 1; w < NW; ++w) v += red[w * 64 + lane];
+            if (col < S) st_f32x4(p.outside + (size_t)col * D + wcol + 4 * kg, v);
+            __builtin_amdgcn_s_waitcnt(0);
+        }
+    }
     const int mine = kNWG - 1 - wg;   // the prompt this workgroup draws for, if there is one
 
     auto kp = (const __attribute__((address_space(4))) ChainP*)__builtin_amdgcn_kernarg_segment_ptr();
     auto part_of = [&](int i) {   // products of micro-step i: [2][S][D]
         return global_of(kp->part) + (u64)((i - 1) / kp->per_slot) * kp->slot_floats + (u64)((i - 1) % kp->per_slot) * kp->part_floats;
     };
-    auto left_product = [&](int left, int j) {
-        return left >= 0 ? *reinterpret_cast<const f32x4*>(global_of(kp->left) + (size_t)left * D + j) : (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto left_product = [&](int left, int c, int j) {
+        if (left == kNone) return (f32x4){0.f, 0.f, 0.f, 0.f};
+        const float* q = left == kOutside ? global_of(kp->outside) + (size_t)c * D : global_of(kp->left) + (size_t)left * D;
+        return *reinterpret_cast<const f32x4*>(q + j);
     };
     auto other_products = [&](int i, int c, int j, f32x4& x, f32x4& y) {
         const float* q = part_of(i) + (size_t)c * D + j;
@@ -242,7 +286,7 @@ __global__ __launch_bounds__(NT, 1) void draft_chain_kernel(ChainP p) {
                             v = *reinterpret_cast<const f32x4*>(global_of(kp->hprev) + (size_t)c * D + j);
                         } else {   // g of the micro-step before
                             other_products(i - 1, c, j, v, y);
-                            v = (v + left_product(s_left[(i - 1) & 1][c % B], j)) + y;
+                            v = (v + left_product(s_left[(i - 1) & 1][c % B], c, j)) + y;
                         }
                     }
                     put_split(make_float4(v[0], v[1], v[2], v[3]), hi + (size_t)c * Kp + j, lo + (size_t)c * Kp + j);
@@ -283,14 +327,14 @@ __global__ __launch_bounds__(NT, 1) void draft_chain_kernel(ChainP p) {
         if (wave < S * CH) sync.wait(kPageRelA + (int)(wg % kReplicas), id);
         for (int it = wave; it < S * CH; it += NW) {
             const int c = it / CH, ch = it - c * CH, j = ch * 256 + lane * 4;
-            int left = -1;
             const int b = c % B;
+            int left = i == 1 ? s_left[1][b] : kNone;
             f32x4 x, y;
             other_products(i, c, j, x, y);   // (asked for ahead of the token)
             const uint2 gn = *reinterpret_cast<const uint2*>(global_of(kp->blob) + kp->gf_off / 2 + j);
-            if (i <= s_ke[b]) left = (i == 1 ? global_of(kp->grid)[(size_t)b * kp->N + s_n[b] - 1] : sync.token(b, id - 1u, kp->sp.samp_lo)) - kp->sp.samp_lo;
-            if (lane == 0) s_left[i & 1][b] = left;
-            const f32x4 g = (x + left_product(left, j)) + y;
+            if (i > 1 && i <= s_ke[b]) left = sync.token(b, id - 1u, kp->sp.samp_lo) - kp->sp.samp_lo;
+            if (i > 1 && lane == 0) s_left[i & 1][b] = left;
+            const f32x4 g = (x + left_product(left, c, j)) + y;
             float ss = (g[0] * g[0] + g[1] * g[1]) + (g[2] * g[2] + g[3] * g[3]);
             ss = wave_sum_f(ss);
             if (lane == 0) ssp[c][ch] = ss;

@@ -1435,6 +1435,7 @@ size_t stream_workspace(const hawk_ctx* c, size_t base, StreamOffsets* o) {
     o->arena = take(o->slot_bytes * (L + 1) * kRing);
     o->bar = take((size_t)(kGroups + 1 + kReplicas) * 4096);
     o->chain = take(kChainBarBytes);
+    o->outside = take(kChainRows * d * 4);
     o->left = take(chain_entries(c->Vs) ? (size_t)c->Vs * d * 4 : 0);
     o->err = take(256);
     o->dbg = take((4 * 4096 * 8 + 2 * 256 * kNWG) * 8);
@@ -1753,6 +1754,7 @@ int launch_draft_chain(hawk_ctx* c, int k, const SampParams& sp, const UniformSr
     p.part = s.arena + s.o_p; p.slot_floats = s.slot_floats;
     p.per_slot = chain_per_slot(c); p.part_floats = up64((size_t)2 * c->S * c->d);
     p.left = wsp<float>(c, o.left);
+    p.outside = wsp<float>(c, o.outside);
     p.hprev = wsp<float>(c, c->off.hprev);
     p.grid = wsp<int32_t>(c, c->off.grid); p.n = s.n;
     p.k_eff = wsp<int32_t>(c, c->off.k_eff); p.draft = wsp<int32_t>(c, c->off.draft); p.step = wsp<int32_t>(c, c->off.step);

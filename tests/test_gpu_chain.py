@@ -63,3 +63,42 @@ def test_draft_chain(H, cfg, batch, scale, vocab, k, top_k, temperature):
         # and micro-step, guidance weighing two streams
         assert worst <= 2e-4 * max(1.0, 2 * scale - 1), worst
     hk.close()
+
+
+# Forcing commits any id of the vocabulary; the table of left-neighbour products has the slice's only.  The first micro-step's
+# left neighbour below, in and behind the slice, at its edges, and all of them at once; two micro-steps carry it on.
+@pytest.mark.parametrize("cfg,batch,scale", [(1, 1, 1.0), (2, 6, 1.0), (1, 8, 2.0), (2, 1, 3.0)])
+@pytest.mark.parametrize("where", ["below", "in", "behind", "all"])
+def test_draft_chain_behind_forced_tokens_outside_the_slice(H, cfg, batch, scale, where):
+    lo, n, vocab, k = 37, 4096, 4800, 4
+    s = synth.CONFIGS[cfg].replace(n_layers=1, vocab=vocab, samp_lo=lo, samp_n=n, batch=batch, cfg_scale=scale, n_cond=6, grid_h=4, grid_w=8, k=k, top_k=300)
+    hk = H.Hawk(H.HawkConfig.from_shape(s))
+    hk.load(synth.make_weights(s, seed=5))
+    rng = np.random.Generator(np.random.PCG64(9))
+    uni = lambda *shp: rng.integers(0, 1 << 24, size=shp).astype(np.float32) / np.float32(1 << 24)  # noqa: E731
+    hk.prefill(synth.make_cond(s, seed=2), synth.make_cond(s, seed=3) if s.use_cfg else None, s.grid_h, s.grid_w, 1.0, s.top_k, scale, uni(batch))
+    ids = {"below": [0, lo - 1, 17], "in": [lo, lo + n - 1, lo + 5], "behind": [lo + n, vocab - 1, vocab - 70]}
+    ids["all"] = sum(ids.values(), [])
+    at, ends = 1, 0
+    while at + 2 <= 24:   # (past the first row of the grid, where there is an upper neighbour as well)
+        last = [ids[where][(at // 2 + b) % len(ids[where])] for b in range(batch)]
+        toks = np.stack([rng.integers(0, vocab, size=batch), last], axis=1).astype(np.int32)
+        hk.force([at] * batch, toks)
+        at += 2
+        u = uni(batch, k)
+        d = hk.draft(k, u)
+        q = hk.draft_logits(k)
+        for b in range(batch):
+            for i in range(k):
+                w, z = oracle.warp(q[b, i], 1.0, s.top_k)
+                assert d[b, i] == lo + oracle.inv_cdf(w, z, float(u[b, i])), (at, b, i)
+        hk.set_path(0)
+        hk.draft_forced(k, d, False)
+        other = hk.draft_logits(k)
+        hk.set_path(1)
+        worst = float(np.abs(q - other).max())
+        # the bound of test_draft_chain; a left block of zeros instead moves these logits (of about 1) by tenths
+        assert worst <= 2e-4 * max(1.0, 2 * scale - 1), (at, last, worst)
+        ends += 1
+    assert ends >= 11
+    hk.close()
