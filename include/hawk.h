@@ -165,7 +165,8 @@ int hawk_generate(hawk_ctx* ctx, const float* cond, const float* uncond, int bat
 /* Runs n_steps speculate-and-verify steps (draft + verify) from the current state with
  * generator uniforms (seed; the step counter continues from the context's), without host
  * outputs: the benchmark's timed region.  replay != 0 drafts from the table given to the
- * last hawk_generate / hawk_set_replay in point-mass mode.  Steps after every prompt has
+ * last hawk_generate / hawk_set_replay in point-mass mode (HAWK_ESTATE where none of the
+ * image's size was given).  Steps after every prompt has
  * finished do nothing.  If ms_draft / ms_verify (host, single floats) are both non-NULL the
  * two phases are bracketed by events, the call synchronises and returns the summed GPU
  * milliseconds of each phase - and in ms_kernel (may be NULL) those of the persistent

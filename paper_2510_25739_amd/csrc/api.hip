@@ -904,6 +904,7 @@ int hawk_generate(hawk_ctx* c, const float* cond, const float* uncond, int batch
                 return fail(c, HAWK_EINVAL, "replayed token outside the sampled slice");
         rc = upload(c, c->off.replay, replay_tokens, (size_t)batch * N * 4);
         if (rc) return rc;
+        c->replay_n = std::max(c->replay_n, (size_t)batch * N);
     }
     UniformSrc us;
     memset(&us, 0, sizeof us);
@@ -966,7 +967,9 @@ int hawk_set_replay(hawk_ctx* c, const int32_t* replay_tokens) {
     for (size_t i = 0; i < (size_t)c->B * c->N; ++i)
         if (replay_tokens[i] < c->cfg.samp_lo || replay_tokens[i] >= c->cfg.samp_lo + c->Vs)
             return fail(c, HAWK_EINVAL, "replayed token outside the sampled slice");
-    return upload(c, c->off.replay, replay_tokens, (size_t)c->B * c->N * 4);
+    const int rc = upload(c, c->off.replay, replay_tokens, (size_t)c->B * c->N * 4);
+    if (rc == HAWK_OK) c->replay_n = std::max(c->replay_n, (size_t)c->B * c->N);
+    return rc;
 }
 
 int hawk_run_steps(hawk_ctx* c, int k, int n_steps, uint64_t seed, int replay, float* ms_draft, float* ms_verify,
@@ -977,6 +980,8 @@ int hawk_run_steps(hawk_ctx* c, int k, int n_steps, uint64_t seed, int replay, f
     if (k < 0 || k > c->kmax || k > c->gw)
         return fail(c, HAWK_EINVAL, "k = %d outside [0, min(k_max = %d, grid_w = %d)]", k, c->kmax, c->gw);
     if (n_steps < 0 || n_steps > 1 << 20) return fail(c, HAWK_EINVAL, "n_steps out of range");
+    // (behind a table's end is whatever the workspace held: no tokens, and so no embeddings' places either)
+    if (replay && k > 0 && c->replay_n < (size_t)c->B * c->N) return fail(c, HAWK_ESTATE, "no replay table for an image of this size");
     const bool timed = ms_draft && ms_verify;
     if (timed && (size_t)(4 * n_steps + 1) > c->n_tev) {
         size_t want = (size_t)(4 * n_steps + 1);

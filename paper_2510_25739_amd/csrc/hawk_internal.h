@@ -112,6 +112,7 @@ struct hawk_ctx {
     float temperature, inv_t, cfg_scale;
     int phase;   // 0 created, 1 loaded, 2 prefilled (draft next), 3 drafted (verify next)
     int k_last;
+    size_t replay_n;   // entries of the replay table that have been given
     int path;
     int launch_failed;
     int last_path;

@@ -402,6 +402,36 @@ def test_a_prefill_leaves_nothing_of_the_image_before(H, cfg):
     hk.close()
 
 
+def test_replay_steps_need_a_table_of_the_images_size(H):
+    # a table that was never given is whatever the workspace held: ids that no embedding has
+    s = synth.CONFIGS[0].replace(n_layers=1, n_cond=6, grid_h=4, grid_w=8, batch=2)
+    hk = H.Hawk(H.HawkConfig.from_shape(s))
+    hk.load(synth.make_weights(s, seed=0))
+    cond = synth.make_cond(s, seed=2)
+
+    def prefill(batch):
+        hk.prefill(cond[:batch], None, 4, 8, 1.0, s.top_k, 1.0, [0.25] * batch)
+
+    def refused():
+        with pytest.raises(H.HawkError) as e:
+            hk.run_steps(s.k, 1, 3, replay=True)
+        assert e.value.code == -2
+
+    prefill(1)
+    refused()
+    hk.run_steps(0, 1, 3, replay=True)   # (no drafts: no table)
+    hk.set_replay(np.full((1, 32), 7, np.int32))
+    hk.run_steps(s.k, 1, 3, replay=True)
+    prefill(2)
+    refused()
+    hk.set_replay(np.full((2, 32), 7, np.int32))
+    hk.run_steps(s.k, 1, 3, replay=True)
+    prefill(1)
+    hk.run_steps(s.k, 1, 3, replay=True)
+    assert hk.n()[0] >= 2
+    hk.close()
+
+
 # ----------------------------------------------------------------------------- bf16: tolerance
 
 def bf16_case(H, shape, k, path, steps, u_seed=1, **kw):
