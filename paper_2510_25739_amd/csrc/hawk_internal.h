@@ -202,6 +202,7 @@ extern "C" int hawk_rows_kernel(int M, int N, int K);                        // 
 extern "C" int hawk_rows_tile(int M, int N, int K);                          // strips * 100 + row tiles of a workgroup of that kernel
 
 // ---- streaming path, implemented in stream.hip ----
+extern "C" int hawk_draft_in_one_launch(const hawk_ctx*, int k);            // does the draft chain take k micro-steps of a prefilled context (chain_ok)? for the tests
 size_t stream_workspace(const hawk_ctx*, size_t base, StreamOffsets* out);  // extra workspace bytes
 StreamPlan* stream_create(hawk_ctx*);     // plans the jobs, uploads tables (context has its workspace)
 void stream_destroy(StreamPlan*);

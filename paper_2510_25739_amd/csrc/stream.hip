@@ -1179,8 +1179,9 @@ __device__ __forceinline__ void draft_logits(const SP& p, const Lds& s, Barrier&
 // blocks of W_d over 3 d/16 strips), one grid barrier, then the output projection.  For slices of more than 16384 entries and
 // more micro-steps than the exchange slots have places for; the others are one launch for all of them (chain.hip).
 // PAIRS: more than one round of the output projection.  One round (slices of up to 8192 entries at the XL widths, 12288 at
-// the B widths) has a kernel of its own: with an empty second job five micro-steps of 16 sequences and their draws took
-// 189.7 us instead of 184.8 at XL (4096 entries), 153.8 instead of 150.1 at B (8192).
+// the B widths; since the chain takes such slices, only with more micro-steps than places) has a kernel of its own: with an
+// empty second job it takes 2 to 3 % longer (five micro-steps of 16 sequences and their draws, when these came here: XL, 4096
+// entries, 189.7 us instead of 184.8; B, 8192, 153.8 instead of 150.1).
 template <int TPS_D, int KREG_D, int RSMAX, bool PAIRS>
 __global__ __launch_bounds__(kThreads, 1) void draft_stream_kernel(SP p) {
     extern __shared__ uint4 smem_raw[];
@@ -1739,6 +1740,8 @@ static int chain_per_slot(const hawk_ctx* c) { return (int)((size_t)kNWG * 8 * k
 bool chain_ok(const hawk_ctx* c, int k) {
     return k >= 1 && stream_draft_ok(c) && chain_shape_ok(c) && k <= chain_per_slot(c) * (c->L + 1);
 }
+
+extern "C" int hawk_draft_in_one_launch(const hawk_ctx* c, int k) { return c->phase >= 2 && chain_ok(c, k); }
 
 // Enqueues the step's plan (drafts in flight, counters) and its k draft micro-steps, draws included.
 int launch_draft_chain(hawk_ctx* c, int k, const SampParams& sp, const UniformSrc& us, const ForcedSrc& fs) {

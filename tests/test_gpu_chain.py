@@ -1,4 +1,5 @@
-"""The draft chain (all micro-steps of a step in one launch) against the batched path's kernels on the same context."""
+"""The draft chain (all micro-steps of a step in one launch), and the launch a micro-step that takes what the chain has no room
+for, against the batched path's kernels on the same context."""
 import numpy as np
 import pytest
 
@@ -22,12 +23,25 @@ def H():
     (1, 1, 1.0, 16384, 5, 1000, 1.0), (2, 1, 1.0, 16384, 5, 4096, 0.8), (2, 3, 3.0, 8208, 7, 500, 1.0), (1, 16, 1.0, 12288, 2, 1000, 1.0),
     (2, 8, 2.0, 4096, 3, 4096, 1.0), (1, 5, 1.0, 2064, 7, 200, 1.0), (2, 16, 1.0, 16384, 1, 1000, 0.0), (1, 2, 1.0, 12304, 4, 3000, 1.0)])
 def test_draft_chain(H, cfg, batch, scale, vocab, k, top_k, temperature):
-    s = synth.CONFIGS[cfg].replace(n_layers=1, vocab=vocab, batch=batch, cfg_scale=scale, n_cond=6, grid_h=4, grid_w=8, k=k, top_k=top_k)
+    compare_with_the_batched_path(H, cfg, batch, scale, vocab, k, top_k, temperature, one_launch=1)
+
+
+# More micro-steps than the exchange slots have places for (at a depth of one layer 10 of sixteen B sequences, 6 of sixteen XL
+# ones): slices of one round of the output projection's jobs, with and without idle workgroups, and of two
+@pytest.mark.parametrize("cfg,batch,scale,vocab,k", [
+    (1, 16, 1.0, 8192, 11), (1, 16, 1.0, 12288, 12), (1, 8, 2.0, 12304, 11), (2, 16, 1.0, 4096, 8), (2, 8, 2.0, 8192, 7), (2, 16, 1.0, 16384, 7)])
+def test_more_drafts_than_the_chain_has_places_for(H, cfg, batch, scale, vocab, k):
+    compare_with_the_batched_path(H, cfg, batch, scale, vocab, k, 1000, 1.0, one_launch=0)
+
+
+def compare_with_the_batched_path(H, cfg, batch, scale, vocab, k, top_k, temperature, one_launch):
+    s = synth.CONFIGS[cfg].replace(n_layers=1, vocab=vocab, batch=batch, cfg_scale=scale, n_cond=6, grid_h=4, grid_w=max(8, k), k=k, top_k=top_k)
     hk = H.Hawk(H.HawkConfig.from_shape(s))
     hk.load(synth.make_weights(s, seed=5))
     rng = np.random.Generator(np.random.PCG64(9))
     uni = lambda *shp: rng.integers(0, 1 << 24, size=shp).astype(np.float32) / np.float32(1 << 24)  # noqa: E731
     hk.prefill(synth.make_cond(s, seed=2), synth.make_cond(s, seed=3) if s.use_cfg else None, s.grid_h, s.grid_w, temperature, top_k, scale, uni(batch))
+    assert hk._L.hawk_draft_in_one_launch(hk._h, k) == one_launch
     N = s.grid_h * s.grid_w
     toks = rng.integers(0, vocab, size=(batch, N)).astype(np.int32)
     at = [1] * batch

@@ -651,8 +651,9 @@ def test_streaming_kernel_row_counts_and_batches(H, cfg, k, batch, scale, path):
 
 @pytest.mark.parametrize("vocab,path", [(2048, 1), (12288, 1), (12304, 1), (16384, 1), (24576, 2)])
 def test_draft_output_projection_over_rounds(H, vocab, path):
-    # the draft kernel takes its output projection's jobs two rounds at a time: one round with idle workgroups and without
-    # (a kernel of its own), a second one that few have, two whole ones, and an odd third (more strips than the XCD kernel's target pass has room for)
+    # The output projection's jobs come in rounds: one round with idle workgroups and without, a second one that few have, two whole
+    # ones - all in the draft chain -, and an odd third, which a launch a micro-step takes, two rounds at a time (more strips than the XCD
+    # kernel's target pass has room for).  That kernel's forms for one and two rounds: test_gpu_chain.py.
     s = synth.CONFIGS[1].replace(n_layers=1, vocab=vocab, n_cond=16, grid_h=6, grid_w=8, k=3, top_k=500)
     total = accumulate_lockstep(H, s, s.k, path, 12, expect_path=1)
     print("draft rounds", vocab, total)
