@@ -38,6 +38,22 @@ def test_draft_kernel_of_one_round_does_not_carry_a_second(tmp_path):
     assert len(one) == 2 and len(pair) == 2 and max(one) <= min(pair) - 60, use
 
 
+def test_draft_chain_keeps_its_weights_in_registers(tmp_path):
+    # A lane of the chain keeps 52 registers of weights at the XL widths, 32 at the B widths, and 4, 8 or 16 entries of a row while
+    # it draws.  What is spilled today, XL and 16 entries: 30, of which 16 are four tiles that a workgroup that draws saves
+    # around the call and seven pairs are addresses, two of them read back in a micro-step.  One more tile is four.
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("no hipcc")
+    cmd = [build.HIPCC, *build.FLAGS, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
+           os.path.join(build.CSRC, "chain.hip"), "-o", str(tmp_path / "chain.o")]
+    report = subprocess.run(cmd, capture_output=True, text=True, check=True).stderr
+    spills = {(int(t), int(e)): int(n) for t, e, n in
+              re.findall(r"Function Name: \S+draft_chain_kernelILi(\d+)ELi(\d+)E.*?VGPRs Spill: (\d+)", report, flags=re.S)}
+    assert set(spills) == {(t, e) for t in (6, 10) for e in (4, 8, 16)}
+    most = {(10, 16): 30, (10, 8): 4, (6, 16): 8}
+    assert {k: n for k, n in spills.items() if n >= most.get(k, 0) + 4} == {}
+
+
 def test_assembly_that_writes_m0_says_so():
     # the compiler does not look into an asm block: it has to be told that what it last put into M0 is gone
     blocks = []
