@@ -198,7 +198,7 @@ void rows_step_pass(hawk_ctx*, const RowMap&, int M);     // step or tree rows: 
 void rows_prompt_pass(hawk_ctx*, const RowMap&, int M);   // condition rows; logits of each sequence's last one
 void rows_draft_pass(hawk_ctx*, int i, size_t off_prev, size_t off_out);   // micro-step i up to its logits
 extern "C" int hawk_rows_attn_waves(int sequences, int heads, int rows);      // rules of the dispatch, for the tests as well
-extern "C" int hawk_rows_kernel(int M, int N, int K);                        // entry of kRowsKernels for a tile-major product (further tiles of an entry's kernel count as it)
+extern "C" int hawk_rows_kernel(int M, int N, int K);                        // entry of kRowsKernels for a tile-major product
 extern "C" int hawk_rows_tile(int M, int N, int K);                          // strips * 100 + row tiles of a workgroup of that kernel
 
 // ---- streaming path, implemented in stream.hip ----

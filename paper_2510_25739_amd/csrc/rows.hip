@@ -1075,7 +1075,6 @@ static const RowsKernel kRowsKernels[] = {
     {3, 2, 1.9f, 0.093f, 32, false}, {4, 2, 1.5f, 0.116f, 32, false}, {6, 2, 2.5f, 0.143f, 32, false},  {4, 3, 2.6f, 0.129f, 32, false},
     {4, 3, 3.9f, 0.243f, 64, false}, {4, 4, 3.3f, 0.146f, 32, false}, {7, 3, 3.9f, 0.179f, 32, false},  {8, 8, 7.5f, 0.398f, 32, true},
     {10, 8, 7.9f, 0.481f, 32, true}, {16, 8, 12.0f, 0.674f, 32, true}, {20, 12, 18.3f, 1.135f, 32, true},
-    // further tiles of the kernel of (20, 12) and, the last one, of (16, 8)
     {16, 12, 16.6f, 0.927f, 32, true}, {18, 12, 15.9f, 0.987f, 32, true}, {16, 16, 21.3f, 1.19f, 32, true}, {8, 12, 11.3f, 0.539f, 32, true}};
 static int pick_kernel(const RowsGemm& g) {
     const int strips = g.N / 16, tiles = (g.M + 15) / 16;
@@ -1096,8 +1095,7 @@ extern "C" int hawk_rows_kernel(int M, int N, int K) {
     RowsGemm g;
     memset(&g, 0, sizeof g);
     g.M = M; g.N = N; g.K = K;
-    const int i = pick_kernel(g);
-    return i < 15 ? i : i < 18 ? 14 : 13;
+    return pick_kernel(g);
 }
 // The tile of that product's kernel, strips * 100 + row tiles.
 extern "C" int hawk_rows_tile(int M, int N, int K) {

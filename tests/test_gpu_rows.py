@@ -88,9 +88,9 @@ SHAPES = [
     (256, 4, 704, 10, 1.0, 50, 6),     # (2, 1), (4, 2), (6, 2)
     (256, 4, 704, 32, 1.0, 63, 2),     # (6, 2), LDS-staged (8, 8)
     (512, 4, 1376, 13, 2.0, 50, 3),    # (4, 1), (4, 3), (4, 4), LDS-staged (8, 8); heads of 128
-    (512, 8, 1376, 32, 1.0, 63, 2),    # LDS-staged (16, 8) with a ragged last group
-    (768, 12, 2048, 16, 2.0, 100, 2),  # LDS-staged (20, 12)
-    (512, 8, 1376, 32, 1.0, 100, 2),   # LDS-staged (10, 8) for the MLP
+    (512, 8, 1376, 32, 1.0, 63, 2),    # LDS-staged (8, 8) for QKV; (8, 12), weights in registers, for W1|W3
+    (768, 12, 2048, 16, 2.0, 100, 2),  # (16, 8) for QKV and (18, 12) for W1|W3, weights in registers, ragged last groups
+    (512, 8, 1376, 32, 1.0, 100, 2),   # LDS-staged (10, 8) for QKV and W1|W3
     (256, 4, 1376, 4, 1.0, 84, 5),     # (7, 3) for W1|W3
     (768, 12, 704, 2, 1.0, 56, 9),     # (3, 2) for QKV
     (768, 12, 1376, 13, 1.0, 80, 5),   # (7, 3) for Wo and W2
@@ -119,7 +119,7 @@ KERNEL_SHAPES = [
     (128, 2, 704, 20, 1.0, 53, 40),    # (4, 3) for QKV, (4, 3) two to a unit and (4, 4) for W1|W3
     (1024, 16, 704, 8, 1.0, 129, 9),   # (4, 1) for QKV, (2, 1) for W1|W3, (4, 3) two to a unit for Wo and W2
     (1280, 20, 352, 32, 1.0, 103, 4),  # LDS-staged (10, 8) for Wo and W2
-    (512, 8, 352, 128, 1.0, 129, 1),   # LDS-staged (20, 12) for Wo and W2
+    (512, 8, 352, 128, 1.0, 129, 1),   # weights in registers: (20, 12) for QKV, (16, 12) for Wo, (16, 16) for W1|W3, (18, 12) for W2
 ]
 
 

@@ -7,6 +7,7 @@ import paper_2510_25739_amd as H
 import synth
 from paper_2510_25739_amd import build
 from test_gpu_rows import KERNEL_SHAPES, SHAPES
+from test_gpu_wide import N_COND, WIDE_SHAPES
 
 
 @pytest.fixture(scope="module")
@@ -40,6 +41,8 @@ def test_every_kernel_a_model_takes_is_compared_with_float64(lib):
     for d, heads, mlp, batch, scale, n_cond, chunk in SHAPES + KERNEL_SHAPES:
         sequences = batch * (2 if scale != 1.0 else 1)
         compared |= took(d, mlp, sequences * n_cond) | took(d, mlp, sequences * chunk)
+    for d, _, mlp, batch in WIDE_SHAPES:
+        compared |= took(d, mlp, batch * N_COND)
     models = {}
     for i in (1, 2, 4):
         s = synth.CONFIGS[i]
@@ -48,4 +51,4 @@ def test_every_kernel_a_model_takes_is_compared_with_float64(lib):
                 models.setdefault(kernel, []).append((s.d_model, rows))
     left = {k: v[0] for k, v in models.items() if k not in compared}
     assert not left, left
-    assert len({k for k, _ in models}) == 15      # no entry of the table without a use
+    assert len({k for k, _ in models}) == 19      # no entry of the table without a use
