@@ -1176,12 +1176,13 @@ __device__ __forceinline__ void draft_logits(const SP& p, const Lds& s, Barrier&
 }
 
 // One draft micro-step up to the logits (the sampling kernel follows): stage W (three column
-// blocks of W_d over 3 d/16 strips), one grid barrier, then the output projection.  For slices of more than 16384 entries and
-// more micro-steps than the exchange slots have places for; the others are one launch for all of them (chain.hip).
+// blocks of W_d over 3 d/16 strips), one grid barrier, then the output projection.  For slices of more than 16384 entries,
+// more micro-steps than the exchange slots have places for, and one or two that do not pay for the chain's start
+// (chain_pays); the others are one launch for all of them (chain.hip).
 // PAIRS: more than one round of the output projection.  One round (slices of up to 8192 entries at the XL widths, 12288 at
-// the B widths; since the chain takes such slices, only with more micro-steps than places) has a kernel of its own: with an
-// empty second job it takes 2 to 3 % longer (five micro-steps of 16 sequences and their draws, when these came here: XL, 4096
-// entries, 189.7 us instead of 184.8; B, 8192, 153.8 instead of 150.1).
+// the B widths) has a kernel of its own: with an
+// empty second job they take 2 to 3 % longer (five of 16 sequences with their draws, when the chain did not take these: XL, 4096 entries,
+// 189.7 us instead of 184.8; B, 8192, 153.8 instead of 150.1).
 template <int TPS_D, int KREG_D, int RSMAX, bool PAIRS>
 __global__ __launch_bounds__(kThreads, 1) void draft_stream_kernel(SP p) {
     extern __shared__ uint4 smem_raw[];
@@ -1735,10 +1736,24 @@ int launch_draft_stream(hawk_ctx* c, int i, size_t off_prev, size_t off_out) {
 // The draft chain in one launch: micro-steps whose partial products have places of their own in the exchange slots.
 static int chain_per_slot(const hawk_ctx* c) { return (int)((size_t)kNWG * 8 * kPS / up64((size_t)2 * c->S * c->d)); }
 
-// Can the k micro-steps of a step run as one launch?  Slices that one workgroup draws from and whose strips fit four to a
+// Do few micro-steps pay for the chain's start (every weight asked for at once, ahead of the first product)?  With one round of
+// the output layer's strips they do; with two, whose tiles are twice as many and whose draws are longer, from three on.
+// A step (drafts, target pass, acceptance) at full depth with 1, 4, 9 and 16 sequences, launches -> chain, us:
+//   k = 1, 16384 entries   B  266 -> 269, 275 -> 281, 376 -> 381, 385 -> 391; XL  775 -> 782, 809 -> 818, 1357 -> 1358, 1330 -> 1330
+//   k = 1, 8192 entries    B  257 -> 257, 266 -> 267, 369 -> 366, 378 -> 372; XL  766 -> 766, 797 -> 798, 1346 -> 1341, 1321 -> 1311
+//   k = 1, 2048 entries    B  255 -> 254, 266 -> 264, 364 -> 365, 378 -> 371; XL within 0.4 %
+//   k = 2, 16384 entries   B, 1 to 3 sequences within 0.3 %, 4 / 8  324 -> 326, 400 -> 403, 9 / 16  406 -> 405, 435 -> 430;
+//                          XL, 1 to 8 sequences  807 -> 810, 918 -> 924, 983 -> 993, 1477 -> 1481, 9 / 16  1488 -> 1483, 1592 -> 1581
+//   k = 3, 16384 entries   B  311 -> 305; XL  834 -> 831, 16 sequences 1764 -> 1739
+static bool chain_pays(const hawk_ctx* c, int k) {
+    if (k > 2 || c->plan->kind[K_LM].rounds == 1) return true;
+    return k == 2 && (c->S > 8 || (c->d < 1280 && c->S <= 3));
+}
+
+// Do the k micro-steps of a step run as one launch?  Slices that one workgroup draws from and whose strips fit four to a
 // workgroup (both end at 16384 entries), and no more micro-steps than there are places for partial products.
 bool chain_ok(const hawk_ctx* c, int k) {
-    return k >= 1 && stream_draft_ok(c) && chain_shape_ok(c) && k <= chain_per_slot(c) * (c->L + 1);
+    return k >= 1 && stream_draft_ok(c) && chain_shape_ok(c) && k <= chain_per_slot(c) * (c->L + 1) && chain_pays(c, k);
 }
 
 extern "C" int hawk_draft_in_one_launch(const hawk_ctx* c, int k) { return c->phase >= 2 && chain_ok(c, k); }

@@ -21,16 +21,19 @@ def H():
 # micro-steps up to what a context of one layer has room for; top-k of the list and of the dense form; greedy
 @pytest.mark.parametrize("cfg,batch,scale,vocab,k,top_k,temperature", [
     (1, 1, 1.0, 16384, 5, 1000, 1.0), (2, 1, 1.0, 16384, 5, 4096, 0.8), (2, 3, 3.0, 8208, 7, 500, 1.0), (1, 16, 1.0, 12288, 2, 1000, 1.0),
-    (2, 8, 2.0, 4096, 3, 4096, 1.0), (1, 5, 1.0, 2064, 7, 200, 1.0), (2, 16, 1.0, 16384, 1, 1000, 0.0), (1, 2, 1.0, 12304, 4, 3000, 1.0)])
+    (2, 8, 2.0, 4096, 3, 4096, 1.0), (1, 5, 1.0, 2064, 7, 200, 1.0), (2, 16, 1.0, 4096, 1, 1000, 0.0), (1, 2, 1.0, 12304, 4, 3000, 1.0),
+    (2, 9, 1.0, 16384, 2, 1000, 1.0), (1, 3, 1.0, 16384, 2, 1000, 1.0), (2, 4, 1.0, 8192, 1, 1000, 1.0)])
 def test_draft_chain(H, cfg, batch, scale, vocab, k, top_k, temperature):
     compare_with_the_batched_path(H, cfg, batch, scale, vocab, k, top_k, temperature, one_launch=1)
 
 
 # More micro-steps than the exchange slots have places for (at a depth of one layer 10 of sixteen B sequences, 6 of sixteen XL
-# ones): slices of one round of the output projection's jobs, with and without idle workgroups, and of two
+# ones): slices of one round of the output projection's jobs, with and without idle workgroups, and of two; and the one or two
+# micro-steps that stay launches of their own
 @pytest.mark.parametrize("cfg,batch,scale,vocab,k", [
-    (1, 16, 1.0, 8192, 11), (1, 16, 1.0, 12288, 12), (1, 8, 2.0, 12304, 11), (2, 16, 1.0, 4096, 8), (2, 8, 2.0, 8192, 7), (2, 16, 1.0, 16384, 7)])
-def test_more_drafts_than_the_chain_has_places_for(H, cfg, batch, scale, vocab, k):
+    (1, 16, 1.0, 8192, 11), (1, 16, 1.0, 12288, 12), (1, 8, 2.0, 12304, 11), (2, 16, 1.0, 4096, 8), (2, 8, 2.0, 8192, 7), (2, 16, 1.0, 16384, 7),
+    (1, 1, 1.0, 16384, 1), (2, 16, 1.0, 16384, 1), (2, 4, 2.0, 8208, 2), (1, 4, 1.0, 12304, 2)])
+def test_drafts_that_the_chain_does_not_take(H, cfg, batch, scale, vocab, k):
     compare_with_the_batched_path(H, cfg, batch, scale, vocab, k, 1000, 1.0, one_launch=0)
 
 
