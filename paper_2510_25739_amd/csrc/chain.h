@@ -5,34 +5,6 @@
 
 namespace hawk {
 
-struct SampParams {
-    int B, N, Vs, samp_lo, kstride, top_k, greedy, use_cfg;
-    float inv_t, cfg_scale;
-};
-// A table of forced draft tokens (teacher-forced drafting, replay).
-struct ForcedSrc {
-    const int32_t* table;  // nullptr: sample
-    int32_t stride;        // row stride of the table
-    int32_t relative;      // 1: column n[b] + i - 1 (replay grid), 0: column i - 1
-    int32_t point_mass;
-};
-
-inline SampParams samp_params(const hawk_ctx* c) {
-    SampParams P;
-    P.B = c->B; P.N = c->N; P.Vs = c->Vs; P.samp_lo = c->cfg.samp_lo; P.kstride = c->kmax + 1;
-    P.top_k = c->top_k; P.greedy = c->greedy; P.use_cfg = c->cfg.use_cfg;
-    P.inv_t = c->inv_t; P.cfg_scale = c->cfg_scale;
-    return P;
-}
-
-inline ForcedSrc forced_src(hawk_ctx* c, int k, const DraftMode& dm) {
-    ForcedSrc fs;
-    fs.table = nullptr; fs.stride = 0; fs.relative = 0; fs.point_mass = dm.point_mass;
-    if (dm.kind == 1) { fs.table = wsp<int32_t>(c, c->off.forced); fs.stride = k; }
-    if (dm.kind == 2) { fs.table = wsp<int32_t>(c, c->off.replay); fs.stride = c->N; fs.relative = 1; }
-    return fs;
-}
-
 constexpr int kChainRows = 16;                 // sequences of a launch
 constexpr size_t kChainBarBytes = 26 * 4096;   // counters, release words and tokens (cleared once per context)
 

@@ -10,7 +10,7 @@
 // Reductions use cross-lane moves, then one LDS exchange across the 16 waves.
 #pragma once
 
-#include "chain.h"
+#include "hawk_internal.h"
 
 namespace hawk {
 
