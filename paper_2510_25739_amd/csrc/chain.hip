@@ -120,7 +120,9 @@ __device__ __forceinline__ void load_fresh_row(const float* lc, const float* lu,
 
 // A draw from one row (index within the slice; statistics to *stat).  guided: logits of the prompt's conditional row, the
 // unconditional one `shift` further on, combined to `row`; null: `row` holds them.  u < 0: `forced` is taken instead.
-// Out of line: inlined in the micro-steps' loop, its constants and addresses are kept across the loop, which spills them.
+// Out of line: inlined in the micro-steps' loop, its constants and addresses are kept across the loop, which spills them (266
+// registers).  What the XL kernel with 16 entries still spills: 16 registers, four tiles of weights, that a workgroup which draws
+// saves around the call, seven address pairs, two of which a micro-step reads back, and scalars that go to lanes of two registers.
 template <int E>
 __device__ __noinline__ int draw(const float* guided, size_t shift, float* row, WarpStat* stat, float u, int forced, int point_mass,
                                  int n, int top_k, int greedy, float inv_t, float cfg_scale) {
@@ -264,7 +266,7 @@ __global__ __launch_bounds__(NT, 1) void draft_chain_kernel(ChainP p) {
 
     for (int i = 1; i <= kp->k; ++i) {
         const unsigned id = kp->epoch0 + (unsigned)i;
-        asm volatile("" : "+v"(lane), "+s"(kp));   // addresses and parameters are made anew in every micro-step: kept across them they spill
+        asm volatile("" : "+v"(lane), "+s"(kp));   // addresses and parameters are made anew in every micro-step: kept across them most would spill
         const int col = lane & 15, kg = lane >> 4;
         const size_t frag = (size_t)(col < S ? col : 0) * Kp + kg * 8;   // columns past the rows repeat row 0; their results are not stored
         if (i > most) {   // nothing left to draft: only the counts go on

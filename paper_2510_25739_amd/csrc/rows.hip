@@ -1068,7 +1068,8 @@ __global__ __launch_bounds__(64 * NWV) void attn_step_kernel(AttnArgs a, W ahead
 // of 72 rows 13.3 and 9.1 us; 384 rows of W2 (4, 2) 26.0 us, since two XCDs had 36 workgroups, (4, 3) 17.6 us.
 // From 200 rows on the entries behind (10, 8) are fitted to 372 products of the same widths, 70 to 4100 rows: the choice is 1.1 %
 // behind the fastest of these kernels on average and 3.6 % ahead of the choice among the staged forms alone (5.3 % behind); it is
-// slower than that one for four sizes, by 5 % at most (W1|W3 of 1000 rows at the 7B widths, 330 us instead of 314).
+// slower than that one for four sizes, by 5 % at most (W1|W3 of 1000 rows at the 7B widths, 330 us instead of 314; the whole prompt pass
+// of 1000 rows, three layers, 3.39 -> 3.35 ms).
 struct RowsKernel { int SR, CT; float fixed, step; int slots; bool staged; };
 static const RowsKernel kRowsKernels[] = {
     {1, 1, 0.9f, 0.038f, 32, false}, {2, 1, 1.5f, 0.049f, 32, false}, {4, 1, 1.8f, 0.09f, 32, false},   {2, 2, 1.2f, 0.080f, 32, false},
@@ -1277,13 +1278,16 @@ static void rows_output_layer(hawk_ctx* c, int M, int partials, size_t off_x, si
 // attention launch those of Wo and W1|W3, which it has time for, Wo's those of W2, W2's those of the next QKV.  A launch of
 // few rows starts with its first weights a memory latency away and ends before the memory system is at its rate; from L2
 // QKV of 18 rows at the XL widths takes 5.1 us instead of 6.6, Wo and W2 12.8 instead of 15.3, W1|W3 7.8 instead of 9.7 and
-// the attention, with the transfer beside it, 9.6 instead of 7.7 (images of three prompts 126.4 -> 116.9 ms); 192 rows, where
-// only the attention has units to spare, W1|W3 13.1 instead of 15.0 and the attention 15.2 instead of 14.1 (211.2 -> 206.5 ms).
+// the attention, with the transfer beside it, 9.6 instead of 7.7 (over images of three prompts: 126.4 -> 116.9 ms); 192 rows,
+// where only the attention has units to spare, W1|W3 13.0 instead of 15.0 and the attention, at about 415 cached positions, 19.2
+// instead of 17.7 (images 211.2 -> 206.5 ms).
 // Not where a workgroup would have more to bring than the launch lasts (16 units for W2 of 192 rows 222 -> 246 ms, for QKV 240),
-// nor for weights that do not fit; nor where all layers' weights stay in the last-level cache (B shape, 170 MB) and the rows
-// are few: 24 rows 19.4 -> 19.7 ms an image, while 96 rows gain, 26.6 -> 26.1; nor for prompt rows (B shape, 91 rows: 475 -> 482 us,
-// XL shape, 80 rows: the same).
-constexpr int kL2Kb = 24 * 1024;   // of 32 MB: the rows' own data has the rest
+// nor for weights that do not fit: a matrix is brought whole or not at all, so passes at the 7B widths, where Wo alone has 32 MB,
+// bring nothing.  Nor for prompt rows (B shape, 91 rows: 475 -> 482 us, XL shape, 80 rows: the same).  Where all layers' weights stay
+// in the last-level cache (B shape, 170 MB) the line is at 64 rows: steps of 64 to 96 rows (18 calls, at 40 and 600 cached
+// positions) take 1.8 % less to 0.7 % more with it, 0.6 % less on average; of 40 to 60 rows 1.8 % less to 0.2 % more; of 18 to 32
+// rows up to 1.8 % more at 40 positions (18 rows 445 -> 453 us) and 1 to 4 % less at 600 (528 -> 509).
+constexpr int kL2Kb = 24 * 1024;   // of the eight L2s' 32 MB: the rows' own data has the rest
 static Ahead plan_ahead(hawk_ctx* c, int M, int grid, int idle, int kb_each, const int* packs, int n) {
     Ahead a;
     memset(&a, 0, sizeof a);

@@ -322,7 +322,9 @@ __device__ int inv_cdf(WF w, int n, double total, float u, Shared& sh) {
 // registers for the whole kernel (one coalesced read of the row).  Same decisions, to the bit, as
 // the generic functions above.
 //
-// What bounds them is the instruction issue of one compute unit: a wave's vector instruction takes
+// What bounds them is a chain of about a dozen phases on one compute unit, 0.35 to 1.3 us each, which wait for each other at
+// barriers: with two thirds of the entries kept out of the histogram a draw is not faster.  What bounded them before was
+// its instruction issue: a wave's vector instruction takes
 // four cycles and a SIMD has four of the block's sixteen waves, so one instruction per entry of a
 // 16384-entry row is 256 cycles (0.1 us), and work that every wave repeats costs four times as much as
 // work of one wave.  So:
